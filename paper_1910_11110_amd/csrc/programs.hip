@@ -1,13 +1,18 @@
 // programs.hip -- structured programs (While / If / sequences of effects) (gfx950).
 //
 // Programs are independent, so one lane runs one program: the statuses of its (at most
-// 64) variables are two 64-bit planes in registers (CPU copy valid, GPU copy valid),
-// and the program's syntax tree, serialised in prefix order, is walked with a stack of
-// resume points in LDS: entering a While body or an If branch pushes where to go when
-// the block ends (the While header, which evaluates its condition again, or the word
-// after the If).  Every reduction costs one step of fuel, as in the rules While-True /
-// While-False / IF-True / IF-False and Effect / Remote Effect; stuck effects are flagged
-// and skipped.
+// 64) variables are two bit planes in registers (CPU copy valid, GPU copy valid).  Every
+// reduction costs one step of fuel, as in the rules While-True / While-False / IF-True /
+// IF-False and Effect / Remote Effect; stuck effects are flagged and skipped.
+//
+// A wave first turns its 64 programs into steps in LDS (k_run_steps): one word per
+// statement holding the effect as bit masks, the condition, and the two statements that
+// can follow, so that running a step is straight-line code with one LDS read, the same
+// for effects, While and If.  Programs too long for that are walked in place
+// (k_run_programs): their syntax tree, serialised in prefix order, with a stack of resume
+// points in LDS, where entering a While body or an If branch pushes where to go when the
+// block ends (the While header, which evaluates its condition again, or the word after
+// the If).
 #include "device.h"
 #include "internal.h"
 #include "prof.h"
@@ -128,15 +133,211 @@ __global__ __launch_bounds__(PROG_BLOCK) void k_run_programs(
     }
 }
 
+// ----------------------------------------------------------------------------------
+// programs as steps in LDS
+// ----------------------------------------------------------------------------------
+// A step: where its variable's status lies (bits 0-5), the copies its effect needs valid
+// (6-7), the change it makes to a status s, (s & a) ^ b (a 8-9, b 10-11; statuses and
+// masks as CPU | GPU << 1); its outcome (12-13: the CPU copy valid, the GPU copy valid,
+// the next choice, always true); the statement that follows a true outcome (14-22) and a
+// false one (23-31).  Statements are named by their first word; the program's length
+// stands for its end, which has a step of its own that changes and counts nothing and
+// follows itself.
+constexpr uint32_t STEP_CHOICE = 2, STEP_TRUE = 3;
+constexpr uint32_t STEP_MAX = 511; // longest program a step can name
+
+__device__ __forceinline__ uint32_t make_step(uint32_t at, uint32_t need, uint32_t a, uint32_t b, uint32_t outcome,
+                                              uint32_t if_true, uint32_t if_false)
+{
+    return at | (need << 6) | (a << 8) | (b << 10) | (outcome << 12) | (if_true << 14) | (if_false << 23);
+}
+
+// The statuses of a program's variables.  Up to 16 variables they are pairs of bits in one
+// register, so that a status is one bit-field read away (a step's low 5 bits are the
+// field's place); up to 32, pairs in 64 bits; up to 64, two planes.
+struct Statuses16 {
+    uint32_t st = 0;
+    __device__ static uint32_t place(uint32_t v) { return 2u * v; }
+    __device__ uint32_t get(uint32_t e) const { return __builtin_amdgcn_ubfe(st, e, 2u); }
+    __device__ void change(uint32_t e, uint32_t d) { st ^= d << (e & 31u); }
+};
+struct Statuses32 {
+    uint64_t st = 0;
+    __device__ static uint32_t place(uint32_t v) { return 2u * v; }
+    __device__ uint32_t get(uint32_t e) const { return (uint32_t)(st >> (e & 63u)) & 3u; }
+    __device__ void change(uint32_t e, uint32_t d) { st ^= (uint64_t)d << (e & 63u); }
+};
+struct Statuses64 {
+    uint64_t cpl = 0, gpl = 0;
+    __device__ static uint32_t place(uint32_t v) { return v; }
+    __device__ uint32_t get(uint32_t e) const
+    {
+        return ((uint32_t)(cpl >> (e & 63u)) & 1u) | (((uint32_t)(gpl >> (e & 63u)) & 1u) << 1);
+    }
+    __device__ void change(uint32_t e, uint32_t d)
+    {
+        cpl ^= (uint64_t)(d & 1u) << (e & 63u);
+        gpl ^= (uint64_t)(d >> 1) << (e & 63u);
+    }
+};
+
+// The statements of one program, held as its words in column `code` (one word every WAVE),
+// become steps in place, in one pass in prefix order.  Blocks nest: `stack` holds the
+// enclosing blocks' ends and what follows them, 16 bits each.  What follows a statement is
+// the next word, or, at the end of its block, what follows the block: the While header,
+// or what follows the If.
+template <class ST>
+__device__ __forceinline__ void compile_steps(uint32_t *code, uint32_t len, uint32_t *stack)
+{
+    uint32_t pc = 0, end = len, exit = len, depth = 0;
+    while (pc < len) {
+        while (pc == end && depth) {
+            depth--;
+            const uint32_t f = stack[depth * WAVE];
+            end = f & 0xFFFFu;
+            exit = f >> 16;
+        }
+        const uint32_t word = code[pc * WAVE], kind = word >> 30, x = word & 63u;
+        if (kind == 0) {
+            const uint32_t op = (word >> 24) & 7u, own = (word & (1u << 27)) ? 2u : 1u;
+            const uint32_t next = pc + 1 == end ? exit : pc + 1;
+            const uint32_t need = (op == OP_R || op == OP_PUSH) ? own : (op == OP_PULL ? own ^ 3u : 0u);
+            const uint32_t set = op == OP_W ? own : ((op == OP_PUSH || op == OP_PULL) ? 3u : 0u);
+            code[pc * WAVE] = make_step(ST::place(x), need, op == OP_W ? 3u : set, set, STEP_TRUE, next, next);
+            pc++;
+            continue;
+        }
+        const uint32_t ck = (word >> 24) & 3u, n = code[(pc + 1) * WAVE];
+        const uint32_t m = kind == 2 ? code[(pc + 2) * WAVE] : 0u, body = pc + (kind == 2 ? 3u : 2u);
+        const uint32_t after = body + n + m, next = after == end ? exit : after;
+        const uint32_t back = kind == 1 ? pc : next; // what follows the body or a branch
+        const uint32_t t = n ? body : back, f = m ? body + n : next;
+        code[pc * WAVE] = make_step(ck == STEP_CHOICE ? 0u : ST::place(x), 0u, 0u, 0u, ck, t, f);
+        if (n || m) {
+            stack[depth++ * WAVE] = end | (exit << 16);
+            if (n && m) // the second branch's frame lies under the first's
+                stack[depth++ * WAVE] = after | (next << 16);
+            end = n ? body + n : after;
+            exit = back;
+        }
+        pc = body;
+    }
+    code[len * WAVE] = make_step(0u, 0u, 0u, 0u, 0u, len, len);
+}
+
+// One wave, 64 programs.  LDS columns of one word per lane (no bank is shared by two
+// lanes, whatever their statements): rows [0, rows) the words and then the steps, rows
+// above the nesting stack.  Reading a program's words from memory at every step bounds the
+// walk in place (64 lanes on 64 cache lines, 2-3 loads a step).  Here it is the issue of
+// about 33 VALU instructions a step, and the two waves per SIMD that 65 rows leave room
+// for: 2^18 programs of up to 64 words over 16 variables, fuel 4096 (8.0e8 reductions),
+// take 1.5 ms against 8.8 ms in place; 2^16 programs of 230 words (one wave on three of
+// four SIMDs) 0.99 ms against 6.8.
+template <class ST>
+__global__ __launch_bounds__(WAVE) void k_run_steps(
+    const uint64_t *__restrict__ prog_off, uint64_t n_prog, const uint32_t *__restrict__ words, uint32_t n_vars,
+    uint32_t rows, const uint64_t *__restrict__ choice, const uint8_t *__restrict__ init, uint32_t fuel,
+    uint64_t *__restrict__ steps_out, uint64_t *__restrict__ effects_out, uint64_t *__restrict__ stuck_out,
+    uint64_t *__restrict__ first_out, uint8_t *__restrict__ done_out, uint8_t *__restrict__ final_out)
+{
+    extern __shared__ uint32_t s_col[];
+    const uint32_t me = threadIdx.x;
+    uint32_t *const code = s_col + me;
+    const uint64_t stride = (uint64_t)gridDim.x * WAVE;
+    for (uint64_t p = (uint64_t)blockIdx.x * WAVE + me; p < n_prog; p += stride) {
+        const uint64_t base = prog_off[p];
+        const uint32_t len = (uint32_t)(prog_off[p + 1] - base);
+        const uint32_t *w = words + base;
+        constexpr uint32_t BATCH = 16; // loads in flight
+        for (uint32_t i = 0; i < len; i += BATCH) {
+            uint32_t v[BATCH];
+#pragma unroll
+            for (uint32_t q = 0; q < BATCH; q++)
+                v[q] = w[i + q < len ? i + q : len - 1];
+#pragma unroll
+            for (uint32_t q = 0; q < BATCH; q++)
+                if (i + q < len)
+                    code[(i + q) * WAVE] = v[q];
+        }
+        compile_steps<ST>(code, len, code + rows * WAVE);
+        ST st;
+        for (uint32_t v = 0; v < n_vars; v++)
+            st.change(ST::place(v), init ? init[p * n_vars + v] & 3u : 1u);
+        const uint64_t ch = choice ? choice[p] : 0ull;
+        uint32_t steps = 0, effects = 0, stuck = 0, first = ~0u, nch = 0, pc = 0;
+        auto step = [&] {
+            const uint32_t e = code[pc * WAVE];
+            const uint32_t s = st.get(e), k = (e >> 12) & 3u;
+            steps += pc != len ? 1u : 0u;
+            // the effect (a condition changes and needs nothing); all arithmetic, so that the
+            // compiler adds no branches
+            const uint32_t lack = (e >> 6) & ~s, bad = (lack | (lack >> 1)) & 1u;
+            const uint32_t cand = effects | (bad - 1u);
+            first = first < cand ? first : cand;
+            stuck += bad;
+            effects += k == STEP_TRUE ? 1u : 0u;
+            st.change(e, ((s & (e >> 8)) ^ (e >> 10)) & 3u & (bad - 1u));
+            // the outcome: rules valid / invalid, rem-valid / rem-invalid, or the
+            // program's next choice bit
+            const uint32_t bit = (uint32_t)(ch >> (nch & 63u)) & 1u;
+            const uint32_t outcomes = s | (bit << STEP_CHOICE) | (1u << STEP_TRUE);
+            nch += k == STEP_CHOICE ? 1u : 0u;
+            pc = (e >> (((outcomes >> k) & 1u) ? 14 : 23)) & STEP_MAX;
+        };
+        // a program that has ended stays at its end, so the ends are looked for once every
+        // UNROLL steps only
+        constexpr uint32_t UNROLL = 4;
+        uint32_t left = fuel;
+        while (left >= UNROLL && pc != len) {
+#pragma unroll
+            for (uint32_t q = 0; q < UNROLL; q++)
+                step();
+            left -= UNROLL;
+        }
+        if (pc != len)
+            for (; left; left--)
+                step();
+        steps_out[p] = steps;
+        effects_out[p] = effects;
+        stuck_out[p] = stuck;
+        first_out[p] = stuck ? first : effects;
+        done_out[p] = pc == len ? 1 : 0;
+        for (uint32_t v = 0; v < n_vars; v++)
+            final_out[p * n_vars + v] = (uint8_t)st.get(ST::place(v));
+    }
+}
+
 } // namespace
+
+// Whether the programs run as steps in LDS: a step names statements by 9 bits, the
+// steps' counters have 32 bits, and a wave's columns (the longest program, its end and two
+// nesting frames per level) fit the 64 KiB that a launch may take.
+static bool fits_steps(uint64_t longest, uint32_t depth, uint64_t fuel)
+{
+    return longest <= STEP_MAX && longest + 1 + 2 * depth <= 65536 / (4 * WAVE) && fuel < (1ull << 32);
+}
 
 void launch_run_programs(const uint64_t *prog_off, uint64_t n_prog, const uint32_t *words, uint32_t n_vars,
                          const uint64_t *choice, const uint8_t *init, uint64_t fuel, uint64_t *steps,
                          uint64_t *effects, uint64_t *stuck, uint64_t *first, uint8_t *done, uint8_t *final_out,
-                         bool short_programs, hipStream_t s)
+                         uint64_t longest, uint32_t depth, hipStream_t s)
 {
     if (!n_prog)
         return;
+    if (fits_steps(longest, depth, fuel)) {
+        const uint64_t waves = ceil_div(n_prog, (uint64_t)WAVE);
+        const unsigned grid = (unsigned)(waves > 1048576 ? 1048576 : waves);
+        const uint32_t rows = (uint32_t)longest + 1;
+        const size_t lds = (rows + 2 * depth) * (size_t)WAVE * 4;
+        const auto kernel = n_vars <= 16   ? k_run_steps<Statuses16>
+                            : n_vars <= 32 ? k_run_steps<Statuses32>
+                                           : k_run_steps<Statuses64>;
+        ProfScope p(s, "run_programs");
+        kernel<<<grid, WAVE, lds, s>>>(prog_off, n_prog, words, n_vars, rows, choice, init, (uint32_t)fuel, steps,
+                                       effects, stuck, first, done, final_out);
+        return;
+    }
+    const bool short_programs = longest < (1ull << 16);
     uint64_t g = ceil_div(n_prog, PROG_BLOCK);
     const unsigned grid = (unsigned)(g > 65535 ? 65535 : g);
     ProfScope p(s, "run_programs");

@@ -14,14 +14,15 @@ namespace vc {
 void launch_run_programs(const uint64_t *prog_off, uint64_t n_prog, const uint32_t *words, uint32_t n_vars,
                          const uint64_t *choice, const uint8_t *init, uint64_t fuel, uint64_t *steps,
                          uint64_t *effects, uint64_t *stuck, uint64_t *first, uint8_t *done, uint8_t *final_out,
-                         bool short_programs, hipStream_t s);
+                         uint64_t longest, uint32_t depth, hipStream_t s);
 }
 
 struct vc_programs {
     vc_ctx *ctx = nullptr;
     uint64_t n_prog = 0, n_words = 0, fuel = 0;
     uint32_t n_vars = 0;
-    bool short_programs = false; // every program shorter than 2^16 words
+    uint64_t longest = 0; // words of the longest program
+    uint32_t depth = 0;   // deepest nesting
     uint64_t *prog_off = nullptr, *choice = nullptr;
     uint32_t *words = nullptr;
     uint8_t *init = nullptr;
@@ -34,9 +35,11 @@ namespace {
 constexpr int MAX_DEPTH = 16;
 
 // words [a, b) of one program: well-formed statements inside their enclosing block
-bool valid_block(const uint32_t *w, uint64_t a, uint64_t b, uint32_t n_vars, int depth, uint64_t *bad)
+bool valid_block(const uint32_t *w, uint64_t a, uint64_t b, uint32_t n_vars, int depth, uint64_t *bad,
+                 int *deepest)
 {
     uint64_t pc = a;
+    *deepest = std::max(*deepest, depth);
     while (pc < b) {
         const uint32_t word = w[pc], kind = word >> 30, x = word & 0xFFFFFFu;
         if (kind == 0) {
@@ -59,8 +62,8 @@ bool valid_block(const uint32_t *w, uint64_t a, uint64_t b, uint32_t n_vars, int
             *bad = pc;
             return false;
         }
-        if (!valid_block(w, pc + hdr, pc + hdr + n, n_vars, depth + 1, bad) ||
-            !valid_block(w, pc + hdr + n, pc + hdr + n + m, n_vars, depth + 1, bad))
+        if (!valid_block(w, pc + hdr, pc + hdr + n, n_vars, depth + 1, bad, deepest) ||
+            !valid_block(w, pc + hdr + n, pc + hdr + n + m, n_vars, depth + 1, bad, deepest))
             return false;
         pc += hdr + n + m;
     }
@@ -102,7 +105,7 @@ extern "C" int vc_programs_run(vc_programs *p)
     ProfGuard pg(p->ctx);
     const uint64_t n = p->n_prog;
     launch_run_programs(p->prog_off, n, p->words, p->n_vars, p->choice, p->init, p->fuel, p->out, p->out + n,
-                        p->out + 2 * n, p->out + 3 * n, p->done, p->fin, p->short_programs, p->ctx->stream);
+                        p->out + 2 * n, p->out + 3 * n, p->done, p->fin, p->longest, p->depth, p->ctx->stream);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? VC_OK : vc_hip_fail(e, "kernel launch");
 }
@@ -118,12 +121,13 @@ extern "C" int vc_run_programs(vc_ctx *c, const uint64_t *prog_off, uint64_t n_p
     if (prog_off[0] != 0)
         return vc_fail(VC_EINVAL, "vc_run_programs: offsets must start at 0");
     uint64_t longest = 0;
+    int deepest = 0;
     for (uint64_t i = 0; i < n_prog; i++) {
         if (prog_off[i + 1] < prog_off[i] || prog_off[i + 1] - prog_off[i] >= (1ull << 31))
             return vc_fail(VC_EINVAL, "vc_run_programs: offsets of program %llu", (unsigned long long)i);
         longest = std::max<uint64_t>(longest, prog_off[i + 1] - prog_off[i]);
         uint64_t bad = 0;
-        if (!valid_block(words, prog_off[i], prog_off[i + 1], n_vars, 0, &bad))
+        if (!valid_block(words, prog_off[i], prog_off[i + 1], n_vars, 0, &bad, &deepest))
             return vc_fail(VC_EINVAL, "malformed program word at index %llu", (unsigned long long)bad);
     }
     if (init)
@@ -138,7 +142,8 @@ extern "C" int vc_run_programs(vc_ctx *c, const uint64_t *prog_off, uint64_t n_p
     p->n_words = prog_off[n_prog];
     p->n_vars = n_vars;
     p->fuel = fuel;
-    p->short_programs = longest < (1ull << 16);
+    p->longest = longest;
+    p->depth = (uint32_t)deepest;
     int r;
     if ((r = upload(&p->prog_off, prog_off, n_prog + 1)) != VC_OK || (r = upload(&p->words, words, p->n_words)) != VC_OK ||
         (choice && (r = upload(&p->choice, choice, n_prog)) != VC_OK) ||

@@ -75,3 +75,39 @@ def test_programs_workload_full_size(ctx):
     say("[programs] generating the full-size workload")
     P = gen.structured_programs(1 << 20, 16, 0)
     assert_parity(ctx, P, 1 << 12, label="full size")
+
+
+def _with_empty_blocks(rng, n_vars, depth):
+    """Statements whose While bodies and If branches are often empty."""
+    out = []
+    for _ in range(int(rng.integers(1, 4))):
+        u = rng.random()
+        cond = (int(rng.integers(3)), int(rng.integers(n_vars)))
+        sub = lambda: _with_empty_blocks(rng, n_vars, depth - 1) if depth and rng.random() < 0.6 else []  # noqa: E731
+        if u < 0.3:
+            out.append(("W", cond, sub()))
+        elif u < 0.6:
+            out.append(("I", cond, sub(), sub()))
+        else:
+            out.append(("E", int(rng.integers(5)), int(rng.integers(2)), int(rng.integers(n_vars))))
+    return out
+
+
+@pytest.mark.parametrize("n_vars", [16, 17, 32, 33])
+@pytest.mark.parametrize("longest", [40, 247, 248, 249, 255, 256, 257, 600])
+def test_programs_step_limits(ctx, n_vars, longest):
+    """Around the longest program that runs as steps in LDS, and the numbers of variables
+    whose statuses fit one and two registers: the padded program is the only long one;
+    blocks are often empty, and fuel ends some."""
+    rng = np.random.default_rng(longest * 100 + n_vars)
+    progs = [gen.program_words(_with_empty_blocks(rng, n_vars, 3)) for _ in range(150)]
+    progs = [p for p in progs if len(p) <= min(longest, 200)]
+    pad = [("E", int(rng.integers(5)), int(rng.integers(2)), n_vars - 1) for _ in range(longest)]
+    progs[len(progs) // 2] = gen.program_words(pad)
+    off = np.zeros(len(progs) + 1, np.uint64)
+    np.cumsum([len(p) for p in progs], out=off[1:])
+    P = gen.Programs(off, np.concatenate([np.array(p, np.uint32) for p in progs]), n_vars,
+                     rng.integers(0, 1 << 63, len(progs), dtype=np.uint64),
+                     rng.integers(0, 4, len(progs) * n_vars).astype(np.uint8))
+    for fuel in (0, 7, 700):
+        assert_parity(ctx, P, fuel, label=f"longest {longest}, {n_vars} variables")
