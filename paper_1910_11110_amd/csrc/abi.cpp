@@ -15,6 +15,7 @@
 
 #include "abi_internal.h"
 #include "bucket.h"
+#include "dense.h"
 #include "internal.h"
 
 using namespace vc;
@@ -476,6 +477,12 @@ static bool use_small_path(const vc_trace *t)
            !getenv("VC_GENERAL_PATH");
 }
 
+// path for id spaces whose statuses fit LDS: chunks of the trace in program order
+static bool use_dense_path(const vc_trace *t)
+{
+    return !t->has_arrays && t->n_ids > small_max_ids() && t->n_ids <= DENSE_MAX_IDS && !getenv("VC_GENERAL_PATH");
+}
+
 // path for larger id spaces: bucket partition, per-bucket scan, replay
 static bool use_bucket_path(const vc_trace *t)
 {
@@ -531,6 +538,16 @@ int enqueue_check(vc_trace *t, hipStream_t s)
             (void)hipMemcpyAsync(fin, t->init, t->n_ids, hipMemcpyDeviceToDevice, s);
         launch_small_check(t->events, t->n, t->n_ids, t->init, (uint8_t *)t->status.p, fin, (uint32_t *)t->viol.p,
                            t->scratch.p, t->ctl, s, 8u * (unsigned)t->ctx->cu_count, t->init ? nullptr : &fill);
+        return VC_OK;
+    }
+    if (use_dense_path(t)) {
+        if ((r = devbuf_reserve(t->status, t->n ? t->n : 1)) != VC_OK ||
+            (r = devbuf_reserve(t->fin, t->n_ids ? t->n_ids : 1)) != VC_OK ||
+            (r = devbuf_reserve(t->viol, (t->n ? t->n : 1) * 4)) != VC_OK ||
+            (r = devbuf_reserve(t->scratch, dense_scratch_bytes(t->n, t->n_ids))) != VC_OK)
+            return r;
+        launch_dense_check(t->events, t->n, t->n_ids, t->init, (uint8_t *)t->status.p, (uint8_t *)t->fin.p,
+                           (uint32_t *)t->viol.p, t->scratch.p, t->ctl, s);
         return VC_OK;
     }
     if (use_bucket_path(t)) {

@@ -89,33 +89,6 @@ constexpr int LB_WIN = 4;
 // ----------------------------------------------------------------------------------
 // Digit ranking
 // ----------------------------------------------------------------------------------
-// bit B of v as 0 or all ones.  An opaque v_bfe_i32: the ballot then tests this word
-// (one compare) instead of the compiler rederiving the bit from v (two more operations).
-template <int B>
-__device__ __forceinline__ uint32_t sign_bit(uint32_t v)
-{
-    uint32_t r;
-    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(r) : "v"(v), "i"(B));
-    return r;
-}
-
-// keeps in (mlo, mhi) the lanes of the wave whose bit agrees with this lane's, given
-// as `sel` (0 or all ones); match_bits does so for bits [B, N) of d
-__device__ __forceinline__ void match_bit(uint32_t sel, uint32_t &mlo, uint32_t &mhi)
-{
-    const uint64_t bb = __ballot(sel != 0);
-    mlo &= ~(sel ^ (uint32_t)bb);
-    mhi &= ~(sel ^ (uint32_t)(bb >> 32));
-}
-template <int B, int N>
-__device__ __forceinline__ void match_bits(uint32_t d, uint32_t &mlo, uint32_t &mhi)
-{
-    if constexpr (B < N) {
-        match_bit(sign_bit<B>(d), mlo, mhi);
-        match_bits<B + 1, N>(d, mlo, mhi);
-    }
-}
-
 // Stable ranking of a tile's words by a digit (striped arrangement: item j of lane l
 // in wave w is tile position w*64*ITEMS + j*64 + l); per-wave digit counters in LDS.
 // The lanes holding the same digit as this lane are found bit by bit: the lane's bit

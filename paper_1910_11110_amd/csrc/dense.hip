@@ -1,0 +1,734 @@
+// dense.hip -- check of a trace in program order, the statuses of all its ids in LDS
+// (gfx950).
+//
+// For id spaces up to 2^16.  The trace is cut into chunks, one wave each, and no event is
+// moved:
+// 1. fold: a wave walks its chunk backwards, 64 events a step, and composes every id's
+//    transition function over the chunk in a table in LDS (3 bits an id); the table is
+//    the chunk's row in memory.  Going backwards, an id whose function has become a
+//    constant (its last write) is done, so frequent ids soon cost nothing.
+// 2. prefix: per word of the rows (8 ids at once by bit operations), the rows composed
+//    in order from the initial statuses give the statuses entering every chunk, in
+//    place, and the final ones.
+// 3. apply: a wave walks its chunk forwards from its entering statuses; an event reads
+//    its id's status, leaves the new one and its status byte is stored.
+// A step's 64 events update the table in one go unless two of them share an id: each event
+// sets its id's touch bit by the same atomic that reads the id's table word, so a lane
+// that finds the bit set knows.  The lanes of a shared id (rare over many ids, the rule
+// over few or over skewed ones) are put in order by composing their functions along them.
+#include "dense.h"
+#include "device.h"
+#include "prof.h"
+
+namespace vc {
+
+namespace {
+
+// ----------------------------------------------------------------------------------
+// Table words: 8 ids of 3 bits and, in the top byte, a touch bit for each (zero between
+// steps).  An id's bits are a monoid element: bit 2 a constant, whose status is bits 0
+// (CPU copy valid) and 1 (GPU); else bit 0 "CPU |= GPU" and bit 1 "GPU |= CPU".
+// ----------------------------------------------------------------------------------
+constexpr uint32_t T_TOUCH = 1u << 24;
+constexpr uint32_t MX = 011111111u, MY = MX << 1, MT = MX << 2;
+
+// h o f (f first), 8 ids at once (counters zero)
+__device__ __forceinline__ uint32_t tw_compose(uint32_t h, uint32_t f)
+{
+    const uint32_t ftx = (f >> 2) & MX, htx = (h >> 2) & MX;
+    const uint32_t ex = f | (h & (~ftx | (f >> 1)));
+    const uint32_t ey = f | (h & (~(ftx << 1) | (f << 1)));
+    const uint32_t hx = htx | (htx << 1); // fields that h makes constant
+    return ((h | f) & MT) | (((h & hx) | (((ex & MX) | (ey & MY)) & ~hx)));
+}
+
+// the same on one id's 3 bits
+__device__ __forceinline__ uint32_t el_compose(uint32_t h, uint32_t f)
+{
+    const uint32_t ft = f >> 2;
+    const uint32_t ex = f | (h & ((ft ^ 1u) | (f >> 1)));
+    const uint32_t ey = f | (h & (((ft ^ 1u) << 1) | (f << 1)));
+    const uint32_t r = ((h | f) & 4u) | (ex & 1u) | (ey & 2u);
+    return (h & 4u) ? h : r;
+}
+
+// Per (op | side << 3): an effect's element; for the backward walk the element h o f for
+// every h, 3 bits each; for the forward walk the status byte for every status before the
+// event, 8 bits each.  In constant memory, copied to LDS by every wave.
+constexpr uint32_t host_compose(uint32_t h, uint32_t f)
+{
+    if (h & 4u)
+        return h;
+    const uint32_t x = (f & 1u) | ((h & 1u) & ((f & 4u) ? (f >> 1) & 1u : 1u));
+    const uint32_t y = ((f >> 1) & 1u) | (((h >> 1) & 1u) & ((f & 4u) ? f & 1u : 1u));
+    return (f & 4u) | x | (y << 1);
+}
+struct StepTable {
+    uint32_t fold[16];  // (h o f) << 3h, the element in bits 24-26
+    uint32_t apply[16]; // status byte << 8s
+};
+constexpr StepTable make_step_table()
+{
+    StepTable t{};
+    for (uint32_t i = 0; i < 16; i++) {
+        const uint32_t op = i & 7u, side = i >> 3, own = side ? 2u : 1u;
+        uint32_t e = 0;
+        if (op == OP_W)
+            e = 4u | own;
+        else if (op == OP_PUSH)
+            e = side ? 1u : 2u;
+        else if (op == OP_PULL)
+            e = side ? 2u : 1u;
+        for (uint32_t h = 0; h < 8; h++)
+            t.fold[i] |= host_compose(h, e) << (3 * h);
+        t.fold[i] |= e << 24;
+        const Effect x = make_effect(op <= OP_NOOP ? op : (uint32_t)OP_NOOP, side);
+        for (uint32_t s = 0; s < 4; s++) {
+            const uint32_t post = (x.f4 >> (8 * s)) & 3u;
+            t.apply[i] |= (post | (s << 2) | (((x.stuck >> s) & 1u) << 7)) << (8 * s);
+        }
+    }
+    return t;
+}
+__constant__ constexpr StepTable STEPS = make_step_table();
+
+__device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory"); }
+
+// (relaxed: one wave, whose LDS operations execute in order)
+__device__ __forceinline__ uint32_t tab_touch(uint32_t *p, uint32_t bit)
+{
+    return __hip_atomic_fetch_or(p, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ __forceinline__ void tab_untouch(uint32_t *p, uint32_t bit)
+{
+    (void)__hip_atomic_fetch_and(p, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ __forceinline__ void tab_xor(uint32_t *p, uint32_t v)
+{
+    (void)__hip_atomic_fetch_xor(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ __forceinline__ uint32_t tab_load(const uint32_t *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
+// the lanes of `among` with this lane's id (ids of `bits` bits, at most 16)
+__device__ __forceinline__ uint64_t same_id(uint32_t id, uint64_t among, uint32_t bits)
+{
+    uint32_t lo = (uint32_t)among, hi = (uint32_t)(among >> 32);
+    match_bits<0, 4>(id, lo, hi);
+    if (bits > 4)
+        match_bits<4, 8>(id, lo, hi);
+    if (bits > 8)
+        match_bits<8, 12>(id, lo, hi);
+    if (bits > 12)
+        match_bits<12, 16>(id, lo, hi);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// Composition of the functions (4-byte form) of the lanes of a lane's id up to and with
+// it, by pointer jumping along them; p is the nearest lower one, 64 if none.  BACK: lower
+// lanes are later events (their function comes last).  The pointer travels in the bits
+// that a function's bytes leave free.  Q steps at once, independent of each other.
+template <bool BACK, int Q>
+__device__ __forceinline__ void compose_along(uint32_t (&f)[Q], uint32_t (&p)[Q])
+{
+    constexpr uint32_t F4 = 0x03030303u, NONE = 64u << 4;
+    for (;;) {
+        bool more = false;
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            // (forwards, nothing before a constant matters: a constant's byte 0 is not 0)
+            if (!BACK && (f[q] & 3u))
+                p[q] = 64u;
+            more = more || p[q] < 64u;
+        }
+        if (!__ballot(more))
+            break;
+        uint32_t v[Q];
+#pragma unroll
+        for (int q = 0; q < Q; q++)
+            v[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(p[q] * 4u),
+                                                          (int)(f[q] | ((p[q] & 63u) << 2) | ((p[q] & 64u) << 4)));
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            const uint32_t g = p[q] < 64u ? v[q] & F4 : F_ID;
+            f[q] = BACK ? fcompose(g, f[q]) : fcompose(f[q], g);
+            p[q] = p[q] < 64u && !(v[q] & NONE) ? (v[q] >> 2) & 63u : 64u;
+        }
+    }
+}
+
+// a function in 4-byte form as an element
+__device__ __forceinline__ uint32_t el_of(uint32_t f4)
+{
+    return ((f4 >> 16) & 1u) | ((f4 >> 8) & 2u) | ((f4 & 3u) ? 4u : 0u);
+}
+
+constexpr int D_UNROLL = 8; // steps whose events are loaded together
+
+// the chunks of one trace: `per` events each (a multiple of 64), the last one the rest
+struct TraceChunks {
+    const uint32_t *ev;
+    uint64_t n, per;
+    uint32_t n_ids, chunks;
+    __device__ uint64_t begin(uint32_t c) const { return (uint64_t)c * per; }
+    __device__ uint64_t end(uint32_t c) const
+    {
+        const uint64_t e = (uint64_t)(c + 1) * per;
+        return e < n ? e : n;
+    }
+    __device__ bool bad(uint32_t w) const
+    {
+        return (w >> 28) != 0 || ((w >> 24) & 7u) > OP_NOOP || (w & 0xFFFFFFu) >= n_ids;
+    }
+};
+
+// ----------------------------------------------------------------------------------
+// A step: 64 events, one a lane.  DIR says what an event does to its id's bits.
+// ----------------------------------------------------------------------------------
+// backwards: the id's function after the event's first.  An event that changes nothing
+// takes no part, nor does one whose id is a constant already.
+struct Fold {
+    static constexpr bool BACK = true;
+    __device__ static uint32_t entry(const uint32_t *tab, uint32_t op) { return tab[op]; }
+    __device__ static bool takes_part(uint32_t e) { return (e >> 24) != 0; }
+    __device__ static bool open(uint32_t h) { return (h & 4u) == 0; }
+    // the bits after the event, and the result byte
+    __device__ static uint32_t next(uint32_t e, uint32_t h, uint32_t &) { return (e >> (3u * h)) & 7u; }
+};
+// forwards: the status after the event, and its status byte
+struct Apply {
+    static constexpr bool BACK = false;
+    __device__ static uint32_t entry(const uint32_t *tab, uint32_t op) { return tab[16 + op]; }
+    __device__ static bool takes_part(uint32_t) { return true; }
+    __device__ static bool open(uint32_t) { return true; }
+    __device__ static uint32_t next(uint32_t e, uint32_t h, uint32_t &byte)
+    {
+        byte = e >> (8u * (h & 3u));
+        return 4u | (byte & 3u);
+    }
+};
+
+struct Lane { // one lane's event in a step
+    uint32_t *p;
+    uint32_t id, entry, old, op; // op | side << 3
+    bool part;
+    __device__ uint32_t sh() const { return 3u * (id & 7u); }
+    __device__ uint32_t touch() const { return T_TOUCH << (id & 7u); }
+    __device__ uint32_t f4(const uint32_t *s_tab) const { return s_tab[16 + op]; }
+    __device__ bool met() const { return part && (old & touch()) != 0; }
+    __device__ void enter()
+    {
+        old = 0;
+        if (part)
+            old = tab_touch(p, touch());
+    }
+    __device__ void leave() const
+    {
+        if (part)
+            tab_untouch(p, touch());
+    }
+};
+
+template <class DIR>
+__device__ __forceinline__ Lane make_lane(uint32_t *s_t, const uint32_t *s_tab, uint32_t w, uint32_t id, bool in)
+{
+    Lane L;
+    L.id = id;
+    L.p = s_t + (id >> 3);
+    L.op = (w >> 24) & 15u;
+    L.entry = DIR::entry(s_tab, L.op);
+    L.part = in && DIR::takes_part(L.entry);
+    L.old = 0;
+    return L;
+}
+
+// no two lanes share an id
+template <class DIR>
+__device__ __forceinline__ uint32_t step_apart(const Lane &L)
+{
+    const uint32_t h = (L.old >> L.sh()) & 7u;
+    uint32_t byte = 0;
+    const uint32_t nh = DIR::next(L.entry, h, byte);
+    if (L.part)
+        tab_xor(L.p, ((h ^ nh) << L.sh()) | L.touch());
+    return byte;
+}
+
+// Q steps whose lanes may share ids, one after the other; no touch bit is set.  What the
+// lanes of an id do together does not depend on the table, so the steps work it out side
+// by side.  `shared` counts the steps where any did.
+template <class DIR, int Q>
+__device__ __forceinline__ void steps_together(const Lane (&L)[Q], uint32_t (&byte)[Q], const uint32_t *s_tab,
+                                               uint32_t bits, uint32_t lane, uint32_t &shared)
+{
+    uint32_t f[Q], p[Q], prev[Q];
+    bool in[Q], last[Q];
+#pragma unroll
+    for (int q = 0; q < Q; q++) // (a later step's id may close before it: it then changes nothing)
+        in[q] = L[q].part && (!DIR::BACK || DIR::open((tab_load(L[q].p) >> L[q].sh()) & 7u));
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+        const uint64_t same = same_id(L[q].id, __ballot(in[q]), bits);
+        const uint32_t rank = mask_rank(same);
+        const uint64_t below = same & ((1ull << lane) - 1);
+        prev[q] = p[q] = in[q] && rank ? 63u - (uint32_t)__builtin_clzll(below) : 64u;
+        last[q] = in[q] && rank + 1 == (uint32_t)__builtin_popcountll(same); // of its id
+        f[q] = (DIR::BACK ? L[q].f4(s_tab) : L[q].entry) & 0x03030303u;
+        shared += __ballot(prev[q] < 64) ? 1u : 0u;
+    }
+    compose_along<DIR::BACK, Q>(f, p);
+    uint32_t g[Q];
+    if constexpr (!DIR::BACK)
+#pragma unroll
+        for (int q = 0; q < Q; q++)
+            g[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((prev[q] & 63u) * 4u), (int)f[q]);
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+        const uint32_t h = (tab_load(L[q].p) >> L[q].sh()) & 7u;
+        uint32_t nh;
+        if constexpr (DIR::BACK)
+            nh = el_compose(h, el_of(f[q]));
+        else
+            nh = DIR::next(L[q].entry, prev[q] < 64 ? fapply(g[q], h & 3u) : h, byte[q]);
+        if (last[q])
+            tab_xor(L[q].p, (h ^ nh) << L[q].sh());
+        compiler_fence();
+    }
+}
+
+// D_PAIR steps at once: all enter, and when no lane met a touched id, neither of its own
+// step nor of the ones before it, their reads are one wait and their changes independent.
+// Otherwise all leave and take their turns.
+constexpr int D_PAIR = 2;
+template <class DIR>
+__device__ __forceinline__ void steps(Lane (&L)[D_PAIR], uint32_t (&byte)[D_PAIR], const uint32_t *s_tab,
+                                      uint32_t bits, uint32_t lane, uint32_t &shared_steps)
+{
+    bool met = false;
+#pragma unroll
+    for (int q = 0; q < D_PAIR; q++)
+        L[q].enter();
+#pragma unroll
+    for (int q = 0; q < D_PAIR; q++)
+        met = met || L[q].met();
+    if (!__ballot(met)) {
+#pragma unroll
+        for (int q = 0; q < D_PAIR; q++)
+            byte[q] = step_apart<DIR>(L[q]);
+        return;
+    }
+    compiler_fence();
+#pragma unroll
+    for (int q = 0; q < D_PAIR; q++)
+        L[q].leave();
+    compiler_fence();
+#pragma unroll
+    for (int q = 0; q < D_PAIR; q++) {
+        if (DIR::BACK && L[q].part) // ids that are constants already take no part
+            L[q].part = DIR::open((tab_load(L[q].p) >> L[q].sh()) & 7u);
+        L[q].enter();
+        if (!__ballot(L[q].met())) {
+            byte[q] = step_apart<DIR>(L[q]);
+        } else {
+            L[q].leave();
+            compiler_fence();
+            const Lane one[1] = {L[q]};
+            uint32_t b[1] = {0};
+            steps_together<DIR, 1>(one, b, s_tab, bits, lane, shared_steps);
+            byte[q] = b[0];
+        }
+        compiler_fence();
+    }
+}
+
+// a round whose last one had shared ids in at least so many of its steps expects them in
+// every step, and looks for them at once
+constexpr uint32_t D_TOGETHER = D_UNROLL / 2;
+
+__device__ __forceinline__ void load_step_table(uint32_t *s_tab, uint32_t lane)
+{
+    if (lane < 32)
+        s_tab[lane] = lane < 16 ? STEPS.fold[lane] : STEPS.apply[lane - 16];
+    compiler_fence();
+}
+
+// 1. every chunk's functions into its row
+__global__ __launch_bounds__(WAVE) void k_dense_fold(TraceChunks T, uint32_t row, uint32_t *__restrict__ rows,
+                                                     Control *ctl)
+{
+    extern __shared__ __align__(16) uint32_t s_t[];
+    uint32_t *const s_tab = s_t + row;
+    const uint32_t lane = threadIdx.x, bits = 32u - (uint32_t)__builtin_clz(T.n_ids | 1u);
+    load_step_table(s_tab, lane);
+    for (uint32_t c = blockIdx.x; c < T.chunks; c += gridDim.x) {
+        const uint64_t i0 = T.begin(c), i1 = T.end(c);
+        const uint32_t len = (uint32_t)(i1 - i0), rounds = len / (D_UNROLL * WAVE);
+        for (uint32_t i = lane; i < row / 4; i += WAVE)
+            reinterpret_cast<uint4 *>(s_t)[i] = make_uint4(0, 0, 0, 0);
+        compiler_fence();
+        // (a malformed word is a Noop on id 0)
+        auto clean = [&](uint32_t w, bool bad) { return bad ? (uint32_t)OP_NOOP << 24 : w; };
+        auto report = [&](uint64_t i) {
+            atomicMin(reinterpret_cast<unsigned long long *>(&ctl->err_index_lo), (unsigned long long)i);
+        };
+        uint32_t shared_steps = 0;
+        // the events past the whole rounds, one step at a time
+        for (uint32_t left = len - rounds * (D_UNROLL * WAVE); left;) {
+            const uint32_t m = left < WAVE ? left : WAVE;
+            const uint64_t i = i0 + rounds * (D_UNROLL * WAVE) + left - 1 - lane;
+            const bool in = lane < m;
+            uint32_t w = in ? T.ev[i] : (uint32_t)OP_NOOP << 24;
+            if (T.bad(w)) {
+                report(i);
+                w = clean(w, true);
+            }
+            const Lane one[1] = {make_lane<Fold>(s_t, s_tab, w, w & 0xFFFFu, in)};
+            uint32_t none[1];
+            steps_together<Fold, 1>(one, none, s_tab, bits, lane, shared_steps);
+            left -= m;
+        }
+        // whole rounds: lane l takes the round's last event but l, then 64 before, ...
+        const uint32_t *const e0 = T.ev + i0 - 1 - lane;
+        uint32_t nxt[D_UNROLL];
+        auto load = [&](uint32_t r) {
+            const uint32_t *e = e0 + (uint64_t)r * (D_UNROLL * WAVE);
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u++)
+                nxt[u] = e[-(u * WAVE)];
+        };
+        if (rounds)
+            load(rounds);
+        for (uint32_t r = rounds; r > 0; r--) {
+            uint32_t w[D_UNROLL], badm = 0;
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u++) {
+                const bool bad = T.bad(nxt[u]);
+                badm |= bad ? 1u << u : 0u;
+                w[u] = clean(nxt[u], bad);
+            }
+            if (r > 1)
+                load(r - 1);
+            if (__ballot(badm != 0)) {
+                if (badm) // the lane's first malformed event is its last step's
+                    report(i0 + (uint64_t)r * (D_UNROLL * WAVE) - 1 - lane -
+                           WAVE * (31u - (uint32_t)__builtin_clz(badm)));
+            }
+            if (shared_steps >= D_TOGETHER) {
+                shared_steps = 0;
+                const uint32_t *e = e0 + (uint64_t)r * (D_UNROLL * WAVE);
+                uint32_t v[D_PAIR] = {w[0], w[1]};
+#pragma unroll 1
+                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
+                    Lane L[D_PAIR];
+                    uint32_t none[D_PAIR];
+                    const int n = u + D_PAIR < D_UNROLL ? u + D_PAIR : u;
+#pragma unroll
+                    for (int q = 0; q < D_PAIR; q++) {
+                        const uint32_t x = clean(v[q], T.bad(v[q]));
+                        v[q] = e[-((n + q) * WAVE)];
+                        L[q] = make_lane<Fold>(s_t, s_tab, x, x & 0xFFFFu, true);
+                    }
+                    steps_together<Fold, D_PAIR>(L, none, s_tab, bits, lane, shared_steps);
+                }
+                continue;
+            }
+            shared_steps = 0;
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u += D_PAIR) {
+                Lane L[D_PAIR];
+                uint32_t byte[D_PAIR];
+#pragma unroll
+                for (int q = 0; q < D_PAIR; q++)
+                    L[q] = make_lane<Fold>(s_t, s_tab, w[u + q], w[u + q] & 0xFFFFu, true);
+                steps<Fold>(L, byte, s_tab, bits, lane, shared_steps);
+            }
+        }
+        compiler_fence();
+        uint4 *out = reinterpret_cast<uint4 *>(rows + (uint64_t)c * row);
+        for (uint32_t i = lane; i < row / 4; i += WAVE)
+            out[i] = reinterpret_cast<const uint4 *>(s_t)[i];
+        compiler_fence();
+    }
+}
+
+// 2. prefix over the rows, by groups of D_GROUP chunks: a thread per word and group.  The
+// first kernel folds every group's rows; the second walks them from the statuses entering
+// the group (the initial ones and the groups before) and leaves every chunk's entering
+// statuses in its row; the last group's end is the final table.
+constexpr uint32_t D_GROUP = 32;
+
+__global__ __launch_bounds__(BLOCK) void k_dense_groups(const uint32_t *__restrict__ rows, uint32_t row,
+                                                        uint32_t chunks, uint32_t *__restrict__ grp)
+{
+    const uint32_t w = blockIdx.x * BLOCK + threadIdx.x, g = blockIdx.y;
+    if (w >= row)
+        return;
+    const uint32_t c0 = g * D_GROUP, c1 = c0 + D_GROUP < chunks ? c0 + D_GROUP : chunks;
+    uint32_t f = 0;
+#pragma unroll 8
+    for (uint32_t c = c0; c < c1; c++)
+        f = tw_compose(rows[(uint64_t)c * row + w], f);
+    grp[(uint64_t)g * row + w] = f;
+}
+
+__global__ __launch_bounds__(BLOCK) void k_dense_prefix(uint32_t *__restrict__ rows, uint32_t row, uint32_t chunks,
+                                                        const uint32_t *__restrict__ grp, uint32_t n_ids,
+                                                        const uint8_t *__restrict__ init,
+                                                        uint8_t *__restrict__ final_out)
+{
+    const uint32_t w = blockIdx.x * BLOCK + threadIdx.x, g = blockIdx.y;
+    if (w >= row)
+        return;
+    uint32_t st = 0; // constants
+#pragma unroll
+    for (uint32_t k = 0; k < 8; k++) {
+        const uint32_t id = w * 8 + k;
+        st |= (4u | (init && id < n_ids ? init[id] & 3u : 1u)) << (3 * k);
+    }
+#pragma unroll 8
+    for (uint32_t q = 0; q < g; q++)
+        st = tw_compose(grp[(uint64_t)q * row + w], st);
+    const uint32_t c0 = g * D_GROUP, c1 = c0 + D_GROUP < chunks ? c0 + D_GROUP : chunks;
+#pragma unroll 8
+    for (uint32_t c = c0; c < c1; c++) {
+        const uint32_t f = rows[(uint64_t)c * row + w];
+        rows[(uint64_t)c * row + w] = st;
+        st = tw_compose(f, st);
+    }
+    if (c1 == chunks)
+#pragma unroll
+        for (uint32_t k = 0; k < 8; k++)
+            if (w * 8 + k < n_ids)
+                final_out[w * 8 + k] = (uint8_t)((st >> (3 * k)) & 3u);
+}
+
+// 3. the events' status bytes from their chunk's entering statuses; per step of 64 events
+// the mask of the flagged ones, per tile of D_TILE events their number
+constexpr uint32_t D_TILE = 1024;
+static_assert(D_TILE % (D_UNROLL * WAVE) == 0, "whole rounds of steps a tile");
+
+__global__ __launch_bounds__(WAVE) void k_dense_apply(TraceChunks T, uint32_t row, const uint32_t *__restrict__ rows,
+                                                      uint8_t *__restrict__ status, uint64_t *__restrict__ masks,
+                                                      uint32_t *__restrict__ tcnt)
+{
+    extern __shared__ __align__(16) uint32_t s_t[];
+    uint32_t *const s_tab = s_t + row;
+    const uint32_t lane = threadIdx.x, bits = 32u - (uint32_t)__builtin_clz(T.n_ids | 1u);
+    load_step_table(s_tab, lane);
+    for (uint32_t c = blockIdx.x; c < T.chunks; c += gridDim.x) {
+        const uint4 *in = reinterpret_cast<const uint4 *>(rows + (uint64_t)c * row);
+        const uint64_t i0 = T.begin(c), i1 = T.end(c);
+        const uint32_t len = (uint32_t)(i1 - i0), rounds = len / (D_UNROLL * WAVE);
+        uint32_t nxt[D_UNROLL];
+        auto load = [&](uint32_t r) {
+            const uint32_t *e = T.ev + i0 + (uint64_t)r * (D_UNROLL * WAVE) + lane;
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u++)
+                nxt[u] = e[u * WAVE];
+        };
+        if (rounds)
+            load(0);
+        for (uint32_t i = lane; i < row / 4; i += WAVE)
+            reinterpret_cast<uint4 *>(s_t)[i] = in[i];
+        compiler_fence();
+        // (a malformed word, which the fold reported, only has to stay inside the table)
+        auto id_of = [&](uint32_t w) {
+            const uint32_t x = w & 0xFFFFFFu;
+            return x < T.n_ids ? x : T.n_ids - 1;
+        };
+        uint32_t flagged = 0, shared_steps = 0;
+        uint64_t mask = 0; // lane u: the flagged events of step u of the round
+        auto put = [&](uint64_t i, int u, uint32_t byte) {
+            status[i + u * WAVE + lane] = (uint8_t)byte;
+            const uint64_t m = __ballot((byte & 0x80u) != 0);
+            mask = lane == (uint32_t)u ? m : mask;
+            flagged += (uint32_t)__builtin_popcountll(m);
+        };
+        for (uint32_t r = 0; r < rounds; r++) {
+            uint32_t w[D_UNROLL];
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u++)
+                w[u] = nxt[u];
+            if (r + 1 < rounds)
+                load(r + 1);
+            const uint64_t i = i0 + (uint64_t)r * (D_UNROLL * WAVE);
+            if (shared_steps >= D_TOGETHER) {
+                shared_steps = 0;
+                uint32_t v[D_PAIR] = {w[0], w[1]};
+#pragma unroll 1
+                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
+                    Lane L[D_PAIR];
+                    uint32_t byte[D_PAIR];
+                    const int n = u + D_PAIR < D_UNROLL ? u + D_PAIR : u;
+#pragma unroll
+                    for (int q = 0; q < D_PAIR; q++) {
+                        L[q] = make_lane<Apply>(s_t, s_tab, v[q], id_of(v[q]), true);
+                        v[q] = T.ev[i + (n + q) * WAVE + lane];
+                    }
+                    steps_together<Apply, D_PAIR>(L, byte, s_tab, bits, lane, shared_steps);
+#pragma unroll
+                    for (int q = 0; q < D_PAIR; q++)
+                        put(i, u + q, byte[q]);
+                }
+            } else {
+                shared_steps = 0;
+#pragma unroll
+                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
+                    Lane L[D_PAIR];
+                    uint32_t byte[D_PAIR];
+#pragma unroll
+                    for (int q = 0; q < D_PAIR; q++)
+                        L[q] = make_lane<Apply>(s_t, s_tab, w[u + q], id_of(w[u + q]), true);
+                    steps<Apply>(L, byte, s_tab, bits, lane, shared_steps);
+#pragma unroll
+                    for (int q = 0; q < D_PAIR; q++)
+                        put(i, u + q, byte[q]);
+                }
+            }
+            if (lane < D_UNROLL)
+                masks[i / WAVE + lane] = mask;
+            if ((i / (D_UNROLL * WAVE) + 1) % (D_TILE / (D_UNROLL * WAVE)) == 0) {
+                if (lane == 0)
+                    tcnt[i / D_TILE] = flagged;
+                flagged = 0;
+            }
+        }
+        // the events past the whole rounds, one step at a time
+        for (uint32_t k = rounds * (D_UNROLL * WAVE); k < len; k += WAVE) {
+            const bool valid = k + lane < len;
+            const uint32_t w = valid ? T.ev[i0 + k + lane] : (uint32_t)OP_NOOP << 24;
+            const Lane one[1] = {make_lane<Apply>(s_t, s_tab, w, id_of(w), valid)};
+            uint32_t b[1];
+            steps_together<Apply, 1>(one, b, s_tab, bits, lane, shared_steps);
+            const uint32_t byte = b[0];
+            if (valid)
+                status[i0 + k + lane] = (uint8_t)byte;
+            const uint64_t m = __ballot(valid && (byte & 0x80u));
+            flagged += (uint32_t)__builtin_popcountll(m);
+            if (lane == 0) {
+                masks[(i0 + k) / WAVE] = m;
+                if (k + WAVE >= len)
+                    tcnt[(i0 + k) / D_TILE] = flagged;
+            }
+        }
+        if (lane == 0 && rounds % (D_TILE / (D_UNROLL * WAVE)) && len == rounds * (D_UNROLL * WAVE))
+            tcnt[(i1 - 1) / D_TILE] = flagged;
+        compiler_fence();
+    }
+}
+
+// ascending indices of the flagged events, one wave per tile
+__global__ __launch_bounds__(BLOCK) void k_mask_scatter(const uint64_t *__restrict__ masks, uint64_t n,
+                                                        const uint64_t *__restrict__ offs, uint64_t ntiles,
+                                                        uint32_t *__restrict__ viol)
+{
+    constexpr uint32_t STEPS = D_TILE / WAVE;
+    const uint32_t lane = lane_id(), wave = threadIdx.x / WAVE;
+    for (uint64_t t = (uint64_t)blockIdx.x * (BLOCK / WAVE) + wave; t < ntiles;
+         t += (uint64_t)gridDim.x * (BLOCK / WAVE)) {
+        uint64_t o = offs[t];
+        const uint64_t nsteps = ceil_div(n, (uint64_t)WAVE);
+        const uint64_t mine = lane < STEPS && t * STEPS + lane < nsteps ? masks[t * STEPS + lane] : 0ull;
+#pragma unroll
+        for (uint32_t q = 0; q < STEPS; q++) {
+            const uint64_t m = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), q) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, q);
+            if ((m >> lane) & 1u)
+                viol[o + mask_rank(m)] = (uint32_t)(t * D_TILE + q * WAVE + lane);
+            o += (uint64_t)__builtin_popcountll(m);
+        }
+    }
+}
+
+// rows, groups, masks and tile counts of a trace; events per chunk
+struct DenseLayout {
+    uint32_t row, chunks, groups;
+    uint64_t per, tiles;
+    uint32_t *rows, *grp, *tcnt;
+    uint64_t *masks, *offs;
+    void *xscan;
+    size_t bytes;
+};
+
+// Events per chunk: whole tiles, and enough of them that a chunk's walk outweighs its row
+// (written, prefixed in place and read back); at most DENSE_CHUNKS chunks, which fill the
+// device with the widest tables (5 waves of 32 KiB on each of 256 CUs).
+// LDS of a wave: its table and the step table
+size_t dense_lds(uint32_t row) { return ((size_t)row + 32) * 4; }
+
+uint64_t dense_chunks(uint32_t row)
+{
+    const uint64_t waves = 163840 / dense_lds(row);
+    return 256 * (waves > 24 ? 24 : waves);
+}
+
+DenseLayout dense_layout(void *scratch, uint64_t n, uint32_t n_ids)
+{
+    DenseLayout L{};
+    const uint32_t words = (uint32_t)ceil_div(n_ids ? n_ids : 1, 8);
+    L.row = (words + 63u) & ~63u;
+    const uint64_t least = D_TILE;
+    uint64_t per = ceil_div(n ? n : 1, dense_chunks(L.row));
+    per = per < least ? least : per;
+    L.per = ceil_div(per, D_TILE) * D_TILE;
+    L.chunks = (uint32_t)ceil_div(n ? n : 1, L.per);
+    L.groups = (uint32_t)ceil_div(L.chunks, D_GROUP);
+    L.tiles = ceil_div(n ? n : 1, (uint64_t)D_TILE);
+    char *p0 = reinterpret_cast<char *>(scratch);
+    size_t off = 0;
+    auto take = [&](size_t sz) {
+        char *r = p0 ? p0 + off : nullptr;
+        off += (sz + 255) & ~size_t(255);
+        return r;
+    };
+    L.rows = (uint32_t *)take((size_t)L.chunks * L.row * 4);
+    L.grp = (uint32_t *)take((size_t)L.groups * L.row * 4);
+    L.masks = (uint64_t *)take(L.tiles * (D_TILE / WAVE) * 8);
+    L.tcnt = (uint32_t *)take(L.tiles * 4);
+    L.offs = (uint64_t *)take((L.tiles + 1) * 8);
+    L.xscan = take(excl_scan_scratch_bytes(L.tiles));
+    L.bytes = off;
+    return L;
+}
+
+} // namespace
+
+size_t dense_scratch_bytes(uint64_t n, uint32_t n_ids) { return dense_layout(nullptr, n, n_ids).bytes; }
+
+void launch_dense_check(const uint32_t *events, uint64_t n, uint32_t n_ids, const uint8_t *init, uint8_t *status,
+                        uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl, hipStream_t s)
+{
+    const DenseLayout L = dense_layout(scratch, n, n_ids);
+    const FillJob job{L.xscan, excl_scan_scratch_bytes(L.tiles), 0};
+    launch_prep(ctl, nullptr, &job, 1, s);
+    const TraceChunks T{events, n, L.per, n_ids, n ? L.chunks : 0u};
+    const size_t lds = dense_lds(L.row);
+    const dim3 pg((unsigned)ceil_div(L.row, BLOCK), L.groups);
+    if (n) {
+        ProfScope p(s, "dense_fold");
+        k_dense_fold<<<L.chunks, WAVE, lds, s>>>(T, L.row, L.rows, ctl);
+    }
+    if (n && L.groups > 1) {
+        ProfScope p(s, "dense_groups");
+        k_dense_groups<<<dim3(pg.x, L.groups - 1), BLOCK, 0, s>>>(L.rows, L.row, L.chunks, L.grp);
+    }
+    {
+        ProfScope p(s, "dense_prefix");
+        k_dense_prefix<<<pg, BLOCK, 0, s>>>(L.rows, L.row, T.chunks, L.grp, n_ids, init, final_out);
+    }
+    if (!n)
+        return;
+    {
+        ProfScope p(s, "dense_apply");
+        k_dense_apply<<<L.chunks, WAVE, lds, s>>>(T, L.row, L.rows, status, L.masks, L.tcnt);
+    }
+    launch_excl_scan(L.tcnt, L.tiles, L.offs, reinterpret_cast<uint64_t *>(&ctl->n_viol), L.xscan, ctl->tickets[10], s,
+                     true);
+    ProfScope p(s, "mask_scatter");
+    const uint64_t blocks = ceil_div(L.tiles, BLOCK / WAVE);
+    k_mask_scatter<<<(unsigned)(blocks < 8192 ? blocks : 8192), BLOCK, 0, s>>>(L.masks, n, L.offs, L.tiles, viol);
+}
+
+} // namespace vc
