@@ -369,7 +369,7 @@ __device__ __forceinline__ Planes lb_planes_exclusive(uint64_t *lb, uint32_t nwo
     Planes acc = first;
     if (tile > 0) {
         if (lane == 0)
-            lb_store(&lb[tile * nwords + w], LB_AGG | pl_pack(agg));
+            lb_store(&lb[tile * nwords + w], (agg.t == PL_MASK ? LB_INC : LB_AGG) | pl_pack(agg));
         acc = Planes{0, 0, 0};
         int64_t t = (int64_t)tile - 1;
         for (;;) {
@@ -390,14 +390,14 @@ __device__ __forceinline__ Planes lb_planes_exclusive(uint64_t *lb, uint32_t nwo
             }
             const Planes r{(uint32_t)__shfl(f.t, 0), (uint32_t)__shfl(f.x, 0), (uint32_t)__shfl(f.y, 0)};
             acc = pl_compose(acc, r);
-            if (inc_at_s)
+            if (inc_at_s || acc.t == PL_MASK)
                 break;
             if (s == 0)
                 __builtin_amdgcn_s_sleep(1);
             t -= (int64_t)s;
         }
     }
-    if (lane == 0)
+    if (lane == 0 && (tile == 0 || agg.t != PL_MASK))
         lb_store(&lb[tile * nwords + w], LB_INC | pl_pack(pl_compose(agg, acc)));
     return acc;
 }

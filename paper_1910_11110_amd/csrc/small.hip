@@ -1,23 +1,25 @@
 // small.hip -- single-pass check of a trace over at most 64 variables (gfx950).
 //
-// No sort.  The trace is cut into tiles of 8192 events in program order (512 threads,
-// eight waves); thread t of a tile owns events [16t, 16t + 16).  The state of all 64 variables is held as 64-bit
-// bit planes (bit v = variable v): a transition function of the 7-element monoid per
-// variable as three planes (T, X, Y), a status as two planes (C = CPU copy valid,
-// G = GPU copy valid).
-//   1. Each thread composes its 16 events into its own function planes (an event
-//      changes one bit of each plane).
-//   2. A wave scan of the function planes (DPP row shifts and row broadcasts) and the
-//      wave totals give every thread the composition of the tile's events before it.
-//   3. The tiles chain their statuses with a decoupled look-back on the tile's
-//      function: four self-flagged 64-bit words of 20 variables each (one wave per
-//      word).
-//   4. Each thread applies its prefix to the statuses entering the tile and replays its
-//      16 events on status planes: status bytes (one 16-byte store per thread) and the
-//      final statuses from the last tile.  The tile's count of flagged events and, per
-//      thread, its flag mask and offset inside the tile are stored; a scan of the tile
-//      counts and a scatter pass then write the ascending violation indices (no second
-//      chain of tiles).
+// No sort.  The trace is cut into tiles of 256 strands of EP consecutive events, one per
+// lane (EP 64, or 16 for short traces).  A lane walks its strand event by event with the
+// 64 variables' functions, then statuses, one byte each in an LDS column of its own, so
+// that neither a variable nor a lane ever waits for another.
+//   1. The tile's events are read in order, packed to 16 bits and handed to their lanes
+//      through LDS.
+//   2. Each lane composes its strand's functions: per event one byte read, one shift of a
+//      table word, one byte written.
+//   3. The bytes become 64-bit planes (T, X, Y: an element of the 7-element monoid per
+//      variable); a wave scan of the planes (DPP) and the wave totals give every lane the
+//      composition of the tile's strands before it.
+//   4. The tiles chain their statuses with a decoupled look-back on the tile's function:
+//      four self-flagged 64-bit words of 20 variables each (one wave per word).  A word
+//      whose variables were all written in the tile is final at once, so in an ordinary
+//      trace no tile waits for more than the one before it.
+//   5. Each lane applies its prefix to the statuses entering the tile and walks its strand
+//      again for the status bytes, which go out in order through LDS, and the final
+//      statuses come from the last tile.  The count of flagged events and, per 16 events,
+//      their mask and offset inside the tile are stored; a scan of the counts and a scatter
+//      pass then write the ascending violation indices (no second chain of tiles).
 #include "device.h"
 #include "internal.h"
 #include "prof.h"
@@ -26,30 +28,69 @@ namespace vc {
 
 namespace {
 
-constexpr EffectTable TABLE = make_table();
 constexpr int SK = 64;               // variables
-constexpr int SB = 512;              // threads per tile
+constexpr int SB = 256;              // threads per tile
 constexpr int SW = SB / WAVE;        // waves per tile
-constexpr int SE = FLAG_EVENTS;      // events per thread
-constexpr int STILE = SB * SE;       // events per tile
 constexpr int SPW = (SK + 19) / 20;  // look-back words per tile (20 variables each)
 static_assert(SPW <= SW, "one wave per look-back word");
-static_assert(SB >= 256, "one thread per entry of the event-byte table");
 
-// status after a monoid element (3-bit code) from a status: 2 bits at 2 * (code * 4 + s)
-constexpr uint64_t make_apply_table()
+// Events per lane: long strands share the cost of a strand's planes and scan, short ones
+// keep a short trace on more lanes and its walks short.  The line lies where the long ones
+// fill the device: 2^22 events take 20.1 us with 64 a lane and 17.7 with 16, 2^23 events
+// 22.8 and 30.0; 2^13 events 18.2 and 10.0.
+constexpr int EP_LONG = 64, EP_SHORT = 16;
+constexpr uint64_t LONG_FROM = 3ull << 21; // events
+constexpr int strand_of(uint64_t n) { return n >= LONG_FROM ? EP_LONG : EP_SHORT; }
+
+// Per effect (op | side << 3): for the composition walk the element after it for every
+// element before it, a nibble each (bit 2 a constant, whose status is bits 0 CPU and 1
+// GPU; else bit 0 "CPU |= GPU", bit 1 "GPU |= CPU"), with bit 3 of nibble 0 set for an op
+// past Noop; for the status walk the status byte for every status before it, a byte each.
+struct StrandTable {
+    uint32_t fold[16], apply[16];
+};
+constexpr StrandTable make_strand_table()
 {
-    uint64_t t = 0;
-    for (uint32_t c = 0; c < 8; c++)
-        for (uint32_t s = 0; s < 4; s++) {
-            const uint32_t T = (c >> 2) & 1u, X = (c >> 1) & 1u, Y = c & 1u;
-            const uint32_t cb = s & 1u, gb = (s >> 1) & 1u;
-            const uint32_t r = T ? (X | (Y << 1)) : ((cb | (X & gb)) | ((gb | (Y & cb)) << 1));
-            t |= (uint64_t)r << (2 * (c * 4 + s));
+    StrandTable t{};
+    for (uint32_t i = 0; i < 16; i++) {
+        const uint32_t op = i & 7u;
+        const Effect e = make_effect(op <= OP_NOOP ? op : (uint32_t)OP_NOOP, i >> 3);
+        for (uint32_t h = 0; h < 8; h++) {
+            // the element as a function, followed by the effect, as an element again
+            uint32_t f[4] = {};
+            for (uint32_t s = 0; s < 4; s++) {
+                const uint32_t x = h & 1u, y = (h >> 1) & 1u, c = s & 1u, g = s >> 1;
+                const uint32_t m = (h & 4u) ? (h & 3u) : ((c | (x & g)) | ((g | (y & c)) << 1));
+                f[s] = (e.f4 >> (8 * m)) & 3u;
+            }
+            const uint32_t r = (h & 4u) || (f[0] == f[3]) ? 4u | f[0] : (f[2] & 1u) | (f[1] & 2u);
+            t.fold[i] |= r << (4 * h);
         }
+        t.fold[i] |= op > OP_NOOP ? 8u : 0u;
+        for (uint32_t s = 0; s < 4; s++)
+            t.apply[i] |= (((e.f4 >> (8 * s)) & 3u) | (s << 2) | (((e.stuck >> s) & 1u) << 7)) << (8 * s);
+    }
     return t;
 }
-constexpr uint64_t APPLY = make_apply_table();
+__constant__ constexpr StrandTable STRAND = make_strand_table();
+
+// A packed event: variable >> 2 in bits 8-11 and variable & 3 in bits 0-1, the place of its
+// byte in a column of words WAVE apart; 4 * (op | side << 3) in bits 2-5, the place of its
+// table word.
+__device__ __forceinline__ uint32_t pack_event(uint32_t w)
+{
+    return ((w & 0x3Cu) << 6) | (w & 3u) | ((w >> 22) & 0x3Cu);
+}
+constexpr uint32_t PLACE = 0xF03u, TABLE_AT = 0x3Cu;
+
+// bits `bit` of the four bytes of v as bits 0-3, added to acc << bit
+__device__ __forceinline__ uint32_t gather4(uint32_t v, uint32_t mask, uint32_t weights, uint32_t acc)
+{
+    return __builtin_amdgcn_udot4(v & mask, weights, acc, false);
+}
+constexpr uint32_t W_LO = 0x08040201u, W_HI = 0x80402010u;
+
+__device__ __forceinline__ void lds_fence() { asm volatile("" ::: "memory"); } // a wave's LDS operations are in order
 
 // one 32-bit half of the function planes of up to 64 variables
 struct Fn32 {
@@ -104,6 +145,19 @@ __device__ __forceinline__ uint32_t bits20(uint32_t lo, uint32_t hi, uint32_t k)
     return (uint32_t)(v >> (20 * k)) & PL_MASK;
 }
 
+// flag words per scatter tile (k_flag_scatter<512> or <256>)
+template <int EP>
+constexpr uint32_t scatter_threads()
+{
+    return EP == EP_LONG ? 512 : 256;
+}
+
+// Bound by the issue of about 25 VALU instructions and 7 LDS operations per event, with
+// three workgroups per CU (the packed events and the columns take 53 KB).  Composing 16
+// events a lane in registers, with 64-bit planes, took about 100 instructions per event:
+// 2^28 events x 64 variables 877 us, 746 with words final at once, 391 this way (3.4 TB/s
+// of events in and status bytes out); 2^26 events 229 and 110 us; 10^4 events 12.8 and 10.7.
+template <int EP>
 __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__ ev, uint64_t n, uint32_t n_ids,
                                                        const uint8_t *__restrict__ init, uint8_t *__restrict__ status,
                                                        uint8_t *__restrict__ final_out,
@@ -111,102 +165,117 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
                                                        uint32_t *__restrict__ fw, uint32_t *__restrict__ ticket,
                                                        uint64_t ntiles, Control *ctl)
 {
-    // per top byte of an event word (op | side << 3 | reserved << 4): the effect's monoid
-    // code (bits 0-2), its stuck mask (bits 3-6), malformed (bit 7: reserved bits set or
-    // op past Noop)
-    __shared__ uint8_t s_info[256];
+    constexpr int ROW = EP / 2 + 4;          // words of a lane's packed events, padded (16-byte rows on all banks)
+    constexpr int WE = WAVE * EP;            // events of a wave
+    constexpr int GROUPS = EP / FLAG_EVENTS; // flag words per lane
+    __shared__ __align__(16) uint32_t s_ev[SW][WAVE * ROW];
+    __shared__ __align__(16) uint8_t s_fn[SW * SK * WAVE];
+    __shared__ uint32_t s_fold[16], s_apply[16];
     __shared__ Fn32 s_wtot[SW][2];           // per wave: composition of its threads
     __shared__ uint32_t s_in[SPW][2];        // statuses entering the tile, 20 variables a word
     __shared__ uint32_t s_wsum[SW];
     __shared__ uint32_t s_tile;
 
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / WAVE;
-    if (tid < 256) {
-        const uint32_t op = tid & 7u, side = (tid >> 3) & 1u;
-        const bool bad = (tid >> 4) != 0 || op > OP_NOOP;
-        const uint32_t fc = bad ? fcode(OP_NOOP, 0) : fcode(op, side);
-        s_info[tid] = (uint8_t)(mon_code(TABLE.f4[fc]) | (TABLE.stuck[fc] << 3) | ((bad ? 1u : 0u) << 7));
+    if (tid < 16) {
+        s_fold[tid] = STRAND.fold[tid];
+        s_apply[tid] = STRAND.apply[tid];
     }
     __syncthreads();
-    constexpr uint32_t NOOP_INFO = 0; // identity, never stuck
+    uint32_t *const rows = s_ev[wave], *const row = rows + lane * ROW;
+    const uint32_t column = wave * (SK * WAVE) + lane * 4; // this lane's bytes: s_fn[place | column]
+    uint32_t *const colw = reinterpret_cast<uint32_t *>(s_fn + column);
+    auto table = [](const uint32_t *t, uint32_t x) {
+        return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(t) + (x & TABLE_AT));
+    };
 
     for (;;) {
         const uint32_t tile = take_ticket(ticket, &s_tile);
         if (tile >= ntiles)
             break;
-        const uint64_t base = (uint64_t)tile * STILE;
-        const uint64_t my0 = base + (uint64_t)tid * SE;
+        const uint64_t wb = ((uint64_t)tile * SW + wave) * WE; // the wave's first event
 
-        // ---- load and decode 16 consecutive events: id (6 bits) | info << 8 -----------
-        uint32_t w[SE];
-        uint32_t valid = 0xFFFFu;
-        if (my0 + SE <= n) {
-            const uint4 *p = reinterpret_cast<const uint4 *>(ev + my0);
+        // ---- 1. the wave's events, four consecutive ones a lane, packed to their rows ----
+        uint32_t badm = 0, top = 0;
+        constexpr int LOADS = EP / 4, BATCH = LOADS < 8 ? LOADS : 8;
+        for (int q0 = 0; q0 < LOADS; q0 += BATCH) {
+            uint4 v[BATCH];
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const uint4 v = p[q];
-                w[4 * q] = v.x;
-                w[4 * q + 1] = v.y;
-                w[4 * q + 2] = v.z;
-                w[4 * q + 3] = v.w;
+            for (int q = 0; q < BATCH; q++) {
+                const uint64_t g = wb + (uint32_t)(q0 + q) * (4 * WAVE) + lane * 4;
+                if (g + 4 <= n) {
+                    v[q] = *reinterpret_cast<const uint4 *>(ev + g);
+                } else {
+                    constexpr uint32_t NOOP = (uint32_t)OP_NOOP << 24;
+                    v[q].x = g < n ? ev[g] : NOOP;
+                    v[q].y = g + 1 < n ? ev[g + 1] : NOOP;
+                    v[q].z = g + 2 < n ? ev[g + 2] : NOOP;
+                    v[q].w = g + 3 < n ? ev[g + 3] : NOOP;
+                }
             }
-        } else {
-            valid = 0;
 #pragma unroll
-            for (int j = 0; j < SE; j++) {
-                const bool in = my0 + j < n;
-                w[j] = in ? ev[my0 + j] : (OP_NOOP << 24);
-                valid |= (in ? 1u : 0u) << j;
+            for (int q = 0; q < BATCH; q++) {
+                const uint32_t e = (uint32_t)(q0 + q) * (4 * WAVE) + lane * 4;
+                badm |= (v[q].x | v[q].y | v[q].z | v[q].w) & 0xF0FFFFC0u;
+                if (n_ids < SK) {
+                    const uint32_t a = v[q].x & 63u, b = v[q].y & 63u, c = v[q].z & 63u, d = v[q].w & 63u;
+                    const uint32_t ab = a > b ? a : b, cd = c > d ? c : d, m = ab > cd ? ab : cd;
+                    top = top > m ? top : m;
+                }
+                *reinterpret_cast<uint2 *>(rows + (e / EP) * ROW + (e % EP) / 2) =
+                    make_uint2(pack_event(v[q].x) | (pack_event(v[q].y) << 16),
+                               pack_event(v[q].z) | (pack_event(v[q].w) << 16));
             }
         }
-        uint32_t iv[SE];
-        uint32_t badm = 0;
 #pragma unroll
-        for (int j = 0; j < SE; j++) {
-            const uint32_t info = s_info[w[j] >> 24];
-            const uint32_t id = w[j] & 0xFFFFFFu;
-            const bool bad = (info >> 7) != 0 || id >= n_ids;
-            badm |= (bad ? 1u : 0u) << j;
-            iv[j] = (id & 63u) | (info << 8);
+        for (int k = 0; k < SK / 4; k++)
+            colw[k * WAVE] = 0; // identity
+        lds_fence();
+
+        // ---- 2. this strand's functions ------------------------------------------------
+        uint32_t seen = 0;
+        for (int c = 0; c < EP / 8; c++) {
+            const uint4 v = reinterpret_cast<const uint4 *>(row)[c];
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            uint32_t t[8];
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                t[j] = table(s_fold, w[j >> 1] >> (16 * (j & 1)));
+                seen |= t[j];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                uint8_t &h = s_fn[((w[j >> 1] >> (16 * (j & 1))) & PLACE) | column];
+                h = (uint8_t)(t[j] >> ((4u * h) & 31u)); // (bits above the element are left over)
+            }
         }
-        if (__ballot(badm != 0)) {
-            // malformed words count as Noop on variable 0; the first index is reported
-#pragma unroll
-            for (int j = 0; j < SE; j++) {
-                if ((badm >> j) & 1u) {
-                    if ((valid >> j) & 1u) {
-                        unsigned long long *e = reinterpret_cast<unsigned long long *>(&ctl->err_index_lo);
-                        atomicMin(e, (unsigned long long)(my0 + j));
-                    }
-                    iv[j] = NOOP_INFO << 8;
+        // malformed words: the first index is reported (the walks stay inside the columns)
+        if (__ballot(badm != 0 || top >= n_ids || (seen & 8u))) {
+            for (uint32_t k = 0; k < (uint32_t)EP; k++) {
+                const uint64_t g = wb + (uint64_t)lane * EP + k;
+                const uint32_t x = g < n ? ev[g] : (uint32_t)OP_NOOP << 24;
+                if ((x >> 28) != 0 || ((x >> 24) & 7u) > OP_NOOP || (x & 0xFFFFFFu) >= n_ids) {
+                    if (g < n)
+                        atomicMin(reinterpret_cast<unsigned long long *>(&ctl->err_index_lo), (unsigned long long)g);
+                    break;
                 }
             }
         }
 
-        // ---- 1. this thread's function planes --------------------------------------
+        // ---- 3. the functions as planes; the composition of the strands before this one --
         Fn32 lo{0, 0, 0}, hi{0, 0, 0};
 #pragma unroll
-        for (int j = 0; j < SE; j++) {
-            const uint32_t id = iv[j] & 63u, code = (iv[j] >> 8) & 7u;
-            const uint32_t ct = (uint32_t)-(int32_t)((code >> 2) & 1u), cx = (uint32_t)-(int32_t)((code >> 1) & 1u),
-                           cy = (uint32_t)-(int32_t)(code & 1u);
-            // the event's variable lives in one half: its new bits are computed from that
-            // half and inserted under the variable's mask
-            const bool up = id >= 32;
-            const uint32_t m = 1u << (id & 31u), mlo = up ? 0u : m, mhi = up ? m : 0u;
-            const uint32_t ft = up ? hi.t : lo.t, fx = up ? hi.x : lo.x, fy = up ? hi.y : lo.y;
-            const uint32_t nx = (ct & cx) | (~ct & (fx | (cx & (~ft | fy))));
-            const uint32_t ny = (ct & cy) | (~ct & (fy | (cy & (~ft | fx))));
-            lo.t |= mlo & ct;
-            hi.t |= mhi & ct;
-            lo.x = (mlo & nx) | (~mlo & lo.x);
-            hi.x = (mhi & nx) | (~mhi & hi.x);
-            lo.y = (mlo & ny) | (~mlo & lo.y);
-            hi.y = (mhi & ny) | (~mhi & hi.y);
+        for (int k = 0; k < SK / 4; k += 2) {
+            const uint32_t a = colw[k * WAVE], b = colw[(k + 1) * WAVE];
+            // eight variables a pair of words
+            const uint32_t x = gather4(b, 0x01010101u, W_HI, gather4(a, 0x01010101u, W_LO, 0));
+            const uint32_t y = gather4(b, 0x02020202u, W_HI, gather4(a, 0x02020202u, W_LO, 0)) >> 1;
+            const uint32_t z = gather4(b, 0x04040404u, W_HI, gather4(a, 0x04040404u, W_LO, 0)) >> 2;
+            Fn32 &f = k < SK / 8 ? lo : hi;
+            f.x |= x << (4 * (k % (SK / 8)));
+            f.y |= y << (4 * (k % (SK / 8)));
+            f.t |= z << (4 * (k % (SK / 8)));
         }
-
-        // ---- 2. composition of the tile's events before this thread ------------------
-        const Fn32 own_lo = lo, own_hi = hi;
         fn_wave_scan(lo, hi);
         if (lane == WAVE - 1) {
             s_wtot[wave][0] = lo;
@@ -214,8 +283,6 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
         }
         // exclusive: the inclusive prefix of the lane before (lane 0: identity)
         const Fn32 xlo = fn_move<DPP_WAVE_SHR1>(lo), xhi = fn_move<DPP_WAVE_SHR1>(hi);
-        (void)own_lo;
-        (void)own_hi;
         __syncthreads();
         // earlier waves, then the wave's own prefix
         Fn32 plo{0, 0, 0}, phi{0, 0, 0}, alo{0, 0, 0}, ahi{0, 0, 0};
@@ -231,10 +298,12 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
         plo = fn_compose(xlo, plo);
         phi = fn_compose(xhi, phi);
 
-        // ---- 3. statuses entering the tile: look-back, one wave per word of 20 --------
+        // ---- 4. statuses entering the tile: look-back, one wave per word of 20 --------
         if (wave < SPW) {
             const uint32_t k = wave;
-            const Planes agg{bits20(alo.t, ahi.t, k), bits20(alo.x, ahi.x, k), bits20(alo.y, ahi.y, k)};
+            // (places past the ids count as constants, so that a word can be all constant)
+            const uint32_t past = n_ids > k * 20 + 20 ? 0u : PL_MASK & ~((1u << (n_ids > k * 20 ? n_ids - k * 20 : 0)) - 1u);
+            const Planes agg{bits20(alo.t, ahi.t, k) | past, bits20(alo.x, ahi.x, k), bits20(alo.y, ahi.y, k)};
             Planes first{PL_MASK, 0, 0};
             if (tile == 0) {
                 const uint32_t v = k * 20 + lane;
@@ -265,46 +334,99 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
         fn_apply(plo, clo, glo);
         fn_apply(phi, chi, ghi);
 
-        // ---- 4. replay this thread's events ------------------------------------------
-        uint64_t C = ((uint64_t)chi << 32) | clo, G = ((uint64_t)ghi << 32) | glo;
-        uint32_t out[4] = {0, 0, 0, 0};
-        uint32_t flags = 0;
+        // ---- 5. the strand's statuses --------------------------------------------------
 #pragma unroll
-        for (int j = 0; j < SE; j++) {
-            const uint32_t id = iv[j] & 63u, info = iv[j] >> 8, code = info & 7u;
-            const uint32_t pre = (uint32_t)((C >> id) & 1u) | ((uint32_t)((G >> id) & 1u) << 1);
-            const uint32_t post = (uint32_t)(APPLY >> (2u * (code * 4u + pre))) & 3u;
-            const uint32_t flag = (info >> (3u + pre)) & 1u & ((valid >> j) & 1u);
-            const uint32_t d = post ^ pre;
-            C ^= (uint64_t)(d & 1u) << id;
-            G ^= (uint64_t)(d >> 1) << id;
-            out[j >> 2] |= (post | (pre << 2) | (flag << 7)) << (8 * (j & 3));
-            flags |= flag << j;
+        for (int k = 0; k < SK / 4; k++) {
+            const uint32_t c = k < SK / 8 ? clo : chi, g = k < SK / 8 ? glo : ghi, at = 4 * (k % (SK / 8));
+            // four variables' bits to four bytes (the partial products land on distinct bits)
+            const uint32_t cb = __umul24((c >> at) & 15u, 0x204081u) & 0x01010101u;
+            const uint32_t gb = __umul24((g >> at) & 15u, 0x204081u) & 0x01010101u;
+            colw[k * WAVE] = cb | (gb << 1);
         }
-        if (my0 + SE <= n) {
-            *reinterpret_cast<uint4 *>(status + my0) = make_uint4(out[0], out[1], out[2], out[3]);
-        } else {
-            for (int j = 0; j < SE; j++)
-                if (my0 + j < n)
-                    status[my0 + j] = (uint8_t)(out[j >> 2] >> (8 * (j & 3)));
+        lds_fence();
+        uint32_t flags[GROUPS];
+        uint32_t cnt = 0;
+#pragma unroll 1
+        for (int c = 0; c < EP / 16; c++) {
+            uint32_t out[4];
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                const uint4 v = reinterpret_cast<const uint4 *>(row)[2 * c + h];
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+                uint32_t t[8], r[8];
+#pragma unroll
+                for (int j = 0; j < 8; j++)
+                    t[j] = table(s_apply, w[j >> 1] >> (16 * (j & 1)));
+#pragma unroll
+                for (int j = 0; j < 8; j++) {
+                    uint8_t &s8 = s_fn[((w[j >> 1] >> (16 * (j & 1))) & PLACE) | column];
+                    r[j] = t[j] >> ((8u * s8) & 31u); // (the status is the byte's low bits)
+                    s8 = (uint8_t)r[j];
+                }
+#pragma unroll
+                for (int j = 0; j < 8; j += 4) // the low bytes of four words
+                    out[2 * h + j / 4] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(r[j + 3], r[j + 2], 0x0C0C0400u),
+                                                               __builtin_amdgcn_perm(r[j + 1], r[j], 0x0C0C0400u),
+                                                               0x05040100u);
+            }
+            // the row's words up to 8c + 7 have been read: the status words take their place
+            reinterpret_cast<uint4 *>(row)[c] = make_uint4(out[0], out[1], out[2], out[3]);
+            const uint32_t m = (gather4(out[1], 0x80808080u, W_HI, gather4(out[0], 0x80808080u, W_LO, 0)) >> 7) |
+                               (gather4(out[3], 0x80808080u, W_HI, gather4(out[2], 0x80808080u, W_LO, 0)) << 1);
+#pragma unroll
+            for (int q = 0; q < GROUPS; q++)
+                flags[q] = q == c ? m : flags[q];
+            cnt += __builtin_popcount(m);
+        }
+        lds_fence();
+        // the wave's status bytes, 16 consecutive ones a lane
+#pragma unroll
+        for (int q = 0; q < EP / 16; q++) {
+            const uint32_t e = (q * WAVE + lane) * 16;
+            const uint4 v = *reinterpret_cast<const uint4 *>(rows + (e / EP) * ROW + (e % EP) / 4);
+            const uint64_t g = wb + e;
+            if (g + 16 <= n) {
+                *reinterpret_cast<uint4 *>(status + g) = v;
+            } else {
+                const uint32_t o[4] = {v.x, v.y, v.z, v.w};
+                for (int j = 0; j < 16; j++)
+                    if (g + j < n)
+                        status[g + j] = (uint8_t)(o[j >> 2] >> (8 * (j & 3)));
+            }
         }
 
-        // ---- flagged events: per thread its mask and offset inside the tile, per tile
-        // the count
-        const uint32_t cnt = __builtin_popcount(flags);
+        // ---- flagged events: per 16 their mask and offset inside the scatter tile, per
+        // scatter tile the count
         const uint32_t inc = wave_scan_add(cnt, lane);
         if (lane == WAVE - 1)
             s_wsum[wave] = inc;
         __syncthreads();
+        constexpr uint32_t TW = scatter_threads<EP>() / (WAVE * GROUPS); // waves per scatter tile
         uint32_t woff = 0, total = 0;
+#pragma unroll
         for (uint32_t w2 = 0; w2 < SW; w2++) {
-            if (w2 < wave)
-                woff += s_wsum[w2];
-            total += s_wsum[w2];
+            if (w2 / TW == wave / TW) {
+                if (w2 < wave)
+                    woff += s_wsum[w2];
+                total += s_wsum[w2];
+            }
         }
-        fw[(uint64_t)tile * SB + tid] = flags | ((woff + inc - cnt) << 16);
-        if (tid == 0)
-            tcnt[tile] = total;
+        uint32_t o = woff + inc - cnt;
+        uint32_t *const f = fw + ((uint64_t)tile * SB + tid) * GROUPS;
+        uint32_t words[GROUPS];
+#pragma unroll
+        for (int q = 0; q < GROUPS; q++) {
+            words[q] = flags[q] | (o << 16);
+            o += __builtin_popcount(flags[q]);
+        }
+        if constexpr (GROUPS == 4)
+            *reinterpret_cast<uint4 *>(f) = make_uint4(words[0], words[1], words[2], words[3]);
+        else
+#pragma unroll
+            for (int q = 0; q < GROUPS; q++)
+                f[q] = words[q];
+        if (lane == 0 && wave % TW == 0)
+            tcnt[(uint64_t)tile * (SW / TW) + wave / TW] = total;
     }
 }
 
@@ -313,6 +435,7 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
 // scratch: look-back words, tile counts, their offsets, the chunk scan's scratch, the
 // per-thread flag words
 struct SmallLayout {
+    uint64_t tiles, stiles; // tiles of the check, tiles of the scatter
     uint64_t *lbv;
     uint32_t *tcnt;
     uint64_t *offs;
@@ -323,7 +446,10 @@ struct SmallLayout {
 
 static SmallLayout small_layout(void *scratch, uint64_t n)
 {
-    const uint64_t tiles = ceil_div(n ? n : 1, STILE);
+    const int ep = strand_of(n);
+    const uint64_t tiles = ceil_div(n ? n : 1, (uint64_t)SB * ep);
+    const uint64_t words = tiles * SB * (ep / FLAG_EVENTS);
+    const uint64_t stiles = words / (ep == EP_LONG ? scatter_threads<EP_LONG>() : scatter_threads<EP_SHORT>());
     char *p = reinterpret_cast<char *>(scratch);
     size_t off = 0;
     auto take = [&](size_t sz) {
@@ -332,15 +458,19 @@ static SmallLayout small_layout(void *scratch, uint64_t n)
         return r;
     };
     SmallLayout L;
+    L.tiles = tiles;
+    L.stiles = stiles;
     L.lbv = reinterpret_cast<uint64_t *>(take(tiles * SPW * sizeof(uint64_t)));
-    L.tcnt = reinterpret_cast<uint32_t *>(take(tiles * 4));
-    L.offs = reinterpret_cast<uint64_t *>(take((tiles + 1) * 8));
-    L.xscan = take(excl_scan_scratch_bytes(tiles));
-    L.fw = reinterpret_cast<uint32_t *>(take(tiles * SB * 4));
+    L.tcnt = reinterpret_cast<uint32_t *>(take(stiles * 4));
+    L.offs = reinterpret_cast<uint64_t *>(take((stiles + 1) * 8));
+    L.xscan = take(excl_scan_scratch_bytes(stiles));
+    L.fw = reinterpret_cast<uint32_t *>(take(words * 4));
     L.bytes = off;
     return L;
 }
 
+// (no shorter trace needs more: the short strands' look-back words reach their most just
+// below the first long trace, where the flag words are a fraction of the largest trace's)
 size_t small_scratch_bytes(uint64_t n) { return small_layout(nullptr, n).bytes; }
 
 uint32_t small_max_ids() { return SK; }
@@ -351,7 +481,8 @@ void excl_scan_warm_launch_shape();
 // no host-side allocation
 void small_warm_launch_shapes()
 {
-    (void)resident_grid((const void *)k_small_check, 1, 0, SB);
+    (void)resident_grid((const void *)k_small_check<EP_LONG>, 1, 0, SB);
+    (void)resident_grid((const void *)k_small_check<EP_SHORT>, 1, 0, SB);
     excl_scan_warm_launch_shape();
 }
 
@@ -359,26 +490,28 @@ void launch_small_check(const uint32_t *events, uint64_t n, uint32_t n_ids, cons
                         uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl, hipStream_t s,
                         unsigned grid_cap, const FillJob *fin_fill)
 {
-    const uint64_t tiles = ceil_div(n, STILE);
     const SmallLayout L = small_layout(scratch, n);
     // one set-up launch: the control block, both look-back arrays, the caller's fill
-    FillJob jobs[3] = {FillJob{L.lbv, (size_t)tiles * SPW * sizeof(uint64_t), 0},
-                       FillJob{L.xscan, excl_scan_scratch_bytes(tiles), 0}, FillJob{nullptr, 0, 0}};
+    FillJob jobs[3] = {FillJob{L.lbv, (size_t)L.tiles * SPW * sizeof(uint64_t), 0},
+                       FillJob{L.xscan, excl_scan_scratch_bytes(L.stiles), 0}, FillJob{nullptr, 0, 0}};
     if (fin_fill)
         jobs[2] = *fin_fill;
     launch_prep(ctl, nullptr, jobs, 3, s);
     if (n == 0)
         return;
+    const bool is_long = strand_of(n) == EP_LONG;
     {
-        const unsigned grid = resident_grid((const void *)k_small_check, tiles, grid_cap, SB);
+        const auto kernel = is_long ? k_small_check<EP_LONG> : k_small_check<EP_SHORT>;
+        const unsigned grid = resident_grid((const void *)kernel, L.tiles, grid_cap, SB);
         ProfScope prof_(s, "small_check");
-        k_small_check<<<grid, SB, 0, s>>>(events, n, n_ids, init, status, final_out, L.lbv, L.tcnt, L.fw,
-                                             ctl->tickets[7], tiles, ctl);
+        kernel<<<grid, SB, 0, s>>>(events, n, n_ids, init, status, final_out, L.lbv, L.tcnt, L.fw, ctl->tickets[7],
+                                   L.tiles, ctl);
     }
     // the violation count lands in ctl->n_viol
-    launch_excl_scan(L.tcnt, tiles, L.offs, reinterpret_cast<uint64_t *>(&ctl->n_viol), L.xscan, ctl->tickets[8], s,
-                     true);
-    launch_flag_scatter(L.fw, L.offs, tiles, SB, viol, s);
+    launch_excl_scan(L.tcnt, L.stiles, L.offs, reinterpret_cast<uint64_t *>(&ctl->n_viol), L.xscan, ctl->tickets[8],
+                     s, true);
+    launch_flag_scatter(L.fw, L.offs, L.stiles, is_long ? (int)scatter_threads<EP_LONG>() : (int)scatter_threads<EP_SHORT>(),
+                        viol, s);
 }
 
 } // namespace vc
