@@ -73,7 +73,7 @@ constexpr StepTable make_step_table()
     for (uint32_t i = 0; i < 16; i++) {
         const uint32_t op = i & 7u, side = i >> 3, own = side ? 2u : 1u;
         uint32_t e = 0;
-        if (op == OP_W)
+        if (op == OP_W || op == OP_RWIND)
             e = 4u | own;
         else if (op == OP_PUSH)
             e = side ? 1u : 2u;
@@ -82,7 +82,7 @@ constexpr StepTable make_step_table()
         for (uint32_t h = 0; h < 8; h++)
             t.fold[i] |= host_compose(h, e) << (3 * h);
         t.fold[i] |= e << 24;
-        const Effect x = make_effect(op <= OP_NOOP ? op : (uint32_t)OP_NOOP, side);
+        const Effect x = make_effect(op <= OP_RWIND ? op : (uint32_t)OP_NOOP, side);
         for (uint32_t s = 0; s < 4; s++) {
             const uint32_t post = (x.f4 >> (8 * s)) & 3u;
             t.apply[i] |= (post | (s << 2) | (((x.stuck >> s) & 1u) << 7)) << (8 * s);
@@ -165,6 +165,7 @@ __device__ __forceinline__ uint32_t el_of(uint32_t f4)
     return ((f4 >> 16) & 1u) | ((f4 >> 8) & 2u) | ((f4 & 3u) ? 4u : 0u);
 }
 
+constexpr uint32_t OP_PROBE = DENSE_OP_PROBE;
 constexpr int D_UNROLL = 8; // steps whose events are loaded together
 
 // the chunks of one trace: `per` events each (a multiple of 64), the last one the rest
@@ -181,6 +182,25 @@ struct TraceChunks {
     __device__ bool bad(uint32_t w) const
     {
         return (w >> 28) != 0 || ((w >> 24) & 7u) > OP_NOOP || (w & 0xFFFFFFu) >= n_ids;
+    }
+};
+
+// the chunks of a combined stream: the words of `per` tiles of events each
+struct TileChunks {
+    const uint32_t *ev;
+    const uint64_t *tpos; // first word of every tile, their number at the end
+    uint64_t n, tiles, per;
+    uint32_t n_ids, chunks;
+    __device__ uint64_t at(uint64_t tile) const
+    {
+        const uint64_t p = tpos[tile < tiles ? tile : tiles];
+        return p < n ? p : n; // (events that changed since the stream was sized)
+    }
+    __device__ uint64_t begin(uint32_t c) const { return at((uint64_t)c * per); }
+    __device__ uint64_t end(uint32_t c) const { return at((uint64_t)(c + 1) * per); }
+    __device__ bool bad(uint32_t w) const
+    {
+        return (w >> 28) != 0 || ((w >> 24) & 7u) > OP_PROBE || (w & 0xFFFFFFu) >= n_ids;
     }
 };
 
@@ -355,7 +375,8 @@ __device__ __forceinline__ void load_step_table(uint32_t *s_tab, uint32_t lane)
 }
 
 // 1. every chunk's functions into its row
-__global__ __launch_bounds__(WAVE) void k_dense_fold(TraceChunks T, uint32_t row, uint32_t *__restrict__ rows,
+template <class CHUNKS>
+__global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uint32_t *__restrict__ rows,
                                                      Control *ctl)
 {
     extern __shared__ __align__(16) uint32_t s_t[];
@@ -455,8 +476,8 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(TraceChunks T, uint32_t row
 
 // 2. prefix over the rows, by groups of D_GROUP chunks: a thread per word and group.  The
 // first kernel folds every group's rows; the second walks them from the statuses entering
-// the group (the initial ones and the groups before) and leaves every chunk's entering
-// statuses in its row; the last group's end is the final table.
+// the group (the initial ones and the groups before) and leaves the statuses entering
+// every chunk (`entering` may be `rows`); the last group's end is the final table.
 constexpr uint32_t D_GROUP = 32;
 
 __global__ __launch_bounds__(BLOCK) void k_dense_groups(const uint32_t *__restrict__ rows, uint32_t row,
@@ -473,8 +494,9 @@ __global__ __launch_bounds__(BLOCK) void k_dense_groups(const uint32_t *__restri
     grp[(uint64_t)g * row + w] = f;
 }
 
-__global__ __launch_bounds__(BLOCK) void k_dense_prefix(uint32_t *__restrict__ rows, uint32_t row, uint32_t chunks,
-                                                        const uint32_t *__restrict__ grp, uint32_t n_ids,
+__global__ __launch_bounds__(BLOCK) void k_dense_prefix(const uint32_t *rows, uint32_t *entering, uint32_t row,
+                                                        uint32_t chunks, const uint32_t *__restrict__ grp,
+                                                        uint32_t n_ids,
                                                         const uint8_t *__restrict__ init,
                                                         uint8_t *__restrict__ final_out)
 {
@@ -494,24 +516,104 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prefix(uint32_t *__restrict__ r
 #pragma unroll 8
     for (uint32_t c = c0; c < c1; c++) {
         const uint32_t f = rows[(uint64_t)c * row + w];
-        rows[(uint64_t)c * row + w] = st;
+        entering[(uint64_t)c * row + w] = st;
         st = tw_compose(f, st);
     }
-    if (c1 == chunks)
+    if (c1 == chunks && final_out)
 #pragma unroll
         for (uint32_t k = 0; k < 8; k++)
             if (w * 8 + k < n_ids)
                 final_out[w * 8 + k] = (uint8_t)((st >> (3 * k)) & 3u);
 }
 
-// 3. the events' status bytes from their chunk's entering statuses; per step of 64 events
-// the mask of the flagged ones, per tile of D_TILE events their number
+// 3. the events' statuses from their chunk's entering ones.  OUT takes the results: step()
+// a step's (u: its number in its round or in the chunk's last, partial one), round() at
+// the end of each, chunk() at the chunk's.
 constexpr uint32_t D_TILE = 1024;
 static_assert(D_TILE % (D_UNROLL * WAVE) == 0, "whole rounds of steps a tile");
 
-__global__ __launch_bounds__(WAVE) void k_dense_apply(TraceChunks T, uint32_t row, const uint32_t *__restrict__ rows,
-                                                      uint8_t *__restrict__ status, uint64_t *__restrict__ masks,
-                                                      uint32_t *__restrict__ tcnt)
+// a trace: status bytes; per step of 64 events the mask of the flagged ones, per tile of
+// D_TILE events their number
+struct TraceOut {
+    uint8_t *status;
+    uint64_t *masks;
+    uint32_t *tcnt;
+    uint64_t mask; // lane u: the flagged events of step u
+    uint32_t flagged;
+    template <class CHUNKS>
+    __device__ void begin(const CHUNKS &, uint32_t)
+    {
+        flagged = 0;
+    }
+    __device__ void step(uint32_t lane, uint32_t u, uint64_t i, uint32_t, uint32_t byte, bool valid)
+    {
+        if (valid)
+            status[i + lane] = (uint8_t)byte;
+        const uint64_t m = __ballot(valid && (byte & 0x80u));
+        mask = lane == u ? m : mask;
+        flagged += (uint32_t)__builtin_popcountll(m);
+    }
+    __device__ void round(uint32_t lane, uint64_t i, uint32_t steps, bool last)
+    {
+        if (lane < steps)
+            masks[i / WAVE + lane] = mask;
+        if (last || (i / (D_UNROLL * WAVE) + 1) % (D_TILE / (D_UNROLL * WAVE)) == 0) {
+            if (lane == 0)
+                tcnt[i / D_TILE] = flagged;
+            flagged = 0;
+        }
+    }
+    __device__ void chunk(uint32_t) const {}
+};
+
+// a combined stream: the status bytes of the events, in their order; flagged induced
+// items are counted
+struct PrimaryOut {
+    uint8_t *status;
+    uint64_t n; // events
+    uint32_t tile; // events per tile
+    unsigned long long *induced;
+    uint64_t next;
+    uint32_t count;
+    __device__ void begin(const TileChunks &T, uint32_t c)
+    {
+        next = (uint64_t)c * T.per * tile;
+        count = 0;
+    }
+    __device__ void step(uint32_t lane, uint32_t, uint64_t, uint32_t w, uint32_t byte, bool valid)
+    {
+        const uint32_t op = (w >> 24) & 7u;
+        const bool event = valid && op <= OP_NOOP;
+        const uint64_t m = __ballot(event);
+        const uint64_t at = next + mask_rank(m);
+        if (event && at < n)
+            status[at] = (uint8_t)byte;
+        next += (uint32_t)__builtin_popcountll(m);
+        count += (uint32_t)__builtin_popcountll(__ballot(valid && op == OP_RWIND && (byte & 0x80u)));
+    }
+    __device__ void round(uint32_t, uint64_t, uint32_t, bool) const {}
+    __device__ void chunk(uint32_t lane) const
+    {
+        if (lane == 0 && count)
+            atomicAdd(induced, (unsigned long long)count);
+    }
+};
+
+// the statuses the probes see, at their positions
+struct ProbeOut {
+    uint8_t *pre;
+    __device__ void begin(const TileChunks &, uint32_t) const {}
+    __device__ void step(uint32_t lane, uint32_t, uint64_t i, uint32_t w, uint32_t byte, bool valid) const
+    {
+        if (valid && ((w >> 24) & 7u) == OP_PROBE)
+            pre[i + lane] = (uint8_t)((byte >> 2) & 3u);
+    }
+    __device__ void round(uint32_t, uint64_t, uint32_t, bool) const {}
+    __device__ void chunk(uint32_t) const {}
+};
+
+template <class CHUNKS, class OUT>
+__global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, const uint32_t *__restrict__ rows, OUT out)
 {
     extern __shared__ __align__(16) uint32_t s_t[];
     uint32_t *const s_tab = s_t + row;
@@ -521,6 +623,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(TraceChunks T, uint32_t ro
         const uint4 *in = reinterpret_cast<const uint4 *>(rows + (uint64_t)c * row);
         const uint64_t i0 = T.begin(c), i1 = T.end(c);
         const uint32_t len = (uint32_t)(i1 - i0), rounds = len / (D_UNROLL * WAVE);
+        out.begin(T, c);
         uint32_t nxt[D_UNROLL];
         auto load = [&](uint32_t r) {
             const uint32_t *e = T.ev + i0 + (uint64_t)r * (D_UNROLL * WAVE) + lane;
@@ -538,14 +641,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(TraceChunks T, uint32_t ro
             const uint32_t x = w & 0xFFFFFFu;
             return x < T.n_ids ? x : T.n_ids - 1;
         };
-        uint32_t flagged = 0, shared_steps = 0;
-        uint64_t mask = 0; // lane u: the flagged events of step u of the round
-        auto put = [&](uint64_t i, int u, uint32_t byte) {
-            status[i + u * WAVE + lane] = (uint8_t)byte;
-            const uint64_t m = __ballot((byte & 0x80u) != 0);
-            mask = lane == (uint32_t)u ? m : mask;
-            flagged += (uint32_t)__builtin_popcountll(m);
-        };
+        uint32_t shared_steps = 0;
         for (uint32_t r = 0; r < rounds; r++) {
             uint32_t w[D_UNROLL];
 #pragma unroll
@@ -560,17 +656,18 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(TraceChunks T, uint32_t ro
 #pragma unroll 1
                 for (int u = 0; u < D_UNROLL; u += D_PAIR) {
                     Lane L[D_PAIR];
-                    uint32_t byte[D_PAIR];
+                    uint32_t byte[D_PAIR], now[D_PAIR];
                     const int n = u + D_PAIR < D_UNROLL ? u + D_PAIR : u;
 #pragma unroll
                     for (int q = 0; q < D_PAIR; q++) {
+                        now[q] = v[q];
                         L[q] = make_lane<Apply>(s_t, s_tab, v[q], id_of(v[q]), true);
                         v[q] = T.ev[i + (n + q) * WAVE + lane];
                     }
                     steps_together<Apply, D_PAIR>(L, byte, s_tab, bits, lane, shared_steps);
 #pragma unroll
                     for (int q = 0; q < D_PAIR; q++)
-                        put(i, u + q, byte[q]);
+                        out.step(lane, u + q, i + (u + q) * WAVE, now[q], byte[q], true);
                 }
             } else {
                 shared_steps = 0;
@@ -584,37 +681,24 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(TraceChunks T, uint32_t ro
                     steps<Apply>(L, byte, s_tab, bits, lane, shared_steps);
 #pragma unroll
                     for (int q = 0; q < D_PAIR; q++)
-                        put(i, u + q, byte[q]);
+                        out.step(lane, u + q, i + (u + q) * WAVE, w[u + q], byte[q], true);
                 }
             }
-            if (lane < D_UNROLL)
-                masks[i / WAVE + lane] = mask;
-            if ((i / (D_UNROLL * WAVE) + 1) % (D_TILE / (D_UNROLL * WAVE)) == 0) {
-                if (lane == 0)
-                    tcnt[i / D_TILE] = flagged;
-                flagged = 0;
-            }
+            out.round(lane, i, D_UNROLL, (r + 1) * (D_UNROLL * WAVE) == len);
         }
         // the events past the whole rounds, one step at a time
-        for (uint32_t k = rounds * (D_UNROLL * WAVE); k < len; k += WAVE) {
+        const uint32_t past = rounds * (D_UNROLL * WAVE);
+        for (uint32_t k = past; k < len; k += WAVE) {
             const bool valid = k + lane < len;
-            const uint32_t w = valid ? T.ev[i0 + k + lane] : (uint32_t)OP_NOOP << 24;
-            const Lane one[1] = {make_lane<Apply>(s_t, s_tab, w, id_of(w), valid)};
+            const uint32_t w = valid ? T.ev[i0 + k + lane] : (uint32_t)OP_NOOP << 24, id = id_of(w);
+            const Lane one[1] = {make_lane<Apply>(s_t, s_tab, w, id, valid)};
             uint32_t b[1];
             steps_together<Apply, 1>(one, b, s_tab, bits, lane, shared_steps);
-            const uint32_t byte = b[0];
-            if (valid)
-                status[i0 + k + lane] = (uint8_t)byte;
-            const uint64_t m = __ballot(valid && (byte & 0x80u));
-            flagged += (uint32_t)__builtin_popcountll(m);
-            if (lane == 0) {
-                masks[(i0 + k) / WAVE] = m;
-                if (k + WAVE >= len)
-                    tcnt[(i0 + k) / D_TILE] = flagged;
-            }
+            out.step(lane, (k - past) / WAVE, i0 + k, w, b[0], valid);
         }
-        if (lane == 0 && rounds % (D_TILE / (D_UNROLL * WAVE)) && len == rounds * (D_UNROLL * WAVE))
-            tcnt[(i1 - 1) / D_TILE] = flagged;
+        if (past < len)
+            out.round(lane, i0 + past, (len - past + WAVE - 1) / WAVE, true);
+        out.chunk(lane);
         compiler_fence();
     }
 }
@@ -642,93 +726,182 @@ __global__ __launch_bounds__(BLOCK) void k_mask_scatter(const uint64_t *__restri
     }
 }
 
-// rows, groups, masks and tile counts of a trace; events per chunk
-struct DenseLayout {
+// LDS of a wave: its table and the step table
+size_t dense_lds(uint32_t row) { return ((size_t)row + 32) * 4; }
+
+// a row's words (a multiple of 64 of them, 8 ids each)
+uint32_t dense_row(uint32_t n_ids) { return ((uint32_t)ceil_div(n_ids ? n_ids : 1, 8) + 63u) & ~63u; }
+
+// Chunks that fill the device: as many waves as have their tables in a CU's 160 KB (4 of
+// 2^16 ids; 5 would leave no room for the step table), at most 24, on 256 CUs.
+uint64_t dense_chunks(uint32_t n_ids)
+{
+    const uint64_t waves = 163840 / dense_lds(dense_row(n_ids));
+    return 256 * (waves > 24 ? 24 : waves);
+}
+
+struct Rows { // chunks' rows and groups' rows
     uint32_t row, chunks, groups;
+    uint32_t *rows, *entering, *grp;
+};
+
+class Carve {
+public:
+    explicit Carve(void *scratch) : p0(reinterpret_cast<char *>(scratch)) {}
+    template <class T>
+    T *take(size_t n)
+    {
+        T *r = p0 ? reinterpret_cast<T *>(p0 + off) : nullptr;
+        off += (n * sizeof(T) + 255) & ~size_t(255);
+        return r;
+    }
+    size_t bytes() const { return off; }
+
+private:
+    char *p0;
+    size_t off = 0;
+};
+
+// (keep: the chunks' functions stay beside the entering statuses, for another prefix)
+Rows take_rows(Carve &c, uint32_t n_ids, uint32_t chunks, bool keep)
+{
+    Rows R{};
+    R.row = dense_row(n_ids);
+    R.chunks = chunks;
+    R.groups = (uint32_t)ceil_div(chunks, D_GROUP);
+    R.rows = c.take<uint32_t>((size_t)chunks * R.row);
+    R.entering = keep ? c.take<uint32_t>((size_t)chunks * R.row) : R.rows;
+    R.grp = c.take<uint32_t>((size_t)R.groups * R.row);
+    return R;
+}
+
+template <class CHUNKS>
+void launch_fold(const CHUNKS &T, const Rows &R, Control *ctl, hipStream_t s)
+{
+    if (!T.chunks)
+        return;
+    {
+        ProfScope p(s, "dense_fold");
+        k_dense_fold<CHUNKS><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.rows, ctl);
+    }
+    if (R.groups > 1) {
+        ProfScope p(s, "dense_groups");
+        k_dense_groups<<<dim3((unsigned)ceil_div(R.row, BLOCK), R.groups - 1), BLOCK, 0, s>>>(R.rows, R.row, R.chunks,
+                                                                                            R.grp);
+    }
+}
+
+void launch_prefix(const Rows &R, uint32_t chunks, uint32_t n_ids, const uint8_t *init, uint8_t *final_out,
+                   hipStream_t s)
+{
+    ProfScope p(s, "dense_prefix");
+    k_dense_prefix<<<dim3((unsigned)ceil_div(R.row, BLOCK), R.groups), BLOCK, 0, s>>>(
+        R.rows, R.entering, R.row, chunks, R.grp, n_ids, init, final_out);
+}
+
+template <class CHUNKS, class OUT>
+void launch_apply(const CHUNKS &T, const Rows &R, const OUT &out, hipStream_t s)
+{
+    if (!T.chunks)
+        return;
+    ProfScope p(s, "dense_apply");
+    k_dense_apply<CHUNKS, OUT><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.entering, out);
+}
+
+// rows, masks and tile counts of a trace
+struct TraceLayout {
+    Rows R;
     uint64_t per, tiles;
-    uint32_t *rows, *grp, *tcnt;
+    uint32_t *tcnt;
     uint64_t *masks, *offs;
     void *xscan;
     size_t bytes;
 };
 
-// Events per chunk: whole tiles, and enough of them that a chunk's walk outweighs its row
-// (written, prefixed in place and read back); at most DENSE_CHUNKS chunks, which fill the
-// device with the widest tables (5 waves of 32 KiB on each of 256 CUs).
-// LDS of a wave: its table and the step table
-size_t dense_lds(uint32_t row) { return ((size_t)row + 32) * 4; }
-
-uint64_t dense_chunks(uint32_t row)
+TraceLayout trace_layout(void *scratch, uint64_t n, uint32_t n_ids)
 {
-    const uint64_t waves = 163840 / dense_lds(row);
-    return 256 * (waves > 24 ? 24 : waves);
+    TraceLayout L{};
+    L.tiles = ceil_div(n ? n : 1, (uint64_t)D_TILE);
+    L.per = ceil_div(L.tiles, dense_chunks(n_ids)) * D_TILE;
+    Carve c(scratch);
+    L.R = take_rows(c, n_ids, (uint32_t)ceil_div(n ? n : 1, L.per), false);
+    L.masks = c.take<uint64_t>(L.tiles * (D_TILE / WAVE));
+    L.tcnt = c.take<uint32_t>(L.tiles);
+    L.offs = c.take<uint64_t>(L.tiles + 1);
+    L.xscan = c.take<char>(excl_scan_scratch_bytes(L.tiles));
+    L.bytes = c.bytes();
+    return L;
 }
 
-DenseLayout dense_layout(void *scratch, uint64_t n, uint32_t n_ids)
+// tiles of events per chunk of a combined stream
+uint64_t tiles_per_chunk(uint64_t tiles, uint32_t n_ids) { return ceil_div(tiles ? tiles : 1, dense_chunks(n_ids)); }
+
+Rows words_layout(Carve &c, uint64_t tiles, uint32_t n_ids, bool keep)
 {
-    DenseLayout L{};
-    const uint32_t words = (uint32_t)ceil_div(n_ids ? n_ids : 1, 8);
-    L.row = (words + 63u) & ~63u;
-    const uint64_t least = D_TILE;
-    uint64_t per = ceil_div(n ? n : 1, dense_chunks(L.row));
-    per = per < least ? least : per;
-    L.per = ceil_div(per, D_TILE) * D_TILE;
-    L.chunks = (uint32_t)ceil_div(n ? n : 1, L.per);
-    L.groups = (uint32_t)ceil_div(L.chunks, D_GROUP);
-    L.tiles = ceil_div(n ? n : 1, (uint64_t)D_TILE);
-    char *p0 = reinterpret_cast<char *>(scratch);
-    size_t off = 0;
-    auto take = [&](size_t sz) {
-        char *r = p0 ? p0 + off : nullptr;
-        off += (sz + 255) & ~size_t(255);
-        return r;
-    };
-    L.rows = (uint32_t *)take((size_t)L.chunks * L.row * 4);
-    L.grp = (uint32_t *)take((size_t)L.groups * L.row * 4);
-    L.masks = (uint64_t *)take(L.tiles * (D_TILE / WAVE) * 8);
-    L.tcnt = (uint32_t *)take(L.tiles * 4);
-    L.offs = (uint64_t *)take((L.tiles + 1) * 8);
-    L.xscan = take(excl_scan_scratch_bytes(L.tiles));
-    L.bytes = off;
-    return L;
+    return take_rows(c, n_ids, (uint32_t)ceil_div(tiles ? tiles : 1, tiles_per_chunk(tiles, n_ids)), keep);
+}
+
+TileChunks words_chunks(const DenseWords &W, const Rows &R)
+{
+    const uint64_t per = tiles_per_chunk(W.tiles, W.n_ids);
+    return TileChunks{W.words, W.tpos, W.m, W.tiles, per, W.n_ids, W.m ? R.chunks : 0u};
 }
 
 } // namespace
 
-size_t dense_scratch_bytes(uint64_t n, uint32_t n_ids) { return dense_layout(nullptr, n, n_ids).bytes; }
+size_t dense_scratch_bytes(uint64_t n, uint32_t n_ids) { return trace_layout(nullptr, n, n_ids).bytes; }
 
 void launch_dense_check(const uint32_t *events, uint64_t n, uint32_t n_ids, const uint8_t *init, uint8_t *status,
                         uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl, hipStream_t s)
 {
-    const DenseLayout L = dense_layout(scratch, n, n_ids);
+    const TraceLayout L = trace_layout(scratch, n, n_ids);
     const FillJob job{L.xscan, excl_scan_scratch_bytes(L.tiles), 0};
     launch_prep(ctl, nullptr, &job, 1, s);
-    const TraceChunks T{events, n, L.per, n_ids, n ? L.chunks : 0u};
-    const size_t lds = dense_lds(L.row);
-    const dim3 pg((unsigned)ceil_div(L.row, BLOCK), L.groups);
-    if (n) {
-        ProfScope p(s, "dense_fold");
-        k_dense_fold<<<L.chunks, WAVE, lds, s>>>(T, L.row, L.rows, ctl);
-    }
-    if (n && L.groups > 1) {
-        ProfScope p(s, "dense_groups");
-        k_dense_groups<<<dim3(pg.x, L.groups - 1), BLOCK, 0, s>>>(L.rows, L.row, L.chunks, L.grp);
-    }
-    {
-        ProfScope p(s, "dense_prefix");
-        k_dense_prefix<<<pg, BLOCK, 0, s>>>(L.rows, L.row, T.chunks, L.grp, n_ids, init, final_out);
-    }
+    const TraceChunks T{events, n, L.per, n_ids, n ? L.R.chunks : 0u};
+    launch_fold(T, L.R, ctl, s);
+    launch_prefix(L.R, T.chunks, n_ids, init, final_out, s);
     if (!n)
         return;
-    {
-        ProfScope p(s, "dense_apply");
-        k_dense_apply<<<L.chunks, WAVE, lds, s>>>(T, L.row, L.rows, status, L.masks, L.tcnt);
-    }
+    launch_apply(T, L.R, TraceOut{status, L.masks, L.tcnt, 0, 0}, s);
     launch_excl_scan(L.tcnt, L.tiles, L.offs, reinterpret_cast<uint64_t *>(&ctl->n_viol), L.xscan, ctl->tickets[10], s,
                      true);
     ProfScope p(s, "mask_scatter");
     const uint64_t blocks = ceil_div(L.tiles, BLOCK / WAVE);
     k_mask_scatter<<<(unsigned)(blocks < 8192 ? blocks : 8192), BLOCK, 0, s>>>(L.masks, n, L.offs, L.tiles, viol);
+}
+
+size_t dense_words_scratch_bytes(uint64_t tiles, uint32_t n_ids, bool probes)
+{
+    Carve c(nullptr);
+    (void)words_layout(c, tiles, n_ids, probes);
+    return c.bytes();
+}
+
+void launch_dense_words_fold(const DenseWords &W, bool probes, void *scratch, Control *ctl, hipStream_t s)
+{
+    launch_reset_control(ctl, s);
+    Carve c(scratch);
+    const Rows R = words_layout(c, W.tiles, W.n_ids, probes);
+    launch_fold(words_chunks(W, R), R, ctl, s);
+}
+
+void launch_dense_words_probe(const DenseWords &W, const uint8_t *init, uint8_t *pre, void *scratch, hipStream_t s)
+{
+    Carve c(scratch);
+    const Rows R = words_layout(c, W.tiles, W.n_ids, true);
+    const TileChunks T = words_chunks(W, R);
+    launch_prefix(R, T.chunks, W.n_ids, init, nullptr, s);
+    launch_apply(T, R, ProbeOut{pre}, s);
+}
+
+void launch_dense_words_apply(const DenseWords &W, bool probes, const uint8_t *init, uint64_t n, uint32_t tile,
+                              uint8_t *status, uint8_t *final_out, void *scratch, Control *ctl, hipStream_t s)
+{
+    Carve c(scratch);
+    const Rows R = words_layout(c, W.tiles, W.n_ids, probes);
+    const TileChunks T = words_chunks(W, R);
+    launch_prefix(R, T.chunks, W.n_ids, init, final_out, s);
+    launch_apply(T, R, PrimaryOut{status, n, tile, &ctl->n_induced_stuck, 0, 0}, s);
 }
 
 } // namespace vc

@@ -150,7 +150,8 @@ __global__ __launch_bounds__(BLOCK) void k_dyn_tiles(const uint32_t *__restrict_
                                                      const uint2 *__restrict__ life, uint64_t ntiles,
                                                      uint32_t *__restrict__ tcnt, const uint64_t *__restrict__ tpos,
                                                      uint64_t *__restrict__ items, uint32_t *__restrict__ words,
-                                                     uint32_t *__restrict__ pos32, uint64_t cap, Control *ctl)
+                                                     uint32_t *__restrict__ pos32, uint64_t cap, Control *ctl,
+                                                     uint32_t probe_op)
 {
     constexpr bool EMIT = MODE != D_COUNT;
     __shared__ uint32_t s_start[DWAVES][DTILE + 1];
@@ -253,7 +254,7 @@ __global__ __launch_bounds__(BLOCK) void k_dyn_tiles(const uint32_t *__restrict_
                     if (MODE == D_ITEMS)
                         item = make_item(y[u], fcode(OP_NOOP, 0), (uint32_t)(n + t));
                     if (MODE == D_WORDS)
-                        word = y[u] | (uint32_t)OP_NOOP << 24;
+                        word = y[u] | probe_op << 24;
                 } else {
                     keep = (lf[u].x == NO_POS || lf[u].x < t) && (lf[u].y == NO_POS || t < lf[u].y);
                     if (MODE == D_ITEMS)
@@ -271,7 +272,7 @@ __global__ __launch_bounds__(BLOCK) void k_dyn_tiles(const uint32_t *__restrict_
                     items[p] = item;
                 } else {
                     words[p] = word;
-                    if (primary)
+                    if (primary && (probe_op == OP_NOOP || ((s_word[wv][o] >> 24) & 7u) == OP_CREATE))
                         pos32[i0 + o] = (uint32_t)p; // below 2^32 on this route
                 }
             }
@@ -346,6 +347,8 @@ void launch_dyn_life(const uint32_t *ev, uint64_t n, uint32_t n_ids, uint32_t *c
     }
 }
 
+uint32_t dyn_tile_events() { return DTILE; }
+
 uint64_t dyn_tiles(uint64_t n) { return ceil_div(n, (uint64_t)DTILE); }
 
 void launch_dyn_count(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint32_t *mother, const uint32_t *cpos,
@@ -361,7 +364,7 @@ void launch_dyn_count(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint
         ProfScope p(s, "dyn_count");
         k_dyn_tiles<D_COUNT><<<(unsigned)ceil_div(ntiles, (uint64_t)DWAVES), BLOCK, 0, s>>>(
             ev, n, n_ids, mother, cpos, dpos, o->off, o->nbr, life, ntiles, tcnt, nullptr, nullptr, nullptr, nullptr, 0,
-            ctl);
+            ctl, OP_NOOP);
     }
 }
 
@@ -374,20 +377,20 @@ void launch_dyn_emit(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint3
         ProfScope p(s, "dyn_emit");
         k_dyn_tiles<D_ITEMS><<<(unsigned)ceil_div(ntiles, (uint64_t)DWAVES), BLOCK, 0, s>>>(
             ev, n, n_ids, mother, cpos, dpos, o->off, o->nbr, life, ntiles, nullptr, tpos, items, nullptr, nullptr, cap,
-            ctl);
+            ctl, OP_NOOP);
     }
 }
 
 void launch_dyn_words(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint32_t *mother, const uint32_t *cpos,
                       const uint32_t *dpos, const OverlapSets *o, const uint2 *life, const uint64_t *tpos,
-                      uint32_t *words, uint32_t *pos32, uint64_t cap, Control *ctl, hipStream_t s)
+                      uint32_t *words, uint32_t *pos32, uint64_t cap, Control *ctl, hipStream_t s, uint32_t probe_op)
 {
     const uint64_t ntiles = dyn_tiles(n);
     if (ntiles) {
         ProfScope p(s, "dyn_words");
         k_dyn_tiles<D_WORDS><<<(unsigned)ceil_div(ntiles, (uint64_t)DWAVES), BLOCK, 0, s>>>(
             ev, n, n_ids, mother, cpos, dpos, o->off, o->nbr, life, ntiles, nullptr, tpos, nullptr, words, pos32, cap,
-            ctl);
+            ctl, probe_op);
     }
 }
 

@@ -188,11 +188,14 @@ void launch_dyn_count(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint
 void launch_dyn_emit(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint32_t *mother, const uint32_t *cpos,
                      const uint32_t *dpos, const OverlapSets *o, const uint2 *life, const uint64_t *tpos,
                      uint64_t *items, uint64_t cap, Control *ctl, hipStream_t s);
-// bucket route: the same items as 32-bit words (creates, destroys and probes no-ops on
-// their array, induced items op 5), pos32[t] = event t's position among them
+uint32_t dyn_tile_events();
+// the same items as 32-bit words (creates and destroys no-ops on their array, probes of op
+// probe_op, induced items op 5), pos32[t] = event t's position among them (only creates'
+// unless the probes are no-ops too)
 void launch_dyn_words(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint32_t *mother, const uint32_t *cpos,
                       const uint32_t *dpos, const OverlapSets *o, const uint2 *life, const uint64_t *tpos,
-                      uint32_t *words, uint32_t *pos32, uint64_t cap, Control *ctl, hipStream_t s);
+                      uint32_t *words, uint32_t *pos32, uint64_t cap, Control *ctl, hipStream_t s,
+                      uint32_t probe_op = 4);
 // bucket route: the initial statuses of the second check from the words' pre-statuses
 // (bits 0-1 of pre[i], read through dstidx[i] when it is given; a create's probe right
 // after it)
@@ -250,6 +253,7 @@ void launch_overlap_count(const uint32_t *ev, uint64_t n, uint32_t n_arrays, con
 // places the tiles, and the word pass writes the stream (cap words) and, when pos32 is
 // given, every event's position in it
 uint64_t overlap_word_tiles(uint64_t n);
+uint32_t overlap_tile_events();
 void launch_overlap_tile_count(const uint32_t *ev, uint64_t n, uint32_t n_arrays, const OverlapSets *o,
                                uint32_t *tcnt, Control *ctl, hipStream_t s);
 void launch_overlap_words(const uint32_t *ev, uint64_t n, uint32_t n_arrays, const OverlapSets *o, const uint64_t *tpos,

@@ -456,6 +456,8 @@ void launch_overlap_count(const uint32_t *ev, uint64_t n, uint32_t n_arrays, con
         }
 }
 
+uint32_t overlap_tile_events() { return XTILE; }
+
 uint64_t overlap_word_tiles(uint64_t n) { return ceil_div(n, (uint64_t)XTILE); }
 
 void launch_overlap_tile_count(const uint32_t *ev, uint64_t n, uint32_t n_arrays, const OverlapSets *o,

@@ -5,6 +5,7 @@
 
 #include "abi_internal.h"
 #include "bucket.h"
+#include "dense.h"
 #include "internal.h"
 
 using namespace vc;
@@ -274,6 +275,43 @@ extern "C" int vc_trace_set_dynamic_arrays(vc_trace *t, const uint32_t *lo, cons
     return VC_OK;
 }
 
+// the check of a dynamic trace whose statuses fit LDS: the items as 32-bit words, checked in
+// their order twice from the chunks' functions found once, for the statuses the probes see
+// (the inherited statuses) and, from them, for every status byte and the final table.
+// The expansion reports its errors into a control block of its own, merged at the end.
+static int dynamic_dense_enqueue(vc_trace *t, hipStream_t s)
+{
+    const uint64_t n = t->n, m = t->n_items, ntiles = dyn_tiles(n);
+    int r;
+    if ((r = devbuf_reserve(t->status, n ? n : 1)) != VC_OK ||
+        (r = devbuf_reserve(t->fin, t->n_ids ? t->n_ids : 1)) != VC_OK ||
+        (r = devbuf_reserve(t->viol, (n ? n : 1) * 4)) != VC_OK ||
+        (r = devbuf_reserve(t->items_a, (m ? m : 1) * 4)) != VC_OK ||
+        (r = devbuf_reserve(t->items_b, m ? m : 1)) != VC_OK ||
+        (r = devbuf_reserve(t->scratch, std::max({dense_words_scratch_bytes(ntiles, t->n_ids, true),
+                                                  compact_scratch_bytes(n), t->scratch.bytes}))) != VC_OK ||
+        (r = devbuf_reserve(t->aux, dyn_aux(nullptr, n).bytes)) != VC_OK)
+        return r;
+    const DynAux A = dyn_aux(t->aux.p, n);
+    launch_reset_control(A.xctl, s);
+    if ((r = dyn_count_items(t, s, A.xctl)) != VC_OK)
+        return r;
+    const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
+    uint32_t *words = (uint32_t *)t->items_a.p;
+    uint8_t *pre = (uint8_t *)t->items_b.p, *fin = (uint8_t *)t->fin.p;
+    launch_dyn_words(t->events, n, t->n_ids, t->mother, L.cpos, L.dpos, &t->sets, L.life, A.tpos, words, A.pos32, m,
+                     A.xctl, s, DENSE_OP_PROBE);
+    const DenseWords W{words, m, A.tpos, ntiles, t->n_ids};
+    launch_dense_words_fold(W, true, t->scratch.p, t->ctl, s);
+    launch_dense_words_probe(W, t->init, pre, t->scratch.p, s);
+    launch_dyn_inherit_words(t->mother, L.cpos, pre, nullptr, A.pos32, n, m, t->init, t->n_ids, L.init2, fin, s);
+    launch_dense_words_apply(W, true, L.init2, n, dyn_tile_events(), (uint8_t *)t->status.p, fin, t->scratch.p, t->ctl,
+                             s);
+    launch_compact((uint8_t *)t->status.p, n, (uint32_t *)t->viol.p, t->scratch.p, t->ctl, s);
+    launch_merge_errors(t->ctl, A.xctl, s);
+    return VC_OK;
+}
+
 // the check of a dynamic trace through the bucket engine: the items as 32-bit words, a
 // first check for the statuses the probes see (the inherited statuses), a second from
 // them for every status byte and the final table; the primaries' bytes gathered back
@@ -281,6 +319,8 @@ extern "C" int vc_trace_set_dynamic_arrays(vc_trace *t, const uint32_t *lo, cons
 // (each check resets the trace's), merged at the end.
 static int dynamic_bucket_enqueue(vc_trace *t, hipStream_t s)
 {
+    if (t->n_ids <= DENSE_MAX_IDS)
+        return dynamic_dense_enqueue(t, s);
     const uint64_t n = t->n, m = t->n_items;
     int r;
     if ((r = devbuf_reserve(t->status, n ? n : 1)) != VC_OK ||
@@ -375,12 +415,47 @@ bool overlap_bucket_path(const vc_trace *t)
            !getenv("VC_GENERAL_PATH");
 }
 
+// the check of a trace over overlapping arrays whose statuses fit LDS: the combined stream
+// as 32-bit words, checked in its order; the expansion reports its errors into a second
+// control block (the check resets the trace's)
+static int overlap_dense_enqueue(vc_trace *t, hipStream_t s)
+{
+    const uint64_t n = t->n, m = t->n + t->n_induced, ntiles = overlap_word_tiles(n);
+    int r;
+    const size_t tcnt_bytes = (ntiles * 4 + 255) & ~size_t(255), tpos_bytes = ((ntiles + 1) * 8 + 255) & ~size_t(255);
+    if ((r = devbuf_reserve(t->aux, tcnt_bytes + tpos_bytes + CONTROL_BYTES)) != VC_OK ||
+        (r = devbuf_reserve(t->status, n ? n : 1)) != VC_OK ||
+        (r = devbuf_reserve(t->fin, t->n_ids ? t->n_ids : 1)) != VC_OK ||
+        (r = devbuf_reserve(t->viol, (n ? n : 1) * 4)) != VC_OK ||
+        (r = devbuf_reserve(t->items_a, (m ? m : 1) * 4)) != VC_OK ||
+        (r = devbuf_reserve(t->scratch, std::max({dense_words_scratch_bytes(ntiles, t->n_ids, false),
+                                                  excl_scan_scratch_bytes(ntiles), compact_scratch_bytes(n)}))) != VC_OK)
+        return r;
+    uint32_t *tcnt = (uint32_t *)t->aux.p;
+    uint64_t *tpos = (uint64_t *)((char *)t->aux.p + tcnt_bytes);
+    Control *xctl = (Control *)((char *)t->aux.p + tcnt_bytes + tpos_bytes);
+    uint32_t *words = (uint32_t *)t->items_a.p;
+    launch_reset_control(xctl, s);
+    launch_overlap_tile_count(t->events, n, t->n_ids, &t->sets, tcnt, xctl, s);
+    launch_excl_scan(tcnt, ntiles, tpos, nullptr, t->scratch.p, xctl->tickets[5], s);
+    launch_overlap_words(t->events, n, t->n_ids, &t->sets, tpos, words, m, nullptr, xctl, s);
+    const DenseWords W{words, m, tpos, ntiles, t->n_ids};
+    launch_dense_words_fold(W, false, t->scratch.p, t->ctl, s);
+    launch_dense_words_apply(W, false, t->init, n, overlap_tile_events(), (uint8_t *)t->status.p, (uint8_t *)t->fin.p,
+                             t->scratch.p, t->ctl, s);
+    launch_compact((uint8_t *)t->status.p, n, (uint32_t *)t->viol.p, t->scratch.p, t->ctl, s);
+    launch_merge_errors(t->ctl, xctl, s);
+    return VC_OK;
+}
+
 // the check of a trace over overlapping arrays through the bucket engine: the combined
 // stream (events and induced RW items) as 32-bit words, checked like a plain trace, the
 // primaries' bytes gathered back and compacted; the expansion reports its errors into a
 // second control block (the bucket check resets the trace's)
 int overlap_bucket_enqueue(vc_trace *t, hipStream_t s)
 {
+    if (t->n_ids <= DENSE_MAX_IDS)
+        return overlap_dense_enqueue(t, s);
     const uint64_t n = t->n, m = t->n + t->n_induced, ntiles = overlap_word_tiles(n);
     int r;
     const size_t pos_bytes = (n * 4 + 255) & ~size_t(255), tcnt_bytes = (ntiles * 4 + 255) & ~size_t(255),

@@ -72,3 +72,79 @@ def test_dense_malformed(ctx, at):
         ctx.sync()
     assert x.value.code == V.VC_EINVAL and f"index {at}" in str(x.value)
     t.free()
+
+
+@pytest.mark.parametrize("n_ids", [1, 64, 65, 4097, 1 << 16, (1 << 16) + 1, 80_000])
+@pytest.mark.parametrize("n", [1, 511, 512, 513, 40_000, 700_001])
+def test_overlap_words(ctx, n, n_ids):
+    """The combined stream in program order (up to 2^16 arrays) and through the buckets
+    (more), at tile ends, with arrays in clusters that all overlap each other."""
+    from paper_1910_11110_amd import vcheck as V
+    print(f"[dense] overlap {n} x {n_ids}", flush=True)
+    rng = np.random.default_rng(n + n_ids)
+    lo = (np.arange(n_ids) // 7 * 16 + rng.integers(0, 8, n_ids)).astype(np.uint32)
+    hi = lo + rng.integers(1, 12, n_ids).astype(np.uint32)
+    op = rng.integers(0, 5, n) if n != 513 else np.zeros(n, np.int64)
+    e = gen.pack_events(np.minimum(rng.integers(0, n_ids, n), rng.integers(0, n_ids, n)), op, rng.integers(0, 2, n))
+    init = rng.integers(0, 4, n_ids).astype(np.uint8)
+    t = V.Trace.load(ctx, e, n_ids, init)
+    t.set_arrays(lo, hi)
+    ref = O.check_overlap(e, lo, hi, init)
+    for _ in range(2):
+        t.check()
+        assert np.array_equal(t.status(), ref.status)
+        assert np.array_equal(t.final(), ref.final)
+        v = t.violations()
+        assert np.array_equal(v.indices, ref.violations) and v.first == ref.first
+        assert t.induced_stuck() == ref.n_induced_stuck
+    t.free()
+
+
+@pytest.mark.parametrize("nv,npv", [(2, 30), (64, (1 << 16) - 64), (64, (1 << 16) - 63)])
+@pytest.mark.parametrize("n", [513, 300_001])
+def test_dynamic_words(ctx, n, nv, npv):
+    from paper_1910_11110_amd import vcheck as V
+    npv = min(npv, n // 4)
+    print(f"[dense] dynamic {n} x {nv}+{npv}", flush=True)
+    d = gen.dynamic_trace(n, nv, npv, n + npv, space=nv << 14)
+    rng = np.random.default_rng(n)
+    init = rng.integers(1, 4, d.lo.size).astype(np.uint8)
+    ref = O.check_dynamic(d.events, d.lo, d.hi, d.mother, init)
+    t = V.Trace.load(ctx, d.events, d.lo.size, init, lifetimes=True)
+    t.set_dynamic_arrays(d.lo, d.hi, d.mother)
+    for _ in range(2):
+        t.check()
+        assert np.array_equal(t.status(), ref.status)
+        assert np.array_equal(t.final(), ref.final)
+        v = t.violations()
+        assert np.array_equal(v.indices, ref.violations) and v.first == ref.first
+    t.free()
+
+
+def test_overlap_events_changed(ctx):
+    """Device events rewritten after the arrays were set: more induced items than the stream
+    holds are refused and reported, and the check stays in bounds; the old events again
+    give the old results."""
+    import torch
+    from paper_1910_11110_amd import vcheck as V
+    n, n_ids = 50_000, 300
+    rng = np.random.default_rng(3)
+    lo = (np.arange(n_ids) // 10 * 16).astype(np.uint32)
+    hi = lo + 8
+    e = gen.pack_events(rng.integers(0, n_ids, n), rng.integers(0, 5, n), rng.integers(0, 2, n))
+    d = torch.from_numpy(e.view(np.int32).copy()).cuda()
+    torch.cuda.synchronize()
+    t = V.Trace.load(ctx, d, n_ids)
+    t.set_arrays(lo, hi)
+    t.check()
+    want = t.status()
+    d.copy_((d & 0x08FFFFFF) | (1 << 24))  # every event a write
+    torch.cuda.synchronize()
+    t.check()
+    with pytest.raises(V.VCError):
+        ctx.sync()
+    d.copy_(torch.from_numpy(e.view(np.int32)))
+    torch.cuda.synchronize()
+    t.check()
+    assert np.array_equal(t.status(), want)
+    t.free()
