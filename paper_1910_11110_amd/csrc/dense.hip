@@ -17,156 +17,14 @@
 // that finds the bit set knows.  The lanes of a shared id (rare over many ids, the rule
 // over few or over skewed ones) are put in order by composing their functions along them.
 #include "dense.h"
-#include "device.h"
+#include "dense_steps.h"
 #include "prof.h"
 
 namespace vc {
 
 namespace {
 
-// ----------------------------------------------------------------------------------
-// Table words: 8 ids of 3 bits and, in the top byte, a touch bit for each (zero between
-// steps).  An id's bits are a monoid element: bit 2 a constant, whose status is bits 0
-// (CPU copy valid) and 1 (GPU); else bit 0 "CPU |= GPU" and bit 1 "GPU |= CPU".
-// ----------------------------------------------------------------------------------
-constexpr uint32_t T_TOUCH = 1u << 24;
-constexpr uint32_t MX = 011111111u, MY = MX << 1, MT = MX << 2;
-
-// h o f (f first), 8 ids at once (counters zero)
-__device__ __forceinline__ uint32_t tw_compose(uint32_t h, uint32_t f)
-{
-    const uint32_t ftx = (f >> 2) & MX, htx = (h >> 2) & MX;
-    const uint32_t ex = f | (h & (~ftx | (f >> 1)));
-    const uint32_t ey = f | (h & (~(ftx << 1) | (f << 1)));
-    const uint32_t hx = htx | (htx << 1); // fields that h makes constant
-    return ((h | f) & MT) | (((h & hx) | (((ex & MX) | (ey & MY)) & ~hx)));
-}
-
-// the same on one id's 3 bits
-__device__ __forceinline__ uint32_t el_compose(uint32_t h, uint32_t f)
-{
-    const uint32_t ft = f >> 2;
-    const uint32_t ex = f | (h & ((ft ^ 1u) | (f >> 1)));
-    const uint32_t ey = f | (h & (((ft ^ 1u) << 1) | (f << 1)));
-    const uint32_t r = ((h | f) & 4u) | (ex & 1u) | (ey & 2u);
-    return (h & 4u) ? h : r;
-}
-
-// Per (op | side << 3): an effect's element; for the backward walk the element h o f for
-// every h, 3 bits each; for the forward walk the status byte for every status before the
-// event, 8 bits each.  In constant memory, copied to LDS by every wave.
-constexpr uint32_t host_compose(uint32_t h, uint32_t f)
-{
-    if (h & 4u)
-        return h;
-    const uint32_t x = (f & 1u) | ((h & 1u) & ((f & 4u) ? (f >> 1) & 1u : 1u));
-    const uint32_t y = ((f >> 1) & 1u) | (((h >> 1) & 1u) & ((f & 4u) ? f & 1u : 1u));
-    return (f & 4u) | x | (y << 1);
-}
-struct StepTable {
-    uint32_t fold[16];  // (h o f) << 3h, the element in bits 24-26
-    uint32_t apply[16]; // status byte << 8s
-};
-constexpr StepTable make_step_table()
-{
-    StepTable t{};
-    for (uint32_t i = 0; i < 16; i++) {
-        const uint32_t op = i & 7u, side = i >> 3, own = side ? 2u : 1u;
-        uint32_t e = 0;
-        if (op == OP_W || op == OP_RWIND)
-            e = 4u | own;
-        else if (op == OP_PUSH)
-            e = side ? 1u : 2u;
-        else if (op == OP_PULL)
-            e = side ? 2u : 1u;
-        for (uint32_t h = 0; h < 8; h++)
-            t.fold[i] |= host_compose(h, e) << (3 * h);
-        t.fold[i] |= e << 24;
-        const Effect x = make_effect(op <= OP_RWIND ? op : (uint32_t)OP_NOOP, side);
-        for (uint32_t s = 0; s < 4; s++) {
-            const uint32_t post = (x.f4 >> (8 * s)) & 3u;
-            t.apply[i] |= (post | (s << 2) | (((x.stuck >> s) & 1u) << 7)) << (8 * s);
-        }
-    }
-    return t;
-}
-__constant__ constexpr StepTable STEPS = make_step_table();
-
-__device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory"); }
-
-// (relaxed: one wave, whose LDS operations execute in order)
-__device__ __forceinline__ uint32_t tab_touch(uint32_t *p, uint32_t bit)
-{
-    return __hip_atomic_fetch_or(p, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-}
-__device__ __forceinline__ void tab_untouch(uint32_t *p, uint32_t bit)
-{
-    (void)__hip_atomic_fetch_and(p, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-}
-__device__ __forceinline__ void tab_xor(uint32_t *p, uint32_t v)
-{
-    (void)__hip_atomic_fetch_xor(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-}
-__device__ __forceinline__ uint32_t tab_load(const uint32_t *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-}
-
-// the lanes of `among` with this lane's id (ids of `bits` bits, at most 16)
-__device__ __forceinline__ uint64_t same_id(uint32_t id, uint64_t among, uint32_t bits)
-{
-    uint32_t lo = (uint32_t)among, hi = (uint32_t)(among >> 32);
-    match_bits<0, 4>(id, lo, hi);
-    if (bits > 4)
-        match_bits<4, 8>(id, lo, hi);
-    if (bits > 8)
-        match_bits<8, 12>(id, lo, hi);
-    if (bits > 12)
-        match_bits<12, 16>(id, lo, hi);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// Composition of the functions (4-byte form) of the lanes of a lane's id up to and with
-// it, by pointer jumping along them; p is the nearest lower one, 64 if none.  BACK: lower
-// lanes are later events (their function comes last).  The pointer travels in the bits
-// that a function's bytes leave free.  Q steps at once, independent of each other.
-template <bool BACK, int Q>
-__device__ __forceinline__ void compose_along(uint32_t (&f)[Q], uint32_t (&p)[Q])
-{
-    constexpr uint32_t F4 = 0x03030303u, NONE = 64u << 4;
-    for (;;) {
-        bool more = false;
-#pragma unroll
-        for (int q = 0; q < Q; q++) {
-            // (forwards, nothing before a constant matters: a constant's byte 0 is not 0)
-            if (!BACK && (f[q] & 3u))
-                p[q] = 64u;
-            more = more || p[q] < 64u;
-        }
-        if (!__ballot(more))
-            break;
-        uint32_t v[Q];
-#pragma unroll
-        for (int q = 0; q < Q; q++)
-            v[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(p[q] * 4u),
-                                                          (int)(f[q] | ((p[q] & 63u) << 2) | ((p[q] & 64u) << 4)));
-#pragma unroll
-        for (int q = 0; q < Q; q++) {
-            const uint32_t g = p[q] < 64u ? v[q] & F4 : F_ID;
-            f[q] = BACK ? fcompose(g, f[q]) : fcompose(f[q], g);
-            p[q] = p[q] < 64u && !(v[q] & NONE) ? (v[q] >> 2) & 63u : 64u;
-        }
-    }
-}
-
-// a function in 4-byte form as an element
-__device__ __forceinline__ uint32_t el_of(uint32_t f4)
-{
-    return ((f4 >> 16) & 1u) | ((f4 >> 8) & 2u) | ((f4 & 3u) ? 4u : 0u);
-}
-
 constexpr uint32_t OP_PROBE = DENSE_OP_PROBE;
-constexpr int D_UNROLL = 8; // steps whose events are loaded together
 
 // the chunks of one trace: `per` events each (a multiple of 64), the last one the rest
 struct TraceChunks {
@@ -204,176 +62,6 @@ struct TileChunks {
     }
 };
 
-// ----------------------------------------------------------------------------------
-// A step: 64 events, one a lane.  DIR says what an event does to its id's bits.
-// ----------------------------------------------------------------------------------
-// backwards: the id's function after the event's first.  An event that changes nothing
-// takes no part, nor does one whose id is a constant already.
-struct Fold {
-    static constexpr bool BACK = true;
-    __device__ static uint32_t entry(const uint32_t *tab, uint32_t op) { return tab[op]; }
-    __device__ static bool takes_part(uint32_t e) { return (e >> 24) != 0; }
-    __device__ static bool open(uint32_t h) { return (h & 4u) == 0; }
-    // the bits after the event, and the result byte
-    __device__ static uint32_t next(uint32_t e, uint32_t h, uint32_t &) { return (e >> (3u * h)) & 7u; }
-};
-// forwards: the status after the event, and its status byte
-struct Apply {
-    static constexpr bool BACK = false;
-    __device__ static uint32_t entry(const uint32_t *tab, uint32_t op) { return tab[16 + op]; }
-    __device__ static bool takes_part(uint32_t) { return true; }
-    __device__ static bool open(uint32_t) { return true; }
-    __device__ static uint32_t next(uint32_t e, uint32_t h, uint32_t &byte)
-    {
-        byte = e >> (8u * (h & 3u));
-        return 4u | (byte & 3u);
-    }
-};
-
-struct Lane { // one lane's event in a step
-    uint32_t *p;
-    uint32_t id, entry, old, op; // op | side << 3
-    bool part;
-    __device__ uint32_t sh() const { return 3u * (id & 7u); }
-    __device__ uint32_t touch() const { return T_TOUCH << (id & 7u); }
-    __device__ uint32_t f4(const uint32_t *s_tab) const { return s_tab[16 + op]; }
-    __device__ bool met() const { return part && (old & touch()) != 0; }
-    __device__ void enter()
-    {
-        old = 0;
-        if (part)
-            old = tab_touch(p, touch());
-    }
-    __device__ void leave() const
-    {
-        if (part)
-            tab_untouch(p, touch());
-    }
-};
-
-template <class DIR>
-__device__ __forceinline__ Lane make_lane(uint32_t *s_t, const uint32_t *s_tab, uint32_t w, uint32_t id, bool in)
-{
-    Lane L;
-    L.id = id;
-    L.p = s_t + (id >> 3);
-    L.op = (w >> 24) & 15u;
-    L.entry = DIR::entry(s_tab, L.op);
-    L.part = in && DIR::takes_part(L.entry);
-    L.old = 0;
-    return L;
-}
-
-// no two lanes share an id
-template <class DIR>
-__device__ __forceinline__ uint32_t step_apart(const Lane &L)
-{
-    const uint32_t h = (L.old >> L.sh()) & 7u;
-    uint32_t byte = 0;
-    const uint32_t nh = DIR::next(L.entry, h, byte);
-    if (L.part)
-        tab_xor(L.p, ((h ^ nh) << L.sh()) | L.touch());
-    return byte;
-}
-
-// Q steps whose lanes may share ids, one after the other; no touch bit is set.  What the
-// lanes of an id do together does not depend on the table, so the steps work it out side
-// by side.  `shared` counts the steps where any did.
-template <class DIR, int Q>
-__device__ __forceinline__ void steps_together(const Lane (&L)[Q], uint32_t (&byte)[Q], const uint32_t *s_tab,
-                                               uint32_t bits, uint32_t lane, uint32_t &shared)
-{
-    uint32_t f[Q], p[Q], prev[Q];
-    bool in[Q], last[Q];
-#pragma unroll
-    for (int q = 0; q < Q; q++) // (a later step's id may close before it: it then changes nothing)
-        in[q] = L[q].part && (!DIR::BACK || DIR::open((tab_load(L[q].p) >> L[q].sh()) & 7u));
-#pragma unroll
-    for (int q = 0; q < Q; q++) {
-        const uint64_t same = same_id(L[q].id, __ballot(in[q]), bits);
-        const uint32_t rank = mask_rank(same);
-        const uint64_t below = same & ((1ull << lane) - 1);
-        prev[q] = p[q] = in[q] && rank ? 63u - (uint32_t)__builtin_clzll(below) : 64u;
-        last[q] = in[q] && rank + 1 == (uint32_t)__builtin_popcountll(same); // of its id
-        f[q] = (DIR::BACK ? L[q].f4(s_tab) : L[q].entry) & 0x03030303u;
-        shared += __ballot(prev[q] < 64) ? 1u : 0u;
-    }
-    compose_along<DIR::BACK, Q>(f, p);
-    uint32_t g[Q];
-    if constexpr (!DIR::BACK)
-#pragma unroll
-        for (int q = 0; q < Q; q++)
-            g[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((prev[q] & 63u) * 4u), (int)f[q]);
-#pragma unroll
-    for (int q = 0; q < Q; q++) {
-        const uint32_t h = (tab_load(L[q].p) >> L[q].sh()) & 7u;
-        uint32_t nh;
-        if constexpr (DIR::BACK)
-            nh = el_compose(h, el_of(f[q]));
-        else
-            nh = DIR::next(L[q].entry, prev[q] < 64 ? fapply(g[q], h & 3u) : h, byte[q]);
-        if (last[q])
-            tab_xor(L[q].p, (h ^ nh) << L[q].sh());
-        compiler_fence();
-    }
-}
-
-// D_PAIR steps at once: all enter, and when no lane met a touched id, neither of its own
-// step nor of the ones before it, their reads are one wait and their changes independent.
-// Otherwise all leave and take their turns.
-constexpr int D_PAIR = 2;
-template <class DIR>
-__device__ __forceinline__ void steps(Lane (&L)[D_PAIR], uint32_t (&byte)[D_PAIR], const uint32_t *s_tab,
-                                      uint32_t bits, uint32_t lane, uint32_t &shared_steps)
-{
-    bool met = false;
-#pragma unroll
-    for (int q = 0; q < D_PAIR; q++)
-        L[q].enter();
-#pragma unroll
-    for (int q = 0; q < D_PAIR; q++)
-        met = met || L[q].met();
-    if (!__ballot(met)) {
-#pragma unroll
-        for (int q = 0; q < D_PAIR; q++)
-            byte[q] = step_apart<DIR>(L[q]);
-        return;
-    }
-    compiler_fence();
-#pragma unroll
-    for (int q = 0; q < D_PAIR; q++)
-        L[q].leave();
-    compiler_fence();
-#pragma unroll
-    for (int q = 0; q < D_PAIR; q++) {
-        if (DIR::BACK && L[q].part) // ids that are constants already take no part
-            L[q].part = DIR::open((tab_load(L[q].p) >> L[q].sh()) & 7u);
-        L[q].enter();
-        if (!__ballot(L[q].met())) {
-            byte[q] = step_apart<DIR>(L[q]);
-        } else {
-            L[q].leave();
-            compiler_fence();
-            const Lane one[1] = {L[q]};
-            uint32_t b[1] = {0};
-            steps_together<DIR, 1>(one, b, s_tab, bits, lane, shared_steps);
-            byte[q] = b[0];
-        }
-        compiler_fence();
-    }
-}
-
-// a round whose last one had shared ids in at least so many of its steps expects them in
-// every step, and looks for them at once
-constexpr uint32_t D_TOGETHER = D_UNROLL / 2;
-
-__device__ __forceinline__ void load_step_table(uint32_t *s_tab, uint32_t lane)
-{
-    if (lane < 32)
-        s_tab[lane] = lane < 16 ? STEPS.fold[lane] : STEPS.apply[lane - 16];
-    compiler_fence();
-}
-
 // 1. every chunk's functions into its row
 template <class CHUNKS>
 __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uint32_t *__restrict__ rows,
@@ -405,9 +93,9 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uin
                 report(i);
                 w = clean(w, true);
             }
-            const Lane one[1] = {make_lane<Fold>(s_t, s_tab, w, w & 0xFFFFu, in)};
+            const Lane<Fold<Two>> one[1] = {make_lane<Fold<Two>>(s_t, s_tab, w, w & 0xFFFFu, in)};
             uint32_t none[1];
-            steps_together<Fold, 1>(one, none, s_tab, bits, lane, shared_steps);
+            steps_together<Fold<Two>, 1>(one, none, s_tab, bits, lane, shared_steps);
             left -= m;
         }
         // whole rounds: lane l takes the round's last event but l, then 64 before, ...
@@ -442,28 +130,28 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uin
                 uint32_t v[D_PAIR] = {w[0], w[1]};
 #pragma unroll 1
                 for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                    Lane L[D_PAIR];
+                    Lane<Fold<Two>> L[D_PAIR];
                     uint32_t none[D_PAIR];
                     const int n = u + D_PAIR < D_UNROLL ? u + D_PAIR : u;
 #pragma unroll
                     for (int q = 0; q < D_PAIR; q++) {
                         const uint32_t x = clean(v[q], T.bad(v[q]));
                         v[q] = e[-((n + q) * WAVE)];
-                        L[q] = make_lane<Fold>(s_t, s_tab, x, x & 0xFFFFu, true);
+                        L[q] = make_lane<Fold<Two>>(s_t, s_tab, x, x & 0xFFFFu, true);
                     }
-                    steps_together<Fold, D_PAIR>(L, none, s_tab, bits, lane, shared_steps);
+                    steps_together<Fold<Two>, D_PAIR>(L, none, s_tab, bits, lane, shared_steps);
                 }
                 continue;
             }
             shared_steps = 0;
 #pragma unroll
             for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                Lane L[D_PAIR];
+                Lane<Fold<Two>> L[D_PAIR];
                 uint32_t byte[D_PAIR];
 #pragma unroll
                 for (int q = 0; q < D_PAIR; q++)
-                    L[q] = make_lane<Fold>(s_t, s_tab, w[u + q], w[u + q] & 0xFFFFu, true);
-                steps<Fold>(L, byte, s_tab, bits, lane, shared_steps);
+                    L[q] = make_lane<Fold<Two>>(s_t, s_tab, w[u + q], w[u + q] & 0xFFFFu, true);
+                steps<Fold<Two>>(L, byte, s_tab, bits, lane, shared_steps);
             }
         }
         compiler_fence();
@@ -655,16 +343,16 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, co
                 uint32_t v[D_PAIR] = {w[0], w[1]};
 #pragma unroll 1
                 for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                    Lane L[D_PAIR];
+                    Lane<Apply<Two>> L[D_PAIR];
                     uint32_t byte[D_PAIR], now[D_PAIR];
                     const int n = u + D_PAIR < D_UNROLL ? u + D_PAIR : u;
 #pragma unroll
                     for (int q = 0; q < D_PAIR; q++) {
                         now[q] = v[q];
-                        L[q] = make_lane<Apply>(s_t, s_tab, v[q], id_of(v[q]), true);
+                        L[q] = make_lane<Apply<Two>>(s_t, s_tab, v[q], id_of(v[q]), true);
                         v[q] = T.ev[i + (n + q) * WAVE + lane];
                     }
-                    steps_together<Apply, D_PAIR>(L, byte, s_tab, bits, lane, shared_steps);
+                    steps_together<Apply<Two>, D_PAIR>(L, byte, s_tab, bits, lane, shared_steps);
 #pragma unroll
                     for (int q = 0; q < D_PAIR; q++)
                         out.step(lane, u + q, i + (u + q) * WAVE, now[q], byte[q], true);
@@ -673,12 +361,12 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, co
                 shared_steps = 0;
 #pragma unroll
                 for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                    Lane L[D_PAIR];
+                    Lane<Apply<Two>> L[D_PAIR];
                     uint32_t byte[D_PAIR];
 #pragma unroll
                     for (int q = 0; q < D_PAIR; q++)
-                        L[q] = make_lane<Apply>(s_t, s_tab, w[u + q], id_of(w[u + q]), true);
-                    steps<Apply>(L, byte, s_tab, bits, lane, shared_steps);
+                        L[q] = make_lane<Apply<Two>>(s_t, s_tab, w[u + q], id_of(w[u + q]), true);
+                    steps<Apply<Two>>(L, byte, s_tab, bits, lane, shared_steps);
 #pragma unroll
                     for (int q = 0; q < D_PAIR; q++)
                         out.step(lane, u + q, i + (u + q) * WAVE, w[u + q], byte[q], true);
@@ -691,9 +379,9 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, co
         for (uint32_t k = past; k < len; k += WAVE) {
             const bool valid = k + lane < len;
             const uint32_t w = valid ? T.ev[i0 + k + lane] : (uint32_t)OP_NOOP << 24, id = id_of(w);
-            const Lane one[1] = {make_lane<Apply>(s_t, s_tab, w, id, valid)};
+            const Lane<Apply<Two>> one[1] = {make_lane<Apply<Two>>(s_t, s_tab, w, id, valid)};
             uint32_t b[1];
-            steps_together<Apply, 1>(one, b, s_tab, bits, lane, shared_steps);
+            steps_together<Apply<Two>, 1>(one, b, s_tab, bits, lane, shared_steps);
             out.step(lane, (k - past) / WAVE, i0 + k, w, b[0], valid);
         }
         if (past < len)

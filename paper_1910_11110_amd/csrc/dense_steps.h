@@ -1,0 +1,383 @@
+// dense_steps.h -- 64 events at a time on a table of all ids' functions or statuses in LDS
+// (one wave; used by the dense and the wide check).
+//
+// A domain says what a table word holds: Two, the two memory spaces, 8 ids a word; its
+// functions are passed between lanes in 4-byte form.  Fold walks events backwards and
+// composes every id's function, Apply walks them forwards on the ids' statuses.
+#pragma once
+#include "device.h"
+#include "internal.h"
+
+namespace vc {
+namespace {
+
+// ----------------------------------------------------------------------------------
+// Table words: 8 ids of 3 bits and, in the top byte, a touch bit for each (zero between
+// steps).  An id's bits are a monoid element: bit 2 a constant, whose status is bits 0
+// (CPU copy valid) and 1 (GPU); else bit 0 "CPU |= GPU" and bit 1 "GPU |= CPU".
+// ----------------------------------------------------------------------------------
+constexpr uint32_t T_TOUCH = 1u << 24;
+constexpr uint32_t MX = 011111111u, MY = MX << 1, MT = MX << 2;
+
+// h o f (f first), 8 ids at once (counters zero)
+__device__ __forceinline__ uint32_t tw_compose(uint32_t h, uint32_t f)
+{
+    const uint32_t ftx = (f >> 2) & MX, htx = (h >> 2) & MX;
+    const uint32_t ex = f | (h & (~ftx | (f >> 1)));
+    const uint32_t ey = f | (h & (~(ftx << 1) | (f << 1)));
+    const uint32_t hx = htx | (htx << 1); // fields that h makes constant
+    return ((h | f) & MT) | (((h & hx) | (((ex & MX) | (ey & MY)) & ~hx)));
+}
+
+// the same on one id's 3 bits
+__device__ __forceinline__ uint32_t el_compose(uint32_t h, uint32_t f)
+{
+    const uint32_t ft = f >> 2;
+    const uint32_t ex = f | (h & ((ft ^ 1u) | (f >> 1)));
+    const uint32_t ey = f | (h & (((ft ^ 1u) << 1) | (f << 1)));
+    const uint32_t r = ((h | f) & 4u) | (ex & 1u) | (ey & 2u);
+    return (h & 4u) ? h : r;
+}
+
+// Per (op | side << 3): an effect's element; for the backward walk the element h o f for
+// every h, 3 bits each; for the forward walk the status byte for every status before the
+// event, 8 bits each.  In constant memory, copied to LDS by every wave.
+constexpr uint32_t host_compose(uint32_t h, uint32_t f)
+{
+    if (h & 4u)
+        return h;
+    const uint32_t x = (f & 1u) | ((h & 1u) & ((f & 4u) ? (f >> 1) & 1u : 1u));
+    const uint32_t y = ((f >> 1) & 1u) | (((h >> 1) & 1u) & ((f & 4u) ? f & 1u : 1u));
+    return (f & 4u) | x | (y << 1);
+}
+struct StepTable {
+    uint32_t fold[16];  // (h o f) << 3h, the element in bits 24-26
+    uint32_t apply[16]; // status byte << 8s
+};
+constexpr StepTable make_step_table()
+{
+    StepTable t{};
+    for (uint32_t i = 0; i < 16; i++) {
+        const uint32_t op = i & 7u, side = i >> 3, own = side ? 2u : 1u;
+        uint32_t e = 0;
+        if (op == OP_W || op == OP_RWIND)
+            e = 4u | own;
+        else if (op == OP_PUSH)
+            e = side ? 1u : 2u;
+        else if (op == OP_PULL)
+            e = side ? 2u : 1u;
+        for (uint32_t h = 0; h < 8; h++)
+            t.fold[i] |= host_compose(h, e) << (3 * h);
+        t.fold[i] |= e << 24;
+        const Effect x = make_effect(op <= OP_RWIND ? op : (uint32_t)OP_NOOP, side);
+        for (uint32_t s = 0; s < 4; s++) {
+            const uint32_t post = (x.f4 >> (8 * s)) & 3u;
+            t.apply[i] |= (post | (s << 2) | (((x.stuck >> s) & 1u) << 7)) << (8 * s);
+        }
+    }
+    return t;
+}
+__constant__ constexpr StepTable STEPS = make_step_table();
+
+__device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory"); }
+
+// (relaxed: one wave, whose LDS operations execute in order)
+__device__ __forceinline__ uint32_t tab_touch(uint32_t *p, uint32_t bit)
+{
+    return __hip_atomic_fetch_or(p, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ __forceinline__ void tab_untouch(uint32_t *p, uint32_t bit)
+{
+    (void)__hip_atomic_fetch_and(p, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ __forceinline__ void tab_xor(uint32_t *p, uint32_t v)
+{
+    (void)__hip_atomic_fetch_xor(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ __forceinline__ uint32_t tab_load(const uint32_t *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
+// a function in 4-byte form as an element
+__device__ __forceinline__ uint32_t el_of(uint32_t f4)
+{
+    return ((f4 >> 16) & 1u) | ((f4 >> 8) & 2u) | ((f4 & 3u) ? 4u : 0u);
+}
+
+// ----------------------------------------------------------------------------------
+// Domains: where an id lies in the table, and an event's part in each walk (`entry`, from
+// its word; `next`: the id's bits after it, and its result; `open`: whether an event can
+// still change the id in the fold), and the functions lanes pass along, with the lane
+// they came from (64: none) in spare bits.
+// ----------------------------------------------------------------------------------
+struct Two {
+    static constexpr uint32_t MASK = 7, IDENTITY = F_ID;
+    __device__ static uint32_t word(uint32_t id) { return id >> 3; }
+    __device__ static uint32_t shift(uint32_t id) { return 3u * (id & 7u); }
+    __device__ static uint32_t touch(uint32_t id) { return T_TOUCH << (id & 7u); }
+    __device__ static uint32_t fold_entry(const uint32_t *tab, uint32_t w) { return tab[(w >> 24) & 15u]; }
+    __device__ static bool fold_part(uint32_t e) { return (e >> 24) != 0; }
+    __device__ static uint32_t fold_next(uint32_t e, uint32_t h) { return (e >> (3u * h)) & 7u; }
+    __device__ static bool fold_open(uint32_t h) { return (h & 4u) == 0; }
+    __device__ static uint32_t apply_entry(const uint32_t *tab, uint32_t w) { return tab[16 + ((w >> 24) & 15u)]; }
+    __device__ static uint32_t apply_next(uint32_t e, uint32_t h, uint32_t &byte)
+    {
+        byte = e >> (8u * (h & 3u));
+        return 4u | (byte & 3u);
+    }
+    __device__ static uint32_t function(const uint32_t *tab, uint32_t w) { return apply_entry(tab, w) & 0x03030303u; }
+    __device__ static uint32_t compose(uint32_t g, uint32_t f) { return fcompose(g, f); }
+    __device__ static bool constant(uint32_t f) { return (f & 3u) != 0; } // (a constant's byte 0 is not 0)
+    __device__ static uint32_t pack(uint32_t f, uint32_t p) { return f | ((p & 63u) << 2) | ((p & 64u) << 4); }
+    __device__ static uint32_t packed_function(uint32_t v) { return v & 0x03030303u; }
+    __device__ static uint32_t packed_lane(uint32_t v) { return (v & (64u << 4)) ? 64u : (v >> 2) & 63u; }
+    __device__ static uint32_t fold_all(uint32_t h, uint32_t f) { return el_compose(h, el_of(f)); }
+    __device__ static uint32_t status_after(uint32_t f, uint32_t h) { return fapply(f, h & 3u); }
+};
+
+// the lanes of `among` with this lane's id (ids of `bits` bits, at most 16)
+__device__ __forceinline__ uint64_t same_id(uint32_t id, uint64_t among, uint32_t bits)
+{
+    uint32_t lo = (uint32_t)among, hi = (uint32_t)(among >> 32);
+    match_bits<0, 4>(id, lo, hi);
+    if (bits > 4)
+        match_bits<4, 8>(id, lo, hi);
+    if (bits > 8)
+        match_bits<8, 12>(id, lo, hi);
+    if (bits > 12)
+        match_bits<12, 16>(id, lo, hi);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// Composition of the functions of the lanes of a lane's id up to and with it, by pointer
+// jumping along them; p is the nearest lower one, 64 if none.  BACK: lower lanes are later
+// events (their function comes last).  Q steps at once, independent of each other.
+template <class D, bool BACK, int Q>
+__device__ __forceinline__ void compose_along(uint32_t (&f)[Q], uint32_t (&p)[Q])
+{
+    for (;;) {
+        bool more = false;
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            if (!BACK && D::constant(f[q])) // nothing before a constant matters
+                p[q] = 64u;
+            more = more || p[q] < 64u;
+        }
+        if (!__ballot(more))
+            break;
+        uint32_t v[Q];
+#pragma unroll
+        for (int q = 0; q < Q; q++)
+            v[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(p[q] * 4u), (int)D::pack(f[q], p[q]));
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            const uint32_t g = p[q] < 64u ? D::packed_function(v[q]) : D::IDENTITY;
+            f[q] = BACK ? D::compose(g, f[q]) : D::compose(f[q], g);
+            p[q] = p[q] < 64u ? D::packed_lane(v[q]) : 64u;
+        }
+    }
+}
+
+template <class D>
+struct Fold {
+    static constexpr bool BACK = true;
+    using Dom = D;
+    __device__ static uint32_t entry(const uint32_t *tab, uint32_t w) { return D::fold_entry(tab, w); }
+    __device__ static bool takes_part(uint32_t e) { return D::fold_part(e); }
+    __device__ static bool open(uint32_t h) { return D::fold_open(h); }
+    __device__ static uint32_t next(uint32_t e, uint32_t h, uint32_t &) { return D::fold_next(e, h); }
+};
+template <class D>
+struct Apply {
+    static constexpr bool BACK = false;
+    using Dom = D;
+    __device__ static uint32_t entry(const uint32_t *tab, uint32_t w) { return D::apply_entry(tab, w); }
+    __device__ static bool takes_part(uint32_t) { return true; }
+    __device__ static bool open(uint32_t) { return true; }
+    __device__ static uint32_t next(uint32_t e, uint32_t h, uint32_t &result) { return D::apply_next(e, h, result); }
+};
+
+template <class DIR>
+struct Lane { // one lane's event in a step
+    using D = typename DIR::Dom;
+    uint32_t *p;
+    uint32_t id, w, entry, old;
+    bool part;
+    __device__ uint32_t touch() const { return D::touch(id); }
+    __device__ uint32_t field(uint32_t word) const { return (word >> D::shift(id)) & D::MASK; }
+    __device__ uint32_t change(uint32_t h, uint32_t nh) const { return (h ^ nh) << D::shift(id); }
+    __device__ bool met() const { return part && (old & touch()) != 0; }
+    __device__ void enter()
+    {
+        old = 0;
+        if (part)
+            old = tab_touch(p, touch());
+    }
+    __device__ void leave() const
+    {
+        if (part)
+            tab_untouch(p, touch());
+    }
+};
+
+template <class DIR>
+__device__ __forceinline__ Lane<DIR> make_lane(uint32_t *s_t, const uint32_t *s_tab, uint32_t w, uint32_t id, bool in)
+{
+    Lane<DIR> L;
+    L.id = id;
+    L.w = w;
+    L.p = s_t + DIR::Dom::word(id);
+    L.entry = DIR::entry(s_tab, w);
+    L.part = in && DIR::takes_part(L.entry);
+    L.old = 0;
+    return L;
+}
+
+// no two lanes share an id (all have entered)
+template <class DIR>
+__device__ __forceinline__ uint32_t step_apart(const Lane<DIR> &L)
+{
+    const uint32_t h = L.field(L.old);
+    uint32_t result = 0;
+    const uint32_t nh = DIR::next(L.entry, h, result);
+    if (L.part)
+        tab_xor(L.p, L.change(h, nh) | L.touch());
+    return result;
+}
+
+// few lanes share ids (`met`: all but the first of each id to enter; none is in the table
+// any more): the lanes of an id take turns in their order
+template <class DIR>
+__device__ __forceinline__ uint32_t step_in_turn(const Lane<DIR> &L, uint64_t met)
+{
+    uint32_t turn = 0, turns = 0;
+    while (met) {
+        const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)L.id, __builtin_ctzll(met));
+        const bool mine = L.part && L.id == other;
+        const uint64_t same = __ballot(mine);
+        if (mine)
+            turn = mask_rank(same);
+        const uint32_t n = (uint32_t)__builtin_popcountll(same) - 1;
+        turns = turns > n ? turns : n;
+        met &= ~same;
+    }
+    uint32_t result = 0;
+    for (uint32_t k = 0; k <= turns; k++) {
+        if (L.part && turn == k) {
+            const uint32_t h = L.field(tab_load(L.p));
+            tab_xor(L.p, L.change(h, DIR::next(L.entry, h, result)));
+        }
+        compiler_fence();
+    }
+    return result;
+}
+
+// Q steps whose lanes may share ids, one after the other; no lane is in the table.  What
+// the lanes of an id do together does not depend on the table, so the steps work it out
+// side by side.  `shared` counts the steps where any did.
+template <class DIR, int Q>
+__device__ __forceinline__ void steps_together(const Lane<DIR> (&L)[Q], uint32_t (&result)[Q], const uint32_t *s_tab,
+                                               uint32_t bits, uint32_t lane, uint32_t &shared)
+{
+    using D = typename DIR::Dom;
+    uint32_t f[Q], p[Q], prev[Q];
+    bool in[Q], last[Q];
+#pragma unroll
+    for (int q = 0; q < Q; q++) // (a later step's id may close before it: it then changes nothing)
+        in[q] = L[q].part && (!DIR::BACK || DIR::open(L[q].field(tab_load(L[q].p))));
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+        const uint64_t same = same_id(L[q].id, __ballot(in[q]), bits);
+        const uint32_t rank = mask_rank(same);
+        const uint64_t below = same & ((1ull << lane) - 1);
+        prev[q] = p[q] = in[q] && rank ? 63u - (uint32_t)__builtin_clzll(below) : 64u;
+        last[q] = in[q] && rank + 1 == (uint32_t)__builtin_popcountll(same); // of its id
+        f[q] = D::function(s_tab, L[q].w);
+        shared += __ballot(prev[q] < 64) ? 1u : 0u;
+    }
+    compose_along<D, DIR::BACK, Q>(f, p);
+    uint32_t g[Q];
+    if constexpr (!DIR::BACK)
+#pragma unroll
+        for (int q = 0; q < Q; q++)
+            g[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((prev[q] & 63u) * 4u), (int)f[q]);
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+        const uint32_t h = L[q].field(tab_load(L[q].p));
+        uint32_t nh;
+        if constexpr (DIR::BACK)
+            nh = D::fold_all(h, f[q]);
+        else
+            nh = DIR::next(L[q].entry, prev[q] < 64 ? D::status_after(g[q], h) : h, result[q]);
+        if (last[q])
+            tab_xor(L[q].p, L[q].change(h, nh));
+        compiler_fence();
+    }
+}
+
+// D_PAIR steps at once: all enter, and when no lane met a touched id, neither of its own
+// step nor of the ones before it, their reads are one wait and their changes independent.
+// Otherwise all leave and the steps take their turns; lanes that share ids within a step
+// take turns too when they are few, else they work their changes out together.
+constexpr int D_PAIR = 2;
+constexpr int D_FEW = 5;
+template <class DIR>
+__device__ __forceinline__ void steps(Lane<DIR> (&L)[D_PAIR], uint32_t (&result)[D_PAIR], const uint32_t *s_tab,
+                                      uint32_t bits, uint32_t lane, uint32_t &shared_steps)
+{
+    bool met = false;
+#pragma unroll
+    for (int q = 0; q < D_PAIR; q++)
+        L[q].enter();
+#pragma unroll
+    for (int q = 0; q < D_PAIR; q++)
+        met = met || L[q].met();
+    if (!__ballot(met)) {
+#pragma unroll
+        for (int q = 0; q < D_PAIR; q++)
+            result[q] = step_apart<DIR>(L[q]);
+        return;
+    }
+    compiler_fence();
+#pragma unroll
+    for (int q = 0; q < D_PAIR; q++)
+        L[q].leave();
+    compiler_fence();
+#pragma unroll
+    for (int q = 0; q < D_PAIR; q++) {
+        if (DIR::BACK && L[q].part) // ids that are constants already take no part
+            L[q].part = DIR::open(L[q].field(tab_load(L[q].p)));
+        L[q].enter();
+        const uint64_t m = __ballot(L[q].met());
+        if (!m) {
+            result[q] = step_apart<DIR>(L[q]);
+        } else {
+            L[q].leave();
+            compiler_fence();
+            if (__builtin_popcountll(m) <= D_FEW) {
+                result[q] = step_in_turn<DIR>(L[q], m);
+            } else {
+                const Lane<DIR> one[1] = {L[q]};
+                uint32_t r[1] = {0};
+                steps_together<DIR, 1>(one, r, s_tab, bits, lane, shared_steps);
+                result[q] = r[0];
+            }
+        }
+        compiler_fence();
+    }
+}
+
+constexpr int D_UNROLL = 8; // steps whose events are loaded together
+// a round whose last one worked out at least so many of its steps together does so for all
+constexpr uint32_t D_TOGETHER = D_UNROLL / 2;
+
+__device__ __forceinline__ void load_step_table(uint32_t *s_tab, uint32_t lane)
+{
+    if (lane < 32)
+        s_tab[lane] = lane < 16 ? STEPS.fold[lane] : STEPS.apply[lane - 16];
+    compiler_fence();
+}
+
+} // namespace
+} // namespace vc
