@@ -494,6 +494,23 @@ static int spaces_enqueue(vc_trace *t, hipStream_t s)
 {
     const uint64_t n = t->n;
     int r;
+    if (t->n_ids <= bucket_max_ids() && !getenv("VC_GENERAL_PATH")) {
+        // through buckets of variables
+        if ((r = devbuf_reserve(t->status, n ? n : 1)) != VC_OK ||
+            (r = devbuf_reserve(t->status16, (n ? n : 1) * 2)) != VC_OK ||
+            (r = devbuf_reserve(t->fin, t->n_ids ? t->n_ids : 1)) != VC_OK ||
+            (r = devbuf_reserve(t->viol, (n ? n : 1) * 4)) != VC_OK ||
+            (r = devbuf_reserve(t->scratch, wide_spaces_scratch_bytes(n, t->n_ids))) != VC_OK)
+            return r;
+        uint8_t *fin = (uint8_t *)t->fin.p;
+        const FillJob fill{fin, t->n_ids, 1};
+        if (t->init)
+            (void)hipMemcpyAsync(fin, t->init, t->n_ids, hipMemcpyDeviceToDevice, s);
+        launch_wide_spaces(t->events, n, t->n_ids, t->spaces, t->init, (uint16_t *)t->status16.p,
+                           (uint8_t *)t->status.p, fin, (uint32_t *)t->viol.p, t->scratch.p, t->ctl, s,
+                           t->init ? nullptr : &fill);
+        return VC_OK;
+    }
     if ((r = devbuf_reserve(t->status, n ? n : 1)) != VC_OK ||
         (r = devbuf_reserve(t->status16, (n ? n : 1) * 2)) != VC_OK ||
         (r = devbuf_reserve(t->fin, t->n_ids ? t->n_ids : 1)) != VC_OK ||

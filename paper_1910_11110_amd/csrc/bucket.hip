@@ -17,9 +17,14 @@
 //    program order and handed to the consumer (status bytes and violation compaction
 //    for a trace; the pre-statuses of the declarations for a translation).
 #include "bucket.h"
+
+#include <algorithm>
+
 #include "device.h"
 #include "internal.h"
 #include "prof.h"
+#include "spaces.h"
+#include "wide.h"
 
 namespace vc {
 
@@ -81,6 +86,14 @@ struct DeclWords {
         const uint32_t mode = ok(w, n_ids) ? (w >> 24) & 3u : 0u;
         return mode == 0 ? 3u : (mode == 1 ? 2u : 5u);
     }
+};
+
+// words of a trace over K memory spaces
+template <uint32_t K>
+struct SpaceWords {
+    __device__ static bool ok(uint32_t w, uint32_t n_ids) { return !k_malformed(w, n_ids, K); }
+    __device__ static uint32_t key(uint32_t w, uint32_t n_ids) { return ok(w, n_ids) ? (w & 0xFFFFFFu) : 0u; }
+    __device__ static uint32_t arity(uint32_t, uint32_t) { return 0; }
 };
 
 // predecessors read per look-back round
@@ -896,16 +909,21 @@ __device__ __forceinline__ void store16(uint8_t *__restrict__ out, uint64_t n, u
 // result bytes are the runs res[tpre[tile][b] .. tpre[tile + 1][b]) of its buckets, in
 // the tile's bucket-sorted order: they are copied run by run into LDS, and every word
 // takes its byte at its position li16 in that order.
+// R: status bytes, or the uint16 statuses of memory spaces (whose flag bytes go to
+// `flag`).
+template <class R>
 __global__ __launch_bounds__(BLOCK) void k_replay_status(const uint16_t *__restrict__ li16,
                                                          const uint32_t *__restrict__ tpre,
                                                          const uint64_t *__restrict__ base, uint32_t nb, uint64_t n,
-                                                         const uint8_t *__restrict__ res, uint8_t *__restrict__ status,
+                                                         const R *__restrict__ res, R *__restrict__ status,
+                                                         uint8_t *__restrict__ flag,
                                                          uint32_t *__restrict__ fw, uint32_t *__restrict__ tcnt,
                                                          uint64_t ntiles)
 {
     static_assert(P_ITEMS == FLAG_EVENTS, "one flag word per thread");
     constexpr int BPT = MAX_BUCKETS / BLOCK; // buckets per thread
-    __shared__ __align__(16) uint8_t s_res[PTILE];
+    constexpr uint32_t STUCK = 8 * sizeof(R) - 1, PER = 4 / sizeof(R); // results a word
+    __shared__ __align__(16) R s_res[PTILE];
     __shared__ uint32_t s_start[MAX_BUCKETS + 1]; // run starts in the tile's sorted order
     __shared__ uint32_t s_src[MAX_BUCKETS];       // run starts in res
     __shared__ uint16_t s_bkt[PTILE];             // bucket of every sorted position
@@ -964,7 +982,7 @@ __global__ __launch_bounds__(BLOCK) void k_replay_status(const uint16_t *__restr
         __syncthreads();
         // 16 consecutive words per thread
         const uint64_t my0 = t0 + (uint64_t)tid * 16;
-        uint32_t q[4] = {0, 0, 0, 0};
+        uint32_t q[16 / PER] = {}, fb[4] = {};
         uint32_t flags = 0;
         if (my0 + 16 <= n) {
             const uint4 *lv = reinterpret_cast<const uint4 *>(li16 + my0);
@@ -975,19 +993,27 @@ __global__ __launch_bounds__(BLOCK) void k_replay_status(const uint16_t *__restr
 #pragma unroll
                 for (int k = 0; k < 8; k++) {
                     const uint32_t li = (w[k >> 1] >> (16 * (k & 1))) & (PTILE - 1);
-                    const uint32_t byte = s_res[li];
+                    const uint32_t r = s_res[li], stuck = (r >> STUCK) & 1u;
                     const int e = h * 8 + k;
-                    q[e >> 2] |= byte << (8 * (e & 3));
-                    flags |= ((byte >> 7) & 1u) << e;
+                    q[e / PER] |= r << (8 * sizeof(R) * (e % PER));
+                    fb[e >> 2] |= stuck << (8 * (e & 3) + 7);
+                    flags |= stuck << e;
                 }
             }
-            *reinterpret_cast<uint4 *>(status + my0) = make_uint4(q[0], q[1], q[2], q[3]);
+#pragma unroll
+            for (uint32_t h = 0; h < 4 / PER; h++)
+                reinterpret_cast<uint4 *>(status + my0)[h] =
+                    make_uint4(q[4 * h], q[4 * h + 1], q[4 * h + 2], q[4 * h + 3]);
+            if (sizeof(R) > 1)
+                *reinterpret_cast<uint4 *>(flag + my0) = make_uint4(fb[0], fb[1], fb[2], fb[3]);
         } else {
             for (int e = 0; e < 16; e++) {
                 if (my0 + e < n) {
-                    const uint32_t byte = s_res[li16[my0 + e] & (PTILE - 1)];
-                    status[my0 + e] = (uint8_t)byte;
-                    flags |= ((byte >> 7) & 1u) << e;
+                    const uint32_t r = s_res[li16[my0 + e] & (PTILE - 1)], stuck = (r >> STUCK) & 1u;
+                    status[my0 + e] = (R)r;
+                    if (sizeof(R) > 1)
+                        flag[my0 + e] = (uint8_t)(stuck << 7);
+                    flags |= stuck << e;
                 }
             }
         }
@@ -1197,9 +1223,9 @@ static void bucket_check(const uint32_t *events, uint64_t n, uint32_t n_ids, con
     }
     {
         ProfScope p(s, "replay_status");
-        const unsigned grid = resident_grid((const void *)k_replay_status, L.ptiles);
-        k_replay_status<<<grid, BLOCK, 0, s>>>(L.li16, L.tpre, L.base, L.nb, n, L.res, status, L.fw, L.tcnt,
-                                               L.ptiles);
+        const unsigned grid = resident_grid((const void *)k_replay_status<uint8_t>, L.ptiles);
+        k_replay_status<uint8_t><<<grid, BLOCK, 0, s>>>(L.li16, L.tpre, L.base, L.nb, n, L.res, status, nullptr, L.fw,
+                                                        L.tcnt, L.ptiles);
     }
     if (!viol)
         return;
@@ -1281,6 +1307,124 @@ DeclPre launch_bucket_decl_pre_partitioned(const uint32_t *decls, uint64_t n_dec
     if (L.nb == 1)
         return DeclPre{pre, nullptr};
     return DeclPre{L.res, L.dstidx};
+}
+
+// ----------------------------------------------------------------------------------
+// k memory spaces: partition, wide scan, replay
+// ----------------------------------------------------------------------------------
+namespace {
+
+struct SpacesLayout {
+    int bits;
+    uint32_t nb, most; // buckets, chunks at most
+    uint64_t ptiles, per;
+    uint32_t *tot, *gsum, *gpre, *cbase, *cb, *tcnt, *fw, *part, *tpre;
+    uint64_t *base, *offs;
+    uint16_t *li16, *res;
+    void *rows, *xscan;
+    size_t bytes;
+};
+
+SpacesLayout spaces_layout(void *scratch, uint64_t n, uint32_t n_ids)
+{
+    SpacesLayout L{};
+    L.bits = bucket_bits_for(n_ids);
+    L.nb = 1u << L.bits;
+    L.ptiles = ceil_div(n ? n : 1, PTILE);
+    L.per = wide_chunk_events(n, wide_row_spaces(LBITS));
+    L.most = wide_max_chunks(n, L.nb, L.per);
+    char *p0 = reinterpret_cast<char *>(scratch);
+    size_t off = 0;
+    auto take = [&](size_t sz) {
+        char *r = p0 ? p0 + off : nullptr;
+        off += (sz + 255) & ~size_t(255);
+        return r;
+    };
+    L.tot = (uint32_t *)take(MAX_BUCKETS * 4);
+    L.gsum = (uint32_t *)take((size_t)MAX_RANGES * L.nb * 4);
+    L.gpre = (uint32_t *)take((size_t)MAX_RANGES * L.nb * 4);
+    L.base = (uint64_t *)take((MAX_BUCKETS + 1) * 8);
+    L.cbase = (uint32_t *)take((MAX_BUCKETS + 1) * 4);
+    L.cb = (uint32_t *)take((size_t)L.most * 4);
+    L.rows = take(wide_rows_bytes(L.most, wide_row_spaces(LBITS)));
+    L.tcnt = (uint32_t *)take(L.ptiles * 4);
+    L.offs = (uint64_t *)take((L.ptiles + 1) * 8);
+    L.xscan = take(std::max(excl_scan_scratch_bytes(L.ptiles), compact_scratch_bytes(n)));
+    if (L.nb > 1) {
+        L.fw = (uint32_t *)take(L.ptiles * BLOCK * 4);
+        L.part = (uint32_t *)take(n * 4);
+        L.li16 = (uint16_t *)take(n * 2);
+        L.tpre = (uint32_t *)take(L.ptiles * L.nb * 4);
+        L.res = (uint16_t *)take(n * 2);
+    }
+    L.bytes = off;
+    return L;
+}
+
+template <class SRC>
+void partition_spaces(const uint32_t *ev, uint64_t n, uint32_t n_ids, const SpacesLayout &L, const WideChunks &W,
+                      Control *ctl, hipStream_t s)
+{
+    const bool small_nb = L.nb <= 256;
+    const auto part_k = small_nb ? k_partition<SRC, 256> : k_partition<SRC, MAX_BUCKETS>;
+    uint32_t nranges = resident_grid((const void *)part_k, L.ptiles);
+    nranges = std::min<uint32_t>(nranges, MAX_RANGES / HIST_SPLIT);
+    nranges = (uint32_t)std::min<uint64_t>(nranges, L.ptiles);
+    const uint32_t nrows = nranges * HIST_SPLIT;
+    {
+        ProfScope p(s, "bucket_hist");
+        k_bucket_hist<SRC><<<nrows, BLOCK, 0, s>>>(ev, n, n_ids, L.nb, nrows, L.ptiles, L.gsum, ctl, nullptr);
+    }
+    {
+        ProfScope p(s, "bucket_colscan");
+        k_bucket_colscan<<<L.nb, BLOCK, 0, s>>>(L.gsum, L.nb, nrows, L.gpre, L.tot);
+    }
+    launch_wide_bases(W, s);
+    if (L.nb > 1) {
+        ProfScope p(s, "partition");
+        part_k<<<nranges, BLOCK, 0, s>>>(ev, n, n_ids, L.bits, L.base, L.gpre, nranges, L.part, nullptr, L.li16, L.tpre,
+                                         L.ptiles, ctl);
+    }
+}
+
+} // namespace
+
+size_t wide_spaces_scratch_bytes(uint64_t n, uint32_t n_ids) { return spaces_layout(nullptr, n, n_ids).bytes; }
+
+void launch_wide_spaces(const uint32_t *ev, uint64_t n, uint32_t n_ids, uint32_t k, const uint8_t *init,
+                        uint16_t *st16, uint8_t *flag, uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl,
+                        hipStream_t s, const FillJob *fin_fill)
+{
+    const SpacesLayout L = spaces_layout(scratch, n, n_ids);
+    FillJob jobs[2] = {FillJob{L.xscan, L.nb > 1 ? excl_scan_scratch_bytes(L.ptiles) : compact_scratch_bytes(n), 0},
+                       FillJob{}};
+    if (fin_fill)
+        jobs[1] = *fin_fill;
+    launch_prep(ctl, nullptr, jobs, fin_fill ? 2 : 1, s);
+    if (n == 0)
+        return;
+    const WideChunks W{L.nb > 1 ? L.part : ev, L.tot, L.base, L.cbase, L.cb, L.nb, n_ids, LBITS, n, L.per};
+    if (k == 2)
+        partition_spaces<SpaceWords<2>>(ev, n, n_ids, L, W, ctl, s);
+    else if (k == 3)
+        partition_spaces<SpaceWords<3>>(ev, n, n_ids, L, W, ctl, s);
+    else
+        partition_spaces<SpaceWords<4>>(ev, n, n_ids, L, W, ctl, s);
+    launch_wide_scan_spaces(W, k, init, final_out, L.rows, L.nb > 1 ? L.res : st16, ctl, s);
+    if (L.nb == 1) { // one bucket: the events were scanned in their order
+        launch_flags_k(st16, n, flag, s);
+        launch_compact(flag, n, viol, L.xscan, ctl, s, nullptr, nullptr, true);
+        return;
+    }
+    {
+        ProfScope p(s, "replay_status");
+        const unsigned grid = resident_grid((const void *)k_replay_status<uint16_t>, L.ptiles);
+        k_replay_status<uint16_t><<<grid, BLOCK, 0, s>>>(L.li16, L.tpre, L.base, L.nb, n, L.res, st16, flag, L.fw, L.tcnt,
+                                                         L.ptiles);
+    }
+    launch_excl_scan(L.tcnt, L.ptiles, L.offs, reinterpret_cast<uint64_t *>(&ctl->n_viol), L.xscan, ctl->tickets[10], s,
+                     true);
+    launch_flag_scatter(L.fw, L.offs, L.ptiles, BLOCK, viol, s);
 }
 
 } // namespace vc

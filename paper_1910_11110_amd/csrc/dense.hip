@@ -31,6 +31,15 @@ struct TraceChunks {
     const uint32_t *ev;
     uint64_t n, per;
     uint32_t n_ids, chunks;
+    static constexpr bool REPORT = true;
+    __device__ uint32_t count() const { return chunks; }
+    __device__ uint32_t id_bits() const { return 32u - (uint32_t)__builtin_clz(n_ids | 1u); }
+    __device__ uint32_t local(uint32_t w) const { return w & 0xFFFFu; }
+    __device__ uint32_t clamped(uint32_t w) const
+    {
+        const uint32_t x = w & 0xFFFFFFu;
+        return x < n_ids ? x : n_ids - 1;
+    }
     __device__ uint64_t begin(uint32_t c) const { return (uint64_t)c * per; }
     __device__ uint64_t end(uint32_t c) const
     {
@@ -49,6 +58,15 @@ struct TileChunks {
     const uint64_t *tpos; // first word of every tile, their number at the end
     uint64_t n, tiles, per;
     uint32_t n_ids, chunks;
+    static constexpr bool REPORT = true;
+    __device__ uint32_t count() const { return chunks; }
+    __device__ uint32_t id_bits() const { return 32u - (uint32_t)__builtin_clz(n_ids | 1u); }
+    __device__ uint32_t local(uint32_t w) const { return w & 0xFFFFu; }
+    __device__ uint32_t clamped(uint32_t w) const
+    {
+        const uint32_t x = w & 0xFFFFFFu;
+        return x < n_ids ? x : n_ids - 1;
+    }
     __device__ uint64_t at(uint64_t tile) const
     {
         const uint64_t p = tpos[tile < tiles ? tile : tiles];
@@ -61,106 +79,6 @@ struct TileChunks {
         return (w >> 28) != 0 || ((w >> 24) & 7u) > OP_PROBE || (w & 0xFFFFFFu) >= n_ids;
     }
 };
-
-// 1. every chunk's functions into its row
-template <class CHUNKS>
-__global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uint32_t *__restrict__ rows,
-                                                     Control *ctl)
-{
-    extern __shared__ __align__(16) uint32_t s_t[];
-    uint32_t *const s_tab = s_t + row;
-    const uint32_t lane = threadIdx.x, bits = 32u - (uint32_t)__builtin_clz(T.n_ids | 1u);
-    load_step_table(s_tab, lane);
-    for (uint32_t c = blockIdx.x; c < T.chunks; c += gridDim.x) {
-        const uint64_t i0 = T.begin(c), i1 = T.end(c);
-        const uint32_t len = (uint32_t)(i1 - i0), rounds = len / (D_UNROLL * WAVE);
-        for (uint32_t i = lane; i < row / 4; i += WAVE)
-            reinterpret_cast<uint4 *>(s_t)[i] = make_uint4(0, 0, 0, 0);
-        compiler_fence();
-        // (a malformed word is a Noop on id 0)
-        auto clean = [&](uint32_t w, bool bad) { return bad ? (uint32_t)OP_NOOP << 24 : w; };
-        auto report = [&](uint64_t i) {
-            atomicMin(reinterpret_cast<unsigned long long *>(&ctl->err_index_lo), (unsigned long long)i);
-        };
-        uint32_t shared_steps = 0;
-        // the events past the whole rounds, one step at a time
-        for (uint32_t left = len - rounds * (D_UNROLL * WAVE); left;) {
-            const uint32_t m = left < WAVE ? left : WAVE;
-            const uint64_t i = i0 + rounds * (D_UNROLL * WAVE) + left - 1 - lane;
-            const bool in = lane < m;
-            uint32_t w = in ? T.ev[i] : (uint32_t)OP_NOOP << 24;
-            if (T.bad(w)) {
-                report(i);
-                w = clean(w, true);
-            }
-            const Lane<Fold<Two>> one[1] = {make_lane<Fold<Two>>(s_t, s_tab, w, w & 0xFFFFu, in)};
-            uint32_t none[1];
-            steps_together<Fold<Two>, 1>(one, none, s_tab, bits, lane, shared_steps);
-            left -= m;
-        }
-        // whole rounds: lane l takes the round's last event but l, then 64 before, ...
-        const uint32_t *const e0 = T.ev + i0 - 1 - lane;
-        uint32_t nxt[D_UNROLL];
-        auto load = [&](uint32_t r) {
-            const uint32_t *e = e0 + (uint64_t)r * (D_UNROLL * WAVE);
-#pragma unroll
-            for (int u = 0; u < D_UNROLL; u++)
-                nxt[u] = e[-(u * WAVE)];
-        };
-        if (rounds)
-            load(rounds);
-        for (uint32_t r = rounds; r > 0; r--) {
-            uint32_t w[D_UNROLL], badm = 0;
-#pragma unroll
-            for (int u = 0; u < D_UNROLL; u++) {
-                const bool bad = T.bad(nxt[u]);
-                badm |= bad ? 1u << u : 0u;
-                w[u] = clean(nxt[u], bad);
-            }
-            if (r > 1)
-                load(r - 1);
-            if (__ballot(badm != 0)) {
-                if (badm) // the lane's first malformed event is its last step's
-                    report(i0 + (uint64_t)r * (D_UNROLL * WAVE) - 1 - lane -
-                           WAVE * (31u - (uint32_t)__builtin_clz(badm)));
-            }
-            if (shared_steps >= D_TOGETHER) {
-                shared_steps = 0;
-                const uint32_t *e = e0 + (uint64_t)r * (D_UNROLL * WAVE);
-                uint32_t v[D_PAIR] = {w[0], w[1]};
-#pragma unroll 1
-                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                    Lane<Fold<Two>> L[D_PAIR];
-                    uint32_t none[D_PAIR];
-                    const int n = u + D_PAIR < D_UNROLL ? u + D_PAIR : u;
-#pragma unroll
-                    for (int q = 0; q < D_PAIR; q++) {
-                        const uint32_t x = clean(v[q], T.bad(v[q]));
-                        v[q] = e[-((n + q) * WAVE)];
-                        L[q] = make_lane<Fold<Two>>(s_t, s_tab, x, x & 0xFFFFu, true);
-                    }
-                    steps_together<Fold<Two>, D_PAIR>(L, none, s_tab, bits, lane, shared_steps);
-                }
-                continue;
-            }
-            shared_steps = 0;
-#pragma unroll
-            for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                Lane<Fold<Two>> L[D_PAIR];
-                uint32_t byte[D_PAIR];
-#pragma unroll
-                for (int q = 0; q < D_PAIR; q++)
-                    L[q] = make_lane<Fold<Two>>(s_t, s_tab, w[u + q], w[u + q] & 0xFFFFu, true);
-                steps<Fold<Two>>(L, byte, s_tab, bits, lane, shared_steps);
-            }
-        }
-        compiler_fence();
-        uint4 *out = reinterpret_cast<uint4 *>(rows + (uint64_t)c * row);
-        for (uint32_t i = lane; i < row / 4; i += WAVE)
-            out[i] = reinterpret_cast<const uint4 *>(s_t)[i];
-        compiler_fence();
-    }
-}
 
 // 2. prefix over the rows, by groups of D_GROUP chunks: a thread per word and group.  The
 // first kernel folds every group's rows; the second walks them from the statuses entering
@@ -214,9 +132,7 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prefix(const uint32_t *rows, ui
                 final_out[w * 8 + k] = (uint8_t)((st >> (3 * k)) & 3u);
 }
 
-// 3. the events' statuses from their chunk's entering ones.  OUT takes the results: step()
-// a step's (u: its number in its round or in the chunk's last, partial one), round() at
-// the end of each, chunk() at the chunk's.
+// 3. what becomes of the events' statuses
 constexpr uint32_t D_TILE = 1024;
 static_assert(D_TILE % (D_UNROLL * WAVE) == 0, "whole rounds of steps a tile");
 
@@ -300,97 +216,6 @@ struct ProbeOut {
     __device__ void chunk(uint32_t) const {}
 };
 
-template <class CHUNKS, class OUT>
-__global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, const uint32_t *__restrict__ rows, OUT out)
-{
-    extern __shared__ __align__(16) uint32_t s_t[];
-    uint32_t *const s_tab = s_t + row;
-    const uint32_t lane = threadIdx.x, bits = 32u - (uint32_t)__builtin_clz(T.n_ids | 1u);
-    load_step_table(s_tab, lane);
-    for (uint32_t c = blockIdx.x; c < T.chunks; c += gridDim.x) {
-        const uint4 *in = reinterpret_cast<const uint4 *>(rows + (uint64_t)c * row);
-        const uint64_t i0 = T.begin(c), i1 = T.end(c);
-        const uint32_t len = (uint32_t)(i1 - i0), rounds = len / (D_UNROLL * WAVE);
-        out.begin(T, c);
-        uint32_t nxt[D_UNROLL];
-        auto load = [&](uint32_t r) {
-            const uint32_t *e = T.ev + i0 + (uint64_t)r * (D_UNROLL * WAVE) + lane;
-#pragma unroll
-            for (int u = 0; u < D_UNROLL; u++)
-                nxt[u] = e[u * WAVE];
-        };
-        if (rounds)
-            load(0);
-        for (uint32_t i = lane; i < row / 4; i += WAVE)
-            reinterpret_cast<uint4 *>(s_t)[i] = in[i];
-        compiler_fence();
-        // (a malformed word, which the fold reported, only has to stay inside the table)
-        auto id_of = [&](uint32_t w) {
-            const uint32_t x = w & 0xFFFFFFu;
-            return x < T.n_ids ? x : T.n_ids - 1;
-        };
-        uint32_t shared_steps = 0;
-        for (uint32_t r = 0; r < rounds; r++) {
-            uint32_t w[D_UNROLL];
-#pragma unroll
-            for (int u = 0; u < D_UNROLL; u++)
-                w[u] = nxt[u];
-            if (r + 1 < rounds)
-                load(r + 1);
-            const uint64_t i = i0 + (uint64_t)r * (D_UNROLL * WAVE);
-            if (shared_steps >= D_TOGETHER) {
-                shared_steps = 0;
-                uint32_t v[D_PAIR] = {w[0], w[1]};
-#pragma unroll 1
-                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                    Lane<Apply<Two>> L[D_PAIR];
-                    uint32_t byte[D_PAIR], now[D_PAIR];
-                    const int n = u + D_PAIR < D_UNROLL ? u + D_PAIR : u;
-#pragma unroll
-                    for (int q = 0; q < D_PAIR; q++) {
-                        now[q] = v[q];
-                        L[q] = make_lane<Apply<Two>>(s_t, s_tab, v[q], id_of(v[q]), true);
-                        v[q] = T.ev[i + (n + q) * WAVE + lane];
-                    }
-                    steps_together<Apply<Two>, D_PAIR>(L, byte, s_tab, bits, lane, shared_steps);
-#pragma unroll
-                    for (int q = 0; q < D_PAIR; q++)
-                        out.step(lane, u + q, i + (u + q) * WAVE, now[q], byte[q], true);
-                }
-            } else {
-                shared_steps = 0;
-#pragma unroll
-                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                    Lane<Apply<Two>> L[D_PAIR];
-                    uint32_t byte[D_PAIR];
-#pragma unroll
-                    for (int q = 0; q < D_PAIR; q++)
-                        L[q] = make_lane<Apply<Two>>(s_t, s_tab, w[u + q], id_of(w[u + q]), true);
-                    steps<Apply<Two>>(L, byte, s_tab, bits, lane, shared_steps);
-#pragma unroll
-                    for (int q = 0; q < D_PAIR; q++)
-                        out.step(lane, u + q, i + (u + q) * WAVE, w[u + q], byte[q], true);
-                }
-            }
-            out.round(lane, i, D_UNROLL, (r + 1) * (D_UNROLL * WAVE) == len);
-        }
-        // the events past the whole rounds, one step at a time
-        const uint32_t past = rounds * (D_UNROLL * WAVE);
-        for (uint32_t k = past; k < len; k += WAVE) {
-            const bool valid = k + lane < len;
-            const uint32_t w = valid ? T.ev[i0 + k + lane] : (uint32_t)OP_NOOP << 24, id = id_of(w);
-            const Lane<Apply<Two>> one[1] = {make_lane<Apply<Two>>(s_t, s_tab, w, id, valid)};
-            uint32_t b[1];
-            steps_together<Apply<Two>, 1>(one, b, s_tab, bits, lane, shared_steps);
-            out.step(lane, (k - past) / WAVE, i0 + k, w, b[0], valid);
-        }
-        if (past < len)
-            out.round(lane, i0 + past, (len - past + WAVE - 1) / WAVE, true);
-        out.chunk(lane);
-        compiler_fence();
-    }
-}
-
 // ascending indices of the flagged events, one wave per tile
 __global__ __launch_bounds__(BLOCK) void k_mask_scatter(const uint64_t *__restrict__ masks, uint64_t n,
                                                         const uint64_t *__restrict__ offs, uint64_t ntiles,
@@ -470,7 +295,7 @@ void launch_fold(const CHUNKS &T, const Rows &R, Control *ctl, hipStream_t s)
         return;
     {
         ProfScope p(s, "dense_fold");
-        k_dense_fold<CHUNKS><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.rows, ctl);
+        k_dense_fold<Two, CHUNKS><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.rows, ctl);
     }
     if (R.groups > 1) {
         ProfScope p(s, "dense_groups");
@@ -493,7 +318,7 @@ void launch_apply(const CHUNKS &T, const Rows &R, const OUT &out, hipStream_t s)
     if (!T.chunks)
         return;
     ProfScope p(s, "dense_apply");
-    k_dense_apply<CHUNKS, OUT><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.entering, out);
+    k_dense_apply<Two, CHUNKS, OUT><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.entering, out);
 }
 
 // rows, masks and tile counts of a trace

@@ -112,7 +112,7 @@ __device__ __forceinline__ uint32_t el_of(uint32_t f4)
 // they came from (64: none) in spare bits.
 // ----------------------------------------------------------------------------------
 struct Two {
-    static constexpr uint32_t MASK = 7, IDENTITY = F_ID;
+    static constexpr uint32_t MASK = 7, IDENTITY = F_ID, NOOP = (uint32_t)OP_NOOP << 24;
     __device__ static uint32_t word(uint32_t id) { return id >> 3; }
     __device__ static uint32_t shift(uint32_t id) { return 3u * (id & 7u); }
     __device__ static uint32_t touch(uint32_t id) { return T_TOUCH << (id & 7u); }
@@ -321,7 +321,7 @@ __device__ __forceinline__ void steps_together(const Lane<DIR> (&L)[Q], uint32_t
 // Otherwise all leave and the steps take their turns; lanes that share ids within a step
 // take turns too when they are few, else they work their changes out together.
 constexpr int D_PAIR = 2;
-constexpr int D_FEW = 5;
+constexpr int D_FEW = 10;
 template <class DIR>
 __device__ __forceinline__ void steps(Lane<DIR> (&L)[D_PAIR], uint32_t (&result)[D_PAIR], const uint32_t *s_tab,
                                       uint32_t bits, uint32_t lane, uint32_t &shared_steps)
@@ -377,6 +377,203 @@ __device__ __forceinline__ void load_step_table(uint32_t *s_tab, uint32_t lane)
     if (lane < 32)
         s_tab[lane] = lane < 16 ? STEPS.fold[lane] : STEPS.apply[lane - 16];
     compiler_fence();
+}
+
+// ----------------------------------------------------------------------------------
+// The walks: one wave per chunk.  CHUNKS: the words (ev), the number of chunks, a chunk's
+// words [begin, end), malformed words, and the table's id of a word (local: of a
+// well-formed one; clamped: inside the table for any).
+// ----------------------------------------------------------------------------------
+// every chunk's functions into its row
+template <class D, class CHUNKS>
+__global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uint32_t *__restrict__ rows,
+                                                     Control *ctl)
+{
+    extern __shared__ __align__(16) uint32_t s_t[];
+    uint32_t *const s_tab = s_t + row;
+    const uint32_t lane = threadIdx.x, bits = T.id_bits(), chunks = T.count();
+    load_step_table(s_tab, lane);
+    for (uint32_t c = blockIdx.x; c < chunks; c += gridDim.x) {
+        const uint64_t i0 = T.begin(c), i1 = T.end(c);
+        const uint32_t len = (uint32_t)(i1 - i0), rounds = len / (D_UNROLL * WAVE);
+        for (uint32_t i = lane; i < row / 4; i += WAVE)
+            reinterpret_cast<uint4 *>(s_t)[i] = make_uint4(0, 0, 0, 0);
+        compiler_fence();
+        // (a malformed word is a Noop on id 0)
+        auto clean = [&](uint32_t w, bool bad) { return bad ? D::NOOP : w; };
+        auto report = [&](uint64_t i) {
+            if (CHUNKS::REPORT)
+                atomicMin(reinterpret_cast<unsigned long long *>(&ctl->err_index_lo), (unsigned long long)i);
+        };
+        uint32_t shared_steps = 0;
+        // the events past the whole rounds, one step at a time
+        for (uint32_t left = len - rounds * (D_UNROLL * WAVE); left;) {
+            const uint32_t m = left < WAVE ? left : WAVE;
+            const uint64_t i = i0 + rounds * (D_UNROLL * WAVE) + left - 1 - lane;
+            const bool in = lane < m;
+            uint32_t w = in ? T.ev[i] : D::NOOP;
+            if (T.bad(w)) {
+                report(i);
+                w = clean(w, true);
+            }
+            const Lane<Fold<D>> one[1] = {make_lane<Fold<D>>(s_t, s_tab, w, T.local(w), in)};
+            uint32_t none[1];
+            steps_together<Fold<D>, 1>(one, none, s_tab, bits, lane, shared_steps);
+            left -= m;
+        }
+        // whole rounds: lane l takes the round's last event but l, then 64 before, ...
+        const uint32_t *const e0 = T.ev + i0 - 1 - lane;
+        uint32_t nxt[D_UNROLL];
+        auto load = [&](uint32_t r) {
+            const uint32_t *e = e0 + (uint64_t)r * (D_UNROLL * WAVE);
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u++)
+                nxt[u] = e[-(u * WAVE)];
+        };
+        if (rounds)
+            load(rounds);
+        for (uint32_t r = rounds; r > 0; r--) {
+            uint32_t w[D_UNROLL], badm = 0;
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u++) {
+                const bool bad = T.bad(nxt[u]);
+                badm |= bad ? 1u << u : 0u;
+                w[u] = clean(nxt[u], bad);
+            }
+            if (r > 1)
+                load(r - 1);
+            if (__ballot(badm != 0)) {
+                if (badm) // the lane's first malformed event is its last step's
+                    report(i0 + (uint64_t)r * (D_UNROLL * WAVE) - 1 - lane -
+                           WAVE * (31u - (uint32_t)__builtin_clz(badm)));
+            }
+            if (shared_steps >= D_TOGETHER) {
+                shared_steps = 0;
+                const uint32_t *e = e0 + (uint64_t)r * (D_UNROLL * WAVE);
+                uint32_t v[D_PAIR] = {w[0], w[1]};
+#pragma unroll 1
+                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
+                    Lane<Fold<D>> L[D_PAIR];
+                    uint32_t none[D_PAIR];
+                    const int n = u + D_PAIR < D_UNROLL ? u + D_PAIR : u;
+#pragma unroll
+                    for (int q = 0; q < D_PAIR; q++) {
+                        const uint32_t x = clean(v[q], T.bad(v[q]));
+                        v[q] = e[-((n + q) * WAVE)];
+                        L[q] = make_lane<Fold<D>>(s_t, s_tab, x, T.local(x), true);
+                    }
+                    steps_together<Fold<D>, D_PAIR>(L, none, s_tab, bits, lane, shared_steps);
+                }
+                continue;
+            }
+            shared_steps = 0;
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u += D_PAIR) {
+                Lane<Fold<D>> L[D_PAIR];
+                uint32_t byte[D_PAIR];
+#pragma unroll
+                for (int q = 0; q < D_PAIR; q++)
+                    L[q] = make_lane<Fold<D>>(s_t, s_tab, w[u + q], T.local(w[u + q]), true);
+                steps<Fold<D>>(L, byte, s_tab, bits, lane, shared_steps);
+            }
+        }
+        compiler_fence();
+        uint4 *out = reinterpret_cast<uint4 *>(rows + (uint64_t)c * row);
+        for (uint32_t i = lane; i < row / 4; i += WAVE)
+            out[i] = reinterpret_cast<const uint4 *>(s_t)[i];
+        compiler_fence();
+    }
+}
+
+// The events' results from their chunk's entering statuses.  OUT takes them: step() a
+// step's (u: its number in its round or in the chunk's last, partial one), round() at the
+// end of each, chunk() at the chunk's.
+template <class D, class CHUNKS, class OUT>
+__global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, const uint32_t *__restrict__ rows, OUT out)
+{
+    extern __shared__ __align__(16) uint32_t s_t[];
+    uint32_t *const s_tab = s_t + row;
+    const uint32_t lane = threadIdx.x, bits = T.id_bits(), chunks = T.count();
+    load_step_table(s_tab, lane);
+    for (uint32_t c = blockIdx.x; c < chunks; c += gridDim.x) {
+        const uint4 *in = reinterpret_cast<const uint4 *>(rows + (uint64_t)c * row);
+        const uint64_t i0 = T.begin(c), i1 = T.end(c);
+        const uint32_t len = (uint32_t)(i1 - i0), rounds = len / (D_UNROLL * WAVE);
+        out.begin(T, c);
+        uint32_t nxt[D_UNROLL];
+        auto load = [&](uint32_t r) {
+            const uint32_t *e = T.ev + i0 + (uint64_t)r * (D_UNROLL * WAVE) + lane;
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u++)
+                nxt[u] = e[u * WAVE];
+        };
+        if (rounds)
+            load(0);
+        for (uint32_t i = lane; i < row / 4; i += WAVE)
+            reinterpret_cast<uint4 *>(s_t)[i] = in[i];
+        compiler_fence();
+        // (a malformed word, which was reported, only has to stay inside the table)
+        auto id_of = [&](uint32_t w) { return T.clamped(w); };
+        uint32_t shared_steps = 0;
+        for (uint32_t r = 0; r < rounds; r++) {
+            uint32_t w[D_UNROLL];
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u++)
+                w[u] = nxt[u];
+            if (r + 1 < rounds)
+                load(r + 1);
+            const uint64_t i = i0 + (uint64_t)r * (D_UNROLL * WAVE);
+            if (shared_steps >= D_TOGETHER) {
+                shared_steps = 0;
+                uint32_t v[D_PAIR] = {w[0], w[1]};
+#pragma unroll 1
+                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
+                    Lane<Apply<D>> L[D_PAIR];
+                    uint32_t byte[D_PAIR], now[D_PAIR];
+                    const int n = u + D_PAIR < D_UNROLL ? u + D_PAIR : u;
+#pragma unroll
+                    for (int q = 0; q < D_PAIR; q++) {
+                        now[q] = v[q];
+                        L[q] = make_lane<Apply<D>>(s_t, s_tab, v[q], id_of(v[q]), true);
+                        v[q] = T.ev[i + (n + q) * WAVE + lane];
+                    }
+                    steps_together<Apply<D>, D_PAIR>(L, byte, s_tab, bits, lane, shared_steps);
+#pragma unroll
+                    for (int q = 0; q < D_PAIR; q++)
+                        out.step(lane, u + q, i + (u + q) * WAVE, now[q], byte[q], true);
+                }
+            } else {
+                shared_steps = 0;
+#pragma unroll
+                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
+                    Lane<Apply<D>> L[D_PAIR];
+                    uint32_t byte[D_PAIR];
+#pragma unroll
+                    for (int q = 0; q < D_PAIR; q++)
+                        L[q] = make_lane<Apply<D>>(s_t, s_tab, w[u + q], id_of(w[u + q]), true);
+                    steps<Apply<D>>(L, byte, s_tab, bits, lane, shared_steps);
+#pragma unroll
+                    for (int q = 0; q < D_PAIR; q++)
+                        out.step(lane, u + q, i + (u + q) * WAVE, w[u + q], byte[q], true);
+                }
+            }
+            out.round(lane, i, D_UNROLL, (r + 1) * (D_UNROLL * WAVE) == len);
+        }
+        // the events past the whole rounds, one step at a time
+        const uint32_t past = rounds * (D_UNROLL * WAVE);
+        for (uint32_t k = past; k < len; k += WAVE) {
+            const bool valid = k + lane < len;
+            const uint32_t w = valid ? T.ev[i0 + k + lane] : D::NOOP, id = id_of(w);
+            const Lane<Apply<D>> one[1] = {make_lane<Apply<D>>(s_t, s_tab, w, id, valid)};
+            uint32_t b[1];
+            steps_together<Apply<D>, 1>(one, b, s_tab, bits, lane, shared_steps);
+            out.step(lane, (k - past) / WAVE, i0 + k, w, b[0], valid);
+        }
+        if (past < len)
+            out.round(lane, i0 + past, (len - past + WAVE - 1) / WAVE, true);
+        out.chunk(lane);
+        compiler_fence();
+    }
 }
 
 } // namespace

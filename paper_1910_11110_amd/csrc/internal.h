@@ -219,6 +219,15 @@ size_t spaces_scan_scratch_bytes(uint64_t n);
 void launch_segscan_k(const uint64_t *sorted, uint64_t n, const uint8_t *init, uint32_t n_ids, uint16_t *st16,
                       uint8_t *flag, uint8_t *final_out, void *scratch, Control *ctl, hipStream_t s);
 
+// flag[i] = stuck << 7 from the status words
+void launch_flags_k(const uint16_t *st16, uint64_t n, uint8_t *flag, hipStream_t s);
+// the check through buckets of 2^12 variables (n_ids up to bucket_max_ids()): statuses,
+// flag bytes, final table (holding the initial statuses) and violations, ctl reset first
+size_t wide_spaces_scratch_bytes(uint64_t n, uint32_t n_ids);
+void launch_wide_spaces(const uint32_t *ev, uint64_t n, uint32_t n_ids, uint32_t k, const uint8_t *init,
+                        uint16_t *st16, uint8_t *flag, uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl,
+                        hipStream_t s, const FillJob *fin_fill);
+
 // ------------------------------- overlap ------------------------------------------
 struct OverlapSets {
     uint64_t *off = nullptr; // n_arrays + 1

@@ -15,65 +15,11 @@
 #include "device.h"
 #include "internal.h"
 #include "prof.h"
+#include "spaces.h"
 
 namespace vc {
 
 namespace {
-
-constexpr uint32_t KF_CONST = 1u << 16;
-constexpr uint32_t KF_ID = 0u;
-constexpr uint32_t K_OP_R = 0, K_OP_W = 1, K_OP_COPY = 2;
-
-// function of an event (op byte: op | a << 2 | b << 4)
-__device__ __forceinline__ uint32_t kf_of(uint32_t ob)
-{
-    const uint32_t op = ob & 3u, a = (ob >> 2) & 3u, b = (ob >> 4) & 3u;
-    if (op == K_OP_W)
-        return KF_CONST | (1u << a);
-    if (op == K_OP_COPY)
-        return (1u << b) << (4u * a);
-    return KF_ID;
-}
-
-// the locations a set reaches through a relation (the rows the set selects): each bit a
-// of the set is spread to a mask of row a (bit a to bit 4a, times 15), and the selected
-// rows are folded together
-__device__ __forceinline__ uint32_t kf_reach(uint32_t rel, uint32_t s)
-{
-    const uint32_t t = (s | (s << 3) | (s << 6) | (s << 9)) & 0x1111u;
-    uint32_t r = rel & (t * 15u);
-    r |= r >> 8;
-    r |= r >> 4;
-    return r & 15u;
-}
-
-__device__ __forceinline__ uint32_t kf_apply(uint32_t f, uint32_t s)
-{
-    return (f & KF_CONST) ? (f & 15u) : (s | kf_reach(f & 0xFFFFu, s));
-}
-
-// g o f (f first).  For two relations, row a of the product is the union of the rows b
-// of g that row a of f selects: column b of f (bits 4a + b, shifted to 4a) times row b
-// of g places row b of g in every row a that selects it, without carries.
-__device__ __forceinline__ uint32_t kf_compose(uint32_t g, uint32_t f)
-{
-    if (g & KF_CONST)
-        return g;
-    if (f & KF_CONST)
-        return KF_CONST | kf_apply(g, f & 15u);
-    uint32_t p = 0;
-#pragma unroll
-    for (uint32_t b = 0; b < 4; b++)
-        p |= ((f >> b) & 0x1111u) * ((g >> (4u * b)) & 15u);
-    return f | g | p;
-}
-
-// stuck: a read at a, or a copy from a, with location a invalid
-__device__ __forceinline__ uint32_t k_stuck(uint32_t ob, uint32_t pre)
-{
-    const uint32_t op = ob & 3u, a = (ob >> 2) & 3u;
-    return (op == K_OP_R || op == K_OP_COPY) ? (((pre >> a) & 1u) ^ 1u) : 0u;
-}
 
 __device__ __forceinline__ void report_bad(Control *ctl, uint64_t i)
 {
@@ -88,9 +34,7 @@ __global__ void k_items_k(const uint32_t *__restrict__ ev, uint64_t n, uint32_t 
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         const uint32_t e = ev[i];
         uint32_t x = e & 0xFFFFFFu, op = (e >> 24) & 3u, a = (e >> 26) & 3u, b = (e >> 28) & 3u;
-        const bool bad = (e >> 30) != 0 || x >= n_ids || a >= k || b >= k || (op != K_OP_COPY && b != 0) ||
-                         (op == 3 && a != 0);
-        if (bad) {
+        if (k_malformed(e, n_ids, k)) {
             report_bad(ctl, i);
             x = 0;
             op = 3;
@@ -280,6 +224,14 @@ unsigned grid_k(uint64_t n)
 
 } // namespace
 
+void launch_flags_k(const uint16_t *st16, uint64_t n, uint8_t *flag, hipStream_t s)
+{
+    if (!n)
+        return;
+    ProfScope p(s, "flags_k");
+    k_flags_k<<<grid_k(ceil_div(n, (uint64_t)8)), BLOCK, 0, s>>>(st16, n, flag);
+}
+
 size_t spaces_scan_scratch_bytes(uint64_t n) { return ceil_div(n ? n : 1, KTILE) * sizeof(uint64_t); }
 
 void launch_items_k(const uint32_t *ev, uint64_t n, uint32_t n_ids, uint32_t k, uint64_t *items, Control *ctl,
@@ -304,8 +256,7 @@ void launch_segscan_k(const uint64_t *sorted, uint64_t n, const uint8_t *init, u
         ProfScope p(s, "segscan_k");
         k_segscan_k<<<grid, BLOCK, 0, s>>>(sorted, n, init, n_ids, st16, final_out, lb, ctl->tickets[1], tiles);
     }
-    ProfScope p(s, "flags_k");
-    k_flags_k<<<grid_k(ceil_div(n, (uint64_t)8)), BLOCK, 0, s>>>(st16, n, flag);
+    launch_flags_k(st16, n, flag, s);
 }
 
 } // namespace vc

@@ -1,0 +1,250 @@
+// wide.hip -- scan of partitioned events, a bucket's ids in LDS (gfx950).
+//
+// For id spaces whose table does not fit a wave's LDS the events are first partitioned by
+// buckets of ids; a chunk is then a run of one bucket's events, and the walks are those of
+// the dense check (dense_steps.h) on the bucket's table.  The prefix over the chunks'
+// rows starts from the initial statuses at every bucket's first chunk.
+#include "dense_steps.h"
+#include "prof.h"
+#include "spaces.h"
+#include "wide.h"
+
+namespace vc {
+
+namespace {
+
+// k memory spaces: a word per id, its function (17 bits) and the touch bit
+struct Spaces {
+    static constexpr uint32_t MASK = 0x1FFFFu, IDENTITY = KF_ID, NOOP = 3u << 24, IDS = 1;
+    __device__ static uint32_t word(uint32_t id) { return id; }
+    __device__ static uint32_t shift(uint32_t) { return 0; }
+    __device__ static uint32_t touch(uint32_t) { return 1u << 31; }
+    __device__ static uint32_t fold_entry(const uint32_t *, uint32_t w) { return w >> 24; }
+    __device__ static bool fold_part(uint32_t ob) { return (ob & 3u) == K_OP_W || (ob & 3u) == K_OP_COPY; }
+    __device__ static uint32_t fold_next(uint32_t ob, uint32_t h) { return kf_compose(h, kf_of(ob)); }
+    __device__ static bool fold_open(uint32_t h) { return (h & KF_CONST) == 0; }
+    __device__ static uint32_t apply_entry(const uint32_t *, uint32_t w) { return w >> 24; }
+    __device__ static uint32_t apply_next(uint32_t ob, uint32_t h, uint32_t &st)
+    {
+        const uint32_t pre = h & 15u, stuck = k_stuck(ob, pre);
+        const uint32_t post = stuck ? pre : kf_apply(kf_of(ob), pre);
+        st = post | (pre << 4) | (stuck << 15);
+        return KF_CONST | post;
+    }
+    __device__ static uint32_t function(const uint32_t *, uint32_t w) { return kf_of(w >> 24); }
+    __device__ static uint32_t compose(uint32_t g, uint32_t f) { return kf_compose(g, f); }
+    __device__ static bool constant(uint32_t f) { return (f & KF_CONST) != 0; }
+    __device__ static uint32_t pack(uint32_t f, uint32_t p) { return f | (p << 17); }
+    __device__ static uint32_t packed_function(uint32_t v) { return v & MASK; }
+    __device__ static uint32_t packed_lane(uint32_t v) { return v >> 17; }
+    __device__ static uint32_t fold_all(uint32_t h, uint32_t f) { return kf_compose(h, f); }
+    __device__ static uint32_t status_after(uint32_t f, uint32_t h) { return kf_apply(f, h & 15u); }
+    // rows: a word's composition, its initial statuses, its final ones
+    __device__ static uint32_t compose_word(uint32_t g, uint32_t f) { return kf_compose(g, f); }
+    __device__ static uint32_t initial(const uint8_t *init, uint32_t id) { return KF_CONST | (init ? init[id] & 15u : 1u); }
+    __device__ static uint32_t final_status(uint32_t w, uint32_t) { return w & 15u; }
+};
+
+struct SpaceChunks {
+    const uint32_t *ev;
+    const uint64_t *base;
+    const uint32_t *cbase, *cb;
+    uint32_t nb, n_ids, bits, k;
+    uint64_t per;
+    static constexpr bool REPORT = false; // (the histogram did, in program order)
+    __device__ uint32_t count() const { return cbase[nb]; }
+    __device__ uint32_t id_bits() const { return bits; }
+    __device__ uint32_t local(uint32_t w) const { return w & ((1u << bits) - 1u); }
+    __device__ uint32_t clamped(uint32_t w) const { return local(w); }
+    __device__ uint64_t begin(uint32_t c) const
+    {
+        const uint32_t b = cb[c];
+        return base[b] + (uint64_t)(c - cbase[b]) * per;
+    }
+    __device__ uint64_t end(uint32_t c) const
+    {
+        const uint64_t e = begin(c) + per, last = base[cb[c] + 1];
+        return e < last ? e : last;
+    }
+    __device__ bool bad(uint32_t w) const { return k_malformed(w, n_ids, k); }
+};
+
+struct StatusOut {
+    uint16_t *res;
+    template <class CHUNKS>
+    __device__ void begin(const CHUNKS &, uint32_t) const {}
+    __device__ void step(uint32_t lane, uint32_t, uint64_t i, uint32_t, uint32_t st, bool valid) const
+    {
+        if (valid)
+            res[i + lane] = (uint16_t)st;
+    }
+    __device__ void round(uint32_t, uint64_t, uint32_t, bool) const {}
+    __device__ void chunk(uint32_t) const {}
+};
+
+// bases of the buckets' events and chunks, and every chunk's bucket
+__global__ __launch_bounds__(1024) void k_wide_bases(const uint32_t *__restrict__ tot, uint32_t nb, uint64_t per,
+                                                     uint64_t *__restrict__ base, uint32_t *__restrict__ cbase,
+                                                     uint32_t *__restrict__ cb)
+{
+    __shared__ uint64_t s_a[1024];
+    __shared__ uint32_t s_t[1024 + 1];
+    const uint32_t i = threadIdx.x;
+    const uint64_t c = i < nb ? tot[i] : 0;
+    const uint32_t k = (uint32_t)ceil_div(c, per);
+    s_a[i] = c;
+    s_t[i] = k;
+    __syncthreads();
+    for (uint32_t d = 1; d < 1024; d <<= 1) {
+        const uint64_t a = i >= d ? s_a[i - d] : 0;
+        const uint32_t t = i >= d ? s_t[i - d] : 0;
+        __syncthreads();
+        s_a[i] += a;
+        s_t[i] += t;
+        __syncthreads();
+    }
+    const uint64_t a0 = s_a[i] - c;
+    const uint32_t t0 = s_t[i] - k, chunks = s_t[1023];
+    if (i < nb) {
+        base[i] = a0;
+        cbase[i] = t0;
+    }
+    if (i == nb - 1) {
+        base[nb] = s_a[i];
+        cbase[nb] = s_t[i];
+    }
+    // s_t: the first chunk after bucket i's; a chunk's bucket is the first that ends past it
+    for (uint32_t q = i; q < chunks; q += 1024) {
+        uint32_t lo = 0, hi = nb - 1;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) / 2;
+            if (s_t[mid] > q)
+                hi = mid;
+            else
+                lo = mid + 1;
+        }
+        cb[q] = lo;
+    }
+}
+
+// Prefix over the rows by groups of W_GROUP chunks, as in the dense check; a group's row is
+// the composition since the last bucket that starts in it.
+constexpr uint32_t W_GROUP = 16;
+
+template <class D>
+__global__ __launch_bounds__(BLOCK) void k_wide_groups(const uint32_t *__restrict__ rows, uint32_t row, uint32_t nb,
+                                                       const uint32_t *__restrict__ cbase,
+                                                       const uint32_t *__restrict__ cb, uint32_t *__restrict__ grp)
+{
+    const uint32_t w = blockIdx.x * BLOCK + threadIdx.x, g = blockIdx.y, chunks = cbase[nb];
+    const uint32_t c0 = g * W_GROUP, c1 = c0 + W_GROUP < chunks ? c0 + W_GROUP : chunks;
+    if (w >= row || c0 >= chunks)
+        return;
+    uint32_t f = D::IDENTITY;
+    for (uint32_t c = c0; c < c1; c++) {
+        if (c == cbase[cb[c]])
+            f = D::IDENTITY;
+        f = D::compose_word(rows[(uint64_t)c * row + w], f);
+    }
+    grp[(uint64_t)g * row + w] = f;
+}
+
+template <class D>
+__global__ __launch_bounds__(BLOCK) void k_wide_prefix(uint32_t *__restrict__ rows, uint32_t row, uint32_t nb,
+                                                       const uint32_t *__restrict__ cbase,
+                                                       const uint32_t *__restrict__ cb,
+                                                       const uint32_t *__restrict__ grp, uint32_t n_ids, uint32_t bits,
+                                                       const uint8_t *__restrict__ init,
+                                                       uint8_t *__restrict__ final_out)
+{
+    const uint32_t w = blockIdx.x * BLOCK + threadIdx.x, g = blockIdx.y, chunks = cbase[nb];
+    const uint32_t c0 = g * W_GROUP, c1 = c0 + W_GROUP < chunks ? c0 + W_GROUP : chunks;
+    if (w >= row || c0 >= chunks)
+        return;
+    auto initial = [&](uint32_t b) {
+        uint32_t st = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < D::IDS; k++) {
+            const uint32_t id = (b << bits) + w * D::IDS + k;
+            st |= D::initial(id < n_ids ? init : nullptr, id) << D::shift(k);
+        }
+        return st;
+    };
+    uint32_t b = cb[c0], first = cbase[b], st = initial(b);
+    if (first < c0)
+        for (uint32_t q = first / W_GROUP; q < g; q++)
+            st = D::compose_word(grp[(uint64_t)q * row + w], st);
+    for (uint32_t c = c0; c < c1; c++) {
+        if (cb[c] != b) {
+            b = cb[c];
+            st = initial(b);
+        }
+        const uint32_t f = rows[(uint64_t)c * row + w];
+        rows[(uint64_t)c * row + w] = st;
+        st = D::compose_word(f, st);
+        if (c + 1 == cbase[b + 1])
+#pragma unroll
+            for (uint32_t k = 0; k < D::IDS; k++) {
+                const uint32_t id = (b << bits) + w * D::IDS + k;
+                if (id < n_ids)
+                    final_out[id] = (uint8_t)D::final_status(st, k);
+            }
+    }
+}
+
+size_t wide_lds(uint32_t row) { return ((size_t)row + 32) * 4; }
+
+uint32_t groups_of(uint32_t max_chunks) { return (uint32_t)ceil_div(max_chunks, W_GROUP); }
+
+} // namespace
+
+// Chunks that fill the device (as many waves as have their tables in a CU's 160 KB, at most
+// 24, on 256 CUs), of whole rounds of steps and long enough that a chunk's walk outweighs
+// its row.
+uint64_t wide_chunk_events(uint64_t n, uint32_t row)
+{
+    const uint64_t waves = 163840 / wide_lds(row), chunks = 256 * (waves > 24 ? 24 : waves);
+    const uint64_t round = WAVE * D_UNROLL, per = ceil_div(n ? n : 1, chunks);
+    return ceil_div(per < 4 * round ? 4 * round : per, round) * round;
+}
+
+uint32_t wide_max_chunks(uint64_t n, uint32_t nb, uint64_t per) { return (uint32_t)(n / per) + nb; }
+
+void launch_wide_bases(const WideChunks &W, hipStream_t s)
+{
+    ProfScope p(s, "wide_bases");
+    k_wide_bases<<<1, 1024, 0, s>>>(W.tot, W.nb, W.per, W.base, W.cbase, W.cb);
+}
+
+uint32_t wide_row_spaces(uint32_t bits) { return 1u << bits; }
+
+size_t wide_rows_bytes(uint32_t max_chunks, uint32_t row)
+{
+    return ((size_t)max_chunks + groups_of(max_chunks)) * row * 4;
+}
+
+void launch_wide_scan_spaces(const WideChunks &W, uint32_t k, const uint8_t *init, uint8_t *final_out, void *scratch,
+                             uint16_t *res, Control *ctl, hipStream_t s)
+{
+    const uint32_t row = wide_row_spaces(W.bits), most = wide_max_chunks(W.n, W.nb, W.per), groups = groups_of(most);
+    uint32_t *rows = (uint32_t *)scratch, *grp = rows + (size_t)most * row;
+    const SpaceChunks T{W.part, W.base, W.cbase, W.cb, W.nb, W.n_ids, W.bits, k, W.per};
+    const dim3 pg((unsigned)ceil_div(row, BLOCK), groups);
+    {
+        ProfScope p(s, "wide_fold");
+        k_dense_fold<Spaces, SpaceChunks><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, ctl);
+    }
+    {
+        ProfScope p(s, "wide_groups");
+        k_wide_groups<Spaces><<<pg, BLOCK, 0, s>>>(rows, row, W.nb, W.cbase, W.cb, grp);
+    }
+    {
+        ProfScope p(s, "wide_prefix");
+        k_wide_prefix<Spaces><<<pg, BLOCK, 0, s>>>(rows, row, W.nb, W.cbase, W.cb, grp, W.n_ids, W.bits, init,
+                                                   final_out);
+    }
+    ProfScope p(s, "wide_apply");
+    k_dense_apply<Spaces, SpaceChunks, StatusOut><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, StatusOut{res});
+}
+
+} // namespace vc
