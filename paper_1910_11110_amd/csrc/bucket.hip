@@ -92,9 +92,16 @@ struct DeclWords {
 template <uint32_t K>
 struct SpaceWords {
     __device__ static bool ok(uint32_t w, uint32_t n_ids) { return !k_malformed(w, n_ids, K); }
-    __device__ static uint32_t key(uint32_t w, uint32_t n_ids) { return ok(w, n_ids) ? (w & 0xFFFFFFu) : 0u; }
     __device__ static uint32_t arity(uint32_t, uint32_t) { return 0; }
 };
+
+// the bucket of a word, whatever its bits (malformed words are reported, their results
+// are undefined, and they only have to stay inside the buckets)
+__device__ __forceinline__ uint32_t bucket_of(uint32_t w, uint32_t nb)
+{
+    const uint32_t b = (w & 0xFFFFFFu) >> LBITS;
+    return b < nb ? b : nb - 1;
+}
 
 // predecessors read per look-back round
 constexpr int LB_WIN = 4;
@@ -211,7 +218,7 @@ __global__ __launch_bounds__(BLOCK) void k_bucket_hist(const uint32_t *__restric
                 unsigned long long *e = reinterpret_cast<unsigned long long *>(&ctl->err_index_lo);
                 atomicMin(e, (unsigned long long)(i0 + u));
             }
-            const uint32_t b = in ? SRC::key(w[u], n_ids) >> LBITS : 0xFFFFFFFFu;
+            const uint32_t b = in ? bucket_of(w[u], nb) : 0xFFFFFFFFu;
             if (b != cur) {
                 if (run)
                     atomicAdd(&s_h[cur], run);
@@ -383,8 +390,8 @@ __global__ __launch_bounds__(BLOCK) void k_bucket_order(const uint32_t *__restri
 // and, per tile, the start of every bucket's run (row `tile` of tpre).  MAXB bounds the
 // number of buckets (LDS tables sized for it); global positions are kept modulo 2^32
 // (they are below 2^32).
-template <class SRC, int MAXB>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MAXB <= 256 ? 4 : 3))) void k_partition(const uint32_t *__restrict__ src, uint64_t n, uint32_t n_ids,
+template <int MAXB>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MAXB <= 256 ? 4 : 3))) void k_partition(const uint32_t *__restrict__ src, uint64_t n,
                                                      int bits, const uint64_t *__restrict__ base,
                                                      const uint32_t *__restrict__ gpre, uint32_t nranges,
                                                      uint32_t *__restrict__ dst, uint32_t *__restrict__ dstidx,
@@ -433,7 +440,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MAXB <= 2
             uint64_t g = wb + (uint64_t)j * WAVE + lane;
             w[j] = nxt[j];
             valid |= (g < n ? 1u : 0u) << j;
-            d[j] = SRC::key(w[j], n_ids) >> LBITS;
+            d[j] = bucket_of(w[j], nb);
         }
         if (tile + 1 < t1)
             load_tile(tile + 1);
@@ -502,7 +509,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MAXB <= 2
         uint64_t vn = n - tbase < (uint64_t)PTILE ? n - tbase : (uint64_t)PTILE;
         for (uint32_t pos = tid; pos < vn; pos += BLOCK) {
             uint32_t x = s_words[pos];
-            uint32_t b = SRC::key(x, n_ids) >> LBITS;
+            const uint32_t b = bucket_of(x, nb);
             const uint32_t gi = s_gbase[b] + pos;
             if (gi < n) // always true for consistent counts; never write outside
                 dst[gi] = x;
@@ -1134,7 +1141,7 @@ static void partition_and_scan(const uint32_t *src, uint64_t n, uint32_t n_ids, 
     // partition workgroups are resident at once
     // (the histogram splits every range in HIST_SPLIT, for more workgroups in flight)
     const bool small_nb = L.nb <= 256;
-    const void *part_k = small_nb ? (const void *)k_partition<SRC, 256> : (const void *)k_partition<SRC, MAX_BUCKETS>;
+    const void *part_k = small_nb ? (const void *)k_partition<256> : (const void *)k_partition<MAX_BUCKETS>;
     uint32_t gres = resident_grid(part_k, L.ptiles);
     gres = gres < (uint32_t)(MAX_RANGES / HIST_SPLIT) ? gres : (uint32_t)(MAX_RANGES / HIST_SPLIT);
     const uint32_t nranges = (uint32_t)(L.ptiles < gres ? L.ptiles : gres);
@@ -1165,12 +1172,12 @@ static void partition_and_scan(const uint32_t *src, uint64_t n, uint32_t n_ids, 
         // partitioned results, dest) by destinations
         const bool runs = mode == BK_STATUS && !dest;
         if (small_nb)
-            k_partition<SRC, 256><<<nranges, BLOCK, 0, s>>>(src, n, n_ids, L.bits, L.base, L.gpre, nranges,
+            k_partition<256><<<nranges, BLOCK, 0, s>>>(src, n, L.bits, L.base, L.gpre, nranges,
                                                             L.part, runs ? nullptr : L.dstidx,
                                                             runs ? L.li16 : nullptr, runs ? L.tpre : nullptr, L.ptiles,
                                                             ctl);
         else
-            k_partition<SRC, MAX_BUCKETS><<<nranges, BLOCK, 0, s>>>(src, n, n_ids, L.bits, L.base, L.gpre, nranges,
+            k_partition<MAX_BUCKETS><<<nranges, BLOCK, 0, s>>>(src, n, L.bits, L.base, L.gpre, nranges,
                                                                     L.part, runs ? nullptr : L.dstidx,
                                                                     runs ? L.li16 : nullptr, runs ? L.tpre : nullptr,
                                                                     L.ptiles, ctl);
@@ -1366,7 +1373,7 @@ void partition_spaces(const uint32_t *ev, uint64_t n, uint32_t n_ids, const Spac
                       Control *ctl, hipStream_t s)
 {
     const bool small_nb = L.nb <= 256;
-    const auto part_k = small_nb ? k_partition<SRC, 256> : k_partition<SRC, MAX_BUCKETS>;
+    const auto part_k = small_nb ? k_partition<256> : k_partition<MAX_BUCKETS>;
     uint32_t nranges = resident_grid((const void *)part_k, L.ptiles);
     nranges = std::min<uint32_t>(nranges, MAX_RANGES / HIST_SPLIT);
     nranges = (uint32_t)std::min<uint64_t>(nranges, L.ptiles);
@@ -1382,7 +1389,7 @@ void partition_spaces(const uint32_t *ev, uint64_t n, uint32_t n_ids, const Spac
     launch_wide_bases(W, s);
     if (L.nb > 1) {
         ProfScope p(s, "partition");
-        part_k<<<nranges, BLOCK, 0, s>>>(ev, n, n_ids, L.bits, L.base, L.gpre, nranges, L.part, nullptr, L.li16, L.tpre,
+        part_k<<<nranges, BLOCK, 0, s>>>(ev, n, L.bits, L.base, L.gpre, nranges, L.part, nullptr, L.li16, L.tpre,
                                          L.ptiles, ctl);
     }
 }
@@ -1410,7 +1417,7 @@ void launch_wide_spaces(const uint32_t *ev, uint64_t n, uint32_t n_ids, uint32_t
         partition_spaces<SpaceWords<3>>(ev, n, n_ids, L, W, ctl, s);
     else
         partition_spaces<SpaceWords<4>>(ev, n, n_ids, L, W, ctl, s);
-    launch_wide_scan_spaces(W, k, init, final_out, L.rows, L.nb > 1 ? L.res : st16, ctl, s);
+    launch_wide_scan_spaces(W, init, final_out, L.rows, L.nb > 1 ? L.res : st16, ctl, s);
     if (L.nb == 1) { // one bucket: the events were scanned in their order
         launch_flags_k(st16, n, flag, s);
         launch_compact(flag, n, viol, L.xscan, ctl, s, nullptr, nullptr, true);

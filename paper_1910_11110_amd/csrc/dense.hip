@@ -25,6 +25,7 @@ namespace vc {
 namespace {
 
 constexpr uint32_t OP_PROBE = DENSE_OP_PROBE;
+constexpr int D_PAIR = 2;
 
 // the chunks of one trace: `per` events each (a multiple of 64), the last one the rest
 struct TraceChunks {
@@ -295,7 +296,7 @@ void launch_fold(const CHUNKS &T, const Rows &R, Control *ctl, hipStream_t s)
         return;
     {
         ProfScope p(s, "dense_fold");
-        k_dense_fold<Two, CHUNKS><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.rows, ctl);
+        k_dense_fold<Two, D_PAIR, CHUNKS><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.rows, ctl);
     }
     if (R.groups > 1) {
         ProfScope p(s, "dense_groups");
@@ -318,7 +319,7 @@ void launch_apply(const CHUNKS &T, const Rows &R, const OUT &out, hipStream_t s)
     if (!T.chunks)
         return;
     ProfScope p(s, "dense_apply");
-    k_dense_apply<Two, CHUNKS, OUT><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.entering, out);
+    k_dense_apply<Two, D_PAIR, CHUNKS, OUT><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.entering, out);
 }
 
 // rows, masks and tile counts of a trace

@@ -316,39 +316,41 @@ __device__ __forceinline__ void steps_together(const Lane<DIR> (&L)[Q], uint32_t
     }
 }
 
-// D_PAIR steps at once: all enter, and when no lane met a touched id, neither of its own
+// PAIR steps at once: all enter, and when no lane met a touched id, neither of its own
 // step nor of the ones before it, their reads are one wait and their changes independent.
 // Otherwise all leave and the steps take their turns; lanes that share ids within a step
 // take turns too when they are few, else they work their changes out together.
-constexpr int D_PAIR = 2;
 constexpr int D_FEW = 10;
-template <class DIR>
-__device__ __forceinline__ void steps(Lane<DIR> (&L)[D_PAIR], uint32_t (&result)[D_PAIR], const uint32_t *s_tab,
+template <class DIR, int PAIR>
+__device__ __forceinline__ void steps(Lane<DIR> (&L)[PAIR], uint32_t (&result)[PAIR], const uint32_t *s_tab,
                                       uint32_t bits, uint32_t lane, uint32_t &shared_steps)
 {
     bool met = false;
 #pragma unroll
-    for (int q = 0; q < D_PAIR; q++)
+    for (int q = 0; q < PAIR; q++)
         L[q].enter();
 #pragma unroll
-    for (int q = 0; q < D_PAIR; q++)
+    for (int q = 0; q < PAIR; q++)
         met = met || L[q].met();
     if (!__ballot(met)) {
 #pragma unroll
-        for (int q = 0; q < D_PAIR; q++)
+        for (int q = 0; q < PAIR; q++)
             result[q] = step_apart<DIR>(L[q]);
         return;
     }
     compiler_fence();
+    if (PAIR > 1 || DIR::BACK) {
 #pragma unroll
-    for (int q = 0; q < D_PAIR; q++)
-        L[q].leave();
-    compiler_fence();
+        for (int q = 0; q < PAIR; q++)
+            L[q].leave();
+        compiler_fence();
+    }
 #pragma unroll
-    for (int q = 0; q < D_PAIR; q++) {
+    for (int q = 0; q < PAIR; q++) {
         if (DIR::BACK && L[q].part) // ids that are constants already take no part
             L[q].part = DIR::open(L[q].field(tab_load(L[q].p)));
-        L[q].enter();
+        if (PAIR > 1 || DIR::BACK)
+            L[q].enter();
         const uint64_t m = __ballot(L[q].met());
         if (!m) {
             result[q] = step_apart<DIR>(L[q]);
@@ -385,7 +387,7 @@ __device__ __forceinline__ void load_step_table(uint32_t *s_tab, uint32_t lane)
 // well-formed one; clamped: inside the table for any).
 // ----------------------------------------------------------------------------------
 // every chunk's functions into its row
-template <class D, class CHUNKS>
+template <class D, int PAIR, class CHUNKS>
 __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uint32_t *__restrict__ rows,
                                                      Control *ctl)
 {
@@ -450,31 +452,34 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uin
             if (shared_steps >= D_TOGETHER) {
                 shared_steps = 0;
                 const uint32_t *e = e0 + (uint64_t)r * (D_UNROLL * WAVE);
-                uint32_t v[D_PAIR] = {w[0], w[1]};
-#pragma unroll 1
-                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                    Lane<Fold<D>> L[D_PAIR];
-                    uint32_t none[D_PAIR];
-                    const int n = u + D_PAIR < D_UNROLL ? u + D_PAIR : u;
+                uint32_t v[PAIR];
 #pragma unroll
-                    for (int q = 0; q < D_PAIR; q++) {
+                for (int q = 0; q < PAIR; q++)
+                    v[q] = w[q];
+#pragma unroll 1
+                for (int u = 0; u < D_UNROLL; u += PAIR) {
+                    Lane<Fold<D>> L[PAIR];
+                    uint32_t none[PAIR];
+                    const int n = u + PAIR < D_UNROLL ? u + PAIR : u;
+#pragma unroll
+                    for (int q = 0; q < PAIR; q++) {
                         const uint32_t x = clean(v[q], T.bad(v[q]));
                         v[q] = e[-((n + q) * WAVE)];
                         L[q] = make_lane<Fold<D>>(s_t, s_tab, x, T.local(x), true);
                     }
-                    steps_together<Fold<D>, D_PAIR>(L, none, s_tab, bits, lane, shared_steps);
+                    steps_together<Fold<D>, PAIR>(L, none, s_tab, bits, lane, shared_steps);
                 }
                 continue;
             }
             shared_steps = 0;
 #pragma unroll
-            for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                Lane<Fold<D>> L[D_PAIR];
-                uint32_t byte[D_PAIR];
+            for (int u = 0; u < D_UNROLL; u += PAIR) {
+                Lane<Fold<D>> L[PAIR];
+                uint32_t byte[PAIR];
 #pragma unroll
-                for (int q = 0; q < D_PAIR; q++)
+                for (int q = 0; q < PAIR; q++)
                     L[q] = make_lane<Fold<D>>(s_t, s_tab, w[u + q], T.local(w[u + q]), true);
-                steps<Fold<D>>(L, byte, s_tab, bits, lane, shared_steps);
+                steps<Fold<D>, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
             }
         }
         compiler_fence();
@@ -488,7 +493,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uin
 // The events' results from their chunk's entering statuses.  OUT takes them: step() a
 // step's (u: its number in its round or in the chunk's last, partial one), round() at the
 // end of each, chunk() at the chunk's.
-template <class D, class CHUNKS, class OUT>
+template <class D, int PAIR, class CHUNKS, class OUT>
 __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, const uint32_t *__restrict__ rows, OUT out)
 {
     extern __shared__ __align__(16) uint32_t s_t[];
@@ -525,35 +530,38 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, co
             const uint64_t i = i0 + (uint64_t)r * (D_UNROLL * WAVE);
             if (shared_steps >= D_TOGETHER) {
                 shared_steps = 0;
-                uint32_t v[D_PAIR] = {w[0], w[1]};
-#pragma unroll 1
-                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                    Lane<Apply<D>> L[D_PAIR];
-                    uint32_t byte[D_PAIR], now[D_PAIR];
-                    const int n = u + D_PAIR < D_UNROLL ? u + D_PAIR : u;
+                uint32_t v[PAIR];
 #pragma unroll
-                    for (int q = 0; q < D_PAIR; q++) {
+                for (int q = 0; q < PAIR; q++)
+                    v[q] = w[q];
+#pragma unroll 1
+                for (int u = 0; u < D_UNROLL; u += PAIR) {
+                    Lane<Apply<D>> L[PAIR];
+                    uint32_t byte[PAIR], now[PAIR];
+                    const int n = u + PAIR < D_UNROLL ? u + PAIR : u;
+#pragma unroll
+                    for (int q = 0; q < PAIR; q++) {
                         now[q] = v[q];
                         L[q] = make_lane<Apply<D>>(s_t, s_tab, v[q], id_of(v[q]), true);
                         v[q] = T.ev[i + (n + q) * WAVE + lane];
                     }
-                    steps_together<Apply<D>, D_PAIR>(L, byte, s_tab, bits, lane, shared_steps);
+                    steps_together<Apply<D>, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
 #pragma unroll
-                    for (int q = 0; q < D_PAIR; q++)
+                    for (int q = 0; q < PAIR; q++)
                         out.step(lane, u + q, i + (u + q) * WAVE, now[q], byte[q], true);
                 }
             } else {
                 shared_steps = 0;
 #pragma unroll
-                for (int u = 0; u < D_UNROLL; u += D_PAIR) {
-                    Lane<Apply<D>> L[D_PAIR];
-                    uint32_t byte[D_PAIR];
+                for (int u = 0; u < D_UNROLL; u += PAIR) {
+                    Lane<Apply<D>> L[PAIR];
+                    uint32_t byte[PAIR];
 #pragma unroll
-                    for (int q = 0; q < D_PAIR; q++)
+                    for (int q = 0; q < PAIR; q++)
                         L[q] = make_lane<Apply<D>>(s_t, s_tab, w[u + q], id_of(w[u + q]), true);
-                    steps<Apply<D>>(L, byte, s_tab, bits, lane, shared_steps);
+                    steps<Apply<D>, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
 #pragma unroll
-                    for (int q = 0; q < D_PAIR; q++)
+                    for (int q = 0; q < PAIR; q++)
                         out.step(lane, u + q, i + (u + q) * WAVE, w[u + q], byte[q], true);
                 }
             }

@@ -30,7 +30,7 @@ size_t wide_rows_bytes(uint32_t max_chunks, uint32_t row);
 
 // k-space words: the uint16 status of every word at its place, final statuses of the
 // buckets with events
-void launch_wide_scan_spaces(const WideChunks &W, uint32_t k, const uint8_t *init, uint8_t *final_out, void *rows,
-                             uint16_t *res, Control *ctl, hipStream_t s);
+void launch_wide_scan_spaces(const WideChunks &W, const uint8_t *init, uint8_t *final_out, void *rows, uint16_t *res,
+                             Control *ctl, hipStream_t s);
 
 } // namespace vc

@@ -15,19 +15,31 @@ namespace {
 
 // k memory spaces: a word per id, its function (17 bits) and the touch bit
 struct Spaces {
+    static constexpr uint32_t SELF = 0x8421u; // every location reaches itself
     static constexpr uint32_t MASK = 0x1FFFFu, IDENTITY = KF_ID, NOOP = 3u << 24, IDS = 1;
     __device__ static uint32_t word(uint32_t id) { return id; }
     __device__ static uint32_t shift(uint32_t) { return 0; }
     __device__ static uint32_t touch(uint32_t) { return 1u << 31; }
     __device__ static uint32_t fold_entry(const uint32_t *, uint32_t w) { return w >> 24; }
     __device__ static bool fold_part(uint32_t ob) { return (ob & 3u) == K_OP_W || (ob & 3u) == K_OP_COPY; }
-    __device__ static uint32_t fold_next(uint32_t ob, uint32_t h) { return kf_compose(h, kf_of(ob)); }
+    // a write at a, then h: the constant h({a}); a copy from a to b, then h: what b reaches
+    // joins a's row
+    __device__ static uint32_t fold_next(uint32_t ob, uint32_t h)
+    {
+        const bool wr = (ob & 3u) == K_OP_W;
+        const uint32_t a4 = ob & 12u, from = wr ? a4 : (ob >> 2) & 12u;
+        const uint32_t reach = ((h | SELF) >> from) & 15u;
+        return (h & KF_CONST) ? h : wr ? KF_CONST | reach : h | (reach << a4);
+    }
     __device__ static bool fold_open(uint32_t h) { return (h & KF_CONST) == 0; }
     __device__ static uint32_t apply_entry(const uint32_t *, uint32_t w) { return w >> 24; }
     __device__ static uint32_t apply_next(uint32_t ob, uint32_t h, uint32_t &st)
     {
-        const uint32_t pre = h & 15u, stuck = k_stuck(ob, pre);
-        const uint32_t post = stuck ? pre : kf_apply(kf_of(ob), pre);
+        const uint32_t op = ob & 3u, pre = h & 15u, at_a = (pre >> ((ob >> 2) & 3u)) & 1u;
+        const uint32_t a = (SELF >> (ob & 12u)) & 15u, b = (SELF >> ((ob >> 2) & 12u)) & 15u;
+        const uint32_t copied = op == K_OP_COPY ? b & (0u - at_a) : 0u; // nothing when stuck
+        const uint32_t post = op == K_OP_W ? a : pre | copied;
+        const uint32_t stuck = (op == K_OP_R || op == K_OP_COPY) ? at_a ^ 1u : 0u;
         st = post | (pre << 4) | (stuck << 15);
         return KF_CONST | post;
     }
@@ -45,13 +57,15 @@ struct Spaces {
     __device__ static uint32_t final_status(uint32_t w, uint32_t) { return w & 15u; }
 };
 
+constexpr int K_PAIR = 1;
+
 struct SpaceChunks {
     const uint32_t *ev;
     const uint64_t *base;
     const uint32_t *cbase, *cb;
-    uint32_t nb, n_ids, bits, k;
+    uint32_t nb, bits;
     uint64_t per;
-    static constexpr bool REPORT = false; // (the histogram did, in program order)
+    static constexpr bool REPORT = false; // (the histogram did)
     __device__ uint32_t count() const { return cbase[nb]; }
     __device__ uint32_t id_bits() const { return bits; }
     __device__ uint32_t local(uint32_t w) const { return w & ((1u << bits) - 1u); }
@@ -66,7 +80,7 @@ struct SpaceChunks {
         const uint64_t e = begin(c) + per, last = base[cb[c] + 1];
         return e < last ? e : last;
     }
-    __device__ bool bad(uint32_t w) const { return k_malformed(w, n_ids, k); }
+    __device__ bool bad(uint32_t) const { return false; } // (reported; its bits stay inside the table)
 };
 
 struct StatusOut {
@@ -223,16 +237,16 @@ size_t wide_rows_bytes(uint32_t max_chunks, uint32_t row)
     return ((size_t)max_chunks + groups_of(max_chunks)) * row * 4;
 }
 
-void launch_wide_scan_spaces(const WideChunks &W, uint32_t k, const uint8_t *init, uint8_t *final_out, void *scratch,
+void launch_wide_scan_spaces(const WideChunks &W, const uint8_t *init, uint8_t *final_out, void *scratch,
                              uint16_t *res, Control *ctl, hipStream_t s)
 {
     const uint32_t row = wide_row_spaces(W.bits), most = wide_max_chunks(W.n, W.nb, W.per), groups = groups_of(most);
     uint32_t *rows = (uint32_t *)scratch, *grp = rows + (size_t)most * row;
-    const SpaceChunks T{W.part, W.base, W.cbase, W.cb, W.nb, W.n_ids, W.bits, k, W.per};
+    const SpaceChunks T{W.part, W.base, W.cbase, W.cb, W.nb, W.bits, W.per};
     const dim3 pg((unsigned)ceil_div(row, BLOCK), groups);
     {
         ProfScope p(s, "wide_fold");
-        k_dense_fold<Spaces, SpaceChunks><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, ctl);
+        k_dense_fold<Spaces, K_PAIR, SpaceChunks><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, ctl);
     }
     {
         ProfScope p(s, "wide_groups");
@@ -244,7 +258,7 @@ void launch_wide_scan_spaces(const WideChunks &W, uint32_t k, const uint8_t *ini
                                                    final_out);
     }
     ProfScope p(s, "wide_apply");
-    k_dense_apply<Spaces, SpaceChunks, StatusOut><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, StatusOut{res});
+    k_dense_apply<Spaces, K_PAIR, SpaceChunks, StatusOut><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, StatusOut{res});
 }
 
 } // namespace vc
