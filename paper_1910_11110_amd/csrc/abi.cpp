@@ -473,8 +473,7 @@ void enqueue_check_items(vc_trace *t, uint64_t m, hipStream_t s)
 // path for traces over few ids: one kernel, no sort
 static bool use_small_path(const vc_trace *t)
 {
-    return !t->has_arrays && t->n_ids <= small_max_ids() && ((uintptr_t)t->events & 15) == 0 &&
-           !getenv("VC_GENERAL_PATH");
+    return !t->has_arrays && t->n_ids <= small_max_ids() && !getenv("VC_GENERAL_PATH");
 }
 
 // path for id spaces whose statuses fit LDS: chunks of the trace in program order
@@ -483,8 +482,8 @@ static bool use_dense_path(const vc_trace *t)
     return !t->has_arrays && t->n_ids > small_max_ids() && t->n_ids <= DENSE_MAX_IDS && !getenv("VC_GENERAL_PATH");
 }
 
-// path for larger id spaces: bucket partition, per-bucket scan, replay
-static bool use_bucket_path(const vc_trace *t)
+// path for larger id spaces: partition by buckets, a bucket's statuses in LDS, replay
+static bool use_wide_path(const vc_trace *t)
 {
     return !t->has_arrays && t->n_ids <= bucket_max_ids() && t->n <= 0xFFFFFFFFull && !getenv("VC_GENERAL_PATH");
 }
@@ -567,18 +566,18 @@ int enqueue_check(vc_trace *t, hipStream_t s)
                            (uint32_t *)t->viol.p, t->scratch.p, t->ctl, s);
         return VC_OK;
     }
-    if (use_bucket_path(t)) {
+    if (use_wide_path(t)) {
         if ((r = devbuf_reserve(t->status, t->n ? t->n : 1)) != VC_OK ||
             (r = devbuf_reserve(t->fin, t->n_ids ? t->n_ids : 1)) != VC_OK ||
             (r = devbuf_reserve(t->viol, (t->n ? t->n : 1) * 4)) != VC_OK ||
-            (r = devbuf_reserve(t->scratch, bucket_scratch_bytes(t->n, t->n_ids))) != VC_OK)
+            (r = devbuf_reserve(t->scratch, wide_events_scratch_bytes(t->n, t->n_ids))) != VC_OK)
             return r;
         uint8_t *fin = (uint8_t *)t->fin.p;
         const FillJob fill{fin, t->n_ids, 1};
         if (t->init)
             (void)hipMemcpyAsync(fin, t->init, t->n_ids, hipMemcpyDeviceToDevice, s);
-        launch_bucket_check(t->events, t->n, t->n_ids, t->init, (uint8_t *)t->status.p, fin, (uint32_t *)t->viol.p,
-                            t->scratch.p, t->ctl, s, t->ctx->cu_count, t->init ? nullptr : &fill);
+        launch_wide_events(t->events, t->n, t->n_ids, t->init, (uint8_t *)t->status.p, fin, (uint32_t *)t->viol.p,
+                           t->scratch.p, t->ctl, s, t->init ? nullptr : &fill);
         return VC_OK;
     }
     if (t->dynamic)

@@ -97,9 +97,9 @@ struct SpaceWords {
 
 // the bucket of a word, whatever its bits (malformed words are reported, their results
 // are undefined, and they only have to stay inside the buckets)
-__device__ __forceinline__ uint32_t bucket_of(uint32_t w, uint32_t nb)
+__device__ __forceinline__ uint32_t bucket_of(uint32_t w, uint32_t nb, uint32_t lbits)
 {
-    const uint32_t b = (w & 0xFFFFFFu) >> LBITS;
+    const uint32_t b = (w & 0xFFFFFFu) >> lbits;
     return b < nb ? b : nb - 1;
 }
 
@@ -175,7 +175,7 @@ __host__ __device__ inline void split_range(uint64_t ntiles, uint64_t parts, uin
 // HCHUNK words also gets its total arity (SRC::arity).
 template <class SRC>
 __global__ __launch_bounds__(BLOCK) void k_bucket_hist(const uint32_t *__restrict__ src, uint64_t n, uint32_t n_ids,
-                                                       uint32_t nb, uint32_t nrows, uint64_t ntiles,
+                                                       uint32_t lbits, uint32_t nb, uint32_t nrows, uint64_t ntiles,
                                                        uint32_t *__restrict__ gsum, Control *ctl,
                                                        uint32_t *__restrict__ chunk_sum)
 {
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(BLOCK) void k_bucket_hist(const uint32_t *__restric
                 unsigned long long *e = reinterpret_cast<unsigned long long *>(&ctl->err_index_lo);
                 atomicMin(e, (unsigned long long)(i0 + u));
             }
-            const uint32_t b = in ? bucket_of(w[u], nb) : 0xFFFFFFFFu;
+            const uint32_t b = in ? bucket_of(w[u], nb, lbits) : 0xFFFFFFFFu;
             if (b != cur) {
                 if (run)
                     atomicAdd(&s_h[cur], run);
@@ -391,15 +391,14 @@ __global__ __launch_bounds__(BLOCK) void k_bucket_order(const uint32_t *__restri
 // number of buckets (LDS tables sized for it); global positions are kept modulo 2^32
 // (they are below 2^32).
 template <int MAXB>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MAXB <= 256 ? 4 : 3))) void k_partition(const uint32_t *__restrict__ src, uint64_t n,
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MAXB <= 256 ? 4 : 3))) void k_partition(const uint32_t *__restrict__ src, uint64_t n, uint32_t lbits,
                                                      int bits, const uint64_t *__restrict__ base,
                                                      const uint32_t *__restrict__ gpre, uint32_t nranges,
                                                      uint32_t *__restrict__ dst, uint32_t *__restrict__ dstidx,
                                                      uint16_t *__restrict__ li16, uint32_t *__restrict__ tpre,
                                                      uint64_t ntiles, Control *ctl)
 {
-    static_assert(MAXB % BLOCK == 0, "whole buckets per thread in the scan");
-    constexpr int BPT = MAXB / BLOCK;
+    constexpr int BPT = MAXB > BLOCK ? MAXB / BLOCK : 1; // buckets per thread in the scan
     __shared__ uint32_t s_words[PTILE];
     __shared__ uint32_t s_cnt[4 * MAXB];
     __shared__ uint32_t s_dstart[MAXB];
@@ -440,14 +439,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MAXB <= 2
             uint64_t g = wb + (uint64_t)j * WAVE + lane;
             w[j] = nxt[j];
             valid |= (g < n ? 1u : 0u) << j;
-            d[j] = bucket_of(w[j], nb);
+            d[j] = bucket_of(w[j], nb, lbits);
         }
         if (tile + 1 < t1)
             load_tile(tile + 1);
         // ranked on all the bits MAXB buckets take (a bucket index has none above
         // `bits`), so that the per-bit steps unroll
-        constexpr int RBITS = MAXB <= 256 ? 8 : 10;
-        static_assert((1 << RBITS) == MAXB, "MAXB is 256 or 1024");
+        constexpr int RBITS = MAXB <= 64 ? 6 : MAXB <= 256 ? 8 : 10;
+        static_assert((1 << RBITS) == MAXB, "MAXB is 64, 256 or 1024");
         if (tbase + PTILE <= n)
             rank_digits<P_ITEMS, MAXB, false, RBITS>(d, valid, rank, s_cnt, wave);
         else
@@ -509,7 +508,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MAXB <= 2
         uint64_t vn = n - tbase < (uint64_t)PTILE ? n - tbase : (uint64_t)PTILE;
         for (uint32_t pos = tid; pos < vn; pos += BLOCK) {
             uint32_t x = s_words[pos];
-            const uint32_t b = bucket_of(x, nb);
+            const uint32_t b = bucket_of(x, nb, lbits);
             const uint32_t gi = s_gbase[b] + pos;
             if (gi < n) // always true for consistent counts; never write outside
                 dst[gi] = x;
@@ -1148,7 +1147,7 @@ static void partition_and_scan(const uint32_t *src, uint64_t n, uint32_t n_ids, 
     const uint32_t nrows = nranges * HIST_SPLIT;
     {
         ProfScope p(s, "bucket_hist");
-        k_bucket_hist<SRC><<<nrows, BLOCK, 0, s>>>(src, n, n_ids, L.nb, nrows, L.ptiles, L.gsum, ctl, chunk_sum);
+        k_bucket_hist<SRC><<<nrows, BLOCK, 0, s>>>(src, n, n_ids, LBITS, L.nb, nrows, L.ptiles, L.gsum, ctl, chunk_sum);
     }
     if (after_hist)
         (void)hipEventRecord(after_hist, s);
@@ -1172,12 +1171,12 @@ static void partition_and_scan(const uint32_t *src, uint64_t n, uint32_t n_ids, 
         // partitioned results, dest) by destinations
         const bool runs = mode == BK_STATUS && !dest;
         if (small_nb)
-            k_partition<256><<<nranges, BLOCK, 0, s>>>(src, n, L.bits, L.base, L.gpre, nranges,
+            k_partition<256><<<nranges, BLOCK, 0, s>>>(src, n, LBITS, L.bits, L.base, L.gpre, nranges,
                                                             L.part, runs ? nullptr : L.dstidx,
                                                             runs ? L.li16 : nullptr, runs ? L.tpre : nullptr, L.ptiles,
                                                             ctl);
         else
-            k_partition<MAX_BUCKETS><<<nranges, BLOCK, 0, s>>>(src, n, L.bits, L.base, L.gpre, nranges,
+            k_partition<MAX_BUCKETS><<<nranges, BLOCK, 0, s>>>(src, n, LBITS, L.bits, L.base, L.gpre, nranges,
                                                                     L.part, runs ? nullptr : L.dstidx,
                                                                     runs ? L.li16 : nullptr, runs ? L.tpre : nullptr,
                                                                     L.ptiles, ctl);
@@ -1317,28 +1316,34 @@ DeclPre launch_bucket_decl_pre_partitioned(const uint32_t *decls, uint64_t n_dec
 }
 
 // ----------------------------------------------------------------------------------
-// k memory spaces: partition, wide scan, replay
+// traces over many ids: partition, wide scan, replay
 // ----------------------------------------------------------------------------------
 namespace {
 
-struct SpacesLayout {
-    int bits;
-    uint32_t nb, most; // buckets, chunks at most
+// Ids of a bucket (as bits) on the wide route.  Plain traces: 2^14, a table of 8 KB (2,048
+// words); k spaces: 2^12, one of 16 KB.
+constexpr uint32_t WIDE_BITS = 14, WIDE_SPACES_BITS = LBITS;
+
+struct WideLayout {
+    uint32_t lbits, bits, nb, row, most; // ids of a bucket, buckets, words of a row, chunks at most
     uint64_t ptiles, per;
     uint32_t *tot, *gsum, *gpre, *cbase, *cb, *tcnt, *fw, *part, *tpre;
     uint64_t *base, *offs;
-    uint16_t *li16, *res;
-    void *rows, *xscan;
+    uint16_t *li16;
+    void *rows, *xscan, *res;
     size_t bytes;
 };
 
-SpacesLayout spaces_layout(void *scratch, uint64_t n, uint32_t n_ids)
+WideLayout wide_layout(void *scratch, uint64_t n, uint32_t n_ids, uint32_t lbits, uint32_t row, size_t result)
 {
-    SpacesLayout L{};
-    L.bits = bucket_bits_for(n_ids);
+    WideLayout L{};
+    L.lbits = lbits;
+    L.row = row;
+    while ((n_ids - 1) >> lbits >> L.bits && n_ids)
+        L.bits++;
     L.nb = 1u << L.bits;
     L.ptiles = ceil_div(n ? n : 1, PTILE);
-    L.per = wide_chunk_events(n, wide_row_spaces(LBITS));
+    L.per = wide_chunk_events(n, row);
     L.most = wide_max_chunks(n, L.nb, L.per);
     char *p0 = reinterpret_cast<char *>(scratch);
     size_t off = 0;
@@ -1353,7 +1358,7 @@ SpacesLayout spaces_layout(void *scratch, uint64_t n, uint32_t n_ids)
     L.base = (uint64_t *)take((MAX_BUCKETS + 1) * 8);
     L.cbase = (uint32_t *)take((MAX_BUCKETS + 1) * 4);
     L.cb = (uint32_t *)take((size_t)L.most * 4);
-    L.rows = take(wide_rows_bytes(L.most, wide_row_spaces(LBITS)));
+    L.rows = take(wide_rows_bytes(L.most, row));
     L.tcnt = (uint32_t *)take(L.ptiles * 4);
     L.offs = (uint64_t *)take((L.ptiles + 1) * 8);
     L.xscan = take(std::max(excl_scan_scratch_bytes(L.ptiles), compact_scratch_bytes(n)));
@@ -1362,25 +1367,44 @@ SpacesLayout spaces_layout(void *scratch, uint64_t n, uint32_t n_ids)
         L.part = (uint32_t *)take(n * 4);
         L.li16 = (uint16_t *)take(n * 2);
         L.tpre = (uint32_t *)take(L.ptiles * L.nb * 4);
-        L.res = (uint16_t *)take(n * 2);
+        L.res = take(n * result);
     }
     L.bytes = off;
     return L;
 }
 
-template <class SRC>
-void partition_spaces(const uint32_t *ev, uint64_t n, uint32_t n_ids, const SpacesLayout &L, const WideChunks &W,
-                      Control *ctl, hipStream_t s)
+WideLayout events_layout(void *scratch, uint64_t n, uint32_t n_ids)
 {
-    const bool small_nb = L.nb <= 256;
-    const auto part_k = small_nb ? k_partition<256> : k_partition<MAX_BUCKETS>;
+    return wide_layout(scratch, n, n_ids, WIDE_BITS, wide_row_events(WIDE_BITS), 1);
+}
+WideLayout spaces_layout(void *scratch, uint64_t n, uint32_t n_ids)
+{
+    return wide_layout(scratch, n, n_ids, WIDE_SPACES_BITS, wide_row_spaces(WIDE_SPACES_BITS), 2);
+}
+
+void wide_prep(const WideLayout &L, uint64_t n, Control *ctl, const FillJob *fin_fill, hipStream_t s)
+{
+    FillJob jobs[2] = {FillJob{L.xscan, L.nb > 1 ? excl_scan_scratch_bytes(L.ptiles) : compact_scratch_bytes(n), 0},
+                       FillJob{}};
+    if (fin_fill)
+        jobs[1] = *fin_fill;
+    launch_prep(ctl, nullptr, jobs, fin_fill ? 2 : 1, s);
+}
+
+// histogram (and validation), the buckets' and chunks' bases, partition
+template <class SRC>
+WideChunks wide_partition(const uint32_t *ev, uint64_t n, uint32_t n_ids, const WideLayout &L, Control *ctl,
+                          hipStream_t s)
+{
+    const WideChunks W{L.nb > 1 ? L.part : ev, L.tot, L.base, L.cbase, L.cb, L.nb, n_ids, L.lbits, n, L.per};
+    const auto part_k = L.nb <= 64 ? k_partition<64> : L.nb <= 256 ? k_partition<256> : k_partition<MAX_BUCKETS>;
     uint32_t nranges = resident_grid((const void *)part_k, L.ptiles);
     nranges = std::min<uint32_t>(nranges, MAX_RANGES / HIST_SPLIT);
     nranges = (uint32_t)std::min<uint64_t>(nranges, L.ptiles);
     const uint32_t nrows = nranges * HIST_SPLIT;
     {
         ProfScope p(s, "bucket_hist");
-        k_bucket_hist<SRC><<<nrows, BLOCK, 0, s>>>(ev, n, n_ids, L.nb, nrows, L.ptiles, L.gsum, ctl, nullptr);
+        k_bucket_hist<SRC><<<nrows, BLOCK, 0, s>>>(ev, n, n_ids, L.lbits, L.nb, nrows, L.ptiles, L.gsum, ctl, nullptr);
     }
     {
         ProfScope p(s, "bucket_colscan");
@@ -1389,12 +1413,46 @@ void partition_spaces(const uint32_t *ev, uint64_t n, uint32_t n_ids, const Spac
     launch_wide_bases(W, s);
     if (L.nb > 1) {
         ProfScope p(s, "partition");
-        part_k<<<nranges, BLOCK, 0, s>>>(ev, n, L.bits, L.base, L.gpre, nranges, L.part, nullptr, L.li16, L.tpre,
-                                         L.ptiles, ctl);
+        part_k<<<nranges, BLOCK, 0, s>>>(ev, n, L.lbits, (int)L.bits, L.base, L.gpre, nranges, L.part, nullptr, L.li16,
+                                         L.tpre, L.ptiles, ctl);
     }
+    return W;
+}
+
+// the results back in program order, and the violations
+template <class R>
+void wide_replay(const WideLayout &L, uint64_t n, R *status, uint8_t *flag, uint32_t *viol, Control *ctl, hipStream_t s)
+{
+    {
+        ProfScope p(s, "replay_status");
+        const unsigned grid = resident_grid((const void *)k_replay_status<R>, L.ptiles);
+        k_replay_status<R><<<grid, BLOCK, 0, s>>>(L.li16, L.tpre, L.base, L.nb, n, (const R *)L.res, status, flag, L.fw,
+                                                  L.tcnt, L.ptiles);
+    }
+    launch_excl_scan(L.tcnt, L.ptiles, L.offs, reinterpret_cast<uint64_t *>(&ctl->n_viol), L.xscan, ctl->tickets[10], s,
+                     true);
+    launch_flag_scatter(L.fw, L.offs, L.ptiles, BLOCK, viol, s);
 }
 
 } // namespace
+
+size_t wide_events_scratch_bytes(uint64_t n, uint32_t n_ids) { return events_layout(nullptr, n, n_ids).bytes; }
+
+void launch_wide_events(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint8_t *init, uint8_t *status,
+                        uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl, hipStream_t s,
+                        const FillJob *fin_fill)
+{
+    const WideLayout L = events_layout(scratch, n, n_ids);
+    wide_prep(L, n, ctl, fin_fill, s);
+    if (n == 0)
+        return;
+    const WideChunks W = wide_partition<EventWords>(ev, n, n_ids, L, ctl, s);
+    launch_wide_scan_events(W, init, final_out, L.rows, L.nb > 1 ? (uint8_t *)L.res : status, ctl, s);
+    if (L.nb == 1) // one bucket: the events were scanned in their order
+        launch_compact(status, n, viol, L.xscan, ctl, s, nullptr, nullptr, true);
+    else
+        wide_replay<uint8_t>(L, n, status, nullptr, viol, ctl, s);
+}
 
 size_t wide_spaces_scratch_bytes(uint64_t n, uint32_t n_ids) { return spaces_layout(nullptr, n, n_ids).bytes; }
 
@@ -1402,36 +1460,20 @@ void launch_wide_spaces(const uint32_t *ev, uint64_t n, uint32_t n_ids, uint32_t
                         uint16_t *st16, uint8_t *flag, uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl,
                         hipStream_t s, const FillJob *fin_fill)
 {
-    const SpacesLayout L = spaces_layout(scratch, n, n_ids);
-    FillJob jobs[2] = {FillJob{L.xscan, L.nb > 1 ? excl_scan_scratch_bytes(L.ptiles) : compact_scratch_bytes(n), 0},
-                       FillJob{}};
-    if (fin_fill)
-        jobs[1] = *fin_fill;
-    launch_prep(ctl, nullptr, jobs, fin_fill ? 2 : 1, s);
+    const WideLayout L = spaces_layout(scratch, n, n_ids);
+    wide_prep(L, n, ctl, fin_fill, s);
     if (n == 0)
         return;
-    const WideChunks W{L.nb > 1 ? L.part : ev, L.tot, L.base, L.cbase, L.cb, L.nb, n_ids, LBITS, n, L.per};
-    if (k == 2)
-        partition_spaces<SpaceWords<2>>(ev, n, n_ids, L, W, ctl, s);
-    else if (k == 3)
-        partition_spaces<SpaceWords<3>>(ev, n, n_ids, L, W, ctl, s);
-    else
-        partition_spaces<SpaceWords<4>>(ev, n, n_ids, L, W, ctl, s);
-    launch_wide_scan_spaces(W, init, final_out, L.rows, L.nb > 1 ? L.res : st16, ctl, s);
-    if (L.nb == 1) { // one bucket: the events were scanned in their order
+    const WideChunks W = k == 2   ? wide_partition<SpaceWords<2>>(ev, n, n_ids, L, ctl, s)
+                         : k == 3 ? wide_partition<SpaceWords<3>>(ev, n, n_ids, L, ctl, s)
+                                  : wide_partition<SpaceWords<4>>(ev, n, n_ids, L, ctl, s);
+    launch_wide_scan_spaces(W, init, final_out, L.rows, L.nb > 1 ? (uint16_t *)L.res : st16, ctl, s);
+    if (L.nb == 1) {
         launch_flags_k(st16, n, flag, s);
         launch_compact(flag, n, viol, L.xscan, ctl, s, nullptr, nullptr, true);
-        return;
+    } else {
+        wide_replay<uint16_t>(L, n, st16, flag, viol, ctl, s);
     }
-    {
-        ProfScope p(s, "replay_status");
-        const unsigned grid = resident_grid((const void *)k_replay_status<uint16_t>, L.ptiles);
-        k_replay_status<uint16_t><<<grid, BLOCK, 0, s>>>(L.li16, L.tpre, L.base, L.nb, n, L.res, st16, flag, L.fw, L.tcnt,
-                                                         L.ptiles);
-    }
-    launch_excl_scan(L.tcnt, L.ptiles, L.offs, reinterpret_cast<uint64_t *>(&ctl->n_viol), L.xscan, ctl->tickets[10], s,
-                     true);
-    launch_flag_scatter(L.fw, L.offs, L.ptiles, BLOCK, viol, s);
 }
 
 } // namespace vc

@@ -134,6 +134,11 @@ struct Two {
     __device__ static uint32_t packed_lane(uint32_t v) { return (v & (64u << 4)) ? 64u : (v >> 2) & 63u; }
     __device__ static uint32_t fold_all(uint32_t h, uint32_t f) { return el_compose(h, el_of(f)); }
     __device__ static uint32_t status_after(uint32_t f, uint32_t h) { return fapply(f, h & 3u); }
+    // rows: a word's composition (IDS ids), an id's initial status, its final one in place k
+    static constexpr uint32_t IDS = 8, ROW_IDENTITY = 0;
+    __device__ static uint32_t compose_word(uint32_t g, uint32_t f) { return tw_compose(g, f); }
+    __device__ static uint32_t initial(const uint8_t *init, uint32_t id) { return 4u | (init ? init[id] & 3u : 1u); }
+    __device__ static uint32_t final_status(uint32_t w, uint32_t k) { return (w >> (3u * k)) & 3u; }
 };
 
 // the lanes of `among` with this lane's id (ids of `bits` bits, at most 16)

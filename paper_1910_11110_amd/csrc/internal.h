@@ -111,14 +111,23 @@ void launch_segscan(const uint64_t *sorted, uint64_t n, const uint8_t *init, uin
                     unsigned long long *ind_counts = nullptr, unsigned grid_cap = 1u << 30, uint32_t pre_from = 0);
 
 // ------------------------------- small id spaces ----------------------------------
-// single-kernel check of a trace over at most small_max_ids() ids (events 16-byte
-// aligned): statuses, final table (holding the initial statuses, or filled by fin_fill
+// single-kernel check of a trace over at most small_max_ids() ids:
+// statuses, final table (holding the initial statuses, or filled by fin_fill
 // in the set-up launch), violations (count into ctl->n_viol).  Resets ctl first.
 uint32_t small_max_ids();
 size_t small_scratch_bytes(uint64_t n);
 void launch_small_check(const uint32_t *events, uint64_t n, uint32_t n_ids, const uint8_t *init, uint8_t *status,
                         uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl, hipStream_t s,
                         unsigned grid_cap, const FillJob *fin_fill);
+
+// ------------------------------- many ids ------------------------------------------
+// plain check of n events over n_ids <= bucket_max_ids() ids through buckets of 2^14:
+// status bytes, final table (holding the initial statuses, or filled by fin_fill in the
+// set-up launch) and violations; resets ctl first
+size_t wide_events_scratch_bytes(uint64_t n, uint32_t n_ids);
+void launch_wide_events(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint8_t *init, uint8_t *status,
+                        uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl, hipStream_t s,
+                        const FillJob *fin_fill);
 
 // ------------------------------- compaction ---------------------------------------
 size_t compact_scratch_bytes(uint64_t n);
@@ -221,7 +230,7 @@ void launch_segscan_k(const uint64_t *sorted, uint64_t n, const uint8_t *init, u
 
 // flag[i] = stuck << 7 from the status words
 void launch_flags_k(const uint16_t *st16, uint64_t n, uint8_t *flag, hipStream_t s);
-// the check through buckets of 2^12 variables (n_ids up to bucket_max_ids()): statuses,
+// the check of a k-space trace through buckets of 2^12 variables (n_ids up to bucket_max_ids()): statuses,
 // flag bytes, final table (holding the initial statuses) and violations, ctl reset first
 size_t wide_spaces_scratch_bytes(uint64_t n, uint32_t n_ids);
 void launch_wide_spaces(const uint32_t *ev, uint64_t n, uint32_t n_ids, uint32_t k, const uint8_t *init,

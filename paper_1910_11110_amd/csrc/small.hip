@@ -90,6 +90,11 @@ __device__ __forceinline__ uint32_t gather4(uint32_t v, uint32_t mask, uint32_t 
 }
 constexpr uint32_t W_LO = 0x08040201u, W_HI = 0x80402010u;
 
+// four event words from an address that is a multiple of 4 bytes only
+struct __attribute__((packed, aligned(4))) Words4 {
+    uint32_t x, y, z, w;
+};
+
 __device__ __forceinline__ void lds_fence() { asm volatile("" ::: "memory"); } // a wave's LDS operations are in order
 
 // one 32-bit half of the function planes of up to 64 variables
@@ -204,7 +209,8 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
             for (int q = 0; q < BATCH; q++) {
                 const uint64_t g = wb + (uint32_t)(q0 + q) * (4 * WAVE) + lane * 4;
                 if (g + 4 <= n) {
-                    v[q] = *reinterpret_cast<const uint4 *>(ev + g);
+                    const Words4 e4 = *reinterpret_cast<const Words4 *>(ev + g);
+                    v[q] = make_uint4(e4.x, e4.y, e4.z, e4.w);
                 } else {
                     constexpr uint32_t NOOP = (uint32_t)OP_NOOP << 24;
                     v[q].x = g < n ? ev[g] : NOOP;

@@ -25,9 +25,14 @@ uint32_t wide_max_chunks(uint64_t n, uint32_t nb, uint64_t per);
 void launch_wide_bases(const WideChunks &W, hipStream_t s);
 
 // rows of the scans: words per chunk, and the scratch of `max_chunks` of them
+uint32_t wide_row_events(uint32_t bits);
 uint32_t wide_row_spaces(uint32_t bits);
 size_t wide_rows_bytes(uint32_t max_chunks, uint32_t row);
 
+// event words: the status byte of every word at its place, final statuses of the buckets
+// with events
+void launch_wide_scan_events(const WideChunks &W, const uint8_t *init, uint8_t *final_out, void *rows, uint8_t *res,
+                             Control *ctl, hipStream_t s);
 // k-space words: the uint16 status of every word at its place, final statuses of the
 // buckets with events
 void launch_wide_scan_spaces(const WideChunks &W, const uint8_t *init, uint8_t *final_out, void *rows, uint16_t *res,

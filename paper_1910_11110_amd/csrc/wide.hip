@@ -16,7 +16,7 @@ namespace {
 // k memory spaces: a word per id, its function (17 bits) and the touch bit
 struct Spaces {
     static constexpr uint32_t SELF = 0x8421u; // every location reaches itself
-    static constexpr uint32_t MASK = 0x1FFFFu, IDENTITY = KF_ID, NOOP = 3u << 24, IDS = 1;
+    static constexpr uint32_t MASK = 0x1FFFFu, IDENTITY = KF_ID, NOOP = 3u << 24, IDS = 1, ROW_IDENTITY = KF_ID;
     __device__ static uint32_t word(uint32_t id) { return id; }
     __device__ static uint32_t shift(uint32_t) { return 0; }
     __device__ static uint32_t touch(uint32_t) { return 1u << 31; }
@@ -57,9 +57,11 @@ struct Spaces {
     __device__ static uint32_t final_status(uint32_t w, uint32_t) { return w & 15u; }
 };
 
-constexpr int K_PAIR = 1;
+// steps whose reads share one wait: two over the 2^14 ids of a plain bucket, where they
+// seldom meet, one over a k-space bucket's 2^12
+constexpr int PAIR = 2, K_PAIR = 1;
 
-struct SpaceChunks {
+struct BucketChunks {
     const uint32_t *ev;
     const uint64_t *base;
     const uint32_t *cbase, *cb;
@@ -83,14 +85,15 @@ struct SpaceChunks {
     __device__ bool bad(uint32_t) const { return false; } // (reported; its bits stay inside the table)
 };
 
+template <class R>
 struct StatusOut {
-    uint16_t *res;
+    R *res;
     template <class CHUNKS>
     __device__ void begin(const CHUNKS &, uint32_t) const {}
     __device__ void step(uint32_t lane, uint32_t, uint64_t i, uint32_t, uint32_t st, bool valid) const
     {
         if (valid)
-            res[i + lane] = (uint16_t)st;
+            res[i + lane] = (R)st;
     }
     __device__ void round(uint32_t, uint64_t, uint32_t, bool) const {}
     __device__ void chunk(uint32_t) const {}
@@ -154,10 +157,10 @@ __global__ __launch_bounds__(BLOCK) void k_wide_groups(const uint32_t *__restric
     const uint32_t c0 = g * W_GROUP, c1 = c0 + W_GROUP < chunks ? c0 + W_GROUP : chunks;
     if (w >= row || c0 >= chunks)
         return;
-    uint32_t f = D::IDENTITY;
+    uint32_t f = D::ROW_IDENTITY;
     for (uint32_t c = c0; c < c1; c++) {
         if (c == cbase[cb[c]])
-            f = D::IDENTITY;
+            f = D::ROW_IDENTITY;
         f = D::compose_word(rows[(uint64_t)c * row + w], f);
     }
     grp[(uint64_t)g * row + w] = f;
@@ -230,35 +233,48 @@ void launch_wide_bases(const WideChunks &W, hipStream_t s)
     k_wide_bases<<<1, 1024, 0, s>>>(W.tot, W.nb, W.per, W.base, W.cbase, W.cb);
 }
 
-uint32_t wide_row_spaces(uint32_t bits) { return 1u << bits; }
+uint32_t wide_row_events(uint32_t bits) { return (1u << bits) / Two::IDS; }
+uint32_t wide_row_spaces(uint32_t bits) { return (1u << bits) / Spaces::IDS; }
 
 size_t wide_rows_bytes(uint32_t max_chunks, uint32_t row)
 {
     return ((size_t)max_chunks + groups_of(max_chunks)) * row * 4;
 }
 
-void launch_wide_scan_spaces(const WideChunks &W, const uint8_t *init, uint8_t *final_out, void *scratch,
-                             uint16_t *res, Control *ctl, hipStream_t s)
+template <class D, int Q, class R>
+static void wide_scan(const WideChunks &W, uint32_t row, const uint8_t *init, uint8_t *final_out, void *scratch, R *res,
+                      Control *ctl, hipStream_t s)
 {
-    const uint32_t row = wide_row_spaces(W.bits), most = wide_max_chunks(W.n, W.nb, W.per), groups = groups_of(most);
+    const uint32_t most = wide_max_chunks(W.n, W.nb, W.per), groups = groups_of(most);
     uint32_t *rows = (uint32_t *)scratch, *grp = rows + (size_t)most * row;
-    const SpaceChunks T{W.part, W.base, W.cbase, W.cb, W.nb, W.bits, W.per};
+    const BucketChunks T{W.part, W.base, W.cbase, W.cb, W.nb, W.bits, W.per};
     const dim3 pg((unsigned)ceil_div(row, BLOCK), groups);
     {
         ProfScope p(s, "wide_fold");
-        k_dense_fold<Spaces, K_PAIR, SpaceChunks><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, ctl);
+        k_dense_fold<D, Q, BucketChunks><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, ctl);
     }
     {
         ProfScope p(s, "wide_groups");
-        k_wide_groups<Spaces><<<pg, BLOCK, 0, s>>>(rows, row, W.nb, W.cbase, W.cb, grp);
+        k_wide_groups<D><<<pg, BLOCK, 0, s>>>(rows, row, W.nb, W.cbase, W.cb, grp);
     }
     {
         ProfScope p(s, "wide_prefix");
-        k_wide_prefix<Spaces><<<pg, BLOCK, 0, s>>>(rows, row, W.nb, W.cbase, W.cb, grp, W.n_ids, W.bits, init,
-                                                   final_out);
+        k_wide_prefix<D><<<pg, BLOCK, 0, s>>>(rows, row, W.nb, W.cbase, W.cb, grp, W.n_ids, W.bits, init, final_out);
     }
     ProfScope p(s, "wide_apply");
-    k_dense_apply<Spaces, K_PAIR, SpaceChunks, StatusOut><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, StatusOut{res});
+    k_dense_apply<D, Q, BucketChunks, StatusOut<R>><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, StatusOut<R>{res});
+}
+
+void launch_wide_scan_events(const WideChunks &W, const uint8_t *init, uint8_t *final_out, void *rows, uint8_t *res,
+                             Control *ctl, hipStream_t s)
+{
+    wide_scan<Two, PAIR>(W, wide_row_events(W.bits), init, final_out, rows, res, ctl, s);
+}
+
+void launch_wide_scan_spaces(const WideChunks &W, const uint8_t *init, uint8_t *final_out, void *rows, uint16_t *res,
+                             Control *ctl, hipStream_t s)
+{
+    wide_scan<Spaces, K_PAIR>(W, wide_row_spaces(W.bits), init, final_out, rows, res, ctl, s);
 }
 
 } // namespace vc

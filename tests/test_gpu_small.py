@@ -58,3 +58,21 @@ def test_malformed(ctx, n, at, word):
         ctx.sync()
     assert x.value.code == V.VC_EINVAL and f"index {at}" in str(x.value)
     t.free()
+
+
+@pytest.mark.parametrize("n", [1, 4097, LONG + 3])
+def test_events_off_alignment(ctx, n):
+    """Device events that start 4, 8 or 12 bytes past a 16-byte line."""
+    import torch
+    from paper_1910_11110_amd import vcheck as V
+    e = gen.plain_events(n + 3, 20, 2)
+    d = torch.from_numpy(e.view(np.int32)).cuda()
+    torch.cuda.synchronize()
+    for off in (1, 2, 3):
+        t = V.Trace.load(ctx, d[off:off + n], 20)
+        t.check()
+        ref = O.check(e[off:off + n], 20)
+        assert np.array_equal(t.status(), ref.status)
+        assert np.array_equal(t.final(), ref.final)
+        assert np.array_equal(t.violations().indices, ref.violations)
+        t.free()
