@@ -932,7 +932,7 @@ __global__ __launch_bounds__(BLOCK) void k_replay_status(const uint16_t *__restr
     __shared__ __align__(16) R s_res[PTILE];
     __shared__ uint32_t s_start[MAX_BUCKETS + 1]; // run starts in the tile's sorted order
     __shared__ uint32_t s_src[MAX_BUCKETS];       // run starts in res
-    __shared__ uint16_t s_bkt[PTILE];             // bucket of every sorted position
+    __shared__ __align__(16) uint16_t s_bkt[PTILE]; // bucket of every sorted position
     __shared__ uint32_t s_tmp[BLOCK / WAVE];
     __shared__ uint32_t s_wsum[BLOCK / WAVE];
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / WAVE;
@@ -966,14 +966,43 @@ __global__ __launch_bounds__(BLOCK) void k_replay_status(const uint16_t *__restr
         if (tid == 0)
             s_start[nb] = tn;
         __syncthreads();
-        // bucket of every sorted position, then the runs copied with consecutive lanes on
-        // consecutive positions (a few runs, a few cache lines per wave load)
+        // bucket of every sorted position: the buckets' starts marked, and a running maximum
+        // over the positions (buckets ascend along them; a bucket's own thread filling its
+        // run is slow when few buckets hold the tile), then the runs copied with
+        // consecutive lanes on consecutive positions (a few runs, a few cache lines per
+        // wave load)
+        uint4 *const mine = reinterpret_cast<uint4 *>(s_bkt + tid * P_ITEMS);
+        mine[0] = mine[1] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
 #pragma unroll
         for (int k = 0; k < BPT; k++) {
             const uint32_t b = tid * BPT + k;
-            if (b < nb)
-                for (uint32_t p = s_start[b]; p < s_start[b + 1]; p++)
-                    s_bkt[p] = (uint16_t)b;
+            if (b < nb && len[k])
+                s_bkt[s_start[b]] = (uint16_t)b;
+        }
+        __syncthreads();
+        {
+            auto later = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
+            const uint4 h0 = mine[0], h1 = mine[1];
+            uint32_t w[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w}, top = 0;
+#pragma unroll
+            for (int k = 0; k < 8; k++)
+                top = later(top, later(w[k] & 0xFFFFu, w[k] >> 16));
+            const uint32_t inc = wave_scan_dpp(top, 0u, later);
+            if (lane == WAVE - 1)
+                s_wsum[wave] = inc;
+            __syncthreads();
+            uint32_t run = dpp_move<DPP_WAVE_SHR1>(0u, inc);
+            for (uint32_t w2 = 0; w2 < wave; w2++)
+                run = later(run, s_wsum[w2]);
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                const uint32_t x = run = later(run, w[k] & 0xFFFFu);
+                run = later(run, w[k] >> 16);
+                w[k] = x | (run << 16);
+            }
+            mine[0] = make_uint4(w[0], w[1], w[2], w[3]);
+            mine[1] = make_uint4(w[4], w[5], w[6], w[7]);
         }
         __syncthreads();
 #pragma unroll

@@ -110,12 +110,7 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prefix(const uint32_t *rows, ui
     const uint32_t w = blockIdx.x * BLOCK + threadIdx.x, g = blockIdx.y;
     if (w >= row)
         return;
-    uint32_t st = 0; // constants
-#pragma unroll
-    for (uint32_t k = 0; k < 8; k++) {
-        const uint32_t id = w * 8 + k;
-        st |= (4u | (init && id < n_ids ? init[id] & 3u : 1u)) << (3 * k);
-    }
+    uint32_t st = Two::initial(init, w * 8, n_ids);
 #pragma unroll 8
     for (uint32_t q = 0; q < g; q++)
         st = tw_compose(grp[(uint64_t)q * row + w], st);
@@ -127,14 +122,11 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prefix(const uint32_t *rows, ui
         st = tw_compose(f, st);
     }
     if (c1 == chunks && final_out)
-#pragma unroll
-        for (uint32_t k = 0; k < 8; k++)
-            if (w * 8 + k < n_ids)
-                final_out[w * 8 + k] = (uint8_t)((st >> (3 * k)) & 3u);
+        Two::put_final(st, final_out, w * 8, n_ids);
 }
 
 // 3. what becomes of the events' statuses
-constexpr uint32_t D_TILE = 1024;
+constexpr uint32_t D_TILE = 512;
 static_assert(D_TILE % (D_UNROLL * WAVE) == 0, "whole rounds of steps a tile");
 
 // a trace: status bytes; per step of 64 events the mask of the flagged ones, per tile of

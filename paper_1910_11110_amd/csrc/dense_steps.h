@@ -111,6 +111,10 @@ __device__ __forceinline__ uint32_t el_of(uint32_t f4)
 // still change the id in the fold), and the functions lanes pass along, with the lane
 // they came from (64: none) in spare bits.
 // ----------------------------------------------------------------------------------
+struct __attribute__((packed)) Bytes8 { // at any address
+    uint32_t lo, hi;
+};
+
 struct Two {
     static constexpr uint32_t MASK = 7, IDENTITY = F_ID, NOOP = (uint32_t)OP_NOOP << 24;
     __device__ static uint32_t word(uint32_t id) { return id >> 3; }
@@ -134,11 +138,42 @@ struct Two {
     __device__ static uint32_t packed_lane(uint32_t v) { return (v & (64u << 4)) ? 64u : (v >> 2) & 63u; }
     __device__ static uint32_t fold_all(uint32_t h, uint32_t f) { return el_compose(h, el_of(f)); }
     __device__ static uint32_t status_after(uint32_t f, uint32_t h) { return fapply(f, h & 3u); }
-    // rows: a word's composition (IDS ids), an id's initial status, its final one in place k
+    // rows: a word's composition, the initial statuses of its ids (from id on, n_ids in all)
+    // as constants, and its statuses as final ones
     static constexpr uint32_t IDS = 8, ROW_IDENTITY = 0;
     __device__ static uint32_t compose_word(uint32_t g, uint32_t f) { return tw_compose(g, f); }
-    __device__ static uint32_t initial(const uint8_t *init, uint32_t id) { return 4u | (init ? init[id] & 3u : 1u); }
-    __device__ static uint32_t final_status(uint32_t w, uint32_t k) { return (w >> (3u * k)) & 3u; }
+    __device__ static uint32_t initial(const uint8_t *init, uint32_t id, uint32_t n_ids)
+    {
+        if (!init)
+            return MT | MX; // (V,I) eight times
+        uint32_t st = MT;
+        if (id + 8 <= n_ids) {
+            const Bytes8 b = *reinterpret_cast<const Bytes8 *>(init + id);
+#pragma unroll
+            for (uint32_t k = 0; k < 8; k++)
+                st |= (((k < 4 ? b.lo : b.hi) >> (8u * (k & 3u))) & 3u) << (3 * k);
+        } else {
+            for (uint32_t k = 0; k < 8; k++)
+                st |= (id + k < n_ids ? init[id + k] & 3u : 1u) << (3 * k);
+        }
+        return st;
+    }
+    __device__ static void put_final(uint32_t st, uint8_t *final_out, uint32_t id, uint32_t n_ids)
+    {
+        if (id + 8 <= n_ids) {
+            Bytes8 b{0, 0};
+#pragma unroll
+            for (uint32_t k = 0; k < 4; k++) {
+                b.lo |= ((st >> (3 * k)) & 3u) << (8 * k);
+                b.hi |= ((st >> (3 * k + 12)) & 3u) << (8 * k);
+            }
+            *reinterpret_cast<Bytes8 *>(final_out + id) = b;
+        } else {
+            for (uint32_t k = 0; k < 8; k++)
+                if (id + k < n_ids)
+                    final_out[id + k] = (uint8_t)((st >> (3 * k)) & 3u);
+        }
+    }
 };
 
 // the lanes of `among` with this lane's id (ids of `bits` bits, at most 16)

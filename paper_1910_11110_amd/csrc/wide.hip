@@ -51,15 +51,25 @@ struct Spaces {
     __device__ static uint32_t packed_lane(uint32_t v) { return v >> 17; }
     __device__ static uint32_t fold_all(uint32_t h, uint32_t f) { return kf_compose(h, f); }
     __device__ static uint32_t status_after(uint32_t f, uint32_t h) { return kf_apply(f, h & 15u); }
-    // rows: a word's composition, its initial statuses, its final ones
+    // rows, as in Two
     __device__ static uint32_t compose_word(uint32_t g, uint32_t f) { return kf_compose(g, f); }
-    __device__ static uint32_t initial(const uint8_t *init, uint32_t id) { return KF_CONST | (init ? init[id] & 15u : 1u); }
-    __device__ static uint32_t final_status(uint32_t w, uint32_t) { return w & 15u; }
+    __device__ static uint32_t initial(const uint8_t *init, uint32_t id, uint32_t n_ids)
+    {
+        return KF_CONST | (init && id < n_ids ? init[id] & 15u : 1u);
+    }
+    __device__ static void put_final(uint32_t st, uint8_t *final_out, uint32_t id, uint32_t n_ids)
+    {
+        if (id < n_ids)
+            final_out[id] = (uint8_t)(st & 15u);
+    }
 };
 
 // steps whose reads share one wait: two over the 2^14 ids of a plain bucket, where they
 // seldom meet, one over a k-space bucket's 2^12
 constexpr int PAIR = 2, K_PAIR = 1;
+
+// a chunk's bucket (cb), with a mark on a bucket's first chunk
+constexpr uint32_t W_FIRST = 1u << 31, W_BUCKET = W_FIRST - 1;
 
 struct BucketChunks {
     const uint32_t *ev;
@@ -74,12 +84,12 @@ struct BucketChunks {
     __device__ uint32_t clamped(uint32_t w) const { return local(w); }
     __device__ uint64_t begin(uint32_t c) const
     {
-        const uint32_t b = cb[c];
+        const uint32_t b = cb[c] & W_BUCKET;
         return base[b] + (uint64_t)(c - cbase[b]) * per;
     }
     __device__ uint64_t end(uint32_t c) const
     {
-        const uint64_t e = begin(c) + per, last = base[cb[c] + 1];
+        const uint64_t e = begin(c) + per, last = base[(cb[c] & W_BUCKET) + 1];
         return e < last ? e : last;
     }
     __device__ bool bad(uint32_t) const { return false; } // (reported; its bits stay inside the table)
@@ -104,32 +114,35 @@ __global__ __launch_bounds__(1024) void k_wide_bases(const uint32_t *__restrict_
                                                      uint64_t *__restrict__ base, uint32_t *__restrict__ cbase,
                                                      uint32_t *__restrict__ cb)
 {
-    __shared__ uint64_t s_a[1024];
-    __shared__ uint32_t s_t[1024 + 1];
-    const uint32_t i = threadIdx.x;
-    const uint64_t c = i < nb ? tot[i] : 0;
-    const uint32_t k = (uint32_t)ceil_div(c, per);
-    s_a[i] = c;
-    s_t[i] = k;
-    __syncthreads();
-    for (uint32_t d = 1; d < 1024; d <<= 1) {
-        const uint64_t a = i >= d ? s_a[i - d] : 0;
-        const uint32_t t = i >= d ? s_t[i - d] : 0;
-        __syncthreads();
-        s_a[i] += a;
-        s_t[i] += t;
-        __syncthreads();
+    __shared__ uint32_t s_t[1024];
+    __shared__ uint64_t s_wa[1024 / WAVE];
+    __shared__ uint32_t s_wt[1024 / WAVE];
+    const uint32_t i = threadIdx.x, lane = lane_id(), wave = i / WAVE;
+    const uint32_t c = i < nb ? tot[i] : 0, k = (uint32_t)ceil_div((uint64_t)c, per);
+    const uint64_t ainc = wave_scan_add((uint64_t)c, lane);
+    const uint32_t tinc = wave_scan_add(k, lane);
+    if (lane == WAVE - 1) {
+        s_wa[wave] = ainc;
+        s_wt[wave] = tinc;
     }
-    const uint64_t a0 = s_a[i] - c;
-    const uint32_t t0 = s_t[i] - k, chunks = s_t[1023];
+    __syncthreads();
+    uint64_t a0 = ainc - c;
+    uint32_t t0 = tinc - k, chunks = 0;
+    for (uint32_t w2 = 0; w2 < 1024 / WAVE; w2++) {
+        a0 += w2 < wave ? s_wa[w2] : 0;
+        t0 += w2 < wave ? s_wt[w2] : 0;
+        chunks += s_wt[w2];
+    }
+    s_t[i] = t0 + k;
     if (i < nb) {
         base[i] = a0;
         cbase[i] = t0;
     }
     if (i == nb - 1) {
-        base[nb] = s_a[i];
-        cbase[nb] = s_t[i];
+        base[nb] = a0 + c;
+        cbase[nb] = t0 + k;
     }
+    __syncthreads();
     // s_t: the first chunk after bucket i's; a chunk's bucket is the first that ends past it
     for (uint32_t q = i; q < chunks; q += 1024) {
         uint32_t lo = 0, hi = nb - 1;
@@ -140,13 +153,14 @@ __global__ __launch_bounds__(1024) void k_wide_bases(const uint32_t *__restrict_
             else
                 lo = mid + 1;
         }
-        cb[q] = lo;
+        cb[q] = lo | (q == (lo ? s_t[lo - 1] : 0u) ? W_FIRST : 0u);
     }
 }
 
 // Prefix over the rows by groups of W_GROUP chunks, as in the dense check; a group's row is
 // the composition since the last bucket that starts in it.
-constexpr uint32_t W_GROUP = 16;
+constexpr uint32_t W_GROUP = 32, W_BATCH = 8;
+static_assert(W_GROUP % W_BATCH == 0, "whole batches but for the last group's");
 
 template <class D>
 __global__ __launch_bounds__(BLOCK) void k_wide_groups(const uint32_t *__restrict__ rows, uint32_t row, uint32_t nb,
@@ -158,10 +172,18 @@ __global__ __launch_bounds__(BLOCK) void k_wide_groups(const uint32_t *__restric
     if (w >= row || c0 >= chunks)
         return;
     uint32_t f = D::ROW_IDENTITY;
-    for (uint32_t c = c0; c < c1; c++) {
-        if (c == cbase[cb[c]])
-            f = D::ROW_IDENTITY;
-        f = D::compose_word(rows[(uint64_t)c * row + w], f);
+    for (uint32_t q = c0; q < c1; q += W_BATCH) {
+        uint32_t v[W_BATCH], b[W_BATCH]; // a batch's loads together
+#pragma unroll
+        for (uint32_t k = 0; k < W_BATCH; k++) {
+            const uint32_t c = q + k < c1 ? q + k : c1 - 1;
+            b[k] = cb[c];
+            v[k] = rows[(uint64_t)c * row + w];
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < W_BATCH; k++)
+            if (q + k < c1)
+                f = (b[k] & W_FIRST) ? v[k] : D::compose_word(v[k], f);
     }
     grp[(uint64_t)g * row + w] = f;
 }
@@ -178,34 +200,34 @@ __global__ __launch_bounds__(BLOCK) void k_wide_prefix(uint32_t *__restrict__ ro
     const uint32_t c0 = g * W_GROUP, c1 = c0 + W_GROUP < chunks ? c0 + W_GROUP : chunks;
     if (w >= row || c0 >= chunks)
         return;
-    auto initial = [&](uint32_t b) {
-        uint32_t st = 0;
-#pragma unroll
-        for (uint32_t k = 0; k < D::IDS; k++) {
-            const uint32_t id = (b << bits) + w * D::IDS + k;
-            st |= D::initial(id < n_ids ? init : nullptr, id) << D::shift(k);
-        }
-        return st;
-    };
-    uint32_t b = cb[c0], first = cbase[b], st = initial(b);
+    auto first_id = [&](uint32_t b) { return (b << bits) + w * D::IDS; };
+    const uint32_t b0 = cb[c0] & W_BUCKET, first = cbase[b0];
+    uint32_t st = D::initial(init, first_id(b0), n_ids);
     if (first < c0)
+#pragma unroll 8
         for (uint32_t q = first / W_GROUP; q < g; q++)
             st = D::compose_word(grp[(uint64_t)q * row + w], st);
-    for (uint32_t c = c0; c < c1; c++) {
-        if (cb[c] != b) {
-            b = cb[c];
-            st = initial(b);
-        }
-        const uint32_t f = rows[(uint64_t)c * row + w];
-        rows[(uint64_t)c * row + w] = st;
-        st = D::compose_word(f, st);
-        if (c + 1 == cbase[b + 1])
+    for (uint32_t q = c0; q < c1; q += W_BATCH) {
+        uint32_t v[W_BATCH], b[W_BATCH + 1];
 #pragma unroll
-            for (uint32_t k = 0; k < D::IDS; k++) {
-                const uint32_t id = (b << bits) + w * D::IDS + k;
-                if (id < n_ids)
-                    final_out[id] = (uint8_t)D::final_status(st, k);
-            }
+        for (uint32_t k = 0; k < W_BATCH; k++) {
+            const uint32_t c = q + k < c1 ? q + k : c1 - 1;
+            b[k] = cb[c];
+            v[k] = rows[(uint64_t)c * row + w];
+        }
+        b[W_BATCH] = q + W_BATCH < chunks ? cb[q + W_BATCH] : W_FIRST;
+#pragma unroll
+        for (uint32_t k = 0; k < W_BATCH; k++) {
+            const uint32_t c = q + k;
+            if (c >= c1)
+                continue;
+            if ((b[k] & W_FIRST) && c > c0)
+                st = D::initial(init, first_id(b[k] & W_BUCKET), n_ids);
+            rows[(uint64_t)c * row + w] = st;
+            st = D::compose_word(v[k], st);
+            if (c + 1 == chunks || ((c + 1 < c1 || k + 1 == W_BATCH ? b[k + 1] : cb[c + 1]) & W_FIRST))
+                D::put_final(st, final_out, first_id(b[k] & W_BUCKET), n_ids); // the bucket's last chunk
+        }
     }
 }
 
@@ -222,7 +244,7 @@ uint64_t wide_chunk_events(uint64_t n, uint32_t row)
 {
     const uint64_t waves = 163840 / wide_lds(row), chunks = 256 * (waves > 24 ? 24 : waves);
     const uint64_t round = WAVE * D_UNROLL, per = ceil_div(n ? n : 1, chunks);
-    return ceil_div(per < 4 * round ? 4 * round : per, round) * round;
+    return ceil_div(per, round) * round;
 }
 
 uint32_t wide_max_chunks(uint64_t n, uint32_t nb, uint64_t per) { return (uint32_t)(n / per) + nb; }
@@ -253,7 +275,7 @@ static void wide_scan(const WideChunks &W, uint32_t row, const uint8_t *init, ui
         ProfScope p(s, "wide_fold");
         k_dense_fold<D, Q, BucketChunks><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, ctl);
     }
-    {
+    if (groups > 1) {
         ProfScope p(s, "wide_groups");
         k_wide_groups<D><<<pg, BLOCK, 0, s>>>(rows, row, W.nb, W.cbase, W.cb, grp);
     }
