@@ -1,8 +1,10 @@
 // batch.cpp -- vc_batch_check: independent traces checked in one captured pipeline.
 //
-// The traces' events are relocated into one key space (ids of trace i start at the
-// sum of the id counts before it) and one index space.  When every trace fits the
-// bucket engine, the combined stream (events and induced items) is written as 32-bit
+// When every trace is over at most 2^16 ids, all of them are walked where they lie, with
+// their statuses in LDS (the dense route; only the combined streams of traces with arrays
+// are written).  Otherwise the traces' events are relocated into one key space (ids of
+// trace i start at the sum of the id counts before it) and one index space.  When every
+// trace fits the bucket engine, the combined stream (events and induced items) is written as 32-bit
 // words and the traces are checked by groups of consecutive traces whose ids fit one
 // bucket engine's key space, one bucket pass per group over its slice of the stream,
 // each followed by a pass that takes the group's status bytes through the partition's
@@ -11,8 +13,8 @@
 // compaction of a single trace and one kernel splits the results back into each
 // trace's buffers.  The launch sequence of a batch is captured once in a hipGraph and
 // replayed while the batch (its traces, their sizes and buffers) is unchanged.  The
-// settings (ids per group and events per chunk on the bucket route, the sort's digit
-// width and persistent grid bound otherwise) come from an autotuner that times
+// settings (ids per group and events per chunk on the bucket route, events per chunk on
+// the dense one, the sort's digit width and persistent grid bound otherwise) come from an autotuner that times
 // candidate settings on the batch itself, keeps only settings whose results equal the
 // first candidate's, and caches the choice per shape in a small JSON file.
 #include <hip/hip_runtime.h>
@@ -41,12 +43,14 @@ struct BatchState {
     // host copies of the uploaded descriptor tables (alive until the next upload)
     std::vector<TraceDesc> h_desc;
     std::vector<ChunkDesc> h_chunks;
+    std::vector<ChunkDesc> h_dense;
+    std::vector<PrefixJob> h_jobs;
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
     bool graph_ok = false;
     // device buffers
     DevBuf desc, init_all, fin_all, status_all, viol_all, items_a, items_b, cnt, pos, scratch, ind,
-        chunks, words, comb, vcnt, vpos;
+        chunks, words, comb, vcnt, vpos, dchunks, jobs, rows, grp;
     uint64_t n_chunks = 0;
     Control *ctl = nullptr;
     // bucket route: groups of consecutive traces (their slice of the combined stream and
@@ -57,6 +61,11 @@ struct BatchState {
         uint32_t t_lo, t_hi; // its traces
     };
     bool bucket = false;
+    // dense route (a batch that could take the bucket route, every trace over few enough
+    // ids): h_chunks are the traces' with arrays, h_dense the chunks that are walked
+    bool dense = false;
+    uint32_t class_at[DENSE_CLASSES + 1] = {};
+    uint64_t row_words = 0, grp_words = 0;
     uint64_t MB = 0; // combined slots: every trace's range padded to a multiple of 16
     std::vector<Group> groups;
     Control *gctl = nullptr;
@@ -73,12 +82,15 @@ struct BatchState {
 
 namespace {
 
-// the chunks of every trace (never across traces), and every trace's first chunk
+// the chunks of every trace (never across traces; on the dense route of those with arrays
+// only), and every trace's first chunk
 void build_chunks(BatchState &b, std::vector<TraceDesc> &desc)
 {
     b.h_chunks.clear();
     for (uint32_t t = 0; t < (uint32_t)desc.size(); t++) {
         desc[t].first_chunk = b.h_chunks.size();
+        if (b.dense && !desc[t].off)
+            continue;
         const uint64_t len = desc[t].off ? BATCH_CHUNK : b.plain_chunk;
         for (uint64_t a = 0; a < desc[t].n; a += len)
             b.h_chunks.push_back(ChunkDesc{a, t, (uint32_t)std::min<uint64_t>(len, desc[t].n - a)});
@@ -177,7 +189,9 @@ void tune_store(const std::string &key, const SortTuning &t, unsigned scan_grid)
 }
 
 // chooses the route: the bucket engine when every trace has between 1 and
-// bucket_max_ids() ids and its items fit 32-bit positions; then every trace's first
+// bucket_max_ids() ids and its items fit 32-bit positions, the dense route when all of
+// them have so few ids that a wave holds their statuses in LDS (1,024 traces over 8 to
+// 65,536 ids, 110 M events: 2,133 us of kernels by buckets, 1,012 dense); then every trace's first
 // combined position (its range padded to a multiple of 16 slots, so that every trace's
 // items start 16-byte aligned in the status bytes) and first key inside its group, and
 // the groups (consecutive traces whose ids fit one key space)
@@ -185,18 +199,23 @@ void plan_groups(BatchState &b, std::vector<TraceDesc> &desc)
 {
     b.groups.clear();
     const uint64_t kmax = std::min<uint64_t>(bucket_max_ids(), 1ull << b.group_bits);
-    bool ok = !getenv("VC_GENERAL_PATH") && !desc.empty();
+    bool ok = !getenv("VC_GENERAL_PATH") && !desc.empty(), dense = true;
     uint64_t item = 0, m_all = 0;
     auto padded = [](uint64_t m) { return (m + 15) & ~(uint64_t)15; };
     for (TraceDesc &d : desc) {
         ok = ok && d.n_ids >= 1 && d.n_ids <= bucket_max_ids() && padded(d.m) < (1ull << 32);
-        d.item_base = item;
-        item += padded(d.m);
+        dense = dense && d.n_ids <= 8 * DENSE_CLASS[DENSE_CLASSES - 1];
         m_all += d.m;
     }
     b.bucket = ok && m_all == b.M;
+    b.dense = b.bucket && dense;
+    for (TraceDesc &d : desc) { // (the dense route has words of the traces with arrays only)
+        d.item_base = item;
+        if (!b.dense || d.off)
+            item += padded(d.m);
+    }
     b.MB = item;
-    if (!b.bucket)
+    if (!b.bucket || b.dense)
         return;
     BatchState::Group g{0, 0, 0, 0, 0, 0};
     for (uint32_t t = 0; t < (uint32_t)desc.size(); t++) {
@@ -214,20 +233,92 @@ void plan_groups(BatchState &b, std::vector<TraceDesc> &desc)
     b.groups.push_back(g);
 }
 
+// The dense route's chunks, rows and prefix jobs.  A chunk has the events that give every
+// wave the device holds of its class one chunk, but no more than plain_chunk and no fewer
+// than 512, and at least as many as its row has ids over 8 (a quarter of that in a batch
+// that leaves the device idle): below that its row's traffic would outweigh its events'.
+void plan_dense(BatchState &b, std::vector<TraceDesc> &desc)
+{
+    b.h_dense.clear();
+    b.h_jobs.clear();
+    b.row_words = b.grp_words = 0;
+    uint64_t items[DENSE_CLASSES] = {};
+    auto class_of = [](uint32_t row) {
+        int k = 0;
+        while (row > DENSE_CLASS[k])
+            k++;
+        return k;
+    };
+    for (TraceDesc &d : desc) {
+        d.row = (uint32_t)(((d.n_ids + 7) / 8 + 63) & ~63u);
+        items[class_of(d.row)] += d.m;
+    }
+    for (int k = 0; k < DENSE_CLASSES; k++) {
+        b.class_at[k] = (uint32_t)b.h_dense.size();
+        const uint64_t share = items[k] / dense_class_waves(k);
+        for (uint32_t t = 0; t < (uint32_t)desc.size(); t++) {
+            TraceDesc &d = desc[t];
+            if (class_of(d.row) != k)
+                continue;
+            const uint64_t most = std::max<uint64_t>(b.plain_chunk, 2 * d.row);
+            const uint64_t least = std::max<uint64_t>(BATCH_CHUNK, d.row / 4);
+            uint64_t len = std::min(std::max(share, least), most);
+            len = (len + BATCH_CHUNK - 1) & ~(uint64_t)(BATCH_CHUNK - 1); // (whole tiles of a trace with arrays)
+            d.first_dense = b.h_dense.size();
+            uint64_t a = 0;
+            do { // (an empty trace: one empty chunk, for its final statuses)
+                b.h_dense.push_back(ChunkDesc{a, t, (uint32_t)std::min<uint64_t>(len, d.n - a)});
+                a += len;
+            } while (a < d.n);
+            d.dense_chunks = (uint32_t)(b.h_dense.size() - d.first_dense);
+            const uint32_t groups = (d.dense_chunks + B_GROUP - 1) / B_GROUP;
+            d.row_base = b.row_words;
+            d.grp_base = b.grp_words;
+            b.row_words += (uint64_t)d.dense_chunks * d.row;
+            b.grp_words += (uint64_t)(groups - 1) * d.row;
+            for (uint32_t g = 0; g < groups; g++)
+                for (uint32_t w = 0; w < d.row; w += BLOCK)
+                    b.h_jobs.push_back(PrefixJob{t, g, w});
+        }
+    }
+    b.class_at[DENSE_CLASSES] = (uint32_t)b.h_dense.size();
+}
+
+// route, chunks and groups for the current settings
+void plan(BatchState &b, std::vector<TraceDesc> &desc)
+{
+    plan_groups(b, desc);
+    build_chunks(b, desc);
+    if (b.dense)
+        plan_dense(b, desc);
+}
+
 int reserve_all(BatchState &b, uint32_t n)
 {
     int r;
     uint64_t N = b.N, K = b.K, M = b.M;
     if ((r = devbuf_reserve(b.desc, sizeof(TraceDesc) * (n ? n : 1))) != VC_OK) return r;
-    if ((r = devbuf_reserve(b.init_all, K ? K : 1)) != VC_OK) return r;
-    if ((r = devbuf_reserve(b.fin_all, K ? K : 1)) != VC_OK) return r;
+    if (!b.dense) {
+        if ((r = devbuf_reserve(b.init_all, K ? K : 1)) != VC_OK) return r;
+        if ((r = devbuf_reserve(b.fin_all, K ? K : 1)) != VC_OK) return r;
+    }
     const uint64_t nc = b.n_chunks;
     if ((r = devbuf_reserve(b.cnt, 4 * (nc ? nc : 1))) != VC_OK) return r;
     if ((r = devbuf_reserve(b.pos, 8 * (nc + 1))) != VC_OK) return r;
     if ((r = devbuf_reserve(b.chunks, sizeof(ChunkDesc) * (nc ? nc : 1))) != VC_OK) return r;
     if ((r = devbuf_reserve(b.ind, 8 * (n ? n : 1))) != VC_OK) return r;
     size_t sc = excl_scan_scratch_bytes(nc);
-    if (b.bucket) {
+    if (b.dense) {
+        const uint64_t nd = b.h_dense.size();
+        if ((r = devbuf_reserve(b.dchunks, sizeof(ChunkDesc) * nd)) != VC_OK) return r;
+        if ((r = devbuf_reserve(b.jobs, sizeof(PrefixJob) * b.h_jobs.size())) != VC_OK) return r;
+        if ((r = devbuf_reserve(b.rows, 4 * b.row_words)) != VC_OK) return r;
+        if ((r = devbuf_reserve(b.grp, 4 * (b.grp_words ? b.grp_words : 1))) != VC_OK) return r;
+        if ((r = devbuf_reserve(b.words, 4 * (b.MB ? b.MB : 1))) != VC_OK) return r;
+        if ((r = devbuf_reserve(b.vcnt, 4 * nd)) != VC_OK) return r;
+        if ((r = devbuf_reserve(b.vpos, 8 * (nd + 1))) != VC_OK) return r;
+        sc = std::max(sc, excl_scan_scratch_bytes(nd));
+    } else if (b.bucket) {
         // the status bytes go straight to the traces: no batch-wide status or violation
         // arrays
         const uint64_t MB = b.MB;
@@ -262,14 +353,31 @@ void enqueue_pipeline(BatchState &b, hipStream_t s)
     uint32_t n = b.n_traces;
     launch_reset_control(b.ctl, s);
     launch_batch_reset(d, n, (unsigned long long *)b.ind.p, s);
-    launch_batch_init(d, n, b.K, (uint8_t *)b.init_all.p, (uint8_t *)b.fin_all.p, s);
+    if (!b.dense)
+        launch_batch_init(d, n, b.K, (uint8_t *)b.init_all.p, (uint8_t *)b.fin_all.p, s);
     const ChunkDesc *ch = (const ChunkDesc *)b.chunks.p;
     launch_batch_chunk_count(d, ch, b.n_chunks, (uint32_t *)b.cnt.p, s);
-    launch_excl_scan((uint32_t *)b.cnt.p, b.n_chunks, (uint64_t *)b.pos.p, nullptr, b.scratch.p, b.ctl->tickets[6], s);
+    if (!b.dense || b.n_chunks)
+        launch_excl_scan((uint32_t *)b.cnt.p, b.n_chunks, (uint64_t *)b.pos.p, nullptr, b.scratch.p, b.ctl->tickets[6], s);
+    if (b.dense) {
+        const ChunkDesc *dch = (const ChunkDesc *)b.dchunks.p;
+        const uint64_t nd = b.h_dense.size();
+        uint32_t *words = (uint32_t *)b.words.p, *vcnt = (uint32_t *)b.vcnt.p;
+        uint64_t *vpos = (uint64_t *)b.vpos.p;
+        launch_batch_chunk_words(d, ch, b.n_chunks, (const uint64_t *)b.pos.p, words, b.MB, false, s);
+        DenseBatch B{d, dch, {}, words, (const uint64_t *)b.pos.p, (const PrefixJob *)b.jobs.p, (uint32_t)b.h_jobs.size(),
+                     b.grp_words != 0, (uint32_t *)b.rows.p, (uint32_t *)b.grp.p, vcnt};
+        std::copy(b.class_at, b.class_at + DENSE_CLASSES + 1, B.class_at);
+        launch_batch_dense(B, s);
+        launch_excl_scan(vcnt, nd, vpos, nullptr, b.scratch.p, b.ctl->tickets[7], s);
+        launch_batch_chunk_viol(d, dch, nd, vcnt, vpos, true, s);
+        launch_batch_counts(d, n, vpos, b.ctl, s);
+        return;
+    }
     if (b.bucket) {
         uint32_t *words = (uint32_t *)b.words.p;
         uint8_t *comb = (uint8_t *)b.comb.p, *init_all = (uint8_t *)b.init_all.p, *fin_all = (uint8_t *)b.fin_all.p;
-        launch_batch_chunk_words(d, ch, b.n_chunks, (const uint64_t *)b.pos.p, words, b.MB, s);
+        launch_batch_chunk_words(d, ch, b.n_chunks, (const uint64_t *)b.pos.p, words, b.MB, true, s);
         // one bucket pass per group (final statuses into the group's slice of fin_all,
         // which holds the initial statuses; their errors are folded into the batch's);
         // its results stay in the partitioned order, and the group's chunks take their
@@ -289,7 +397,7 @@ void enqueue_pipeline(BatchState &b, hipStream_t s)
         }
         // the flagged events' offsets, then the violation lists and the counts
         launch_excl_scan(vcnt, b.n_chunks, vpos, nullptr, b.scratch.p, b.ctl->tickets[7], s);
-        launch_batch_chunk_viol(d, ch, b.n_chunks, vcnt, vpos, s);
+        launch_batch_chunk_viol(d, ch, b.n_chunks, vcnt, vpos, false, s);
         launch_batch_finish(d, n, b.n_chunks, vpos, (const uint8_t *)b.fin_all.p, b.ctl,
                             (const unsigned long long *)b.ind.p, s);
         return;
@@ -316,22 +424,32 @@ void drop_graph(BatchState &b)
     b.graph_ok = false;
 }
 
+// the descriptor tables of the batch to the device
+template <class COPY>
+int upload(BatchState &b, COPY &&copy)
+{
+    hipError_t e = copy(b.desc.p, b.h_desc.data(), sizeof(TraceDesc) * b.n_traces);
+    if (e == hipSuccess && b.n_chunks)
+        e = copy(b.chunks.p, b.h_chunks.data(), sizeof(ChunkDesc) * b.n_chunks);
+    if (e == hipSuccess && b.dense)
+        e = copy(b.dchunks.p, b.h_dense.data(), sizeof(ChunkDesc) * b.h_dense.size());
+    if (e == hipSuccess && b.dense)
+        e = copy(b.jobs.p, b.h_jobs.data(), sizeof(PrefixJob) * b.h_jobs.size());
+    return e == hipSuccess ? VC_OK : vc_hip_fail(e, "hipMemcpy(batch descriptors)");
+}
+
 // chunks and groups of the batch in b.h_desc for the current settings, buffers, and the
 // descriptors on the device (synchronous: the set-up of a new batch shape)
 int configure(BatchState &b)
 {
     const uint32_t n = b.n_traces;
-    build_chunks(b, b.h_desc);
-    plan_groups(b, b.h_desc);
+    plan(b, b.h_desc);
     int r = reserve_all(b, n);
     if (r != VC_OK)
         return r;
-    hipError_t e;
-    if ((e = hipMemcpy(b.desc.p, b.h_desc.data(), sizeof(TraceDesc) * n, hipMemcpyHostToDevice)) != hipSuccess ||
-        (b.n_chunks && (e = hipMemcpy(b.chunks.p, b.h_chunks.data(), sizeof(ChunkDesc) * b.n_chunks,
-                                      hipMemcpyHostToDevice)) != hipSuccess))
-        return vc_hip_fail(e, "hipMemcpy(batch descriptors)");
-    return VC_OK;
+    return upload(b, [](void *to, const void *from, size_t bytes) {
+        return hipMemcpy(to, from, bytes, hipMemcpyHostToDevice);
+    });
 }
 
 bool tuning_on() { return !getenv("VC_NO_AUTOTUNE"); }
@@ -385,6 +503,8 @@ int autotune_bucket(vc_ctx *c, BatchState &b)
             break;
         if (!b.bucket)
             break; // (the route does not depend on these settings)
+        if (b.dense && cands[i].group_bits != 22)
+            continue; // (the groups are the bucket engine's)
         enqueue_pipeline(b, s); // warm
         (void)hipEventRecord(e0, s);
         enqueue_pipeline(b, s);
@@ -499,7 +619,7 @@ void batch_free(BatchState *b)
     drop_graph(*b);
     for (DevBuf *d : { &b->desc, &b->init_all, &b->fin_all, &b->status_all, &b->viol_all,
                        &b->items_a, &b->items_b, &b->cnt, &b->pos, &b->scratch, &b->ind, &b->chunks, &b->words,
-                       &b->comb })
+                       &b->comb, &b->vcnt, &b->vpos, &b->dchunks, &b->jobs, &b->rows, &b->grp })
         devbuf_free(*d);
     if (b->ctl)
         (void)hipFree(b->ctl);
@@ -530,8 +650,7 @@ int batch_prepare(BatchState &b, const std::vector<TraceDesc> &desc, uint64_t M,
     b.K = K;
     b.M = M;
     b.n_traces = n;
-    build_chunks(b, b.h_desc);
-    plan_groups(b, b.h_desc);
+    plan(b, b.h_desc);
     int r = reserve_all(b, n);
     if (r != VC_OK)
         return r;
@@ -542,13 +661,9 @@ int batch_prepare(BatchState &b, const std::vector<TraceDesc> &desc, uint64_t M,
         }
         b.tuned = true;
     }
-    hipError_t e;
-    if ((e = hipMemcpyAsync(b.desc.p, b.h_desc.data(), sizeof(TraceDesc) * n, hipMemcpyHostToDevice, s)) !=
-            hipSuccess ||
-        (b.n_chunks && (e = hipMemcpyAsync(b.chunks.p, b.h_chunks.data(), sizeof(ChunkDesc) * b.n_chunks,
-                                           hipMemcpyHostToDevice, s)) != hipSuccess))
-        return vc_hip_fail(e, "hipMemcpyAsync(batch descriptors)");
-    return VC_OK;
+    return upload(b, [s](void *to, const void *from, size_t bytes) {
+        return hipMemcpyAsync(to, from, bytes, hipMemcpyHostToDevice, s);
+    });
 }
 
 void batch_enqueue(BatchState &b, hipStream_t s)

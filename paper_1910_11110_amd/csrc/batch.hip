@@ -540,14 +540,14 @@ __global__ __launch_bounds__(BLOCK) void k_batch_chunk_status(const TraceDesc *_
     }
 }
 
-// bucket route: every chunk's flagged events, ascending, as trace-relative indices into
+// every chunk's flagged events, ascending, as trace-relative indices into
 // its trace's violation list, from the chunk's offset among the trace's flagged events
 // (vpos: exclusive prefix of the chunks' counts over the batch; a trace's chunks are
 // consecutive).  The status bytes are read back 16 per lane (16-byte loads when aligned).
 __global__ __launch_bounds__(BLOCK) void k_batch_chunk_viol(const TraceDesc *__restrict__ d,
                                                             const ChunkDesc *__restrict__ ch, uint64_t n_chunks,
                                                             const uint32_t *__restrict__ vcnt,
-                                                            const uint64_t *__restrict__ vpos)
+                                                            const uint64_t *__restrict__ vpos, bool dense)
 {
     const uint32_t lane = lane_id();
     for (uint64_t c = (uint64_t)blockIdx.x * CH_WAVES + wave_index(); c < n_chunks;
@@ -556,7 +556,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_chunk_viol(const TraceDesc *__r
             continue; // uniform
         const ChunkDesc cd = ch[c];
         const TraceDesc td = d[cd.trace];
-        uint64_t off = vpos[c] - vpos[td.first_chunk];
+        uint64_t off = vpos[c] - vpos[dense ? td.first_dense : td.first_chunk];
         const uint8_t *src = td.status + cd.start;
         const bool vec = (reinterpret_cast<uintptr_t>(src) & 15u) == 0;
         for (uint32_t k0 = 0; k0 < cd.len; k0 += 16 * WAVE) {
@@ -694,11 +694,12 @@ void launch_batch_chunk_emit(const TraceDesc *d, const ChunkDesc *ch, uint64_t n
 }
 
 void launch_batch_chunk_words(const TraceDesc *d, const ChunkDesc *ch, uint64_t n_chunks, const uint64_t *chunk_pos,
-                              uint32_t *words, uint64_t cap, hipStream_t s)
+                              uint32_t *words, uint64_t cap, bool plain, hipStream_t s)
 {
     if (n_chunks) {
         ProfScope prof_(s, "batch_chunk_words");
-        k_batch_chunk_words<true><<<gridn(n_chunks, CH_WAVES), BLOCK, 0, s>>>(d, ch, n_chunks, chunk_pos, words, cap);
+        if (plain)
+            k_batch_chunk_words<true><<<gridn(n_chunks, CH_WAVES), BLOCK, 0, s>>>(d, ch, n_chunks, chunk_pos, words, cap);
         k_batch_chunk_words<false><<<gridn(n_chunks, CH_WAVES), BLOCK, 0, s>>>(d, ch, n_chunks, chunk_pos, words, cap);
     }
 }
@@ -715,11 +716,11 @@ void launch_batch_chunk_status(const TraceDesc *d, const ChunkDesc *ch, uint64_t
 }
 
 void launch_batch_chunk_viol(const TraceDesc *d, const ChunkDesc *ch, uint64_t n_chunks, const uint32_t *vcnt,
-                             const uint64_t *vpos, hipStream_t s)
+                             const uint64_t *vpos, bool dense, hipStream_t s)
 {
     if (n_chunks) {
         ProfScope prof_(s, "batch_chunk_viol");
-        k_batch_chunk_viol<<<gridn(n_chunks, CH_WAVES), BLOCK, 0, s>>>(d, ch, n_chunks, vcnt, vpos);
+        k_batch_chunk_viol<<<gridn(n_chunks, CH_WAVES), BLOCK, 0, s>>>(d, ch, n_chunks, vcnt, vpos, dense);
     }
 }
 

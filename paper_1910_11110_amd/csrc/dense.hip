@@ -31,8 +31,9 @@ constexpr int D_PAIR = 2;
 struct TraceChunks {
     const uint32_t *ev;
     uint64_t n, per;
-    uint32_t n_ids, chunks;
-    static constexpr bool REPORT = true;
+    uint32_t n_ids, row, chunks;
+    __device__ OneChunk<TraceChunks> chunk(uint32_t c) const { return {*this, c}; }
+    __device__ Control *report_to(Control *ctl) const { return ctl; }
     __device__ uint32_t count() const { return chunks; }
     __device__ uint32_t id_bits() const { return 32u - (uint32_t)__builtin_clz(n_ids | 1u); }
     __device__ uint32_t local(uint32_t w) const { return w & 0xFFFFu; }
@@ -41,8 +42,8 @@ struct TraceChunks {
         const uint32_t x = w & 0xFFFFFFu;
         return x < n_ids ? x : n_ids - 1;
     }
-    __device__ uint64_t begin(uint32_t c) const { return (uint64_t)c * per; }
-    __device__ uint64_t end(uint32_t c) const
+    __device__ uint64_t begin_of(uint32_t c) const { return (uint64_t)c * per; }
+    __device__ uint64_t end_of(uint32_t c) const
     {
         const uint64_t e = (uint64_t)(c + 1) * per;
         return e < n ? e : n;
@@ -58,8 +59,9 @@ struct TileChunks {
     const uint32_t *ev;
     const uint64_t *tpos; // first word of every tile, their number at the end
     uint64_t n, tiles, per;
-    uint32_t n_ids, chunks;
-    static constexpr bool REPORT = true;
+    uint32_t n_ids, row, chunks;
+    __device__ OneChunk<TileChunks> chunk(uint32_t c) const { return {*this, c}; }
+    __device__ Control *report_to(Control *ctl) const { return ctl; }
     __device__ uint32_t count() const { return chunks; }
     __device__ uint32_t id_bits() const { return 32u - (uint32_t)__builtin_clz(n_ids | 1u); }
     __device__ uint32_t local(uint32_t w) const { return w & 0xFFFFu; }
@@ -73,8 +75,8 @@ struct TileChunks {
         const uint64_t p = tpos[tile < tiles ? tile : tiles];
         return p < n ? p : n; // (events that changed since the stream was sized)
     }
-    __device__ uint64_t begin(uint32_t c) const { return at((uint64_t)c * per); }
-    __device__ uint64_t end(uint32_t c) const { return at((uint64_t)(c + 1) * per); }
+    __device__ uint64_t begin_of(uint32_t c) const { return at((uint64_t)c * per); }
+    __device__ uint64_t end_of(uint32_t c) const { return at((uint64_t)(c + 1) * per); }
     __device__ bool bad(uint32_t w) const
     {
         return (w >> 28) != 0 || ((w >> 24) & 7u) > OP_PROBE || (w & 0xFFFFFFu) >= n_ids;
@@ -160,7 +162,7 @@ struct TraceOut {
             flagged = 0;
         }
     }
-    __device__ void chunk(uint32_t) const {}
+    __device__ void chunk(uint32_t, const uint32_t *) const {}
 };
 
 // a combined stream: the status bytes of the events, in their order; flagged induced
@@ -172,7 +174,7 @@ struct PrimaryOut {
     unsigned long long *induced;
     uint64_t next;
     uint32_t count;
-    __device__ void begin(const TileChunks &T, uint32_t c)
+    __device__ void begin(const OneChunk<TileChunks> &T, uint32_t c)
     {
         next = (uint64_t)c * T.per * tile;
         count = 0;
@@ -189,7 +191,7 @@ struct PrimaryOut {
         count += (uint32_t)__builtin_popcountll(__ballot(valid && op == OP_RWIND && (byte & 0x80u)));
     }
     __device__ void round(uint32_t, uint64_t, uint32_t, bool) const {}
-    __device__ void chunk(uint32_t lane) const
+    __device__ void chunk(uint32_t lane, const uint32_t *) const
     {
         if (lane == 0 && count)
             atomicAdd(induced, (unsigned long long)count);
@@ -199,14 +201,14 @@ struct PrimaryOut {
 // the statuses the probes see, at their positions
 struct ProbeOut {
     uint8_t *pre;
-    __device__ void begin(const TileChunks &, uint32_t) const {}
+    __device__ void begin(const OneChunk<TileChunks> &, uint32_t) const {}
     __device__ void step(uint32_t lane, uint32_t, uint64_t i, uint32_t w, uint32_t byte, bool valid) const
     {
         if (valid && ((w >> 24) & 7u) == OP_PROBE)
             pre[i + lane] = (uint8_t)((byte >> 2) & 3u);
     }
     __device__ void round(uint32_t, uint64_t, uint32_t, bool) const {}
-    __device__ void chunk(uint32_t) const {}
+    __device__ void chunk(uint32_t, const uint32_t *) const {}
 };
 
 // ascending indices of the flagged events, one wave per tile
@@ -350,7 +352,7 @@ Rows words_layout(Carve &c, uint64_t tiles, uint32_t n_ids, bool keep)
 TileChunks words_chunks(const DenseWords &W, const Rows &R)
 {
     const uint64_t per = tiles_per_chunk(W.tiles, W.n_ids);
-    return TileChunks{W.words, W.tpos, W.m, W.tiles, per, W.n_ids, W.m ? R.chunks : 0u};
+    return TileChunks{W.words, W.tpos, W.m, W.tiles, per, W.n_ids, R.row, W.m ? R.chunks : 0u};
 }
 
 } // namespace
@@ -363,7 +365,7 @@ void launch_dense_check(const uint32_t *events, uint64_t n, uint32_t n_ids, cons
     const TraceLayout L = trace_layout(scratch, n, n_ids);
     const FillJob job{L.xscan, excl_scan_scratch_bytes(L.tiles), 0};
     launch_prep(ctl, nullptr, &job, 1, s);
-    const TraceChunks T{events, n, L.per, n_ids, n ? L.R.chunks : 0u};
+    const TraceChunks T{events, n, L.per, n_ids, L.R.row, n ? L.R.chunks : 0u};
     launch_fold(T, L.R, ctl, s);
     launch_prefix(L.R, T.chunks, n_ids, init, final_out, s);
     if (!n)

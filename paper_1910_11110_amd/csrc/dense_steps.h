@@ -422,21 +422,35 @@ __device__ __forceinline__ void load_step_table(uint32_t *s_tab, uint32_t lane)
 }
 
 // ----------------------------------------------------------------------------------
-// The walks: one wave per chunk.  CHUNKS: the words (ev), the number of chunks, a chunk's
-// words [begin, end), malformed words, and the table's id of a word (local: of a
-// well-formed one; clamped: inside the table for any).
+// The walks: one wave per chunk.  CHUNKS: the number of chunks, and of a chunk its words
+// (ev + [begin, end)), its row (words of it, and where it lies), the bits of its ids,
+// malformed words, and the table's id of a word (local: of a well-formed one; clamped:
+// inside the table for any).  `table`: words of LDS for the table, a row of any chunk.
 // ----------------------------------------------------------------------------------
+// a chunk of a trace, or stream, whose chunks are all alike
+template <class CHUNKS>
+struct OneChunk : CHUNKS {
+    uint64_t begin, end, row_at;
+    uint32_t bits;
+    __device__ OneChunk(const CHUNKS &T, uint32_t c)
+        : CHUNKS(T), begin(T.begin_of(c)), end(T.end_of(c)), row_at((uint64_t)c * T.row), bits(T.id_bits())
+    {
+    }
+};
+
 // every chunk's functions into its row
 template <class D, int PAIR, class CHUNKS>
-__global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uint32_t *__restrict__ rows,
+__global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, uint32_t *__restrict__ rows,
                                                      Control *ctl)
 {
     extern __shared__ __align__(16) uint32_t s_t[];
-    uint32_t *const s_tab = s_t + row;
-    const uint32_t lane = threadIdx.x, bits = T.id_bits(), chunks = T.count();
+    uint32_t *const s_tab = s_t + table;
+    const uint32_t lane = threadIdx.x, chunks = T.count();
     load_step_table(s_tab, lane);
     for (uint32_t c = blockIdx.x; c < chunks; c += gridDim.x) {
-        const uint64_t i0 = T.begin(c), i1 = T.end(c);
+        const auto C = T.chunk(c);
+        const uint64_t i0 = C.begin, i1 = C.end;
+        const uint32_t row = C.row, bits = C.bits;
         const uint32_t len = (uint32_t)(i1 - i0), rounds = len / (D_UNROLL * WAVE);
         for (uint32_t i = lane; i < row / 4; i += WAVE)
             reinterpret_cast<uint4 *>(s_t)[i] = make_uint4(0, 0, 0, 0);
@@ -444,8 +458,8 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uin
         // (a malformed word is a Noop on id 0)
         auto clean = [&](uint32_t w, bool bad) { return bad ? D::NOOP : w; };
         auto report = [&](uint64_t i) {
-            if (CHUNKS::REPORT)
-                atomicMin(reinterpret_cast<unsigned long long *>(&ctl->err_index_lo), (unsigned long long)i);
+            if (Control *const to = C.report_to(ctl))
+                atomicMin(reinterpret_cast<unsigned long long *>(&to->err_index_lo), (unsigned long long)i);
         };
         uint32_t shared_steps = 0;
         // the events past the whole rounds, one step at a time
@@ -453,18 +467,18 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uin
             const uint32_t m = left < WAVE ? left : WAVE;
             const uint64_t i = i0 + rounds * (D_UNROLL * WAVE) + left - 1 - lane;
             const bool in = lane < m;
-            uint32_t w = in ? T.ev[i] : D::NOOP;
-            if (T.bad(w)) {
+            uint32_t w = in ? C.ev[i] : D::NOOP;
+            if (C.bad(w)) {
                 report(i);
                 w = clean(w, true);
             }
-            const Lane<Fold<D>> one[1] = {make_lane<Fold<D>>(s_t, s_tab, w, T.local(w), in)};
+            const Lane<Fold<D>> one[1] = {make_lane<Fold<D>>(s_t, s_tab, w, C.local(w), in)};
             uint32_t none[1];
             steps_together<Fold<D>, 1>(one, none, s_tab, bits, lane, shared_steps);
             left -= m;
         }
         // whole rounds: lane l takes the round's last event but l, then 64 before, ...
-        const uint32_t *const e0 = T.ev + i0 - 1 - lane;
+        const uint32_t *const e0 = C.ev + i0 - 1 - lane;
         uint32_t nxt[D_UNROLL];
         auto load = [&](uint32_t r) {
             const uint32_t *e = e0 + (uint64_t)r * (D_UNROLL * WAVE);
@@ -478,7 +492,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uin
             uint32_t w[D_UNROLL], badm = 0;
 #pragma unroll
             for (int u = 0; u < D_UNROLL; u++) {
-                const bool bad = T.bad(nxt[u]);
+                const bool bad = C.bad(nxt[u]);
                 badm |= bad ? 1u << u : 0u;
                 w[u] = clean(nxt[u], bad);
             }
@@ -503,9 +517,9 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uin
                     const int n = u + PAIR < D_UNROLL ? u + PAIR : u;
 #pragma unroll
                     for (int q = 0; q < PAIR; q++) {
-                        const uint32_t x = clean(v[q], T.bad(v[q]));
+                        const uint32_t x = clean(v[q], C.bad(v[q]));
                         v[q] = e[-((n + q) * WAVE)];
-                        L[q] = make_lane<Fold<D>>(s_t, s_tab, x, T.local(x), true);
+                        L[q] = make_lane<Fold<D>>(s_t, s_tab, x, C.local(x), true);
                     }
                     steps_together<Fold<D>, PAIR>(L, none, s_tab, bits, lane, shared_steps);
                 }
@@ -518,12 +532,12 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uin
                 uint32_t byte[PAIR];
 #pragma unroll
                 for (int q = 0; q < PAIR; q++)
-                    L[q] = make_lane<Fold<D>>(s_t, s_tab, w[u + q], T.local(w[u + q]), true);
+                    L[q] = make_lane<Fold<D>>(s_t, s_tab, w[u + q], C.local(w[u + q]), true);
                 steps<Fold<D>, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
             }
         }
         compiler_fence();
-        uint4 *out = reinterpret_cast<uint4 *>(rows + (uint64_t)c * row);
+        uint4 *out = reinterpret_cast<uint4 *>(rows + C.row_at);
         for (uint32_t i = lane; i < row / 4; i += WAVE)
             out[i] = reinterpret_cast<const uint4 *>(s_t)[i];
         compiler_fence();
@@ -534,20 +548,22 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t row, uin
 // step's (u: its number in its round or in the chunk's last, partial one), round() at the
 // end of each, chunk() at the chunk's.
 template <class D, int PAIR, class CHUNKS, class OUT>
-__global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, const uint32_t *__restrict__ rows, OUT out)
+__global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t table, const uint32_t *__restrict__ rows, OUT out)
 {
     extern __shared__ __align__(16) uint32_t s_t[];
-    uint32_t *const s_tab = s_t + row;
-    const uint32_t lane = threadIdx.x, bits = T.id_bits(), chunks = T.count();
+    uint32_t *const s_tab = s_t + table;
+    const uint32_t lane = threadIdx.x, chunks = T.count();
     load_step_table(s_tab, lane);
     for (uint32_t c = blockIdx.x; c < chunks; c += gridDim.x) {
-        const uint4 *in = reinterpret_cast<const uint4 *>(rows + (uint64_t)c * row);
-        const uint64_t i0 = T.begin(c), i1 = T.end(c);
+        const auto C = T.chunk(c);
+        const uint4 *in = reinterpret_cast<const uint4 *>(rows + C.row_at);
+        const uint64_t i0 = C.begin, i1 = C.end;
+        const uint32_t row = C.row, bits = C.bits;
         const uint32_t len = (uint32_t)(i1 - i0), rounds = len / (D_UNROLL * WAVE);
-        out.begin(T, c);
+        out.begin(C, c);
         uint32_t nxt[D_UNROLL];
         auto load = [&](uint32_t r) {
-            const uint32_t *e = T.ev + i0 + (uint64_t)r * (D_UNROLL * WAVE) + lane;
+            const uint32_t *e = C.ev + i0 + (uint64_t)r * (D_UNROLL * WAVE) + lane;
 #pragma unroll
             for (int u = 0; u < D_UNROLL; u++)
                 nxt[u] = e[u * WAVE];
@@ -558,7 +574,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, co
             reinterpret_cast<uint4 *>(s_t)[i] = in[i];
         compiler_fence();
         // (a malformed word, which was reported, only has to stay inside the table)
-        auto id_of = [&](uint32_t w) { return T.clamped(w); };
+        auto id_of = [&](uint32_t w) { return C.clamped(w); };
         uint32_t shared_steps = 0;
         for (uint32_t r = 0; r < rounds; r++) {
             uint32_t w[D_UNROLL];
@@ -583,7 +599,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, co
                     for (int q = 0; q < PAIR; q++) {
                         now[q] = v[q];
                         L[q] = make_lane<Apply<D>>(s_t, s_tab, v[q], id_of(v[q]), true);
-                        v[q] = T.ev[i + (n + q) * WAVE + lane];
+                        v[q] = C.ev[i + (n + q) * WAVE + lane];
                     }
                     steps_together<Apply<D>, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
 #pragma unroll
@@ -611,7 +627,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, co
         const uint32_t past = rounds * (D_UNROLL * WAVE);
         for (uint32_t k = past; k < len; k += WAVE) {
             const bool valid = k + lane < len;
-            const uint32_t w = valid ? T.ev[i0 + k + lane] : D::NOOP, id = id_of(w);
+            const uint32_t w = valid ? C.ev[i0 + k + lane] : D::NOOP, id = id_of(w);
             const Lane<Apply<D>> one[1] = {make_lane<Apply<D>>(s_t, s_tab, w, id, valid)};
             uint32_t b[1];
             steps_together<Apply<D>, 1>(one, b, s_tab, bits, lane, shared_steps);
@@ -619,7 +635,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t row, co
         }
         if (past < len)
             out.round(lane, i0 + past, (len - past + WAVE - 1) / WAVE, true);
-        out.chunk(lane);
+        out.chunk(lane, s_t);
         compiler_fence();
     }
 }

@@ -77,19 +77,21 @@ struct BucketChunks {
     const uint32_t *cbase, *cb;
     uint32_t nb, bits;
     uint64_t per;
-    static constexpr bool REPORT = false; // (the histogram did)
+    uint32_t row;
+    __device__ OneChunk<BucketChunks> chunk(uint32_t c) const { return {*this, c}; }
+    __device__ Control *report_to(Control *) const { return nullptr; } // (the histogram did)
     __device__ uint32_t count() const { return cbase[nb]; }
     __device__ uint32_t id_bits() const { return bits; }
     __device__ uint32_t local(uint32_t w) const { return w & ((1u << bits) - 1u); }
     __device__ uint32_t clamped(uint32_t w) const { return local(w); }
-    __device__ uint64_t begin(uint32_t c) const
+    __device__ uint64_t begin_of(uint32_t c) const
     {
         const uint32_t b = cb[c] & W_BUCKET;
         return base[b] + (uint64_t)(c - cbase[b]) * per;
     }
-    __device__ uint64_t end(uint32_t c) const
+    __device__ uint64_t end_of(uint32_t c) const
     {
-        const uint64_t e = begin(c) + per, last = base[(cb[c] & W_BUCKET) + 1];
+        const uint64_t e = begin_of(c) + per, last = base[(cb[c] & W_BUCKET) + 1];
         return e < last ? e : last;
     }
     __device__ bool bad(uint32_t) const { return false; } // (reported; its bits stay inside the table)
@@ -106,7 +108,7 @@ struct StatusOut {
             res[i + lane] = (R)st;
     }
     __device__ void round(uint32_t, uint64_t, uint32_t, bool) const {}
-    __device__ void chunk(uint32_t) const {}
+    __device__ void chunk(uint32_t, const uint32_t *) const {}
 };
 
 // bases of the buckets' events and chunks, and every chunk's bucket
@@ -269,7 +271,7 @@ static void wide_scan(const WideChunks &W, uint32_t row, const uint8_t *init, ui
 {
     const uint32_t most = wide_max_chunks(W.n, W.nb, W.per), groups = groups_of(most);
     uint32_t *rows = (uint32_t *)scratch, *grp = rows + (size_t)most * row;
-    const BucketChunks T{W.part, W.base, W.cbase, W.cb, W.nb, W.bits, W.per};
+    const BucketChunks T{W.part, W.base, W.cbase, W.cb, W.nb, W.bits, W.per, row};
     const dim3 pg((unsigned)ceil_div(row, BLOCK), groups);
     {
         ProfScope p(s, "wide_fold");

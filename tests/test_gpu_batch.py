@@ -354,3 +354,31 @@ def test_batch_bucket_route_autotuner(ctx, tmp_path):
             t.free()
     finally:
         del os.environ["VC_TUNE_CACHE"]
+
+
+@pytest.mark.parametrize("n_ids", [1, 64, 8192, 8193, 16385, 32769, 65536, 65537])
+def test_batch_row_sizes(ctx, n_ids):
+    """Traces with the largest and the smallest rows of every size of tables, empty, of one
+    event, around a chunk's events and of more chunks than one group, with initial statuses
+    and with arrays; past 65,536 ids the batch takes the other route.  Replayed twice."""
+    from paper_1910_11110_amd import vcheck as V
+    rng = np.random.default_rng(n_ids)
+    lens = [0, 1, 511, 512, 513, 4097, 40_000] + ([200_000] if n_ids <= 64 else [])
+    inputs = []
+    for i, n in enumerate(lens):
+        init = rng.integers(0, 4, n_ids).astype(np.uint8) if i % 2 else None
+        inputs.append((gen.plain_events(n, n_ids, 30 + i), n_ids, None, None, init))
+    k = min(n_ids, 3000)  # (the oracle compares all pairs of arrays)
+    for i, n in enumerate((0, 513, 20_000)):
+        lo, hi = gen.intervals(k, 40 + i)
+        inputs.append((gen.plain_events(n, k, 50 + i), k, lo, hi, None))
+    say(f"[batch] {len(inputs)} traces over {n_ids} ids")
+    traces = load_all(ctx, inputs)
+    refs = [oracle_of(*inp) for inp in inputs]
+    for turn in range(3):
+        V.batch_check(ctx, traces)
+        ctx.sync()
+        for i, (t, ref) in enumerate(zip(traces, refs)):
+            assert_trace(t, ref, f"trace {i}, turn {turn}")
+    for t in traces:
+        t.free()
