@@ -5,21 +5,10 @@
 #include <algorithm>
 
 #include "abi_internal.h"
+#include "declared.h"
 #include "internal.h"
 
 using namespace vc;
-
-namespace vc {
-void launch_wd_decls(const uint64_t *comp_off, uint64_t n_comp, const uint32_t *decls, uint64_t n_decl,
-                     uint32_t n_vars, const uint32_t *lo, const uint32_t *hi, bool extend, uint32_t *wlen, Control *ctl,
-                     hipStream_t s);
-void launch_wd_body(const uint64_t *comp_off, uint64_t n_comp, const uint32_t *decls, const uint64_t *body_off,
-                    const uint32_t *body, uint64_t n_body, const uint32_t *idx, uint32_t n_vars, const uint32_t *lo,
-                    const uint32_t *hi, const OverlapSets *o, bool extend, const uint64_t *boff, uint32_t *bits,
-                    uint64_t nbits, uint32_t *verdict, Control *ctl, hipStream_t s);
-void launch_wd_finish(const uint64_t *comp_off, uint64_t n_comp, const uint32_t *wlen, const uint64_t *boff,
-                      const uint32_t *bits, uint64_t nbits, const uint32_t *verdict, uint8_t *out, hipStream_t s);
-} // namespace vc
 
 struct DeclaredState {
     uint64_t n_comp = 0, n_decl = 0, n_body = 0, nbits = 0;
@@ -29,7 +18,12 @@ struct DeclaredState {
     uint32_t *decls = nullptr, *body = nullptr, *idx = nullptr;
     uint32_t *lo = nullptr, *hi = nullptr;
     OverlapSets sets{};
-    DevBuf verdict, wlen, boff, bits, scan;
+    DevBuf verdict, wlen, boff, bits, scan, big;
+    WdProgram program() const
+    {
+        return WdProgram{comp_off, body_off, decls, body, idx, lo, hi, lo ? &sets : nullptr,
+                         n_comp, n_decl, n_body, n_vars, extend};
+    }
 };
 
 namespace {
@@ -47,8 +41,7 @@ int to_device(T **dst, const T *src, uint64_t n)
 void enqueue_lengths(vc_trace *t, hipStream_t s)
 {
     DeclaredState &w = *t->wd;
-    launch_wd_decls(w.comp_off, w.n_comp, w.decls, w.n_decl, w.n_vars, w.lo, w.hi, w.extend, (uint32_t *)w.wlen.p,
-                    t->ctl, s);
+    launch_wd_decls(w.program(), (uint32_t *)w.wlen.p, t->ctl, s);
     launch_excl_scan((const uint32_t *)w.wlen.p, w.n_decl, (uint64_t *)w.boff.p, nullptr, w.scan.p, t->ctl->tickets[5],
                      s);
 }
@@ -59,14 +52,8 @@ int declared_enqueue(vc_trace *t, hipStream_t s)
 {
     DeclaredState &w = *t->wd;
     launch_reset_control(t->ctl, s);
-    enqueue_lengths(t, s);
-    launch_fill_u32((uint32_t *)w.verdict.p, 0, w.n_comp ? w.n_comp : 1, s);
-    launch_fill_u32((uint32_t *)w.bits.p, 0, w.nbits / 32 + 1, s);
-    launch_wd_body(w.comp_off, w.n_comp, w.decls, w.body_off, w.body, w.n_body, w.idx, w.n_vars, w.lo, w.hi,
-                   w.lo ? &w.sets : nullptr, w.extend, (const uint64_t *)w.boff.p, (uint32_t *)w.bits.p, w.nbits,
-                   (uint32_t *)w.verdict.p, t->ctl, s);
-    launch_wd_finish(w.comp_off, w.n_comp, (const uint32_t *)w.wlen.p, (const uint64_t *)w.boff.p,
-                     (const uint32_t *)w.bits.p, w.nbits, (const uint32_t *)w.verdict.p, (uint8_t *)t->status.p, s);
+    launch_wd_check(w.program(), (uint32_t *)w.big.p, (uint32_t *)w.wlen.p, (uint64_t *)w.boff.p, (uint32_t *)w.bits.p,
+                    w.nbits, (uint32_t *)w.verdict.p, (uint8_t *)t->status.p, t->ctl, s);
     launch_compact((uint8_t *)t->status.p, w.n_comp, (uint32_t *)t->viol.p, t->scratch.p, t->ctl, s);
     return VC_OK;
 }
@@ -97,6 +84,7 @@ void declared_release(vc_trace *t)
     devbuf_free(w.boff);
     devbuf_free(w.bits);
     devbuf_free(w.scan);
+    devbuf_free(w.big);
     delete t->wd;
     t->wd = nullptr;
 }
@@ -200,6 +188,7 @@ extern "C" int vc_check_declared(vc_ctx *c, const uint64_t *comp_off, uint64_t n
         ((r = devbuf_reserve(w.verdict, (n_comp ? n_comp : 1) * 4)) != VC_OK ||
          (r = devbuf_reserve(w.wlen, (n_decl ? n_decl : 1) * 4)) != VC_OK ||
          (r = devbuf_reserve(w.boff, (n_decl + 1) * 8)) != VC_OK ||
+         (r = devbuf_reserve(w.big, (wd_tiles(n_comp) + 1) * 4)) != VC_OK ||
          (r = devbuf_reserve(w.scan, excl_scan_scratch_bytes(n_decl))) != VC_OK ||
          (r = devbuf_reserve(t->status, n_comp ? n_comp : 1)) != VC_OK ||
          (r = devbuf_reserve(t->fin, 1)) != VC_OK ||
@@ -218,10 +207,12 @@ extern "C" int vc_check_declared(vc_ctx *c, const uint64_t *comp_off, uint64_t n
             r = vc_hip_fail(e, "sizing of the coverage bits");
         } else {
             const uint64_t key = ((uint64_t)h.err_index_hi << 32) | h.err_index_lo;
+            // (a tile's bits start at a word)
+            w.nbits = (w.nbits + 31 + 32 * wd_tiles(n_comp)) & ~(uint64_t)31;
             if (key != ~0ull && !dev)
                 r = declared_error(key);
             else
-                r = devbuf_reserve(w.bits, (w.nbits / 32 + 1) * 4);
+                r = devbuf_reserve(w.bits, w.nbits / 8);
         }
     }
     if (r != VC_OK) {

@@ -130,3 +130,14 @@ def test_declared_wide_components(ctx, kmax):
         p = gen.declared_program(6_001, 2000, 7 + kmax, arrays=arrays, space=1 << 14, max_len=32, kmax=kmax,
                                  p_err=0.1)
         assert_parity(ctx, p, extend, label=f"kmax {kmax} arrays {arrays} extend {extend}")
+
+
+@pytest.mark.parametrize("n_comp,max_len,kmax,extend", [(7, 64, 4, False), (64, 300, 8, True), (65, 300, 8, False),
+                                                        (1_000, 2048, 4, False), (1_000, 2048, 4, True),
+                                                        (300, 9_000, 2, True), (33_000, 200, 12, False)])
+def test_declared_tile_limits(ctx, n_comp, max_len, kmax, extend):
+    """Tiles around the limits of what a wave holds: few components, more elements or more
+    declarations than fit in some of the tiles or in all."""
+    p = gen.declared_program(n_comp, 400, n_comp + max_len, arrays=True, space=1 << 18, max_len=max_len, kmax=kmax,
+                             p_err=0.2)
+    assert_parity(ctx, p, extend, label=f"{n_comp} components, arrays of up to {max_len}")
