@@ -227,7 +227,7 @@ void launch_batch_dense(const DenseBatch &B, hipStream_t s)
     for (int k = 0; k < DENSE_CLASSES; k++)
         if (const BatchChunks T = chunks_of(k); T.chunks) {
             ProfScope p(s, "batch_apply");
-            k_dense_apply<Two, B_PAIR, BatchChunks, BatchOut><<<T.chunks, WAVE, table_lds(DENSE_CLASS[k]), s>>>(
+            k_dense_apply<Apply<Two>, B_PAIR, BatchChunks, BatchOut><<<T.chunks, WAVE, table_lds(DENSE_CLASS[k]), s>>>(
                 T, DENSE_CLASS[k], B.rows, BatchOut{B.vcnt, nullptr, nullptr, 0, 0, 0, 0, false, false, 0, 0, 0, 0});
         }
 }

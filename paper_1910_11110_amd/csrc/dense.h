@@ -19,11 +19,12 @@ void launch_dense_check(const uint32_t *events, uint64_t n, uint32_t n_ids, cons
 
 // A combined stream as 32-bit words (an event's, then its induced items', op 5; probes,
 // which change nothing, DENSE_OP_PROBE), by tiles of `tile` events: tile t's words start at
-// tpos[t] (device, tiles + 1 entries), m words in all.  The fold resets ctl and reports
-// malformed words; then, with probes, the statuses the probes see from `init` (pre, m
-// bytes, at their positions); then, from another `init`, the events' status bytes in
-// their order, all final statuses and the number of flagged induced items
-// (ctl->n_induced_stuck).
+// tpos[t] (device, tiles + 1 entries), m words in all.  Every chunk's functions first: by
+// the fold, which resets ctl and reports malformed words, or (well-formed words only) with
+// the functions that the probes see (pre, m bytes, at their positions: 3 bits, as in the
+// table) and the statuses from `init` entering every chunk.  Then, from an `init` again, the
+// events' status bytes in their order, all final statuses and the number of flagged induced
+// items (ctl->n_induced_stuck).
 constexpr uint32_t DENSE_OP_PROBE = 6;
 struct DenseWords {
     const uint32_t *words;
@@ -33,9 +34,21 @@ struct DenseWords {
     uint32_t n_ids;
 };
 size_t dense_words_scratch_bytes(uint64_t tiles, uint32_t n_ids, bool probes);
-void launch_dense_words_fold(const DenseWords &W, bool probes, void *scratch, Control *ctl, hipStream_t s);
-void launch_dense_words_probe(const DenseWords &W, const uint8_t *init, uint8_t *pre, void *scratch, hipStream_t s);
+void launch_dense_words_fold(const DenseWords &W, void *scratch, Control *ctl, hipStream_t s);
+struct DenseEntering { // chunk c's statuses at rows[c * row], 8 ids a word; the words of tiles [c * per, ...)
+    const uint32_t *rows;
+    uint32_t row;
+    uint64_t per;
+};
+DenseEntering launch_dense_words_probe(const DenseWords &W, const uint8_t *init, uint8_t *pre, void *scratch,
+                                       Control *ctl, hipStream_t s);
 void launch_dense_words_apply(const DenseWords &W, bool probes, const uint8_t *init, uint64_t n, uint32_t tile,
                               uint8_t *status, uint8_t *final_out, void *scratch, Control *ctl, hipStream_t s);
+
+// initial statuses of the check of a dynamic trace from the functions that the probes see:
+// a create's probe lies after it (pos32[create] + 1 of m words)
+void launch_dyn_inherit_dense(const uint32_t *mother, const uint32_t *cpos, const uint8_t *pre, const uint32_t *pos32,
+                              uint64_t n, uint64_t m, const DenseEntering &E, const uint8_t *init, uint32_t n_ids,
+                              uint8_t *init2, hipStream_t s);
 
 } // namespace vc

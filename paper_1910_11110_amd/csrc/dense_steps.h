@@ -52,6 +52,7 @@ constexpr uint32_t host_compose(uint32_t h, uint32_t f)
 }
 struct StepTable {
     uint32_t fold[16];  // (h o f) << 3h, the element in bits 24-26
+    uint32_t onto[16];  // (f o h) << 3h
     uint32_t apply[16]; // status byte << 8s
 };
 constexpr StepTable make_step_table()
@@ -67,7 +68,7 @@ constexpr StepTable make_step_table()
         else if (op == OP_PULL)
             e = side ? 2u : 1u;
         for (uint32_t h = 0; h < 8; h++)
-            t.fold[i] |= host_compose(h, e) << (3 * h);
+            t.fold[i] |= host_compose(h, e) << (3 * h), t.onto[i] |= host_compose(e, h) << (3 * h);
         t.fold[i] |= e << 24;
         const Effect x = make_effect(op <= OP_RWIND ? op : (uint32_t)OP_NOOP, side);
         for (uint32_t s = 0; s < 4; s++) {
@@ -124,6 +125,8 @@ struct Two {
     __device__ static bool fold_part(uint32_t e) { return (e >> 24) != 0; }
     __device__ static uint32_t fold_next(uint32_t e, uint32_t h) { return (e >> (3u * h)) & 7u; }
     __device__ static bool fold_open(uint32_t h) { return (h & 4u) == 0; }
+    __device__ static uint32_t onto_next(uint32_t e, uint32_t h) { return (e >> (3u * h)) & 7u; }
+    __device__ static uint32_t onto_all(uint32_t f, uint32_t h) { return el_compose(el_of(f), h); }
     __device__ static uint32_t apply_entry(const uint32_t *tab, uint32_t w) { return tab[16 + ((w >> 24) & 15u)]; }
     __device__ static uint32_t apply_next(uint32_t e, uint32_t h, uint32_t &byte)
     {
@@ -227,6 +230,7 @@ struct Fold {
     __device__ static bool takes_part(uint32_t e) { return D::fold_part(e); }
     __device__ static bool open(uint32_t h) { return D::fold_open(h); }
     __device__ static uint32_t next(uint32_t e, uint32_t h, uint32_t &) { return D::fold_next(e, h); }
+    __device__ static uint32_t first_table(uint32_t i) { return STEPS.fold[i]; }
 };
 template <class D>
 struct Apply {
@@ -236,6 +240,27 @@ struct Apply {
     __device__ static bool takes_part(uint32_t) { return true; }
     __device__ static bool open(uint32_t) { return true; }
     __device__ static uint32_t next(uint32_t e, uint32_t h, uint32_t &result) { return D::apply_next(e, h, result); }
+    // the status after the functions before the event
+    __device__ static uint32_t after(uint32_t f, uint32_t h) { return D::status_after(f, h); }
+    static constexpr bool FUNCTIONS = false;
+    __device__ static uint32_t first_table(uint32_t i) { return STEPS.fold[i]; }
+};
+// every id's function composed forwards; an event's result is the one before it
+template <class D>
+struct Onto {
+    static constexpr bool BACK = false;
+    using Dom = D;
+    __device__ static uint32_t entry(const uint32_t *tab, uint32_t w) { return D::fold_entry(tab, w); }
+    __device__ static bool takes_part(uint32_t) { return true; }
+    __device__ static bool open(uint32_t) { return true; }
+    __device__ static uint32_t next(uint32_t e, uint32_t h, uint32_t &result)
+    {
+        result = h;
+        return D::onto_next(e, h);
+    }
+    __device__ static uint32_t after(uint32_t f, uint32_t h) { return D::onto_all(f, h); }
+    static constexpr bool FUNCTIONS = true;
+    __device__ static uint32_t first_table(uint32_t i) { return STEPS.onto[i]; } // (in the fold's place)
 };
 
 template <class DIR>
@@ -349,7 +374,7 @@ __device__ __forceinline__ void steps_together(const Lane<DIR> (&L)[Q], uint32_t
         if constexpr (DIR::BACK)
             nh = D::fold_all(h, f[q]);
         else
-            nh = DIR::next(L[q].entry, prev[q] < 64 ? D::status_after(g[q], h) : h, result[q]);
+            nh = DIR::next(L[q].entry, prev[q] < 64 ? DIR::after(g[q], h) : h, result[q]);
         if (last[q])
             tab_xor(L[q].p, L[q].change(h, nh));
         compiler_fence();
@@ -414,10 +439,11 @@ constexpr int D_UNROLL = 8; // steps whose events are loaded together
 // a round whose last one worked out at least so many of its steps together does so for all
 constexpr uint32_t D_TOGETHER = D_UNROLL / 2;
 
+template <class DIR>
 __device__ __forceinline__ void load_step_table(uint32_t *s_tab, uint32_t lane)
 {
     if (lane < 32)
-        s_tab[lane] = lane < 16 ? STEPS.fold[lane] : STEPS.apply[lane - 16];
+        s_tab[lane] = lane < 16 ? DIR::first_table(lane) : STEPS.apply[lane - 16];
     compiler_fence();
 }
 
@@ -446,7 +472,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
     extern __shared__ __align__(16) uint32_t s_t[];
     uint32_t *const s_tab = s_t + table;
     const uint32_t lane = threadIdx.x, chunks = T.count();
-    load_step_table(s_tab, lane);
+    load_step_table<Fold<D>>(s_tab, lane);
     for (uint32_t c = blockIdx.x; c < chunks; c += gridDim.x) {
         const auto C = T.chunk(c);
         const uint64_t i0 = C.begin, i1 = C.end;
@@ -544,19 +570,22 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
     }
 }
 
-// The events' results from their chunk's entering statuses.  OUT takes them: step() a
+// The events' results from their chunk's entering statuses (Apply), or every chunk's
+// functions into its row, the events' results the functions before them (Onto).  OUT takes
+// the results: step() a
 // step's (u: its number in its round or in the chunk's last, partial one), round() at the
 // end of each, chunk() at the chunk's.
-template <class D, int PAIR, class CHUNKS, class OUT>
-__global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t table, const uint32_t *__restrict__ rows, OUT out)
+template <class DIR, int PAIR, class CHUNKS, class OUT>
+__global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t table, uint32_t *__restrict__ rows, OUT out)
 {
+    using D = typename DIR::Dom;
     extern __shared__ __align__(16) uint32_t s_t[];
     uint32_t *const s_tab = s_t + table;
     const uint32_t lane = threadIdx.x, chunks = T.count();
-    load_step_table(s_tab, lane);
+    load_step_table<DIR>(s_tab, lane);
     for (uint32_t c = blockIdx.x; c < chunks; c += gridDim.x) {
         const auto C = T.chunk(c);
-        const uint4 *in = reinterpret_cast<const uint4 *>(rows + C.row_at);
+        uint4 *const chunk_row = reinterpret_cast<uint4 *>(rows + C.row_at);
         const uint64_t i0 = C.begin, i1 = C.end;
         const uint32_t row = C.row, bits = C.bits;
         const uint32_t len = (uint32_t)(i1 - i0), rounds = len / (D_UNROLL * WAVE);
@@ -571,7 +600,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t table, 
         if (rounds)
             load(0);
         for (uint32_t i = lane; i < row / 4; i += WAVE)
-            reinterpret_cast<uint4 *>(s_t)[i] = in[i];
+            reinterpret_cast<uint4 *>(s_t)[i] = DIR::FUNCTIONS ? make_uint4(0, 0, 0, 0) : chunk_row[i];
         compiler_fence();
         // (a malformed word, which was reported, only has to stay inside the table)
         auto id_of = [&](uint32_t w) { return C.clamped(w); };
@@ -592,16 +621,16 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t table, 
                     v[q] = w[q];
 #pragma unroll 1
                 for (int u = 0; u < D_UNROLL; u += PAIR) {
-                    Lane<Apply<D>> L[PAIR];
+                    Lane<DIR> L[PAIR];
                     uint32_t byte[PAIR], now[PAIR];
                     const int n = u + PAIR < D_UNROLL ? u + PAIR : u;
 #pragma unroll
                     for (int q = 0; q < PAIR; q++) {
                         now[q] = v[q];
-                        L[q] = make_lane<Apply<D>>(s_t, s_tab, v[q], id_of(v[q]), true);
+                        L[q] = make_lane<DIR>(s_t, s_tab, v[q], id_of(v[q]), true);
                         v[q] = C.ev[i + (n + q) * WAVE + lane];
                     }
-                    steps_together<Apply<D>, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
+                    steps_together<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
 #pragma unroll
                     for (int q = 0; q < PAIR; q++)
                         out.step(lane, u + q, i + (u + q) * WAVE, now[q], byte[q], true);
@@ -610,12 +639,12 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t table, 
                 shared_steps = 0;
 #pragma unroll
                 for (int u = 0; u < D_UNROLL; u += PAIR) {
-                    Lane<Apply<D>> L[PAIR];
+                    Lane<DIR> L[PAIR];
                     uint32_t byte[PAIR];
 #pragma unroll
                     for (int q = 0; q < PAIR; q++)
-                        L[q] = make_lane<Apply<D>>(s_t, s_tab, w[u + q], id_of(w[u + q]), true);
-                    steps<Apply<D>, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
+                        L[q] = make_lane<DIR>(s_t, s_tab, w[u + q], id_of(w[u + q]), true);
+                    steps<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
 #pragma unroll
                     for (int q = 0; q < PAIR; q++)
                         out.step(lane, u + q, i + (u + q) * WAVE, w[u + q], byte[q], true);
@@ -628,14 +657,18 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t table, 
         for (uint32_t k = past; k < len; k += WAVE) {
             const bool valid = k + lane < len;
             const uint32_t w = valid ? C.ev[i0 + k + lane] : D::NOOP, id = id_of(w);
-            const Lane<Apply<D>> one[1] = {make_lane<Apply<D>>(s_t, s_tab, w, id, valid)};
+            const Lane<DIR> one[1] = {make_lane<DIR>(s_t, s_tab, w, id, valid)};
             uint32_t b[1];
-            steps_together<Apply<D>, 1>(one, b, s_tab, bits, lane, shared_steps);
+            steps_together<DIR, 1>(one, b, s_tab, bits, lane, shared_steps);
             out.step(lane, (k - past) / WAVE, i0 + k, w, b[0], valid);
         }
         if (past < len)
             out.round(lane, i0 + past, (len - past + WAVE - 1) / WAVE, true);
         out.chunk(lane, s_t);
+        compiler_fence();
+        if (DIR::FUNCTIONS)
+            for (uint32_t i = lane; i < row / 4; i += WAVE)
+                chunk_row[i] = reinterpret_cast<const uint4 *>(s_t)[i];
         compiler_fence();
     }
 }

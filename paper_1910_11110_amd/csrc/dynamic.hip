@@ -14,7 +14,9 @@
 // segmented scan twice on the same sorted items: first for the statuses before
 // "probe" items placed on the mother's segment at every creation (the inherited
 // statuses), then, with those as the created arrays' initial statuses, for every
-// status byte and the final table.
+// status byte and the final table.  (The dense check finds the functions that the probes
+// see while it composes its chunks', and needs no first scan.)
+#include "dense.h"
 #include "device.h"
 #include "internal.h"
 #include "prof.h"
@@ -37,13 +39,6 @@ __device__ __forceinline__ bool word_ok(uint32_t e, uint32_t n_ids)
 {
     const uint32_t op = (e >> 24) & 7u;
     return (e >> 28) == 0 && op != OP_RWIND && (e & 0xFFFFFFu) < n_ids && (op < OP_CREATE || ((e >> 27) & 1u) == 0);
-}
-
-// x is live at t: created before t (or live from the start) and not yet destroyed
-__device__ __forceinline__ bool live_at(const uint32_t *cpos, const uint32_t *dpos, uint32_t x, uint64_t t)
-{
-    const uint32_t c = cpos[x], d = dpos[x];
-    return (c == NO_POS || c < t) && (d == NO_POS || t < d);
 }
 
 __global__ void k_dyn_clear(uint32_t *cpos, uint32_t *dpos, uint32_t n_ids)
@@ -70,219 +65,385 @@ __global__ void k_dyn_life(const uint32_t *__restrict__ ev, uint64_t n, uint32_t
     }
 }
 
-// lifetime of every neighbour entry of the overlap CSR: (create, destroy) position of
-// nbr[j], so that the candidates of a write read their neighbours' lifetimes in order
-// instead of gathering them
-__global__ void k_dyn_nbr_life(const uint32_t *__restrict__ nbr, uint64_t n_nbr, const uint32_t *__restrict__ cpos,
-                               const uint32_t *__restrict__ dpos, uint2 *__restrict__ life)
+// a lifetime as it is asked: live at t when x <= t < y
+__device__ __forceinline__ bool life_holds(uint2 lf, uint64_t t)
+{
+    return lf.x <= (uint32_t)t && (uint32_t)t < lf.y; // (t < 2^30)
+}
+
+// lifetimes of every entry of the overlap CSR, so that the neighbours of a write read
+// theirs in order instead of gathering them, and then of every array
+__global__ void k_dyn_nbr_life(const uint32_t *__restrict__ nbr, uint64_t n_nbr, uint32_t n_ids,
+                               const uint32_t *__restrict__ cpos, const uint32_t *__restrict__ dpos,
+                               uint2 *__restrict__ life)
 {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n_nbr; j += stride) {
-        const uint32_t y = nbr[j];
-        life[j] = make_uint2(cpos[y], dpos[y]);
+    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n_nbr + n_ids; j += stride) {
+        const uint32_t y = j < n_nbr ? nbr[j] : (uint32_t)(j - n_nbr);
+        const uint32_t c = cpos[y];
+        life[j] = make_uint2(c == NO_POS ? 0u : c + 1, dpos[y]);
     }
 }
 
-// The combined items by wave tiles of DTILE events.  Each event has a run of candidate
-// items: itself, a probe on its mother (a partial vector's create) and, at a write, one
-// candidate per neighbour of its array; a neighbour's candidate becomes an induced RW
-// item when the neighbour is live at the write.  The candidates of a tile are walked
-// 64 consecutive ones at a time (the lane of a candidate finds its event from a ballot
-// of the event starts among the 64; four such steps find their events before their
-// loads are issued together), and the items kept are compacted in order by a ballot.  The count pass gives every tile its number of items; the emit pass, with
-// the tiles' scanned positions, writes them.
+// The combined items by wave tiles of DTILE events: each event, a probe on its mother (a
+// partial vector's create) and, at a write, an induced RW item on every neighbour of its
+// array that is live at the write.  One pass: a tile's events are checked and their
+// writes' live neighbours found and counted (kept as bits where they fit), the workgroup's
+// tiles take their place by a look-back over the workgroups' totals, and the items are
+// written.  A write's neighbours are looked at after the tile's events: of a write with at
+// most D_SMALL by one lane, 64 writes together, of one with more by the whole wave, 64
+// neighbours a step and several steps' loads issued together.
+// Bound by the requests of its gathers and scattered stores and, at 45% of their time, by
+// the vector instructions (occupancy and loads in flight change little).  2^23 events over
+// 1,024 vectors and 64,512 partial vectors (50 M neighbours of writes, 25 M of them live):
+// a count pass and an emit pass over 64 consecutive neighbours at a time, with a search for
+// the event of each, took 200 and 266 us, and 10 for the scan between them; this pass 310,
+// or 115 when it only counts.
 constexpr int D_PER = 8;                   // events per lane
 constexpr uint32_t DTILE = WAVE * D_PER;   // events per wave tile
 constexpr uint32_t DWAVES = BLOCK / WAVE;
-constexpr int DWALK_U = 4;                 // steps of 64 candidates whose loads are issued together
+constexpr uint32_t D_SMALL = 24;           // neighbours one lane looks at
+constexpr int D_AHEAD = 4;                 // neighbours a lane looks at together
+constexpr int D_WAHEAD = 8;                // writes the wave looks at together
 
-// an event's candidate run and its checks: malformed words and liveness errors are
-// reported at their index (the smallest one is the first error of a sequential
-// reading) and keep only the event itself (a malformed word as a no-op on array 0)
-__device__ __forceinline__ uint32_t dyn_event(uint32_t e, uint64_t t, uint32_t n_ids, const uint32_t *mother,
-                                              const uint32_t *cpos, const uint32_t *dpos, const uint64_t *off,
-                                              bool report, Control *ctl, uint32_t &w, uint64_t &o)
+struct __attribute__((packed, aligned(8))) Bounds { // two entries of the neighbours' offsets
+    uint64_t begin, end;
+};
+
+// a wave tile: its events' words (D_PROBE: a probe follows), their items (later
+// where these start), and its writes with neighbours (from the front of `list` those with
+// few, from its back the others) with their number and the bits of the live ones
+constexpr uint32_t D_PROBE = 1u << 30;
+struct DynTile {
+    uint32_t word[DTILE], items[DTILE];
+    uint32_t deg[DTILE]; // of a write with few: the bits above 8 the live ones
+    uint16_t list[DTILE];
+};
+static_assert(D_SMALL <= 24, "a count and a bit each in a word");
+
+__device__ __forceinline__ void wave_lds_fence() { asm volatile("" ::: "memory"); } // (a wave's LDS operations are in order)
+__device__ __forceinline__ uint32_t lane32(uint32_t v, int l)
 {
-    const uint32_t op = (e >> 24) & 7u, x = e & 0xFFFFFFu;
-    w = e;
-    o = 0;
-    if (!word_ok(e, n_ids)) {
-        if (report)
-            report_bad(ctl, t);
-        w = (uint32_t)OP_NOOP << 24;
-        return 1;
-    }
-    bool bad;
-    uint32_t len = 1;
-    if (op == OP_CREATE) {
-        const uint32_t m = mother[x];
-        bad = cpos[x] != (uint32_t)t || (m != NO_MOTHER && !live_at(cpos, dpos, m, t));
-        len += m != NO_MOTHER ? 1u : 0u;
-    } else if (op == OP_DESTROY) {
-        bad = dpos[x] != (uint32_t)t || !(cpos[x] == NO_POS || cpos[x] < t);
-    } else {
-        bad = !live_at(cpos, dpos, x, t);
-        if (!bad && op == OP_W) {
-            o = off[x];
-            len += (uint32_t)(off[x + 1] - o);
-        }
-    }
-    if (bad) {
-        if (report)
-            report_bad(ctl, t);
-        return 1;
-    }
-    return len;
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+__device__ __forceinline__ uint64_t lane64(uint32_t lo, uint32_t hi, int l)
+{
+    return ((uint64_t)lane32(hi, l) << 32) | lane32(lo, l);
 }
 
-// MODE D_COUNT: tcnt[tile] = the tile's items.  D_ITEMS: 64-bit sort items at tpos[tile]
-// on (cap items; probes carry payload n + t, induced items INDUCED_BIT).  D_WORDS: the
-// same items as 32-bit words for the bucket engine (a create, a destroy and a probe are
-// no-ops on their array, induced items op 5), and pos32[t] = event t's position.
-enum { D_COUNT = 0, D_ITEMS = 1, D_WORDS = 2 };
+// 64 writes with more than D_SMALL neighbours, one a lane: the event, where its neighbours
+// start and their number, and the bits of the first 128 live ones
+struct Writes {
+    uint32_t k, deg, count;
+    uint32_t o_lo, o_hi, live[4];
+    __device__ __forceinline__ void take(const DynTile &T, uint32_t i0, uint32_t many, const uint64_t *__restrict__ off,
+                                         uint32_t lane)
+    {
+        k = T.list[DTILE - 1 - (i0 + lane < many ? i0 + lane : many - 1)];
+        deg = T.deg[k];
+        const uint64_t o = off[T.word[k] & 0xFFFFFFu];
+        o_lo = (uint32_t)o;
+        o_hi = (uint32_t)(o >> 32);
+        count = 0;
+    }
+    __device__ __forceinline__ uint64_t first(int l) const { return lane64(o_lo, o_hi, l); }
+    __device__ __forceinline__ uint64_t bits(int l, int h) const { return lane64(live[2 * h], live[2 * h + 1], l); }
+    // the live neighbours of the first cnt writes: their number and bits
+    __device__ __forceinline__ void look(uint32_t cnt, uint64_t t0, const uint2 *__restrict__ life, uint32_t lane)
+    {
+        for (uint32_t i = 0; i < cnt; i += D_WAHEAD) {
+            uint32_t d[D_WAHEAD];
+            uint2 v[D_WAHEAD][2];
+#pragma unroll
+            for (int u = 0; u < D_WAHEAD; u++) {
+                const int l = (int)(i + u < cnt ? i + u : cnt - 1);
+                d[u] = lane32(deg, l);
+                const uint2 *p = life + first(l);
+                v[u][0] = v[u][1] = make_uint2(~0u, 0);
+                if (lane < d[u])
+                    v[u][0] = p[lane];
+                if (lane + WAVE < d[u])
+                    v[u][1] = p[lane + WAVE];
+            }
+#pragma unroll
+            for (int u = 0; u < D_WAHEAD; u++) {
+                const int l = (int)(i + u < cnt ? i + u : cnt - 1);
+                const uint64_t t = t0 + lane32(k, l);
+                const uint64_t a = __ballot(life_holds(v[u][0], t)), b = __ballot(life_holds(v[u][1], t));
+                uint32_t c = (uint32_t)__builtin_popcountll(a) + (uint32_t)__builtin_popcountll(b);
+                for (uint32_t q = 2 * WAVE; q < d[u]; q += WAVE) // uniform, and rare
+                    c += (uint32_t)__builtin_popcountll(__ballot(
+                        q + lane < d[u] && life_holds(life[first(l) + (q + lane < d[u] ? q + lane : 0)], t)));
+                const bool me = lane == (uint32_t)l;
+                count = me ? c : count;
+                live[0] = me ? (uint32_t)a : live[0];
+                live[1] = me ? (uint32_t)(a >> 32) : live[1];
+                live[2] = me ? (uint32_t)b : live[2];
+                live[3] = me ? (uint32_t)(b >> 32) : live[3];
+            }
+        }
+    }
+};
+
+// MODE: D_COUNT adds the number of items to ctl->n_out.  D_ITEMS: 64-bit sort items from
+// tpos[tile] on (cap at most; probes carry payload n + t, induced items INDUCED_BIT).
+// D_WORDS: 32-bit words for the bucket engine (a create, a destroy and a probe are no-ops
+// on their array, induced items op 5) and every event's position (pos32).  D_DENSE: words
+// for the dense check, probes of their own op, and the creates' positions.
+enum { D_COUNT, D_ITEMS, D_WORDS, D_DENSE };
 template <int MODE>
 __global__ __launch_bounds__(BLOCK) void k_dyn_tiles(const uint32_t *__restrict__ ev, uint64_t n, uint32_t n_ids,
                                                      const uint32_t *__restrict__ mother,
-                                                     const uint32_t *__restrict__ cpos,
-                                                     const uint32_t *__restrict__ dpos,
                                                      const uint64_t *__restrict__ off,
-                                                     const uint32_t *__restrict__ nbr,
-                                                     const uint2 *__restrict__ life, uint64_t ntiles,
-                                                     uint32_t *__restrict__ tcnt, const uint64_t *__restrict__ tpos,
-                                                     uint64_t *__restrict__ items, uint32_t *__restrict__ words,
-                                                     uint32_t *__restrict__ pos32, uint64_t cap, Control *ctl,
-                                                     uint32_t probe_op)
+                                                     const uint2 *__restrict__ life, const uint2 *__restrict__ own,
+                                                     const uint32_t *__restrict__ nbr, uint64_t ntiles,
+                                                     uint64_t *__restrict__ tpos, void *__restrict__ out,
+                                                     uint32_t *__restrict__ pos32, uint64_t cap,
+                                                     uint64_t *__restrict__ lb, uint32_t *__restrict__ ticket,
+                                                     Control *ctl)
 {
-    constexpr bool EMIT = MODE != D_COUNT;
-    __shared__ uint32_t s_start[DWAVES][DTILE + 1];
-    __shared__ uint32_t s_word[DWAVES][DTILE];
-    __shared__ uint64_t s_nb[DWAVES][DTILE];
-    __shared__ uint32_t s_mark[DWAVES][WAVE];
-    const uint32_t lane = lane_id(), wv = threadIdx.x / WAVE;
-    const uint64_t tile = (uint64_t)blockIdx.x * DWAVES + wv;
-    if (tile >= ntiles)
-        return; // whole waves; no workgroup barriers below
-    const uint64_t i0 = tile * DTILE;
-    uint32_t carry = 0;
+    __shared__ DynTile s_tiles[DWAVES];
+    __shared__ uint32_t s_slot;
+    __shared__ uint64_t s_total[DWAVES], s_base;
+    const uint32_t lane = lane_id(), wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    DynTile &T = s_tiles[wv];
+    const uint64_t groups = ceil_div(ntiles, (uint64_t)DWAVES);
+    for (;;) {
+        const uint64_t group = take_ticket(ticket, &s_slot);
+        if (group >= groups)
+            break;
+        const uint64_t tile = group * DWAVES + wv, i0 = tile * DTILE; // (past the end: no events)
+        // ---- the events: their words, lifetimes and neighbours' bounds, each loaded together.
+        // Malformed words and liveness errors are reported at their index (the smallest one
+        // is the first error of a sequential reading) and have only the event itself.
+        uint32_t w[D_PER], few = 0, many = 0;
 #pragma unroll
-    for (int j = 0; j < D_PER; j++) {
-        const uint32_t k = j * WAVE + lane;
-        const uint64_t t = i0 + k;
-        uint32_t len = 0, w = 0;
-        uint64_t o = 0;
-        if (t < n)
-            len = dyn_event(ev[t], t, n_ids, mother, cpos, dpos, off, !EMIT, ctl, w, o);
-        const uint32_t inc = wave_scan_add(len, lane);
-        s_start[wv][k] = carry + inc - len;
-        s_word[wv][k] = w;
-        s_nb[wv][k] = o;
-        carry += __builtin_amdgcn_readlane(inc, WAVE - 1);
-    }
-    const uint32_t total = carry; // candidates of the tile (below 2^31: fewer than 2^22 neighbours each)
-    if (lane == 0)
-        s_start[wv][DTILE] = total;
-    __builtin_amdgcn_wave_barrier();
-    const uint64_t base = EMIT ? tpos[tile] : 0;
-    uint32_t kept = 0;
-    uint32_t ec = 0; // the event covering candidate qc - 1 (event 0 for qc = 0)
-    for (uint32_t qc = 0; qc < total; qc += DWALK_U * WAVE) {
-        // DWALK_U steps of 64 candidates: their events first (LDS only), then their
-        // neighbours' lifetimes and ids loaded together, then the items kept, in order
-        uint32_t own[DWALK_U];
-#pragma unroll
-        for (int u = 0; u < DWALK_U; u++) {
-            const uint32_t q0 = qc + u * WAVE;
-            own[u] = 0;
-            if (q0 >= total)
-                continue; // uniform
-            // events ec + 1 .. ec + 64 hold every start inside [q0, q0 + 64)
-            const uint32_t e = ec + 1 + lane;
-            const uint32_t st = e <= DTILE ? s_start[wv][e] : total;
-            s_mark[wv][lane] = 0;
-            __builtin_amdgcn_wave_barrier();
-            if (st < total && st < q0 + WAVE)
-                s_mark[wv][st - q0] = 1;
-            __builtin_amdgcn_wave_barrier();
-            const uint64_t heads = __ballot(s_mark[wv][lane] != 0);
-            own[u] = ec + mask_rank(heads) + (uint32_t)((heads >> lane) & 1u);
-            ec += (uint32_t)__builtin_popcountll(heads);
-            __builtin_amdgcn_wave_barrier();
+        for (int j = 0; j < D_PER; j++) {
+            const uint64_t t = i0 + j * WAVE + lane;
+            w[j] = t < n ? ev[t] : (uint32_t)OP_NOOP << 24;
         }
-        uint32_t kk[DWALK_U], y[DWALK_U];
-        uint2 lf[DWALK_U];
+        uint2 lf[D_PER];
+        uint32_t bad = 0; // bit j
 #pragma unroll
-        for (int u = 0; u < DWALK_U; u++) {
-            const uint32_t q = qc + u * WAVE + lane;
-            kk[u] = 0;
-            y[u] = 0;
-            lf[u] = make_uint2(NO_POS, NO_POS);
-            if (q < total) {
-                kk[u] = q - s_start[wv][own[u]];
-                const uint32_t w = s_word[wv][own[u]];
-                if (kk[u] != 0) {
-                    if (((w >> 24) & 7u) == OP_CREATE) {
-                        if (EMIT)
-                            y[u] = mother[w & 0xFFFFFFu];
-                    } else {
-                        const uint64_t j = s_nb[wv][own[u]] + kk[u] - 1;
-                        lf[u] = life[j];
-                        if (EMIT)
-                            y[u] = nbr[j];
+        for (int j = 0; j < D_PER; j++) {
+            const bool ok = word_ok(w[j], n_ids);
+            bad |= ok || i0 + j * WAVE + lane >= n ? 0u : 1u << j;
+            w[j] = ok ? w[j] : (uint32_t)OP_NOOP << 24;
+            lf[j] = own[w[j] & 0xFFFFFFu];
+        }
+        Bounds at[D_PER];
+#pragma unroll
+        for (int j = 0; j < D_PER; j++) {
+            at[j] = Bounds{0, 0};
+            if (((w[j] >> 24) & 7u) == OP_W)
+                at[j] = *reinterpret_cast<const Bounds *>(off + (w[j] & 0xFFFFFFu));
+        }
+#pragma unroll
+        for (int j = 0; j < D_PER; j++) {
+            const uint32_t k = j * WAVE + lane, op = (w[j] >> 24) & 7u;
+            const uint64_t t = i0 + k;
+            const bool in = t < n;
+            bool wrong, probe = false;
+            if (__ballot(op >= OP_CREATE)) { // (uniform, and rare)
+                wrong = !life_holds(lf[j], t);
+                if (op == OP_CREATE) {
+                    const uint32_t m = mother[w[j] & 0xFFFFFFu];
+                    probe = m != NO_MOTHER;
+                    wrong = lf[j].x != (uint32_t)t + 1 || (probe && !life_holds(own[m], t));
+                } else if (op == OP_DESTROY) {
+                    wrong = lf[j].y != (uint32_t)t || lf[j].x > (uint32_t)t;
+                }
+            } else {
+                wrong = !life_holds(lf[j], t);
+            }
+            if (!in || ((bad >> j) & 1u)) // (a malformed word is no event on its array)
+                wrong = false;
+            bad |= wrong ? 1u << j : 0u;
+            probe = probe && !wrong;
+            const uint32_t deg = wrong ? 0u : (uint32_t)(at[j].end - at[j].begin); // (0 but for writes)
+            const bool f = deg != 0 && deg <= D_SMALL, m = deg > D_SMALL;
+            const uint64_t fm = __ballot(f), mm = __ballot(m);
+            T.word[k] = w[j] | (probe ? D_PROBE : 0u);
+            T.items[k] = in ? 1u + (probe ? 1u : 0u) : 0u;
+            T.deg[k] = deg;
+            if (f)
+                T.list[few + mask_rank(fm)] = (uint16_t)k;
+            if (m)
+                T.list[DTILE - 1 - (many + mask_rank(mm))] = (uint16_t)k;
+            few += (uint32_t)__builtin_popcountll(fm);
+            many += (uint32_t)__builtin_popcountll(mm);
+        }
+        if (bad)
+            report_bad(ctl, i0 + (uint32_t)__builtin_ctz(bad) * WAVE + lane);
+        wave_lds_fence();
+        // ---- live neighbours of the writes with few
+        for (uint32_t i = lane; i < few; i += WAVE) {
+            const uint32_t k = T.list[i], deg = T.deg[k];
+            const uint64_t o = off[T.word[k] & 0xFFFFFFu];
+            uint32_t live = 0;
+            for (uint32_t q = 0; q < deg; q += D_AHEAD) {
+                uint2 lf[D_AHEAD];
+#pragma unroll
+                for (int u = 0; u < D_AHEAD; u++)
+                    lf[u] = life[o + (q + u < deg ? q + u : deg - 1)];
+#pragma unroll
+                for (int u = 0; u < D_AHEAD; u++)
+                    live |= q + u < deg && life_holds(lf[u], i0 + k) ? 1u << (q + u) : 0u;
+            }
+            T.items[k] += (uint32_t)__builtin_popcount(live);
+            T.deg[k] = deg | (live << 8);
+        }
+        // ---- and of the others, 64 at a time (the first 64's bits stay in registers)
+        Writes W0, W;
+        for (uint32_t i0w = 0; i0w < many; i0w += WAVE) {
+            W.take(T, i0w, many, off, lane);
+            W.look(many - i0w < WAVE ? many - i0w : WAVE, i0, life, lane);
+            if (i0w + lane < many)
+                T.items[W.k] += W.count;
+            if (i0w == 0)
+                W0 = W;
+        }
+        wave_lds_fence();
+        // ---- where the items start
+        uint32_t c[D_PER], total = 0;
+#pragma unroll
+        for (int j = 0; j < D_PER; j++) {
+            c[j] = T.items[j * WAVE + lane];
+            const uint32_t inc = wave_scan_add(c[j], lane);
+            T.items[j * WAVE + lane] = total + inc - c[j];
+            total += (uint32_t)__builtin_amdgcn_readlane((int)inc, WAVE - 1);
+        }
+        if (lane == 0)
+            s_total[wv] = total;
+        __syncthreads();
+        uint64_t before = 0, sum = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < DWAVES; w++) {
+            before += w < wv ? s_total[w] : 0;
+            sum += s_total[w];
+        }
+        if constexpr (MODE == D_COUNT) {
+            if (threadIdx.x == 0)
+                atomicAdd(&ctl->n_out, (unsigned long long)sum);
+            __syncthreads();
+            continue;
+        }
+        if (wv == 0) {
+            const uint64_t at = lb_count_exclusive(lb, group, sum);
+            if (lane == 0)
+                s_base = at;
+        }
+        __syncthreads();
+        const uint64_t base = s_base + before;
+        if (lane == 0 && tile < ntiles) {
+            tpos[tile] = base;
+            if (tile + 1 == ntiles)
+                tpos[ntiles] = base + total;
+        }
+        // ---- the items (past the capacity: the events changed since they were sized)
+        const uint32_t room = base < cap ? (uint32_t)(cap - base < total ? cap - base : total) : 0u;
+        if (room < total && lane == 0)
+            report_bad(ctl, i0);
+        uint64_t *const items = reinterpret_cast<uint64_t *>(out) + base;
+        uint32_t *const words = reinterpret_cast<uint32_t *>(out) + base;
+        auto induced = [&](uint32_t p, uint32_t y, uint32_t head) { // (head: op and side)
+            if (p >= room)
+                return;
+            if (MODE == D_ITEMS)
+                items[p] = make_item(y, fcode(OP_RWIND, (head >> 27) & 1u), INDUCED_BIT);
+            else
+                words[p] = y | head;
+        };
+#pragma unroll
+        for (int j = 0; j < D_PER; j++) {
+            const uint32_t k = j * WAVE + lane;
+            const uint64_t t = i0 + k;
+            if (t >= n)
+                continue;
+            const uint32_t w = T.word[k], p = T.items[k];
+            const uint32_t op = (w >> 24) & 7u, x = w & 0xFFFFFFu, side = (w >> 27) & 1u;
+            if (p < room) {
+                if (MODE == D_ITEMS)
+                    items[p] = make_item(x, op >= OP_CREATE ? fcode(OP_NOOP, 0) : fcode(op, side), (uint32_t)t);
+                else
+                    words[p] = x | (op >= OP_CREATE ? (uint32_t)OP_NOOP << 24 : (w & (15u << 24)));
+            }
+            if (op == OP_CREATE || MODE == D_WORDS)
+                if (MODE != D_ITEMS)
+                    pos32[t] = (uint32_t)base + p; // below 2^32 on these routes
+            if ((w & D_PROBE) && p + 1 < room) {
+                const uint32_t m = mother[x];
+                if (MODE == D_ITEMS)
+                    items[p + 1] = make_item(m, fcode(OP_NOOP, 0), (uint32_t)(n + t));
+                else
+                    words[p + 1] = m | (MODE == D_DENSE ? DENSE_OP_PROBE : (uint32_t)OP_NOOP) << 24;
+            }
+        }
+        for (uint32_t i = lane; i < few; i += WAVE) {
+            const uint32_t k = T.list[i], w = T.word[k];
+            const uint64_t o = off[w & 0xFFFFFFu];
+            uint32_t p = T.items[k] + 1, live = T.deg[k] >> 8;
+            while (live) {
+                uint32_t y[D_AHEAD], c = 0;
+#pragma unroll
+                for (int u = 0; u < D_AHEAD; u++)
+                    if (live) {
+                        y[u] = nbr[o + __builtin_ctz(live)];
+                        live &= live - 1;
+                        c++;
+                    }
+#pragma unroll
+                for (int u = 0; u < D_AHEAD; u++)
+                    if (u < (int)c)
+                        induced(p + u, y[u], OP_RWIND << 24 | (w & (1u << 27)));
+                p += c;
+            }
+        }
+        for (uint32_t i0w = 0; i0w < many; i0w += WAVE) {
+            const uint32_t cnt = many - i0w < WAVE ? many - i0w : WAVE;
+            if (i0w != 0) {
+                W0.take(T, i0w, many, off, lane);
+                W0.look(cnt, i0, life, lane);
+            }
+            const uint32_t start = T.items[W0.k] + 1, head = OP_RWIND << 24 | (T.word[W0.k] & (1u << 27));
+            for (uint32_t i = 0; i < cnt; i += D_WAHEAD) {
+                uint32_t y[D_WAHEAD][2];
+#pragma unroll
+                for (int u = 0; u < D_WAHEAD; u++) {
+                    const int l = (int)(i + u < cnt ? i + u : cnt - 1);
+                    const uint32_t *p = nbr + W0.first(l);
+                    y[u][0] = y[u][1] = 0;
+                    if (__builtin_amdgcn_inverse_ballot_w64(W0.bits(l, 0)))
+                        y[u][0] = p[lane];
+                    if (__builtin_amdgcn_inverse_ballot_w64(W0.bits(l, 1)))
+                        y[u][1] = p[WAVE + lane];
+                }
+#pragma unroll
+                for (int u = 0; u < D_WAHEAD; u++) {
+                    if (i + u >= cnt)
+                        break; // uniform
+                    const int l = (int)(i + u);
+                    const uint32_t h = lane32(head, l), deg = lane32(W0.deg, l);
+                    uint32_t p = lane32(start, l);
+#pragma unroll
+                    for (int q = 0; q < 2; q++) {
+                        const uint64_t m = W0.bits(l, q);
+                        if (__builtin_amdgcn_inverse_ballot_w64(m))
+                            induced(p + mask_rank(m), y[u][q], h);
+                        p += (uint32_t)__builtin_popcountll(m);
+                    }
+                    for (uint32_t q = 2 * WAVE; q < deg; q += WAVE) { // uniform, and rare
+                        const uint64_t at = W0.first(l) + (q + lane < deg ? q + lane : 0);
+                        const uint64_t m = __ballot(q + lane < deg && life_holds(life[at], i0 + lane32(W0.k, l)));
+                        if (__builtin_amdgcn_inverse_ballot_w64(m))
+                            induced(p + mask_rank(m), nbr[at], h);
+                        p += (uint32_t)__builtin_popcountll(m);
                     }
                 }
             }
         }
-#pragma unroll
-        for (int u = 0; u < DWALK_U; u++) {
-            const uint32_t q = qc + u * WAVE + lane;
-            bool keep = false, primary = false;
-            uint64_t item = 0;
-            uint32_t word = 0;
-            const uint32_t o = own[u];
-            if (q < total) {
-                const uint32_t k = kk[u];
-                const uint32_t w = s_word[wv][o], op = (w >> 24) & 7u, x = w & 0xFFFFFFu, side = (w >> 27) & 1u;
-                const uint64_t t = i0 + o;
-                keep = true;
-                if (k == 0) {
-                    primary = true;
-                    if (MODE == D_ITEMS)
-                        item = make_item(x, op >= OP_CREATE ? fcode(OP_NOOP, 0) : fcode(op, side), (uint32_t)t);
-                    if (MODE == D_WORDS)
-                        word = x | (op >= OP_CREATE ? (uint32_t)OP_NOOP << 24 : (w & (15u << 24)));
-                } else if (op == OP_CREATE) {
-                    if (MODE == D_ITEMS)
-                        item = make_item(y[u], fcode(OP_NOOP, 0), (uint32_t)(n + t));
-                    if (MODE == D_WORDS)
-                        word = y[u] | probe_op << 24;
-                } else {
-                    keep = (lf[u].x == NO_POS || lf[u].x < t) && (lf[u].y == NO_POS || t < lf[u].y);
-                    if (MODE == D_ITEMS)
-                        item = make_item(y[u], fcode(OP_RWIND, side), INDUCED_BIT);
-                    if (MODE == D_WORDS)
-                        word = y[u] | (uint32_t)OP_RWIND << 24 | (side << 27);
-                }
-            }
-            const uint64_t km = __ballot(keep);
-            if (EMIT && keep) {
-                const uint64_t p = base + kept + mask_rank(km);
-                if (p >= cap) { // the events changed since the items were sized: refused, in bounds
-                    report_bad(ctl, i0 + o);
-                } else if (MODE == D_ITEMS) {
-                    items[p] = item;
-                } else {
-                    words[p] = word;
-                    if (primary && (probe_op == OP_NOOP || ((s_word[wv][o] >> 24) & 7u) == OP_CREATE))
-                        pos32[i0 + o] = (uint32_t)p; // below 2^32 on this route
-                }
-            }
-            kept += (uint32_t)__builtin_popcountll(km);
-        }
+        __syncthreads(); // (the next ticket's slot, totals and base)
     }
-    if (!EMIT && lane == 0)
-        tcnt[tile] = kept;
-    if (EMIT && lane == 0 && base + kept != tpos[tile + 1])
-        report_bad(ctl, i0); // the events changed since the items were sized
 }
 
 // initial statuses of the second scan: a created partial vector starts at the status
@@ -327,6 +488,27 @@ __global__ void k_dyn_inherit_words(const uint32_t *__restrict__ mother, const u
     }
 }
 
+// the same from the functions that the probes see (pre, at a create's position + 1) and the
+// statuses entering the create's chunk
+__global__ void k_dyn_inherit_dense(const uint32_t *__restrict__ mother, const uint32_t *__restrict__ cpos,
+                                    const uint8_t *__restrict__ pre, const uint32_t *__restrict__ pos32, uint64_t n,
+                                    uint64_t m, DenseEntering E, const uint8_t *__restrict__ init, uint32_t n_ids,
+                                    uint8_t *__restrict__ init2)
+{
+    for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n_ids; x += gridDim.x * blockDim.x) {
+        const uint32_t c = cpos[x], mo = mother[x];
+        uint8_t s = init ? init[x] : (uint8_t)1;
+        if (c != NO_POS && c < n && mo != NO_MOTHER) {
+            const uint64_t p = (uint64_t)pos32[c] + 1;
+            const uint32_t f = pre[p < m ? p : m - 1];
+            const uint32_t h = (E.rows[c / DTILE / E.per * E.row + (mo >> 3)] >> (3 * (mo & 7u))) & 3u;
+            // f of h: a constant, or the copies valid before and those a transfer makes valid
+            s = (uint8_t)((f & 4u) ? f & 3u : h | (f & (h >> 1) & 1u) | ((f & (h << 1)) & 2u));
+        }
+        init2[x] = s;
+    }
+}
+
 unsigned grid_of(uint64_t n, unsigned per = BLOCK * 4)
 {
     uint64_t g = ceil_div(n ? n : 1, per);
@@ -351,47 +533,55 @@ uint32_t dyn_tile_events() { return DTILE; }
 
 uint64_t dyn_tiles(uint64_t n) { return ceil_div(n, (uint64_t)DTILE); }
 
-void launch_dyn_count(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint32_t *mother, const uint32_t *cpos,
-                      const uint32_t *dpos, const OverlapSets *o, uint2 *life, uint32_t *tcnt, Control *ctl,
+void launch_dyn_near(const OverlapSets *o, uint32_t n_ids, const uint32_t *cpos, const uint32_t *dpos, uint2 *life,
+                     hipStream_t s)
+{
+    ProfScope p(s, "dyn_nbr_life");
+    k_dyn_nbr_life<<<grid_of(o->n_nbr + n_ids), BLOCK, 0, s>>>(o->nbr, o->n_nbr, n_ids, cpos, dpos, life);
+}
+
+size_t dyn_scratch_bytes(uint64_t n) { return (ceil_div(dyn_tiles(n), (uint64_t)DWAVES) + 1) * 8; }
+
+namespace {
+
+template <int MODE>
+void launch_tiles(const DynTrace &D, uint64_t *tpos, void *out, uint32_t *pos32, uint64_t cap, void *scratch,
+                  Control *ctl, hipStream_t s)
+{
+    const uint64_t ntiles = dyn_tiles(D.n), groups = ceil_div(ntiles, (uint64_t)DWAVES);
+    uint64_t *lb = reinterpret_cast<uint64_t *>(scratch);
+    launch_clear_lookback(lb, groups, ctl->tickets[5], s);
+    if (!ntiles) {
+        if (tpos)
+            launch_fill_u64(tpos, 0, 1, s);
+        return;
+    }
+    ProfScope p(s, "dyn_tiles");
+    k_dyn_tiles<MODE><<<resident_grid((const void *)k_dyn_tiles<MODE>, groups), BLOCK, 0, s>>>(
+        D.ev, D.n, D.n_ids, D.mother, D.sets->off, D.life, D.life + D.sets->n_nbr, D.sets->nbr, ntiles, tpos, out, pos32, cap,
+        lb, ctl->tickets[5], ctl);
+}
+
+} // namespace
+
+void launch_dyn_count(const DynTrace &D, void *scratch, Control *ctl, hipStream_t s)
+{
+    launch_tiles<D_COUNT>(D, nullptr, nullptr, nullptr, 0, scratch, ctl, s);
+}
+
+void launch_dyn_items(const DynTrace &D, uint64_t *tpos, uint64_t *items, uint64_t cap, void *scratch, Control *ctl,
                       hipStream_t s)
 {
-    if (o->n_nbr) {
-        ProfScope p(s, "dyn_nbr_life");
-        k_dyn_nbr_life<<<grid_of(o->n_nbr), BLOCK, 0, s>>>(o->nbr, o->n_nbr, cpos, dpos, life);
-    }
-    const uint64_t ntiles = dyn_tiles(n);
-    if (ntiles) {
-        ProfScope p(s, "dyn_count");
-        k_dyn_tiles<D_COUNT><<<(unsigned)ceil_div(ntiles, (uint64_t)DWAVES), BLOCK, 0, s>>>(
-            ev, n, n_ids, mother, cpos, dpos, o->off, o->nbr, life, ntiles, tcnt, nullptr, nullptr, nullptr, nullptr, 0,
-            ctl, OP_NOOP);
-    }
+    launch_tiles<D_ITEMS>(D, tpos, items, nullptr, cap, scratch, ctl, s);
 }
 
-void launch_dyn_emit(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint32_t *mother, const uint32_t *cpos,
-                     const uint32_t *dpos, const OverlapSets *o, const uint2 *life, const uint64_t *tpos,
-                     uint64_t *items, uint64_t cap, Control *ctl, hipStream_t s)
+void launch_dyn_words(const DynTrace &D, bool dense, uint64_t *tpos, uint32_t *words, uint32_t *pos32, uint64_t cap,
+                      void *scratch, Control *ctl, hipStream_t s)
 {
-    const uint64_t ntiles = dyn_tiles(n);
-    if (ntiles) {
-        ProfScope p(s, "dyn_emit");
-        k_dyn_tiles<D_ITEMS><<<(unsigned)ceil_div(ntiles, (uint64_t)DWAVES), BLOCK, 0, s>>>(
-            ev, n, n_ids, mother, cpos, dpos, o->off, o->nbr, life, ntiles, nullptr, tpos, items, nullptr, nullptr, cap,
-            ctl, OP_NOOP);
-    }
-}
-
-void launch_dyn_words(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint32_t *mother, const uint32_t *cpos,
-                      const uint32_t *dpos, const OverlapSets *o, const uint2 *life, const uint64_t *tpos,
-                      uint32_t *words, uint32_t *pos32, uint64_t cap, Control *ctl, hipStream_t s, uint32_t probe_op)
-{
-    const uint64_t ntiles = dyn_tiles(n);
-    if (ntiles) {
-        ProfScope p(s, "dyn_words");
-        k_dyn_tiles<D_WORDS><<<(unsigned)ceil_div(ntiles, (uint64_t)DWAVES), BLOCK, 0, s>>>(
-            ev, n, n_ids, mother, cpos, dpos, o->off, o->nbr, life, ntiles, nullptr, tpos, nullptr, words, pos32, cap,
-            ctl, probe_op);
-    }
+    if (dense)
+        launch_tiles<D_DENSE>(D, tpos, words, pos32, cap, scratch, ctl, s);
+    else
+        launch_tiles<D_WORDS>(D, tpos, words, pos32, cap, scratch, ctl, s);
 }
 
 void launch_dyn_inherit_words(const uint32_t *mother, const uint32_t *cpos, const uint8_t *pre, const uint32_t *dstidx,
@@ -401,6 +591,14 @@ void launch_dyn_inherit_words(const uint32_t *mother, const uint32_t *cpos, cons
     ProfScope p(s, "dyn_inherit");
     k_dyn_inherit_words<<<grid_of(n_ids), BLOCK, 0, s>>>(mother, cpos, pre, dstidx, pos32, n, m ? m : 1, init, n_ids,
                                                          init2, fin);
+}
+
+void launch_dyn_inherit_dense(const uint32_t *mother, const uint32_t *cpos, const uint8_t *pre, const uint32_t *pos32,
+                              uint64_t n, uint64_t m, const DenseEntering &E, const uint8_t *init, uint32_t n_ids,
+                              uint8_t *init2, hipStream_t s)
+{
+    ProfScope p(s, "dyn_inherit");
+    k_dyn_inherit_dense<<<grid_of(n_ids), BLOCK, 0, s>>>(mother, cpos, pre, pos32, n, m ? m : 1, E, init, n_ids, init2);
 }
 
 void launch_dyn_inherit(const uint32_t *mother, const uint32_t *cpos, const uint8_t *probe_pre, uint64_t n,

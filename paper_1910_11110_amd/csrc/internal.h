@@ -184,27 +184,35 @@ void launch_translate_emit_fused_dev(const uint64_t *comp_off, uint64_t n_comp, 
 // lifetimes: first create / destroy position of every array (NO_POS if none)
 void launch_dyn_life(const uint32_t *ev, uint64_t n, uint32_t n_ids, uint32_t *cpos, uint32_t *dpos, hipStream_t s);
 struct OverlapSets;
-// the combined items (each event, a probe on its mother at a create, one induced RW
-// per live neighbour at a write) by tiles of events, dyn_tiles(n) of them: the count
-// pass writes every tile's number of items (errors to ctl's error index), the emit pass
-// writes the items at the tiles' positions (tpos: exclusive scan of the counts,
-// dyn_tiles(n) + 1 entries), cap items at most.  The count pass first writes `life`
-// (one (create, destroy) pair per entry of the overlap CSR), which the emit pass reads.
+// the lifetimes of the entries of the overlap CSR and then of the arrays (life, n_nbr +
+// n_ids pairs)
+void launch_dyn_near(const OverlapSets *o, uint32_t n_ids, const uint32_t *cpos, const uint32_t *dpos, uint2 *life,
+                     hipStream_t s);
+// the combined items (each event, a probe on its mother at a create, one induced RW per
+// live neighbour at a write) by tiles of events, dyn_tiles(n) of them, cap items at most;
+// tpos: the tiles' first items, their number at the end.  Errors to ctl's error index;
+// scratch of dyn_scratch_bytes(n).
+struct DynTrace {
+    const uint32_t *ev;
+    uint64_t n;
+    uint32_t n_ids;
+    const uint32_t *mother;
+    const OverlapSets *sets;
+    const uint2 *life;
+};
 uint64_t dyn_tiles(uint64_t n);
-void launch_dyn_count(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint32_t *mother, const uint32_t *cpos,
-                      const uint32_t *dpos, const OverlapSets *o, uint2 *life, uint32_t *tcnt, Control *ctl,
-                      hipStream_t s);
-void launch_dyn_emit(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint32_t *mother, const uint32_t *cpos,
-                     const uint32_t *dpos, const OverlapSets *o, const uint2 *life, const uint64_t *tpos,
-                     uint64_t *items, uint64_t cap, Control *ctl, hipStream_t s);
 uint32_t dyn_tile_events();
-// the same items as 32-bit words (creates and destroys no-ops on their array, probes of op
-// probe_op, induced items op 5), pos32[t] = event t's position among them (only creates'
-// unless the probes are no-ops too)
-void launch_dyn_words(const uint32_t *ev, uint64_t n, uint32_t n_ids, const uint32_t *mother, const uint32_t *cpos,
-                      const uint32_t *dpos, const OverlapSets *o, const uint2 *life, const uint64_t *tpos,
-                      uint32_t *words, uint32_t *pos32, uint64_t cap, Control *ctl, hipStream_t s,
-                      uint32_t probe_op = 4);
+size_t dyn_scratch_bytes(uint64_t n);
+// their number, added to ctl->n_out
+void launch_dyn_count(const DynTrace &D, void *scratch, Control *ctl, hipStream_t s);
+// 64-bit sort items
+void launch_dyn_items(const DynTrace &D, uint64_t *tpos, uint64_t *items, uint64_t cap, void *scratch, Control *ctl,
+                      hipStream_t s);
+// 32-bit words (creates and destroys no-ops on their array, induced items op 5), for the
+// bucket engine, with every event's position among them (pos32; probes no-ops), or for the
+// dense check, with the creates'
+void launch_dyn_words(const DynTrace &D, bool dense, uint64_t *tpos, uint32_t *words, uint32_t *pos32, uint64_t cap,
+                      void *scratch, Control *ctl, hipStream_t s);
 // bucket route: the initial statuses of the second check from the words' pre-statuses
 // (bits 0-1 of pre[i], read through dstidx[i] when it is given; a create's probe right
 // after it)

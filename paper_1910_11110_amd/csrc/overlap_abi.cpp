@@ -147,16 +147,14 @@ DynLayout dyn_layout(void *base, uint64_t n, uint32_t n_ids, uint64_t n_nbr)
     L.dpos = (uint32_t *)take((size_t)(n_ids ? n_ids : 1) * 4);
     L.init2 = (uint8_t *)take(n_ids ? n_ids : 1);
     L.pre = (uint8_t *)take(2 * n + 1);
-    L.life = (uint2 *)take((size_t)(n_nbr ? n_nbr : 1) * sizeof(uint2));
+    L.life = (uint2 *)take((size_t)(n_nbr + n_ids + 1) * sizeof(uint2));
     L.bytes = off;
     return L;
 }
 
-// t->aux of a dynamic trace: per tile of events its item count and their scan, per
-// event its position among the words of the bucket route, and the control block of the
-// expansion's errors on that route
+// t->aux of a dynamic trace: per tile of events its first item, per event its position
+// among the words, and the control block of the expansion's errors
 struct DynAux {
-    uint32_t *tcnt;
     uint64_t *tpos;
     uint32_t *pos32;
     Control *xctl;
@@ -172,34 +170,28 @@ DynAux dyn_aux(void *base, uint64_t n)
         off += (sz + 255) & ~size_t(255);
         return r;
     };
-    const uint64_t ntiles = dyn_tiles(n);
     DynAux A;
-    A.tcnt = (uint32_t *)take((ntiles ? ntiles : 1) * 4);
-    A.tpos = (uint64_t *)take((ntiles + 1) * 8);
+    A.tpos = (uint64_t *)take((dyn_tiles(n) + 1) * 8);
     A.pos32 = (uint32_t *)take((n ? n : 1) * 4);
     A.xctl = (Control *)take(CONTROL_BYTES);
     A.bytes = off;
     return A;
 }
 
-// the tiles' item positions in t->aux (after their counts)
-uint64_t *dyn_tile_pos(vc_trace *t) { return dyn_aux(t->aux.p, t->n).tpos; }
-
-// lifetimes, item counts per tile of events and their scan (in t->aux), on the stream;
-// errors to ctl
-int dyn_count_items(vc_trace *t, hipStream_t s, Control *ctl)
+// the buffers of the expansion, and the lifetimes of the arrays and of their neighbours, on
+// the stream
+int dyn_lifetimes(vc_trace *t, hipStream_t s, DynTrace &D)
 {
     int r;
-    const uint64_t n = t->n, ntiles = dyn_tiles(n);
+    const uint64_t n = t->n;
     if ((r = devbuf_reserve(t->aux, dyn_aux(nullptr, n).bytes)) != VC_OK ||
-        (r = devbuf_reserve(t->scratch, std::max(t->scratch.bytes, excl_scan_scratch_bytes(ntiles)))) != VC_OK ||
+        (r = devbuf_reserve(t->scratch, std::max(t->scratch.bytes, dyn_scratch_bytes(n)))) != VC_OK ||
         (r = devbuf_reserve(t->dyn, dyn_layout(nullptr, n, t->n_ids, t->sets.n_nbr).bytes)) != VC_OK)
         return r;
     const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
-    const DynAux A = dyn_aux(t->aux.p, n);
     launch_dyn_life(t->events, n, t->n_ids, L.cpos, L.dpos, s);
-    launch_dyn_count(t->events, n, t->n_ids, t->mother, L.cpos, L.dpos, &t->sets, L.life, A.tcnt, ctl, s);
-    launch_excl_scan(A.tcnt, ntiles, A.tpos, nullptr, t->scratch.p, ctl->tickets[5], s);
+    launch_dyn_near(&t->sets, t->n_ids, L.cpos, L.dpos, L.life, s);
+    D = DynTrace{t->events, n, t->n_ids, t->mother, &t->sets, L.life};
     return VC_OK;
 }
 
@@ -207,20 +199,19 @@ int dyn_count_items(vc_trace *t, hipStream_t s, Control *ctl)
 int dyn_size(vc_trace *t)
 {
     hipStream_t s = t->ctx->stream;
-    const uint64_t n = t->n;
     launch_reset_control(t->ctl, s);
-    int r = dyn_count_items(t, s, t->ctl);
+    DynTrace D;
+    int r = dyn_lifetimes(t, s, D);
     if (r != VC_OK)
         return r;
-    uint64_t total = 0;
+    launch_dyn_count(D, t->scratch.p, t->ctl, s);
     Control h;
-    hipError_t e = hipMemcpyAsync(&total, dyn_tile_pos(t) + dyn_tiles(n), 8, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(&h, t->ctl, CONTROL_HEADER, hipMemcpyDeviceToHost, s);
+    hipError_t e = hipMemcpyAsync(&h, t->ctl, CONTROL_HEADER, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
     if (e != hipSuccess)
         return vc_hip_fail(e, "sizing of the dynamic trace");
+    const uint64_t total = h.n_out;
     uint64_t bad = ((uint64_t)h.err_index_hi << 32) | h.err_index_lo;
     if (bad != ~0ull)
         return vc_fail(VC_EINVAL, "malformed event word or lifetime error at index %llu", (unsigned long long)bad);
@@ -276,8 +267,9 @@ extern "C" int vc_trace_set_dynamic_arrays(vc_trace *t, const uint32_t *lo, cons
 }
 
 // the check of a dynamic trace whose statuses fit LDS: the items as 32-bit words, checked in
-// their order twice from the chunks' functions found once, for the statuses the probes see
-// (the inherited statuses) and, from them, for every status byte and the final table.
+// their order: first the chunks' functions and those that the probes see, which with the
+// statuses entering the chunks give the inherited statuses, then, from these, every status
+// byte and the final table.
 // The expansion reports its errors into a control block of its own, merged at the end.
 static int dynamic_dense_enqueue(vc_trace *t, hipStream_t s)
 {
@@ -294,17 +286,16 @@ static int dynamic_dense_enqueue(vc_trace *t, hipStream_t s)
         return r;
     const DynAux A = dyn_aux(t->aux.p, n);
     launch_reset_control(A.xctl, s);
-    if ((r = dyn_count_items(t, s, A.xctl)) != VC_OK)
+    DynTrace D;
+    if ((r = dyn_lifetimes(t, s, D)) != VC_OK)
         return r;
     const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
     uint32_t *words = (uint32_t *)t->items_a.p;
     uint8_t *pre = (uint8_t *)t->items_b.p, *fin = (uint8_t *)t->fin.p;
-    launch_dyn_words(t->events, n, t->n_ids, t->mother, L.cpos, L.dpos, &t->sets, L.life, A.tpos, words, A.pos32, m,
-                     A.xctl, s, DENSE_OP_PROBE);
+    launch_dyn_words(D, true, A.tpos, words, A.pos32, m, t->scratch.p, A.xctl, s);
     const DenseWords W{words, m, A.tpos, ntiles, t->n_ids};
-    launch_dense_words_fold(W, true, t->scratch.p, t->ctl, s);
-    launch_dense_words_probe(W, t->init, pre, t->scratch.p, s);
-    launch_dyn_inherit_words(t->mother, L.cpos, pre, nullptr, A.pos32, n, m, t->init, t->n_ids, L.init2, fin, s);
+    const DenseEntering E = launch_dense_words_probe(W, t->init, pre, t->scratch.p, t->ctl, s);
+    launch_dyn_inherit_dense(t->mother, L.cpos, pre, A.pos32, n, m, E, t->init, t->n_ids, L.init2, s);
     launch_dense_words_apply(W, true, L.init2, n, dyn_tile_events(), (uint8_t *)t->status.p, fin, t->scratch.p, t->ctl,
                              s);
     launch_compact((uint8_t *)t->status.p, n, (uint32_t *)t->viol.p, t->scratch.p, t->ctl, s);
@@ -334,13 +325,13 @@ static int dynamic_bucket_enqueue(vc_trace *t, hipStream_t s)
         return r;
     const DynAux A = dyn_aux(t->aux.p, n);
     launch_reset_control(A.xctl, s);
-    if ((r = dyn_count_items(t, s, A.xctl)) != VC_OK)
+    DynTrace D;
+    if ((r = dyn_lifetimes(t, s, D)) != VC_OK)
         return r;
     const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
     uint32_t *words = (uint32_t *)t->items_a.p;
     uint8_t *comb = (uint8_t *)t->items_b.p, *fin = (uint8_t *)t->fin.p;
-    launch_dyn_words(t->events, n, t->n_ids, t->mother, L.cpos, L.dpos, &t->sets, L.life, A.tpos, words, A.pos32, m,
-                     A.xctl, s);
+    launch_dyn_words(D, false, A.tpos, words, A.pos32, m, t->scratch.p, A.xctl, s);
     const int cu = t->ctx->cu_count;
     // the first pass needs only the probes' pre-statuses: read through the partition's
     // destinations, with no replay to program order
@@ -372,11 +363,11 @@ int dynamic_enqueue(vc_trace *t, hipStream_t s)
     if ((r = devbuf_reserve(t->status, 2 * n + 1)) != VC_OK)
         return r;
     launch_reset_control(t->ctl, s);
-    if ((r = dyn_count_items(t, s, t->ctl)) != VC_OK)
+    DynTrace D;
+    if ((r = dyn_lifetimes(t, s, D)) != VC_OK)
         return r;
     const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
-    launch_dyn_emit(t->events, n, t->n_ids, t->mother, L.cpos, L.dpos, &t->sets, L.life, dyn_tile_pos(t),
-                    (uint64_t *)t->items_a.p, m, t->ctl, s);
+    launch_dyn_items(D, dyn_aux(t->aux.p, n).tpos, (uint64_t *)t->items_a.p, m, t->scratch.p, t->ctl, s);
     uint64_t *sorted = sort_items((uint64_t *)t->items_a.p, (uint64_t *)t->items_b.p, m,
                                   (int)key_bits_for(t->n_ids), t->scratch.p, t->ctl, s);
     // the first scan is read only at the probes (payloads n + t)
@@ -440,7 +431,7 @@ static int overlap_dense_enqueue(vc_trace *t, hipStream_t s)
     launch_excl_scan(tcnt, ntiles, tpos, nullptr, t->scratch.p, xctl->tickets[5], s);
     launch_overlap_words(t->events, n, t->n_ids, &t->sets, tpos, words, m, nullptr, xctl, s);
     const DenseWords W{words, m, tpos, ntiles, t->n_ids};
-    launch_dense_words_fold(W, false, t->scratch.p, t->ctl, s);
+    launch_dense_words_fold(W, t->scratch.p, t->ctl, s);
     launch_dense_words_apply(W, false, t->init, n, overlap_tile_events(), (uint8_t *)t->status.p, (uint8_t *)t->fin.p,
                              t->scratch.p, t->ctl, s);
     launch_compact((uint8_t *)t->status.p, n, (uint32_t *)t->viol.p, t->scratch.p, t->ctl, s);

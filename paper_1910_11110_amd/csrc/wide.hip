@@ -286,7 +286,7 @@ static void wide_scan(const WideChunks &W, uint32_t row, const uint8_t *init, ui
         k_wide_prefix<D><<<pg, BLOCK, 0, s>>>(rows, row, W.nb, W.cbase, W.cb, grp, W.n_ids, W.bits, init, final_out);
     }
     ProfScope p(s, "wide_apply");
-    k_dense_apply<D, Q, BucketChunks, StatusOut<R>><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, StatusOut<R>{res});
+    k_dense_apply<Apply<D>, Q, BucketChunks, StatusOut<R>><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, StatusOut<R>{res});
 }
 
 void launch_wide_scan_events(const WideChunks &W, const uint8_t *init, uint8_t *final_out, void *rows, uint8_t *res,

@@ -182,3 +182,16 @@ def test_dynamic_bucket_and_sorted_routes_agree(ctx, n, nv, npv, space, maxlen):
         assert np.array_equal(a[1], b[1]), "final statuses"
         assert a[2].total == b[2].total and np.array_equal(a[2].indices, b[2].indices), "violations"
         assert a[3] == b[3], "stuck induced"
+
+
+@pytest.mark.parametrize("n,nv,npv,space,maxlen", [(3_000, 1, 23, 64, 64), (3_000, 1, 24, 64, 64), (5_000, 1, 63, 64, 64),
+                                                   (5_000, 1, 64, 64, 64), (9_000, 1, 127, 64, 64),
+                                                   (9_000, 2, 400, 128, 64), (40_000, 1, 900, 4096, 4096),
+                                                   (300_000, 64, 70_000, 1 << 20, 64)])
+def test_dynamic_neighbour_limits(ctx, n, nv, npv, space, maxlen):
+    """Writes with as many neighbours as one lane looks at, one more, one and two steps of
+    the wave, more than those whose live ones are kept, and (the last) more ids than the
+    dense check takes."""
+    d = gen.dynamic_trace(n, nv, npv, n + npv, space=space, max_len=maxlen, p_destroyed=0.3)
+    assert_parity(ctx, d.events, d.lo, d.hi, d.mother, label=f"{npv} partial vectors",
+                  sets=O.overlap_sets(d.lo, d.hi))
