@@ -45,9 +45,10 @@ struct vc_ctx {
     // the events that fork it from and join it back to the main stream
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-    // collection of many finished checks at once: their control-block and violation
-    // pointers, and the gathered headers
-    DevBuf gather_ptrs, gather_out;
+    // collection of finished work at a synchronization (pinned host memory, grown as
+    // needed): room for `collect_cap` traces' pointers, then as many traces' words
+    void *collect = nullptr;
+    size_t collect_cap = 0;
     int cu_count = 256;
     std::vector<vc_trace *> pending; // traces with enqueued work not yet collected
     std::vector<vc_trace *> traces;  // live traces (detached when the context goes)
@@ -121,7 +122,6 @@ int vc_hip_fail(hipError_t e, const char *what);
 int devbuf_reserve(DevBuf &b, size_t bytes);
 void devbuf_free(DevBuf &b);
 uint32_t key_bits_for(uint32_t n_ids);
-int trace_collect(vc_trace *t);
 int trace_reserve(vc_trace *t, uint64_t m);
 int trace_set_init(vc_trace *t, const uint8_t *init, uint32_t flags, uint32_t max_code = 3);
 void enqueue_check_items(vc_trace *t, uint64_t m, hipStream_t s);

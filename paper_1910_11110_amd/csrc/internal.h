@@ -56,6 +56,15 @@ void launch_fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t s);
 void launch_reset_control(Control *c, hipStream_t s, Control *c2 = nullptr);
 // zeroes n look-back words and the ticket counters of one kernel (one launch)
 void launch_clear_lookback(uint64_t *lb, size_t n, uint32_t *ticket, hipStream_t s);
+// what a synchronization collects of a trace: the headers of its translation's control block
+// (or null) and of its check's, and the first violation word (read only when there is one);
+// n of them from and to pinned host memory, COLLECT_WORDS words each
+struct CollectPtrs {
+    const Control *translation, *check;
+    const uint32_t *viol;
+};
+constexpr uint32_t COLLECT_WORDS = 2 * (CONTROL_HEADER / 4) + 16;
+void launch_collect(const CollectPtrs *p, uint32_t n, uint32_t *out, hipStream_t s);
 // the host-read headers of n control blocks and the first violation word of each (read
 // only when its block counts violations), GATHER_WORDS words per block into out
 constexpr uint32_t GATHER_WORDS = CONTROL_HEADER / 4 + 1;

@@ -71,6 +71,25 @@ __global__ void k_gather_headers(const Control *const *ctl, const uint32_t *cons
     o[CONTROL_HEADER / 4] = ctl[i]->n_viol ? viol[i][0] : 0u;
 }
 
+// a wave per trace: its translation's header (zeros without one), its check's and its first
+// violation; the pointers and the output lie in pinned host memory
+__global__ __launch_bounds__(WAVE) void k_collect(const CollectPtrs *__restrict__ p, uint32_t *__restrict__ out)
+{
+    constexpr uint32_t H = CONTROL_HEADER / 4;
+    static_assert(2 * H + 1 <= WAVE && COLLECT_WORDS >= 2 * H + 1, "a word a lane");
+    const uint32_t lane = threadIdx.x;
+    const CollectPtrs q = p[blockIdx.x];
+    uint32_t v = 0;
+    if (lane < H && q.translation)
+        v = reinterpret_cast<const uint32_t *>(q.translation)[lane];
+    else if (lane >= H && lane < 2 * H)
+        v = reinterpret_cast<const uint32_t *>(q.check)[lane - H];
+    else if (lane == 2 * H && q.viol && q.check->n_viol)
+        v = q.viol[0];
+    if (lane <= 2 * H)
+        out[(size_t)blockIdx.x * COLLECT_WORDS + lane] = v;
+}
+
 // workgroup k resets control block k (c, then c2)
 __global__ void k_reset_control(Control *c, Control *c2)
 {
@@ -342,6 +361,12 @@ void launch_gather_headers(const Control *const *ctl, const uint32_t *const *vio
 {
     if (n)
         k_gather_headers<<<(n + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(ctl, viol, n, out);
+}
+
+void launch_collect(const CollectPtrs *p, uint32_t n, uint32_t *out, hipStream_t s)
+{
+    if (n)
+        k_collect<<<n, WAVE, 0, s>>>(p, out);
 }
 
 void launch_prep(Control *c, Control *c2, const FillJob *jobs, int njobs, hipStream_t s)
