@@ -198,9 +198,11 @@ struct OverlapSets;
 void launch_dyn_near(const OverlapSets *o, uint32_t n_ids, const uint32_t *cpos, const uint32_t *dpos, uint2 *life,
                      hipStream_t s);
 // the combined items (each event, a probe on its mother at a create, one induced RW per
-// live neighbour at a write) by tiles of events, dyn_tiles(n) of them, cap items at most;
-// tpos: the tiles' first items, their number at the end.  Errors to ctl's error index;
-// scratch of dyn_scratch_bytes(n).
+// live neighbour at a write) by tiles of events, dyn_tiles(n) of them.  The count pass
+// leaves every tile's number (tcnt), something of every event (left) and some bits
+// (dyn_bits_bytes(n)); the emit passes write the items at the tiles' positions (tpos:
+// exclusive scan of the counts, dyn_tiles(n) + 1 entries), cap items at most.  Errors to
+// ctl's error index.
 struct DynTrace {
     const uint32_t *ev;
     uint64_t n;
@@ -211,17 +213,16 @@ struct DynTrace {
 };
 uint64_t dyn_tiles(uint64_t n);
 uint32_t dyn_tile_events();
-size_t dyn_scratch_bytes(uint64_t n);
-// their number, added to ctl->n_out
-void launch_dyn_count(const DynTrace &D, void *scratch, Control *ctl, hipStream_t s);
+size_t dyn_bits_bytes(uint64_t n);
+void launch_dyn_count(const DynTrace &D, uint32_t *left, void *bits, uint32_t *tcnt, Control *ctl, hipStream_t s);
 // 64-bit sort items
-void launch_dyn_items(const DynTrace &D, uint64_t *tpos, uint64_t *items, uint64_t cap, void *scratch, Control *ctl,
-                      hipStream_t s);
+void launch_dyn_items(const DynTrace &D, const uint64_t *tpos, uint32_t *left, const void *bits, uint64_t *items,
+                      uint64_t cap, Control *ctl, hipStream_t s);
 // 32-bit words (creates and destroys no-ops on their array, induced items op 5), for the
-// bucket engine, with every event's position among them (pos32; probes no-ops), or for the
-// dense check, with the creates'
-void launch_dyn_words(const DynTrace &D, bool dense, uint64_t *tpos, uint32_t *words, uint32_t *pos32, uint64_t cap,
-                      void *scratch, Control *ctl, hipStream_t s);
+// bucket engine, with every event's position among them over left (probes no-ops), or for
+// the dense check, with the creates'
+void launch_dyn_words(const DynTrace &D, bool dense, const uint64_t *tpos, uint32_t *left, const void *bits,
+                      uint32_t *words, uint64_t cap, Control *ctl, hipStream_t s);
 // bucket route: the initial statuses of the second check from the words' pre-statuses
 // (bits 0-1 of pre[i], read through dstidx[i] when it is given; a create's probe right
 // after it)

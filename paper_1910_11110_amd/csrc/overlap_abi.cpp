@@ -152,11 +152,14 @@ DynLayout dyn_layout(void *base, uint64_t n, uint32_t n_ids, uint64_t n_nbr)
     return L;
 }
 
-// t->aux of a dynamic trace: per tile of events its first item, per event its position
-// among the words, and the control block of the expansion's errors
+// t->aux of a dynamic trace: per tile of events its items and its first one, per event what
+// the count pass leaves of it and then its position among the words, the count pass's bits,
+// and the control block of the expansion's errors
 struct DynAux {
+    uint32_t *tcnt;
     uint64_t *tpos;
     uint32_t *pos32;
+    void *bits;
     Control *xctl;
     size_t bytes;
 };
@@ -171,27 +174,33 @@ DynAux dyn_aux(void *base, uint64_t n)
         return r;
     };
     DynAux A;
+    A.tcnt = (uint32_t *)take((dyn_tiles(n) + 1) * 4);
     A.tpos = (uint64_t *)take((dyn_tiles(n) + 1) * 8);
     A.pos32 = (uint32_t *)take((n ? n : 1) * 4);
+    A.bits = take(dyn_bits_bytes(n));
     A.xctl = (Control *)take(CONTROL_BYTES);
     A.bytes = off;
     return A;
 }
 
-// the buffers of the expansion, and the lifetimes of the arrays and of their neighbours, on
-// the stream
-int dyn_lifetimes(vc_trace *t, hipStream_t s, DynTrace &D)
+// the buffers of the expansion, the lifetimes of the arrays and of their neighbours, and the
+// items of every tile of events and their scan, on the stream; errors to ctl
+int dyn_count_items(vc_trace *t, hipStream_t s, Control *ctl, DynTrace &D)
 {
     int r;
     const uint64_t n = t->n;
     if ((r = devbuf_reserve(t->aux, dyn_aux(nullptr, n).bytes)) != VC_OK ||
-        (r = devbuf_reserve(t->scratch, std::max(t->scratch.bytes, dyn_scratch_bytes(n)))) != VC_OK ||
+        (r = devbuf_reserve(t->scratch, std::max(t->scratch.bytes, excl_scan_scratch_bytes(dyn_tiles(n))))) != VC_OK ||
         (r = devbuf_reserve(t->dyn, dyn_layout(nullptr, n, t->n_ids, t->sets.n_nbr).bytes)) != VC_OK)
         return r;
     const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
     launch_dyn_life(t->events, n, t->n_ids, L.cpos, L.dpos, s);
     launch_dyn_near(&t->sets, t->n_ids, L.cpos, L.dpos, L.life, s);
     D = DynTrace{t->events, n, t->n_ids, t->mother, &t->sets, L.life};
+    const DynAux A = dyn_aux(t->aux.p, n);
+    launch_dyn_count(D, A.pos32, A.bits, A.tcnt, ctl, s);
+    launch_excl_scan(A.tcnt, dyn_tiles(n), A.tpos, reinterpret_cast<uint64_t *>(&ctl->n_out), t->scratch.p,
+                     ctl->tickets[5], s);
     return VC_OK;
 }
 
@@ -201,17 +210,16 @@ int dyn_size(vc_trace *t)
     hipStream_t s = t->ctx->stream;
     launch_reset_control(t->ctl, s);
     DynTrace D;
-    int r = dyn_lifetimes(t, s, D);
+    int r = dyn_count_items(t, s, t->ctl, D);
     if (r != VC_OK)
         return r;
-    launch_dyn_count(D, t->scratch.p, t->ctl, s);
     Control h;
     hipError_t e = hipMemcpyAsync(&h, t->ctl, CONTROL_HEADER, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
     if (e != hipSuccess)
         return vc_hip_fail(e, "sizing of the dynamic trace");
-    const uint64_t total = h.n_out;
+    const uint64_t total = t->n ? h.n_out : 0;
     uint64_t bad = ((uint64_t)h.err_index_hi << 32) | h.err_index_lo;
     if (bad != ~0ull)
         return vc_fail(VC_EINVAL, "malformed event word or lifetime error at index %llu", (unsigned long long)bad);
@@ -287,12 +295,12 @@ static int dynamic_dense_enqueue(vc_trace *t, hipStream_t s)
     const DynAux A = dyn_aux(t->aux.p, n);
     launch_reset_control(A.xctl, s);
     DynTrace D;
-    if ((r = dyn_lifetimes(t, s, D)) != VC_OK)
+    if ((r = dyn_count_items(t, s, A.xctl, D)) != VC_OK)
         return r;
     const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
     uint32_t *words = (uint32_t *)t->items_a.p;
     uint8_t *pre = (uint8_t *)t->items_b.p, *fin = (uint8_t *)t->fin.p;
-    launch_dyn_words(D, true, A.tpos, words, A.pos32, m, t->scratch.p, A.xctl, s);
+    launch_dyn_words(D, true, A.tpos, A.pos32, A.bits, words, m, A.xctl, s);
     const DenseWords W{words, m, A.tpos, ntiles, t->n_ids};
     const DenseEntering E = launch_dense_words_probe(W, t->init, pre, t->scratch.p, t->ctl, s);
     launch_dyn_inherit_dense(t->mother, L.cpos, pre, A.pos32, n, m, E, t->init, t->n_ids, L.init2, s);
@@ -326,12 +334,12 @@ static int dynamic_bucket_enqueue(vc_trace *t, hipStream_t s)
     const DynAux A = dyn_aux(t->aux.p, n);
     launch_reset_control(A.xctl, s);
     DynTrace D;
-    if ((r = dyn_lifetimes(t, s, D)) != VC_OK)
+    if ((r = dyn_count_items(t, s, A.xctl, D)) != VC_OK)
         return r;
     const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
     uint32_t *words = (uint32_t *)t->items_a.p;
     uint8_t *comb = (uint8_t *)t->items_b.p, *fin = (uint8_t *)t->fin.p;
-    launch_dyn_words(D, false, A.tpos, words, A.pos32, m, t->scratch.p, A.xctl, s);
+    launch_dyn_words(D, false, A.tpos, A.pos32, A.bits, words, m, A.xctl, s);
     const int cu = t->ctx->cu_count;
     // the first pass needs only the probes' pre-statuses: read through the partition's
     // destinations, with no replay to program order
@@ -364,10 +372,11 @@ int dynamic_enqueue(vc_trace *t, hipStream_t s)
         return r;
     launch_reset_control(t->ctl, s);
     DynTrace D;
-    if ((r = dyn_lifetimes(t, s, D)) != VC_OK)
+    if ((r = dyn_count_items(t, s, t->ctl, D)) != VC_OK)
         return r;
     const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
-    launch_dyn_items(D, dyn_aux(t->aux.p, n).tpos, (uint64_t *)t->items_a.p, m, t->scratch.p, t->ctl, s);
+    const DynAux A = dyn_aux(t->aux.p, n);
+    launch_dyn_items(D, A.tpos, A.pos32, A.bits, (uint64_t *)t->items_a.p, m, t->ctl, s);
     uint64_t *sorted = sort_items((uint64_t *)t->items_a.p, (uint64_t *)t->items_b.p, m,
                                   (int)key_bits_for(t->n_ids), t->scratch.p, t->ctl, s);
     // the first scan is read only at the probes (payloads n + t)
