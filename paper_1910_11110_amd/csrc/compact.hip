@@ -1,9 +1,8 @@
 // compact.hip -- coalesced compaction of violation flags (gfx950).
 //
-// Reads the per-event status bytes in program order (16 bytes per thread, one
-// 16-byte load), counts flagged events per tile, obtains the tile's output offset
-// by decoupled look-back, stages the tile's ascending indices in LDS and writes
-// them as one contiguous run.
+// Reads the per-event status bytes in program order (16 bytes per thread and load), counts
+// flagged events per tile, obtains the tile's output offset by decoupled look-back, stages
+// ascending indices in LDS, 4096 events at a time, and writes each as one contiguous run.
 #include "device.h"
 #include "internal.h"
 #include "prof.h"
@@ -13,16 +12,25 @@ namespace vc {
 namespace {
 
 constexpr int CITEMS = 16;
-constexpr int CTILE = BLOCK * CITEMS;
+constexpr int CPART = BLOCK * CITEMS; // events staged together
 
+// Parts a tile: the look-back, whose cost grows with the number of tiles that poll, bounds
+// long traces; short ones want the workgroups.  2^24 events: 34.5 us by 4,096 and 21.5 by
+// 16,384; 2^22 16.2 and 12.6; 2^21 12.7 and no better.
+constexpr int C_LONG = 4;
+constexpr uint64_t C_LONG_FROM = 1ull << 22;
+int parts_of(uint64_t n) { return n >= C_LONG_FROM ? C_LONG : 1; }
+
+template <int PARTS>
 __global__ __launch_bounds__(BLOCK) void k_compact(const uint8_t *__restrict__ status, uint64_t n,
                                                    uint32_t *__restrict__ viol, uint64_t *__restrict__ lb,
                                                    uint32_t *__restrict__ ticket, uint64_t ntiles, Control *ctl,
                                                    const unsigned long long *__restrict__ flagged,
                                                    const unsigned long long *__restrict__ n_dev)
 {
-    __shared__ uint32_t s_idx[CTILE];
-    __shared__ uint32_t s_wsum[BLOCK / WAVE];
+    constexpr uint64_t CTILE = (uint64_t)PARTS * CPART;
+    __shared__ uint32_t s_idx[CPART];
+    __shared__ uint32_t s_wsum[PARTS][BLOCK / WAVE];
     __shared__ uint32_t s_tile;
     __shared__ unsigned long long s_excl;
 
@@ -38,35 +46,47 @@ __global__ __launch_bounds__(BLOCK) void k_compact(const uint8_t *__restrict__ s
         if (tile >= ntiles)
             break;
         const uint64_t base = (uint64_t)tile * CTILE;
-        const uint64_t my0 = base + (uint64_t)tid * CITEMS;
-
-        uint32_t bits = 0;
-        if (my0 + CITEMS <= n) {
-            uint4 v = *reinterpret_cast<const uint4 *>(status + my0);
-            uint32_t w[4] = { v.x, v.y, v.z, v.w };
+        uint4 v[PARTS];
 #pragma unroll
-            for (int q = 0; q < 4; q++)
-#pragma unroll
-                for (int b = 0; b < 4; b++)
-                    bits |= ((w[q] >> (8 * b + 7)) & 1u) << (4 * q + b);
-        } else {
-            for (int k = 0; k < CITEMS; k++)
-                if (my0 + k < n)
-                    bits |= ((status[my0 + k] >> 7) & 1u) << k;
+        for (int p = 0; p < PARTS; p++) {
+            const uint64_t my0 = base + (uint64_t)p * CPART + (uint64_t)tid * CITEMS;
+            v[p] = make_uint4(0, 0, 0, 0);
+            if (my0 + CITEMS <= n) {
+                v[p] = *reinterpret_cast<const uint4 *>(status + my0);
+            } else if (my0 < n) {
+                uint32_t w[4] = {0, 0, 0, 0};
+                for (int k = 0; k < CITEMS; k++)
+                    if (my0 + k < n)
+                        w[k >> 2] |= (uint32_t)status[my0 + k] << (8 * (k & 3));
+                v[p] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
         }
-        uint32_t cnt = __builtin_popcount(bits);
-        uint32_t inc = wave_scan_add(cnt, lane);
-        if (lane == WAVE - 1)
-            s_wsum[wave] = inc;
+        uint32_t bits[PARTS], off[PARTS]; // off: of the thread's flagged events in their part
+#pragma unroll
+        for (int p = 0; p < PARTS; p++) {
+            const uint32_t w[4] = {v[p].x, v[p].y, v[p].z, v[p].w};
+            bits[p] = 0;
+#pragma unroll
+            for (int q = 0; q < 4; q++) // bits 7, 15, 23, 31 to four neighbouring ones
+                bits[p] |= (((w[q] & 0x80808080u) * 0x00204081u) >> 28) << (4 * q);
+            const uint32_t cnt = __builtin_popcount(bits[p]);
+            const uint32_t inc = wave_scan_add(cnt, lane);
+            off[p] = inc - cnt;
+            if (lane == WAVE - 1)
+                s_wsum[p][wave] = inc;
+        }
         __syncthreads();
-        uint32_t woff = 0, total = 0;
-        for (uint32_t w = 0; w < BLOCK / WAVE; w++) {
-            if (w < wave)
-                woff += s_wsum[w];
-            total += s_wsum[w];
+        uint32_t total = 0, part[PARTS];
+#pragma unroll
+        for (int p = 0; p < PARTS; p++) {
+            part[p] = 0;
+            for (uint32_t w = 0; w < BLOCK / WAVE; w++) {
+                if (w < wave)
+                    off[p] += s_wsum[p][w];
+                part[p] += s_wsum[p][w];
+            }
+            total += part[p];
         }
-        uint32_t off = woff + inc - cnt;
-
         if (wave == 0) {
             const uint64_t excl = lb_count_exclusive(lb, tile, total);
             if (lane == 0) {
@@ -75,17 +95,23 @@ __global__ __launch_bounds__(BLOCK) void k_compact(const uint8_t *__restrict__ s
                     ctl->n_viol = excl + total;
             }
         }
-        uint32_t k = off;
-        while (bits) {
-            uint32_t b = __builtin_ctz(bits);
-            bits &= bits - 1;
-            s_idx[k++] = (uint32_t)(my0 + b);
+        uint64_t to = 0;
+#pragma unroll
+        for (int p = 0; p < PARTS; p++) {
+            const uint32_t my0 = (uint32_t)(base + (uint64_t)p * CPART + (uint64_t)tid * CITEMS);
+            uint32_t k = off[p], m = bits[p];
+            while (m) {
+                s_idx[k++] = my0 + __builtin_ctz(m);
+                m &= m - 1;
+            }
+            __syncthreads();
+            if (p == 0)
+                to = s_excl;
+            for (uint32_t i = tid; i < part[p]; i += BLOCK)
+                viol[to + i] = s_idx[i];
+            to += part[p];
+            __syncthreads();
         }
-        __syncthreads();
-        uint64_t excl = s_excl;
-        for (uint32_t i = tid; i < total; i += BLOCK)
-            viol[excl + i] = s_idx[i];
-        __syncthreads();
     }
 }
 
@@ -136,22 +162,28 @@ void launch_flag_scatter(const uint32_t *fw, const uint64_t *offs, uint64_t ntil
         k_flag_scatter<256><<<grid, 256, 0, s>>>(fw, offs, ntiles, viol);
 }
 
-size_t compact_scratch_bytes(uint64_t n) { return ceil_div(n ? n : 1, CTILE) * sizeof(uint64_t); }
+// (the most a trace of n events or fewer takes: a shorter one by single parts)
+size_t compact_scratch_bytes(uint64_t n)
+{
+    const uint64_t part = n < C_LONG_FROM ? n : C_LONG_FROM;
+    const uint64_t a = ceil_div(n ? n : 1, (uint64_t)parts_of(n) * CPART), b = ceil_div(part ? part : 1, (uint64_t)CPART);
+    return (a > b ? a : b) * sizeof(uint64_t);
+}
 
 void launch_compact(const uint8_t *status, uint64_t n, uint32_t *viol, void *scratch, Control *ctl, hipStream_t s,
                     const unsigned long long *flagged, const unsigned long long *n_dev, bool lookback_cleared)
 {
     if (n == 0)
         return;
-    uint64_t tiles = ceil_div(n, CTILE);
+    const bool is_long = parts_of(n) == C_LONG;
+    const uint64_t tiles = ceil_div(n, (uint64_t)parts_of(n) * CPART);
     uint64_t *lb = reinterpret_cast<uint64_t *>(scratch);
     if (!lookback_cleared)
         launch_clear_lookback(lb, tiles, ctl->tickets[2], s);
-    {
-        ProfScope prof_(s, "compact");
-        k_compact<<<resident_grid((const void *)k_compact, tiles), BLOCK, 0, s>>>(status, n, viol, lb, ctl->tickets[2],
-                                                                               tiles, ctl, flagged, n_dev);
-    }
+    const auto kernel = is_long ? k_compact<C_LONG> : k_compact<1>;
+    ProfScope prof_(s, "compact");
+    kernel<<<resident_grid((const void *)kernel, tiles), BLOCK, 0, s>>>(status, n, viol, lb, ctl->tickets[2], tiles, ctl,
+                                                                       flagged, n_dev);
 }
 
 } // namespace vc

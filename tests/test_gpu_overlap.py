@@ -136,3 +136,11 @@ def test_overlap_dense_overlaps(ctx):
     hi = (lo + rng.integers(300, 500, 300)).astype(np.uint32)
     e = gen.plain_events(20_000, 300, 14)
     assert_overlap(ctx, e, lo, hi, label="dense overlaps")
+
+
+@pytest.mark.parametrize("n", [(1 << 22) - 1, 1 << 22, (1 << 22) + 12_289])
+def test_overlap_list_of_long_traces(ctx, n):
+    """Around the length from which the violation list is gathered by larger tiles, with a
+    last tile of one, two and four parts."""
+    lo, hi = gen.intervals(300, 5, space=1 << 14, max_len=16)
+    assert_overlap(ctx, gen.plain_events(n, 300, n), lo, hi, label="long")
