@@ -1265,9 +1265,7 @@ static void bucket_check(const uint32_t *events, uint64_t n, uint32_t n_ids, con
     if (!viol)
         return;
     // the violation count lands in ctl->n_viol
-    launch_excl_scan(L.tcnt, L.ptiles, L.offs, reinterpret_cast<uint64_t *>(&ctl->n_viol), L.xscan,
-                     ctl->tickets[10], s, true);
-    launch_flag_scatter(L.fw, L.offs, L.ptiles, BLOCK, viol, s);
+    launch_flag_list(FlagList{L.fw, L.tcnt, L.offs, L.xscan, L.ptiles}, BLOCK, viol, ctl, ctl->tickets[10], s);
 }
 
 void launch_bucket_check(const uint32_t *events, uint64_t n, uint32_t n_ids, const uint8_t *init, uint8_t *status,
@@ -1458,9 +1456,7 @@ void wide_replay(const WideLayout &L, uint64_t n, R *status, uint8_t *flag, uint
         k_replay_status<R><<<grid, BLOCK, 0, s>>>(L.li16, L.tpre, L.base, L.nb, n, (const R *)L.res, status, flag, L.fw,
                                                   L.tcnt, L.ptiles);
     }
-    launch_excl_scan(L.tcnt, L.ptiles, L.offs, reinterpret_cast<uint64_t *>(&ctl->n_viol), L.xscan, ctl->tickets[10], s,
-                     true);
-    launch_flag_scatter(L.fw, L.offs, L.ptiles, BLOCK, viol, s);
+    launch_flag_list(FlagList{L.fw, L.tcnt, L.offs, L.xscan, L.ptiles}, BLOCK, viol, ctl, ctl->tickets[10], s);
 }
 
 } // namespace

@@ -117,16 +117,28 @@ __global__ __launch_bounds__(BLOCK) void k_compact(const uint8_t *__restrict__ s
 
 // Violation indices from per-thread flag words of 16 consecutive events (flag mask |
 // the thread's offset among its tile's flagged events << 16) and the tiles' offsets
-// among all flagged events (ntiles + 1 entries).  Each thread lists its flagged indices
-// in LDS at its offset, then the tile's run is written out contiguously.
-template <int TB>
+// among all flagged events: offs (ntiles + 1 entries), or, without it, the sums of the
+// tiles' counts tcnt, which every workgroup works out (one workgroup a tile), the last one
+// the whole number.  Each thread lists its flagged indices in LDS at its offset, then the
+// tile's run is written out contiguously.
+template <int TB, bool SUM>
 __global__ __launch_bounds__(TB) void k_flag_scatter(const uint32_t *__restrict__ fw, const uint64_t *__restrict__ offs,
-                                                     uint64_t ntiles, uint32_t *__restrict__ viol)
+                                                     const uint32_t *__restrict__ tcnt, uint64_t ntiles,
+                                                     uint32_t *__restrict__ viol, unsigned long long *n_viol)
 {
     constexpr uint32_t TE = TB * FLAG_EVENTS; // events per tile
     __shared__ uint32_t s_idx[TE];
     for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const uint64_t o0 = offs[tile], total = offs[tile + 1] - o0;
+        uint64_t o0, total;
+        if constexpr (SUM) {
+            o0 = sum_before<TB>(tcnt, (uint32_t)tile);
+            total = tcnt[tile];
+            if (tile + 1 == ntiles && threadIdx.x == 0)
+                *n_viol = o0 + total;
+        } else {
+            o0 = offs[tile];
+            total = offs[tile + 1] - o0;
+        }
         if (total == 0)
             continue; // uniform: no flagged event in the tile
         const uint32_t word = fw[tile * TB + threadIdx.x];
@@ -147,19 +159,31 @@ __global__ __launch_bounds__(TB) void k_flag_scatter(const uint32_t *__restrict_
     }
 }
 
+template <int TB>
+void flag_list(const FlagList &F, uint32_t *viol, Control *ctl, uint32_t *ticket, hipStream_t s)
+{
+    auto *const n_viol = &ctl->n_viol;
+    if (F.tiles <= SUM_TILES) {
+        ProfScope prof_(s, "flag_scatter");
+        k_flag_scatter<TB, true><<<(unsigned)F.tiles, TB, 0, s>>>(F.fw, nullptr, F.tcnt, F.tiles, viol, n_viol);
+        return;
+    }
+    launch_excl_scan(F.tcnt, F.tiles, F.offs, reinterpret_cast<uint64_t *>(n_viol), F.xscan, ticket, s, true);
+    ProfScope prof_(s, "flag_scatter");
+    const unsigned grid = (unsigned)(F.tiles < 8192 ? F.tiles : 8192);
+    k_flag_scatter<TB, false><<<grid, TB, 0, s>>>(F.fw, F.offs, F.tcnt, F.tiles, viol, nullptr);
+}
+
 } // namespace
 
-void launch_flag_scatter(const uint32_t *fw, const uint64_t *offs, uint64_t ntiles, int tb, uint32_t *viol,
-                         hipStream_t s)
+void launch_flag_list(const FlagList &F, int tb, uint32_t *viol, Control *ctl, uint32_t *ticket, hipStream_t s)
 {
-    if (!ntiles)
+    if (!F.tiles)
         return;
-    ProfScope prof_(s, "flag_scatter");
-    const unsigned grid = (unsigned)(ntiles < 8192 ? ntiles : 8192);
     if (tb == 512)
-        k_flag_scatter<512><<<grid, 512, 0, s>>>(fw, offs, ntiles, viol);
+        flag_list<512>(F, viol, ctl, ticket, s);
     else
-        k_flag_scatter<256><<<grid, 256, 0, s>>>(fw, offs, ntiles, viol);
+        flag_list<256>(F, viol, ctl, ticket, s);
 }
 
 // (the most a trace of n events or fewer takes: a shorter one by single parts)

@@ -214,16 +214,27 @@ struct ProbeOut {
     __device__ void chunk(uint32_t, const uint32_t *) const {}
 };
 
-// ascending indices of the flagged events, one wave per tile
+// ascending indices of the flagged events, one wave per tile (SUM: the tiles' offsets are
+// the sums of their counts, worked out by every workgroup for its own)
+template <bool SUM>
 __global__ __launch_bounds__(BLOCK) void k_mask_scatter(const uint64_t *__restrict__ masks, uint64_t n,
-                                                        const uint64_t *__restrict__ offs, uint64_t ntiles,
-                                                        uint32_t *__restrict__ viol)
+                                                        const uint64_t *__restrict__ offs,
+                                                        const uint32_t *__restrict__ tcnt, uint64_t ntiles,
+                                                        uint32_t *__restrict__ viol, unsigned long long *n_viol)
 {
-    constexpr uint32_t STEPS = D_TILE / WAVE;
+    constexpr uint32_t STEPS = D_TILE / WAVE, WAVES = BLOCK / WAVE;
     const uint32_t lane = lane_id(), wave = threadIdx.x / WAVE;
-    for (uint64_t t = (uint64_t)blockIdx.x * (BLOCK / WAVE) + wave; t < ntiles;
-         t += (uint64_t)gridDim.x * (BLOCK / WAVE)) {
-        uint64_t o = offs[t];
+    uint64_t before = 0;
+    if constexpr (SUM) { // (one tile a wave)
+        const uint32_t t0 = blockIdx.x * WAVES;
+        before = sum_before<BLOCK>(tcnt, t0);
+        for (uint32_t w = 0; w < wave; w++)
+            before += t0 + w < ntiles ? tcnt[t0 + w] : 0u;
+    }
+    for (uint64_t t = (uint64_t)blockIdx.x * WAVES + wave; t < ntiles; t += (uint64_t)gridDim.x * WAVES) {
+        uint64_t o = SUM ? before : offs[t];
+        if (SUM && t + 1 == ntiles && lane == 0)
+            *n_viol = o + tcnt[t];
         const uint64_t nsteps = ceil_div(n, (uint64_t)WAVE);
         const uint64_t mine = lane < STEPS && t * STEPS + lane < nsteps ? masks[t * STEPS + lane] : 0ull;
 #pragma unroll
@@ -378,11 +389,17 @@ void launch_dense_check(const uint32_t *events, uint64_t n, uint32_t n_ids, cons
     if (!n)
         return;
     launch_apply(T, L.R, TraceOut{status, L.masks, L.tcnt, 0, 0}, s);
+    const uint64_t blocks = ceil_div(L.tiles, BLOCK / WAVE);
+    if (L.tiles <= SUM_TILES) {
+        ProfScope p(s, "mask_scatter");
+        k_mask_scatter<true><<<(unsigned)blocks, BLOCK, 0, s>>>(L.masks, n, nullptr, L.tcnt, L.tiles, viol, &ctl->n_viol);
+        return;
+    }
     launch_excl_scan(L.tcnt, L.tiles, L.offs, reinterpret_cast<uint64_t *>(&ctl->n_viol), L.xscan, ctl->tickets[10], s,
                      true);
     ProfScope p(s, "mask_scatter");
-    const uint64_t blocks = ceil_div(L.tiles, BLOCK / WAVE);
-    k_mask_scatter<<<(unsigned)(blocks < 8192 ? blocks : 8192), BLOCK, 0, s>>>(L.masks, n, L.offs, L.tiles, viol);
+    k_mask_scatter<false><<<(unsigned)(blocks < 8192 ? blocks : 8192), BLOCK, 0, s>>>(L.masks, n, L.offs, L.tcnt, L.tiles,
+                                                                                      viol, nullptr);
 }
 
 size_t dense_words_scratch_bytes(uint64_t tiles, uint32_t n_ids, bool probes)

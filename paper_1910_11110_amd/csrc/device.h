@@ -438,6 +438,26 @@ __device__ __forceinline__ uint64_t lb_column_sum(const uint64_t *lb, uint64_t s
     }
 }
 
+// The sum of the first n counts, by a workgroup of TB threads (the same in every thread).
+template <int TB>
+__device__ __forceinline__ uint32_t sum_before(const uint32_t *__restrict__ cnt, uint32_t n)
+{
+    __shared__ uint32_t s_sum[TB / WAVE];
+    uint32_t v = 0;
+#pragma unroll 4
+    for (uint32_t i = threadIdx.x; i < n; i += TB)
+        v += cnt[i];
+    v = wave_total_u32(v);
+    if (lane_id() == 0)
+        s_sum[threadIdx.x / WAVE] = v;
+    __syncthreads();
+    uint32_t sum = 0;
+#pragma unroll
+    for (int w = 0; w < TB / WAVE; w++)
+        sum += s_sum[w];
+    return sum;
+}
+
 // Dynamic tile tickets.  One counter per group of workgroups (blockIdx mod
 // TICKET_GROUPS, the round-robin the dispatcher uses across the XCDs), each on its own
 // 128-byte line, so that tickets do not serialize on a single address: group g's k-th

@@ -150,13 +150,24 @@ void launch_compact(const uint8_t *status, uint64_t n, uint32_t *viol, void *scr
                     const unsigned long long *flagged = nullptr, const unsigned long long *n_dev = nullptr,
                     bool lookback_cleared = false);
 
-// violation indices from per-thread flag words over FLAG_EVENTS consecutive events each
-// (flag mask | the thread's offset among the flagged events of its tile << 16; tb = 256
-// or 512 threads per tile, fw[tile * tb + thread]) and the tiles' offsets among all
-// flagged events (offs: ntiles + 1 entries, the exclusive scan of the tile counts)
+// violation indices (their number into ctl->n_viol) from per-thread flag words over
+// FLAG_EVENTS consecutive events each (flag mask | the thread's offset among the flagged
+// events of its tile << 16; tb = 256 or 512 threads per tile, fw[tile * tb + thread]) and
+// the tiles' counts; offs (tiles + 1 entries), xscan (zeroed by the caller, as is the ticket
+// counter) are the scan's of more than SUM_TILES tiles
 constexpr int FLAG_EVENTS = 16;
-void launch_flag_scatter(const uint32_t *fw, const uint64_t *offs, uint64_t ntiles, int tb, uint32_t *viol,
-                         hipStream_t s);
+struct FlagList {
+    const uint32_t *fw, *tcnt;
+    uint64_t *offs;
+    void *xscan;
+    uint64_t tiles;
+};
+void launch_flag_list(const FlagList &F, int tb, uint32_t *viol, Control *ctl, uint32_t *ticket, hipStream_t s);
+// Up to so many tiles a workgroup sums the counts before its own one by itself: at 4,096
+// that is 16 loads a thread, less than the launch of a scan (whole checks: 10^4 events x 64
+// ids 16.5 us with the scan and 13.1 without, 2^21 x 4,096 52.0 and 46.1, 2^24 x 2^20, at
+// 4,096 tiles, 211.9 and 204.4).
+constexpr uint64_t SUM_TILES = 4096;
 
 // ------------------------------- translation --------------------------------------
 // sort items of the declarations: key = variable, fcode = the declaration's effect

@@ -150,7 +150,7 @@ __device__ __forceinline__ uint32_t bits20(uint32_t lo, uint32_t hi, uint32_t k)
     return (uint32_t)(v >> (20 * k)) & PL_MASK;
 }
 
-// flag words per scatter tile (k_flag_scatter<512> or <256>)
+// flag words per scatter tile (512 or 256)
 template <int EP>
 constexpr uint32_t scatter_threads()
 {
@@ -513,11 +513,9 @@ void launch_small_check(const uint32_t *events, uint64_t n, uint32_t n_ids, cons
         kernel<<<grid, SB, 0, s>>>(events, n, n_ids, init, status, final_out, L.lbv, L.tcnt, L.fw, ctl->tickets[7],
                                    L.tiles, ctl);
     }
-    // the violation count lands in ctl->n_viol
-    launch_excl_scan(L.tcnt, L.stiles, L.offs, reinterpret_cast<uint64_t *>(&ctl->n_viol), L.xscan, ctl->tickets[8],
-                     s, true);
-    launch_flag_scatter(L.fw, L.offs, L.stiles, is_long ? (int)scatter_threads<EP_LONG>() : (int)scatter_threads<EP_SHORT>(),
-                        viol, s);
+    launch_flag_list(FlagList{L.fw, L.tcnt, L.offs, L.xscan, L.stiles},
+                     is_long ? (int)scatter_threads<EP_LONG>() : (int)scatter_threads<EP_SHORT>(), viol, ctl,
+                     ctl->tickets[8], s);
 }
 
 } // namespace vc

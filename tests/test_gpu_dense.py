@@ -148,3 +148,19 @@ def test_overlap_events_changed(ctx):
     t.check()
     assert np.array_equal(t.status(), want)
     t.free()
+
+
+@pytest.mark.parametrize("n,n_ids", [(1 << 21, 100), ((1 << 21) + 1, 100), (1 << 25, 64), ((1 << 25) + 1, 64),
+                                     (1 << 24, 70_000), ((1 << 24) + 1, 70_000)])
+def test_list_by_sums_and_by_scan(ctx, n, n_ids):
+    """The last traces whose violation list is placed by sums of the tiles' counts, and the
+    first ones that take a scan, on each of the three plain checks."""
+    from paper_1910_11110_amd import vcheck as V
+    print(f"[list] {n} x {n_ids}", flush=True)
+    e = gen.plain_events(n, n_ids, n_ids)
+    t = V.Trace.load(ctx, e, n_ids)
+    t.check()
+    ref = O.check(e, n_ids)
+    v = t.violations()
+    assert v.total == ref.violations.size and np.array_equal(v.indices, ref.violations) and v.first == ref.first
+    t.free()
