@@ -29,15 +29,8 @@ struct BucketLayout {
     uint2 *order = nullptr; // per ticket: bucket tile (bucket-major index), (index in bucket | bucket << 22)
     uint32_t *gsum = nullptr, *gpre = nullptr; // per tile range: bucket counts, their column prefix
     uint64_t *lbv = nullptr;
-    // trace check: per partition tile the count of flagged events and its offset among
-    // all of them; per thread of a tile its flag word (mask | offset inside the tile << 16)
-    uint32_t *tcnt = nullptr, *fw = nullptr;
-    uint64_t *offs = nullptr;
-    void *xscan = nullptr; // scratch of the scan of the tile counts
     uint32_t *part = nullptr;
     uint32_t *dstidx = nullptr; // per word: its position in the partitioned order
-    uint16_t *li16 = nullptr;   // per word: its position in its tile's bucket-sorted order
-    uint32_t *tpre = nullptr;   // per partition tile: start of every bucket's run
     uint8_t *res = nullptr;
     uint64_t ptiles = 0, btiles_max = 0;
 };
@@ -46,20 +39,6 @@ uint32_t bucket_max_ids();
 int bucket_bits_for(uint32_t n_ids);
 size_t bucket_scratch_bytes(uint64_t n, uint32_t n_ids);
 BucketLayout bucket_layout(void *scratch, uint64_t n, uint32_t n_ids);
-
-// plain check of n events over n_ids <= bucket_max_ids() ids: status bytes in program
-// order, final table (holding the initial statuses, or filled by fin_fill in the set-up
-// launch), violations (count into ctl->n_viol).  Resets ctl first.
-void launch_bucket_check(const uint32_t *events, uint64_t n, uint32_t n_ids, const uint8_t *init, uint8_t *status,
-                         uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl, hipStream_t s, int cu,
-                         const FillJob *fin_fill);
-
-// the same over the combined stream of a trace over overlapping arrays (its events
-// with the induced RW items, op 5, after every write): one status byte per item.  With
-// viol null (either entry point), no violation list is made and ctl->n_viol stays 0.
-void launch_bucket_check_combined(const uint32_t *words, uint64_t m, uint32_t n_ids, const uint8_t *init,
-                                  uint8_t *status, uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl,
-                                  hipStream_t s, int cu, const FillJob *fin_fill);
 
 // status of each declaration's abstract variable before it, in program order, and the
 // final status of every abstract variable (final_out pre-filled by the caller; may be
@@ -83,8 +62,8 @@ DeclPre launch_bucket_decl_pre_partitioned(const uint32_t *decls, uint64_t n_dec
                                            uint8_t *final_out, void *scratch, Control *ctl, hipStream_t s, int cu,
                                            uint32_t *chunk_sum, bool lookback_cleared = false,
                                            hipEvent_t after_hist = nullptr);
-// the status byte of every word of a combined stream (as launch_bucket_check_combined),
-// left in the partitioned order with every word's destination there (res, dstidx), or
+// the status byte of every word of a combined stream (the events of a trace over arrays
+// with the induced RW items, op 5, after every write), left in the partitioned order with every word's destination there (res, dstidx), or
 // in program order in direct_out (m bytes) when all ids fall in one bucket (dstidx
 // null); final statuses into final_out; no violations, no replay.  ctl is reset first,
 // in the same launch as fin_fill when given (the fill of final_out for ids no word

@@ -1,11 +1,15 @@
-// bucket.hip -- segmented scan by variable for large id spaces, in three passes
-// over 32-bit words (gfx950).
+// bucket.hip -- partition of 32-bit words by buckets of ids, and the segmented scan of the
+// buckets by sorting (gfx950).
 //
-// 1. partition: one stable pass splits the words by bucket = id >> 12 (at most 1024
-//    buckets).  A histogram per static range of tiles and a column scan give every
-//    range the start of each bucket's run; each range's workgroup then ranks the words
-//    of its tiles by bucket with wave64 ballots, reorders them in LDS, writes every
-//    bucket's run contiguously and stores each word's destination for step 3.
+// The scan by sorting takes the declarations of a translation, whose ids are skewed, and
+// combined streams over more ids than the dense check holds; plain traces and k memory
+// spaces over as many only use the partition and the replay (their buckets are scanned in
+// LDS tables, wide.hip).
+// 1. partition: one stable pass splits the words by bucket of ids (at most 1024 buckets).
+//    A histogram per static range of tiles and a column scan give every range the start of
+//    each bucket's run; each range's workgroup then ranks the words of its tiles by bucket with wave64 ballots, reorders
+//    them in LDS, writes every bucket's run contiguously and stores what step 3 needs:
+//    each word's destination, or the order of its tile.
 // 2. bucket scan: every bucket (4096 ids) is scanned in its own tiles.  A tile sorts
 //    its words by the low 12 id bits in LDS (three stable 4-bit counting passes), runs a
 //    segmented scan of the transition functions, and chains the dense per-id state of
@@ -13,9 +17,9 @@
 //    carry 20 ids each (3-bit codes: a transition function of the 7-element monoid,
 //    or a status) plus their own readiness flag.  The result byte of every word goes
 //    back to its position in the partitioned order.
-// 3. replay: every word's result byte is gathered through its destination into
-//    program order and handed to the consumer (status bytes and violation compaction
-//    for a trace; the pre-statuses of the declarations for a translation).
+// 3. results: the consumer reads a word's result byte through its destination, or they are
+//    replayed into program order (pre-statuses of declarations; status bytes and flagged
+//    events of a trace, by the tiles' orders).
 #include "bucket.h"
 
 #include <algorithm>
@@ -1118,14 +1122,8 @@ static BucketLayout carve(char *p0, uint64_t n, uint32_t n_ids, size_t *bytes)
     L.tbase = (uint32_t *)take((MAX_BUCKETS + 1) * 4);
     L.order = (uint2 *)take(btiles * 8);
     L.lbv = (uint64_t *)take(btiles * LB_WORDS * 8);
-    L.tcnt = (uint32_t *)take(ptiles * 4);
-    L.offs = (uint64_t *)take((ptiles + 1) * 8);
-    L.xscan = take(excl_scan_scratch_bytes(ptiles));
-    L.fw = (uint32_t *)take(ptiles * BLOCK * 4);
     L.part = (uint32_t *)take((n ? n : 1) * 4);
     L.dstidx = (uint32_t *)take((n ? n : 1) * 4);
-    L.li16 = (uint16_t *)take((n ? n : 1) * 2);
-    L.tpre = (uint32_t *)take(ptiles * nb * 4);
     L.res = (uint8_t *)take(n ? n : 1);
     L.ptiles = ptiles;
     L.btiles_max = btiles;
@@ -1161,7 +1159,7 @@ template <class SRC>
 static void partition_and_scan(const uint32_t *src, uint64_t n, uint32_t n_ids, const uint8_t *init, int mode,
                                uint8_t *final_out, const BucketLayout &L, uint8_t *direct_out, Control *ctl,
                                hipStream_t s, int cu, uint32_t *chunk_sum = nullptr, uint32_t final_dup = 0,
-                               bool lookback_cleared = false, hipEvent_t after_hist = nullptr, bool dest = false)
+                               bool lookback_cleared = false, hipEvent_t after_hist = nullptr)
 {
     if (!lookback_cleared)
         launch_clear_lookback(L.lbv, L.btiles_max * LB_WORDS, ctl->tickets[9], s);
@@ -1196,19 +1194,9 @@ static void partition_and_scan(const uint32_t *src, uint64_t n, uint32_t n_ids, 
     uint8_t *res = direct_out;
     if (L.nb > 1) {
         ProfScope p(s, "partition");
-        // the trace check replays by tile runs, the translation (and a reader of the
-        // partitioned results, dest) by destinations
-        const bool runs = mode == BK_STATUS && !dest;
-        if (small_nb)
-            k_partition<256><<<nranges, BLOCK, 0, s>>>(src, n, LBITS, L.bits, L.base, L.gpre, nranges,
-                                                            L.part, runs ? nullptr : L.dstidx,
-                                                            runs ? L.li16 : nullptr, runs ? L.tpre : nullptr, L.ptiles,
-                                                            ctl);
-        else
-            k_partition<MAX_BUCKETS><<<nranges, BLOCK, 0, s>>>(src, n, LBITS, L.bits, L.base, L.gpre, nranges,
-                                                                    L.part, runs ? nullptr : L.dstidx,
-                                                                    runs ? L.li16 : nullptr, runs ? L.tpre : nullptr,
-                                                                    L.ptiles, ctl);
+        const auto kernel = small_nb ? k_partition<256> : k_partition<MAX_BUCKETS>;
+        kernel<<<nranges, BLOCK, 0, s>>>(src, n, LBITS, L.bits, L.base, L.gpre, nranges, L.part, L.dstidx, nullptr,
+                                         nullptr, L.ptiles, ctl);
         part = L.part;
         res = L.res;
     }
@@ -1227,59 +1215,6 @@ static void partition_and_scan(const uint32_t *src, uint64_t n, uint32_t n_ids, 
             k_bucket_scan<BK_STATUS, SRC><<<grid, BLOCK, 0, s>>>(part, n_ids, L.nb, L.base, L.tbase, init, res,
                                                                  final_out, final_dup, L.lbv, ctl->tickets[9], L.order);
     }
-}
-
-template <class SRC>
-static void bucket_check(const uint32_t *events, uint64_t n, uint32_t n_ids, const uint8_t *init, uint8_t *status,
-                         uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl, hipStream_t s, int cu,
-                         const FillJob *fin_fill)
-{
-    BucketLayout L = bucket_layout(scratch, n, n_ids);
-    // one set-up launch: the control block, the look-back words of the bucket scan and of
-    // the scan after it (or of the compaction, which the flag words' area holds: 1 KiB
-    // per tile against its 8 bytes per tile), and the caller's fill of the final table
-    FillJob jobs[3];
-    int nj = 0;
-    jobs[nj++] = FillJob{L.lbv, (size_t)L.btiles_max * LB_WORDS * sizeof(uint64_t), 0};
-    if (L.nb == 1)
-        jobs[nj++] = FillJob{L.fw, compact_scratch_bytes(n), 0};
-    else
-        jobs[nj++] = FillJob{L.xscan, excl_scan_scratch_bytes(L.ptiles), 0};
-    if (fin_fill)
-        jobs[nj++] = *fin_fill;
-    launch_prep(ctl, nullptr, jobs, nj, s);
-    if (n == 0)
-        return;
-    partition_and_scan<SRC>(events, n, n_ids, init, BK_STATUS, final_out, L, status, ctl, s, cu, nullptr, 0, true);
-    if (L.nb == 1) {
-        if (viol)
-            launch_compact(status, n, viol, L.fw, ctl, s, nullptr, nullptr, true);
-        return;
-    }
-    {
-        ProfScope p(s, "replay_status");
-        const unsigned grid = resident_grid((const void *)k_replay_status<uint8_t>, L.ptiles);
-        k_replay_status<uint8_t><<<grid, BLOCK, 0, s>>>(L.li16, L.tpre, L.base, L.nb, n, L.res, status, nullptr, L.fw,
-                                                        L.tcnt, L.ptiles);
-    }
-    if (!viol)
-        return;
-    // the violation count lands in ctl->n_viol
-    launch_flag_list(FlagList{L.fw, L.tcnt, L.offs, L.xscan, L.ptiles}, BLOCK, viol, ctl, ctl->tickets[10], s);
-}
-
-void launch_bucket_check(const uint32_t *events, uint64_t n, uint32_t n_ids, const uint8_t *init, uint8_t *status,
-                         uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl, hipStream_t s, int cu,
-                         const FillJob *fin_fill)
-{
-    bucket_check<EventWords>(events, n, n_ids, init, status, final_out, viol, scratch, ctl, s, cu, fin_fill);
-}
-
-void launch_bucket_check_combined(const uint32_t *words, uint64_t m, uint32_t n_ids, const uint8_t *init,
-                                  uint8_t *status, uint8_t *final_out, uint32_t *viol, void *scratch, Control *ctl,
-                                  hipStream_t s, int cu, const FillJob *fin_fill)
-{
-    bucket_check<CombinedWords>(words, m, n_ids, init, status, final_out, viol, scratch, ctl, s, cu, fin_fill);
 }
 
 void launch_bucket_decl_pre(const uint32_t *decls, uint64_t n_decl, uint32_t n_vars, uint8_t *pre, uint8_t *final_out,
@@ -1309,7 +1244,7 @@ DeclPre launch_bucket_status_partitioned_combined(const uint32_t *words, uint64_
     if (m == 0)
         return DeclPre{direct_out, nullptr};
     partition_and_scan<CombinedWords>(words, m, n_ids, init, BK_STATUS, final_out, L, direct_out, ctl, s, cu, nullptr,
-                                      0, true, nullptr, true);
+                                      0, true);
     if (L.nb == 1)
         return DeclPre{direct_out, nullptr};
     return DeclPre{L.res, L.dstidx};

@@ -10,8 +10,8 @@ namespace vc {
 // The events of bucket b (ids with id >> bits == b) lie at part[base[b], base[b + 1]) in
 // their order; a chunk is at most `per` events of one bucket.  The bases and the chunks
 // come from the buckets' counts (tot, nb <= 1024): cbase[b] is bucket b's first chunk (nb +
-// 1 entries), cb[c] chunk c's bucket, marked when
-// it is the bucket's first (wide_max_chunks entries).
+// 1 entries), cb[c] chunk c's bucket, marked when it is the bucket's first
+// (wide_max_chunks entries).
 struct WideChunks {
     const uint32_t *part;
     const uint32_t *tot;
