@@ -64,6 +64,7 @@ struct BatchState {
     // dense route (a batch that could take the bucket route, every trace over few enough
     // ids): h_chunks are the traces' with arrays, h_dense the chunks that are walked
     bool dense = false;
+    uint32_t strands = 0; // chunks checked by strands: the first of h_dense
     uint32_t class_at[DENSE_CLASSES + 1] = {};
     uint64_t row_words = 0, grp_words = 0;
     uint64_t MB = 0; // combined slots: every trace's range padded to a multiple of 16
@@ -191,7 +192,7 @@ void tune_store(const std::string &key, const SortTuning &t, unsigned scan_grid)
 // chooses the route: the bucket engine when every trace has between 1 and
 // bucket_max_ids() ids and its items fit 32-bit positions, the dense route when all of
 // them have so few ids that a wave holds their statuses in LDS (1,024 traces over 8 to
-// 65,536 ids, 110 M events: 2,133 us of kernels by buckets, 1,012 dense); then every trace's first
+// 65,536 ids, 110 M events: 2,133 us of kernels by buckets, 950 dense); then every trace's first
 // combined position (its range padded to a multiple of 16 slots, so that every trace's
 // items start 16-byte aligned in the status bytes) and first key inside its group, and
 // the groups (consecutive traces whose ids fit one key space)
@@ -233,7 +234,9 @@ void plan_groups(BatchState &b, std::vector<TraceDesc> &desc)
     b.groups.push_back(g);
 }
 
-// The dense route's chunks, rows and prefix jobs.  A chunk has the events that give every
+// The dense route's chunks, rows and prefix jobs.  Plain traces over few ids are checked by
+// strands (1,024 traces, 23 M of their 110 M events in such: kernels 1,018 us without,
+// 950 with).  A chunk of the others has the events that give every
 // wave the device holds of its class one chunk, but no more than plain_chunk and no fewer
 // than 512, and at least as many as its row has ids over 8 (a quarter of that in a batch
 // that leaves the device idle): below that its row's traffic would outweigh its events'.
@@ -249,16 +252,26 @@ void plan_dense(BatchState &b, std::vector<TraceDesc> &desc)
             k++;
         return k;
     };
-    for (TraceDesc &d : desc) {
+    auto by_strands = [](const TraceDesc &d) { return !d.off && d.n && d.n_ids <= small_max_ids(); };
+    for (uint32_t t = 0; t < (uint32_t)desc.size(); t++) {
+        TraceDesc &d = desc[t];
         d.row = (uint32_t)(((d.n_ids + 7) / 8 + 63) & ~63u);
-        items[class_of(d.row)] += d.m;
+        if (!by_strands(d)) {
+            items[class_of(d.row)] += d.m;
+            continue;
+        }
+        d.first_dense = b.h_dense.size();
+        for (uint64_t a = 0; a < d.n; a += strand_chunk())
+            b.h_dense.push_back(ChunkDesc{a, t, (uint32_t)std::min<uint64_t>(strand_chunk(), d.n - a)});
+        d.dense_chunks = (uint32_t)(b.h_dense.size() - d.first_dense);
     }
+    b.strands = (uint32_t)b.h_dense.size();
     for (int k = 0; k < DENSE_CLASSES; k++) {
         b.class_at[k] = (uint32_t)b.h_dense.size();
         const uint64_t share = items[k] / dense_class_waves(k);
         for (uint32_t t = 0; t < (uint32_t)desc.size(); t++) {
             TraceDesc &d = desc[t];
-            if (class_of(d.row) != k)
+            if (by_strands(d) || class_of(d.row) != k)
                 continue;
             const uint64_t most = std::max<uint64_t>(b.plain_chunk, 2 * d.row);
             const uint64_t least = std::max<uint64_t>(BATCH_CHUNK, d.row / 4);
@@ -311,13 +324,13 @@ int reserve_all(BatchState &b, uint32_t n)
     if (b.dense) {
         const uint64_t nd = b.h_dense.size();
         if ((r = devbuf_reserve(b.dchunks, sizeof(ChunkDesc) * nd)) != VC_OK) return r;
-        if ((r = devbuf_reserve(b.jobs, sizeof(PrefixJob) * b.h_jobs.size())) != VC_OK) return r;
-        if ((r = devbuf_reserve(b.rows, 4 * b.row_words)) != VC_OK) return r;
+        if ((r = devbuf_reserve(b.jobs, sizeof(PrefixJob) * std::max<size_t>(b.h_jobs.size(), 1))) != VC_OK) return r;
+        if ((r = devbuf_reserve(b.rows, 4 * (b.row_words ? b.row_words : 1))) != VC_OK) return r;
         if ((r = devbuf_reserve(b.grp, 4 * (b.grp_words ? b.grp_words : 1))) != VC_OK) return r;
         if ((r = devbuf_reserve(b.words, 4 * (b.MB ? b.MB : 1))) != VC_OK) return r;
         if ((r = devbuf_reserve(b.vcnt, 4 * nd)) != VC_OK) return r;
         if ((r = devbuf_reserve(b.vpos, 8 * (nd + 1))) != VC_OK) return r;
-        sc = std::max(sc, excl_scan_scratch_bytes(nd));
+        sc = std::max({sc, excl_scan_scratch_bytes(nd), batch_strands_bytes(b.strands)});
     } else if (b.bucket) {
         // the status bytes go straight to the traces: no batch-wide status or violation
         // arrays
@@ -368,6 +381,7 @@ void enqueue_pipeline(BatchState &b, hipStream_t s)
         DenseBatch B{d, dch, {}, words, (const uint64_t *)b.pos.p, (const PrefixJob *)b.jobs.p, (uint32_t)b.h_jobs.size(),
                      b.grp_words != 0, (uint32_t *)b.rows.p, (uint32_t *)b.grp.p, vcnt};
         std::copy(b.class_at, b.class_at + DENSE_CLASSES + 1, B.class_at);
+        launch_batch_strands(d, dch, b.strands, vcnt, b.scratch.p, b.ctl->tickets[8], s);
         launch_batch_dense(B, s);
         launch_excl_scan(vcnt, nd, vpos, nullptr, b.scratch.p, b.ctl->tickets[7], s);
         launch_batch_chunk_viol(d, dch, nd, vcnt, vpos, true, s);
@@ -433,7 +447,7 @@ int upload(BatchState &b, COPY &&copy)
         e = copy(b.chunks.p, b.h_chunks.data(), sizeof(ChunkDesc) * b.n_chunks);
     if (e == hipSuccess && b.dense)
         e = copy(b.dchunks.p, b.h_dense.data(), sizeof(ChunkDesc) * b.h_dense.size());
-    if (e == hipSuccess && b.dense)
+    if (e == hipSuccess && b.dense && !b.h_jobs.empty())
         e = copy(b.jobs.p, b.h_jobs.data(), sizeof(PrefixJob) * b.h_jobs.size());
     return e == hipSuccess ? VC_OK : vc_hip_fail(e, "hipMemcpy(batch descriptors)");
 }

@@ -71,7 +71,14 @@ void launch_batch_chunk_viol(const TraceDesc *d, const ChunkDesc *ch, uint64_t n
 void launch_batch_finish(const TraceDesc *d, uint32_t n_traces, uint64_t n_chunks, const uint64_t *vpos,
                          const uint8_t *fin_all, const Control *bctl, const unsigned long long *ind, hipStream_t s);
 
-// dense route (every trace over at most DENSE_CLASS[last] * 8 ids): the chunks of all
+// dense route, the traces without arrays over at most small_max_ids() ids and with an event
+// at least: checked by strands, a chunk (strand_chunk() events, a trace's last one the rest) a
+// tile; flagged events per chunk into vcnt.  Scratch of batch_strands_bytes(chunks).
+uint32_t strand_chunk();
+size_t batch_strands_bytes(uint64_t chunks);
+void launch_batch_strands(const TraceDesc *d, const ChunkDesc *ch, uint32_t chunks, uint32_t *vcnt, void *scratch,
+                          uint32_t *ticket, hipStream_t s);
+// dense route, the others (every trace over at most DENSE_CLASS[last] * 8 ids): the chunks of all
 // traces by classes of row sizes, a trace's consecutive; the groups of B_GROUP chunks of
 // every trace, BLOCK words of their rows a job
 constexpr uint32_t B_GROUP = 32;

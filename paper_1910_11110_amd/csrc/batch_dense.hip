@@ -15,8 +15,9 @@
 // Bound like the dense check by the walks' LDS round trips and their instructions.  1,024
 // traces of 100 to 10^6 events over 8 to 65,536 ids, a fifth of them over arrays (110 M
 // events): kernels 2,133 us through the bucket engine (which relocates every event to a
-// word, partitions, scans and takes the results back), 1,012 this way, of them the folds
-// 288, the applies 432 and the words of the traces with arrays 155.
+// word, partitions, scans and takes the results back), 1,018 this way, 950 with the plain
+// traces over few ids by strands (small.hip): of them the folds 243, the applies 356, the
+// strands 55 and the words of the traces with arrays 155.
 #include "batch.h"
 #include "dense_steps.h"
 #include "prof.h"

@@ -360,14 +360,15 @@ __device__ __forceinline__ uint32_t lb_fn_exclusive(uint64_t *lb, uint64_t tile,
 // whole wave for word w.  Publishes the tile's aggregate planes, folds predecessors 64
 // per round (lane q polls tile t - q; lane 0 is the latest, composed outermost) up to
 // the nearest inclusive word, publishes the inclusive planes (aggregate after the
-// entering statuses) and returns the entering statuses as constant planes.  Tile 0
-// enters with `first` (constant planes).  The result is the same in every lane.
-__device__ __forceinline__ Planes lb_planes_exclusive(uint64_t *lb, uint32_t nwords, uint64_t tile, uint32_t w,
-                                                      Planes agg, Planes first)
+// entering statuses) and returns the entering statuses as constant planes.  A chain's first
+// tile (starts) enters with `first` (constant planes); it publishes nothing but its
+// inclusive word, so no look-back goes past it.  The result is the same in every lane.
+__device__ __forceinline__ Planes lb_planes_exclusive(uint64_t *lb, uint32_t nwords, uint64_t tile, bool starts,
+                                                      uint32_t w, Planes agg, Planes first)
 {
     const uint32_t lane = lane_id();
     Planes acc = first;
-    if (tile > 0) {
+    if (!starts) {
         if (lane == 0)
             lb_store(&lb[tile * nwords + w], (agg.t == PL_MASK ? LB_INC : LB_AGG) | pl_pack(agg));
         acc = Planes{0, 0, 0};
@@ -397,7 +398,7 @@ __device__ __forceinline__ Planes lb_planes_exclusive(uint64_t *lb, uint32_t nwo
             t -= (int64_t)s;
         }
     }
-    if (lane == 0 && (tile == 0 || agg.t != PL_MASK))
+    if (lane == 0 && (starts || agg.t != PL_MASK))
         lb_store(&lb[tile * nwords + w], LB_INC | pl_pack(pl_compose(agg, acc)));
     return acc;
 }

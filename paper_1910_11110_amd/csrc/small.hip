@@ -20,6 +20,7 @@
 //      statuses come from the last tile.  The count of flagged events and, per 16 events,
 //      their mask and offset inside the tile are stored; a scan of the counts and a scatter
 //      pass then write the ascending violation indices (no second chain of tiles).
+#include "batch.h"
 #include "device.h"
 #include "internal.h"
 #include "prof.h"
@@ -162,13 +163,51 @@ constexpr uint32_t scatter_threads()
 // events a lane in registers, with 64-bit planes, took about 100 instructions per event:
 // 2^28 events x 64 variables 877 us, 746 with words final at once, 391 this way (3.4 TB/s
 // of events in and status bytes out); 2^26 events 229 and 110 us; 10^4 events 12.8 and 10.7.
-template <int EP>
-__global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__ ev, uint64_t n, uint32_t n_ids,
-                                                       const uint8_t *__restrict__ init, uint8_t *__restrict__ status,
-                                                       uint8_t *__restrict__ final_out,
-                                                       uint64_t *__restrict__ lbv, uint32_t *__restrict__ tcnt,
-                                                       uint32_t *__restrict__ fw, uint32_t *__restrict__ ticket,
-                                                       uint64_t ntiles, Control *ctl)
+//
+// SRC: the traces.  OneTrace: one, whose flagged events are left as flag words and counts of
+// the scatter tiles.  BatchStrands: a batch's traces over few ids, a chunk a tile (consecutive
+// ones of a trace), whose flagged events are counted per tile; 200 of them of 100 to 10^6
+// events (23 M) take 55 us, 120 by the walks of the dense check.
+struct StrandTile {
+    const uint32_t *ev;
+    uint64_t n; // of the trace
+    uint32_t n_ids;
+    const uint8_t *init;
+    uint8_t *status, *final_out;
+    Control *ctl;
+    uint64_t first; // event
+    bool starts, ends; // the trace
+};
+struct OneTrace {
+    const uint32_t *ev;
+    uint64_t n;
+    uint32_t n_ids;
+    const uint8_t *init;
+    uint8_t *status, *final_out;
+    Control *ctl;
+    uint32_t *fw;
+    static constexpr bool FLAGS = true;
+    __device__ StrandTile tile(uint32_t t, uint64_t ntiles, uint64_t events) const
+    {
+        return StrandTile{ev, n, n_ids, init, status, final_out, ctl, t * events, t == 0, t + 1 == ntiles};
+    }
+};
+struct BatchStrands {
+    const TraceDesc *d;
+    const ChunkDesc *ch;
+    static constexpr bool FLAGS = false;
+    __device__ StrandTile tile(uint32_t t, uint64_t, uint64_t) const
+    {
+        const ChunkDesc c = ch[t];
+        const TraceDesc &T = d[c.trace];
+        return StrandTile{T.events, T.n, T.n_ids, T.init, T.status, T.fin, T.ctl, c.start, c.start == 0,
+                          c.start + c.len == T.n};
+    }
+};
+
+template <int EP, class SRC>
+__global__ __launch_bounds__(SB) void k_small_check(SRC S, uint64_t *__restrict__ lbv, uint32_t *__restrict__ tcnt,
+                                                    uint32_t *__restrict__ ticket, uint64_t ntiles)
 {
     constexpr int ROW = EP / 2 + 4;          // words of a lane's packed events, padded (16-byte rows on all banks)
     constexpr int WE = WAVE * EP;            // events of a wave
@@ -198,7 +237,11 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
         const uint32_t tile = take_ticket(ticket, &s_tile);
         if (tile >= ntiles)
             break;
-        const uint64_t wb = ((uint64_t)tile * SW + wave) * WE; // the wave's first event
+        const StrandTile X = S.tile(tile, ntiles, (uint64_t)SW * WE);
+        const uint32_t *const ev = X.ev;
+        uint8_t *const status = X.status, *const final_out = X.final_out;
+        const uint64_t n = X.n, wb = X.first + wave * WE; // the wave's first event
+        const uint32_t n_ids = X.n_ids;
 
         // ---- 1. the wave's events, four consecutive ones a lane, packed to their rows ----
         uint32_t badm = 0, top = 0;
@@ -262,7 +305,7 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
                 const uint32_t x = g < n ? ev[g] : (uint32_t)OP_NOOP << 24;
                 if ((x >> 28) != 0 || ((x >> 24) & 7u) > OP_NOOP || (x & 0xFFFFFFu) >= n_ids) {
                     if (g < n)
-                        atomicMin(reinterpret_cast<unsigned long long *>(&ctl->err_index_lo), (unsigned long long)g);
+                        atomicMin(reinterpret_cast<unsigned long long *>(&X.ctl->err_index_lo), (unsigned long long)g);
                     break;
                 }
             }
@@ -311,18 +354,18 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
             const uint32_t past = n_ids > k * 20 + 20 ? 0u : PL_MASK & ~((1u << (n_ids > k * 20 ? n_ids - k * 20 : 0)) - 1u);
             const Planes agg{bits20(alo.t, ahi.t, k) | past, bits20(alo.x, ahi.x, k), bits20(alo.y, ahi.y, k)};
             Planes first{PL_MASK, 0, 0};
-            if (tile == 0) {
+            if (X.starts) {
                 const uint32_t v = k * 20 + lane;
-                const uint32_t s0 = (init && lane < 20 && v < n_ids) ? init[v] : 1u;
+                const uint32_t s0 = (X.init && lane < 20 && v < n_ids) ? X.init[v] : 1u;
                 first.x = (uint32_t)__ballot(s0 & 1u) & PL_MASK;
                 first.y = (uint32_t)__ballot((s0 >> 1) & 1u) & PL_MASK;
             }
-            const Planes st = lb_planes_exclusive(lbv, SPW, tile, k, agg, first);
+            const Planes st = lb_planes_exclusive(lbv, SPW, tile, X.starts, k, agg, first);
             if (lane == 0) {
                 s_in[k][0] = st.x;
                 s_in[k][1] = st.y;
             }
-            if (tile + 1 == ntiles && final_out && lane < 20) {
+            if (X.ends && final_out && lane < 20) {
                 const uint32_t v = k * 20 + lane;
                 const Planes inc = pl_compose(agg, st);
                 if (v < n_ids)
@@ -407,6 +450,12 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
         if (lane == WAVE - 1)
             s_wsum[wave] = inc;
         __syncthreads();
+        if constexpr (!SRC::FLAGS) {
+            if (tid == 0)
+                tcnt[tile] = s_wsum[0] + s_wsum[1] + s_wsum[2] + s_wsum[3];
+            __syncthreads(); // (the next tile's sums)
+            continue;
+        } else {
         constexpr uint32_t TW = scatter_threads<EP>() / (WAVE * GROUPS); // waves per scatter tile
         uint32_t woff = 0, total = 0;
 #pragma unroll
@@ -418,7 +467,7 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
             }
         }
         uint32_t o = woff + inc - cnt;
-        uint32_t *const f = fw + ((uint64_t)tile * SB + tid) * GROUPS;
+        uint32_t *const f = S.fw + ((uint64_t)tile * SB + tid) * GROUPS;
         uint32_t words[GROUPS];
 #pragma unroll
         for (int q = 0; q < GROUPS; q++) {
@@ -433,6 +482,7 @@ __global__ __launch_bounds__(SB) void k_small_check(const uint32_t *__restrict__
                 f[q] = words[q];
         if (lane == 0 && wave % TW == 0)
             tcnt[(uint64_t)tile * (SW / TW) + wave / TW] = total;
+        }
     }
 }
 
@@ -487,8 +537,8 @@ void excl_scan_warm_launch_shape();
 // no host-side allocation
 void small_warm_launch_shapes()
 {
-    (void)resident_grid((const void *)k_small_check<EP_LONG>, 1, 0, SB);
-    (void)resident_grid((const void *)k_small_check<EP_SHORT>, 1, 0, SB);
+    (void)resident_grid((const void *)k_small_check<EP_LONG, OneTrace>, 1, 0, SB);
+    (void)resident_grid((const void *)k_small_check<EP_SHORT, OneTrace>, 1, 0, SB);
     excl_scan_warm_launch_shape();
 }
 
@@ -507,15 +557,31 @@ void launch_small_check(const uint32_t *events, uint64_t n, uint32_t n_ids, cons
         return;
     const bool is_long = strand_of(n) == EP_LONG;
     {
-        const auto kernel = is_long ? k_small_check<EP_LONG> : k_small_check<EP_SHORT>;
+        const auto kernel = is_long ? k_small_check<EP_LONG, OneTrace> : k_small_check<EP_SHORT, OneTrace>;
         const unsigned grid = resident_grid((const void *)kernel, L.tiles, grid_cap, SB);
         ProfScope prof_(s, "small_check");
-        kernel<<<grid, SB, 0, s>>>(events, n, n_ids, init, status, final_out, L.lbv, L.tcnt, L.fw, ctl->tickets[7],
-                                   L.tiles, ctl);
+        kernel<<<grid, SB, 0, s>>>(OneTrace{events, n, n_ids, init, status, final_out, ctl, L.fw}, L.lbv, L.tcnt,
+                                   ctl->tickets[7], L.tiles);
     }
     launch_flag_list(FlagList{L.fw, L.tcnt, L.offs, L.xscan, L.stiles},
                      is_long ? (int)scatter_threads<EP_LONG>() : (int)scatter_threads<EP_SHORT>(), viol, ctl,
                      ctl->tickets[8], s);
+}
+
+uint32_t strand_chunk() { return SB * EP_LONG; }
+size_t batch_strands_bytes(uint64_t chunks) { return chunks * SPW * sizeof(uint64_t); }
+
+void launch_batch_strands(const TraceDesc *d, const ChunkDesc *ch, uint32_t chunks, uint32_t *vcnt, void *scratch,
+                          uint32_t *ticket, hipStream_t s)
+{
+    if (!chunks)
+        return;
+    uint64_t *lbv = reinterpret_cast<uint64_t *>(scratch);
+    launch_clear_lookback(lbv, (size_t)chunks * SPW, ticket, s);
+    ProfScope p(s, "batch_strands");
+    const auto kernel = k_small_check<EP_LONG, BatchStrands>;
+    kernel<<<resident_grid((const void *)kernel, chunks, 0, SB), SB, 0, s>>>(BatchStrands{d, ch}, lbv, vcnt, ticket,
+                                                                            chunks);
 }
 
 } // namespace vc

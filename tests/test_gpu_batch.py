@@ -382,3 +382,28 @@ def test_batch_row_sizes(ctx, n_ids):
             assert_trace(t, ref, f"trace {i}, turn {turn}")
     for t in traces:
         t.free()
+
+
+@pytest.mark.parametrize("n", [1, 63, 16_383, 16_384, 16_385, 50_000])
+def test_batch_traces_over_few_ids(ctx, n):
+    """Traces over 1 to 64 ids around a tile of strands, next to each other, with and without
+    initial statuses, beside ones with arrays, without events and over more ids."""
+    from paper_1910_11110_amd import vcheck as V
+    rng = np.random.default_rng(n)
+    inputs = []
+    for k, ids in enumerate((64, 1, 20, 21, 63, 65)):
+        init = rng.integers(0, 4, ids).astype(np.uint8) if k % 2 else None
+        inputs.append((gen.plain_events(n + k, ids, 60 + k), ids, None, None, init))
+    lo, hi = gen.intervals(40, 9)
+    inputs.insert(3, (gen.plain_events(n, 40, 70), 40, lo, hi, None))
+    inputs.insert(1, (np.zeros(0, np.uint32), 7, None, None, np.arange(7, dtype=np.uint8) & 3))
+    say(f"[batch] {len(inputs)} traces of about {n} events over few ids")
+    traces = load_all(ctx, inputs)
+    refs = [oracle_of(*inp) for inp in inputs]
+    for turn in range(3):
+        V.batch_check(ctx, traces)
+        ctx.sync()
+        for i, (t, ref) in enumerate(zip(traces, refs)):
+            assert_trace(t, ref, f"trace {i}, turn {turn}")
+    for t in traces:
+        t.free()
