@@ -207,10 +207,13 @@ def wl_plain(args, V, ctx, stream, n=None, n_ids=64):
 
     own_io = {
         "small_check": (5 * n + 4 * viol + n_ids, n, "event"),
+        "dense_fold": (4 * n, n, "event"),
+        "dense_apply": (5 * n, n, "event"),
         "bucket_hist": (4 * n, n, "event"),
-        "partition": (12 * n, n, "event"),
-        "bucket_scan": (5 * n + n_ids, n, "event"),
-        "replay_status": (6 * n + 4 * viol, n, "event"),
+        "partition": (10 * n, n, "event"),            # words in; words, positions in the tile out
+        "wide_fold": (4 * n, n, "event"),
+        "wide_apply": (5 * n, n, "event"),
+        "replay_status": (4 * n + n // 4, n, "event"),  # positions and results in; statuses, flag words out
     }
     cfg = {"workload": f"plain-{n}x{n_ids}", "n_events": n, "n_ids": n_ids, "violations": int(viol)}
     return dict(step=step, units=n, unit="event", bytes_alg=bytes_alg, cpu=cpu_sample, config=cfg, keep=(t, te),
