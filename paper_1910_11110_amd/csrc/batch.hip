@@ -71,10 +71,20 @@ __device__ __forceinline__ uint32_t clean_word(const TraceDesc &td, uint32_t e, 
     return e;
 }
 
+struct __attribute__((packed, aligned(8))) Bounds { // two entries of the neighbours' offsets
+    uint64_t begin, end;
+};
+__device__ __forceinline__ Bounds bounds_of(const TraceDesc &td, uint32_t e)
+{
+    Bounds b{0, 0};
+    if (((e >> 24) & 7u) == OP_W)
+        b = *reinterpret_cast<const Bounds *>(td.off + (e & 0xFFFFFFu));
+    return b;
+}
 __device__ __forceinline__ uint32_t induced_of(const TraceDesc &td, uint32_t e)
 {
-    const uint32_t x = e & 0xFFFFFFu;
-    return ((e >> 24) & 7u) == OP_W ? (uint32_t)(td.off[x + 1] - td.off[x]) : 0u;
+    const Bounds b = bounds_of(td, e);
+    return (uint32_t)(b.end - b.begin);
 }
 
 // the wave's index in its workgroup, as a wave-uniform (scalar) value: chunk indices,
@@ -126,7 +136,7 @@ __device__ __forceinline__ uint32_t walk_chunk(const TraceDesc &td, const ChunkD
     // the chunk's events, then the neighbour-list bounds of its writes (loads issued
     // together)
     uint32_t ev[CH_PER];
-    uint64_t ob[CH_PER], oe[CH_PER];
+    Bounds at[CH_PER];
 #pragma unroll
     for (int j = 0; j < CH_PER; j++) {
         const uint32_t k = j * WAVE + lane;
@@ -137,18 +147,15 @@ __device__ __forceinline__ uint32_t walk_chunk(const TraceDesc &td, const ChunkD
         const uint32_t k = j * WAVE + lane;
         if (k < cd.len)
             ev[j] = clean_word(td, ev[j], cd.start + k, report);
-        const uint32_t x = ev[j] & 0xFFFFFFu;
-        const bool wr = ((ev[j] >> 24) & 7u) == OP_W;
-        ob[j] = wr ? td.off[x] : 0;
-        oe[j] = wr ? td.off[x + 1] : 0;
+        at[j] = bounds_of(td, ev[j]);
     }
     uint32_t carry = 0;
 #pragma unroll
     for (int j = 0; j < CH_PER; j++) {
         const uint32_t k = j * WAVE + lane;
-        const uint32_t len = k < cd.len ? 1u + (uint32_t)(oe[j] - ob[j]) : 0u;
+        const uint32_t len = k < cd.len ? 1u + (uint32_t)(at[j].end - at[j].begin) : 0u;
         const uint32_t w = k < cd.len ? ev[j] : 0u;
-        const uint64_t o = ob[j];
+        const uint64_t o = at[j].begin;
         const uint32_t inc = wave_scan_add(len, lane);
         S.start[k] = carry + inc - len;
         S.word[k] = w;
@@ -222,11 +229,11 @@ __global__ __launch_bounds__(BLOCK) void k_batch_chunk_count(const TraceDesc *__
 #pragma unroll
             for (int j = 0; j < CH_PER; j++) {
                 const uint32_t q = j * WAVE + lane;
-                ev[j] = q < cd.len ? clean_word(td, td.events[cd.start + q], 0, false) : ((uint32_t)OP_NOOP << 24);
+                ev[j] = q < cd.len ? td.events[cd.start + q] : ((uint32_t)OP_NOOP << 24);
             }
 #pragma unroll
             for (int j = 0; j < CH_PER; j++)
-                k += induced_of(td, ev[j]);
+                k += induced_of(td, clean_word(td, ev[j], 0, false));
         }
         const uint32_t total = wave_total_u32(k);
         if (lane == 0)
