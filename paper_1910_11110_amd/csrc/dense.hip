@@ -32,6 +32,7 @@ struct TraceChunks {
     const uint32_t *ev;
     uint64_t n, per;
     uint32_t n_ids, row, chunks;
+    __device__ uint32_t op_mask() const { return 0x1F1Fu; }
     __device__ OneChunk<TraceChunks> chunk(uint32_t c) const { return {*this, c}; }
     __device__ Control *report_to(Control *ctl) const { return ctl; }
     __device__ uint32_t count() const { return chunks; }
@@ -60,6 +61,7 @@ struct TileChunks {
     const uint64_t *tpos; // first word of every tile, their number at the end
     uint64_t n, tiles, per;
     uint32_t n_ids, row, chunks;
+    __device__ uint32_t op_mask() const { return 0x7F7Fu; }
     __device__ OneChunk<TileChunks> chunk(uint32_t c) const { return {*this, c}; }
     __device__ Control *report_to(Control *ctl) const { return ctl; }
     __device__ uint32_t count() const { return chunks; }
@@ -265,6 +267,7 @@ uint64_t dense_chunks(uint32_t n_ids)
 struct Rows { // chunks' rows and groups' rows
     uint32_t row, chunks, groups;
     uint32_t *rows, *entering, *grp;
+    uint32_t *left; // chunks that the forward fold leaves to the backward one
 };
 
 class Carve {
@@ -294,6 +297,7 @@ Rows take_rows(Carve &c, uint32_t n_ids, uint32_t chunks, bool keep)
     R.rows = c.take<uint32_t>((size_t)chunks * R.row);
     R.entering = keep ? c.take<uint32_t>((size_t)chunks * R.row) : R.rows;
     R.grp = c.take<uint32_t>((size_t)R.groups * R.row);
+    R.left = c.take<uint32_t>(chunks);
     return R;
 }
 
@@ -310,9 +314,15 @@ void launch_fold(const CHUNKS &T, const Rows &R, Control *ctl, hipStream_t s)
 {
     if (!T.chunks)
         return;
+    const bool forward = T.n_ids > FORWARD_IDS && T.n >= DENSE_FORWARD_FROM;
+    if (forward) {
+        ProfScope p(s, "dense_forward");
+        k_dense_forward<Two, D_PAIR, CHUNKS><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.rows, ctl, R.left);
+    }
     {
         ProfScope p(s, "dense_fold");
-        k_dense_fold<Two, D_PAIR, CHUNKS><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.rows, ctl);
+        k_dense_fold<Two, D_PAIR, CHUNKS>
+            <<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.rows, ctl, forward ? R.left : nullptr);
     }
     launch_groups(R, s);
 }

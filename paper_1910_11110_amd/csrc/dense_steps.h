@@ -450,8 +450,9 @@ __device__ __forceinline__ void load_step_table(uint32_t *s_tab, uint32_t lane)
 // ----------------------------------------------------------------------------------
 // The walks: one wave per chunk.  CHUNKS: the number of chunks, and of a chunk its words
 // (ev + [begin, end)), its row (words of it, and where it lies), the bits of its ids,
-// malformed words, and the table's id of a word (local: of a well-formed one; clamped:
-// inside the table for any).  `table`: words of LDS for the table, a row of any chunk.
+// malformed words (op_mask: bit op + 8 side of the known ones, of chunks that go forwards),
+// and the table's id of a word (local: of a well-formed one; clamped: inside the table for
+// any).  `table`: words of LDS for the table, a row of any chunk.
 // ----------------------------------------------------------------------------------
 // a chunk of a trace, or stream, whose chunks are all alike
 template <class CHUNKS>
@@ -464,16 +465,145 @@ struct OneChunk : CHUNKS {
     }
 };
 
-// every chunk's functions into its row
+// malformed words among a round's: the words' upper bits, their largest id and the bits of
+// their ops in C.op_mask together, then (rarely) one by one
+template <class C>
+__device__ __forceinline__ bool any_bad(const C &c, const uint32_t (&w)[D_UNROLL])
+{
+    uint32_t bits = 0, top = 0, known = 1;
+#pragma unroll
+    for (int u = 0; u < D_UNROLL; u++) {
+        const uint32_t id = w[u] & 0xFFFFFFu;
+        bits |= w[u];
+        top = top > id ? top : id;
+        known &= c.op_mask() >> ((w[u] >> 24) & 31u);
+    }
+    return (bits >> 28) != 0 || top >= c.n_ids || !(known & 1u);
+}
+
+// Whole rounds forwards from round 0, whose words are in nxt, then the words past them one
+// step at a time: out takes every event's result.  A malformed word only has to stay inside
+// the table (what a trace with one comes to is not read); PUT sees the words.
+template <class DIR, int PAIR, class C, class PUT, class OUT>
+__device__ __forceinline__ void walk_forward(const C &c, uint32_t *s_t, const uint32_t *s_tab, uint32_t lane,
+                                             uint32_t (&nxt)[D_UNROLL], PUT &&put, OUT &out)
+{
+    using D = typename DIR::Dom;
+    const uint64_t i0 = c.begin;
+    const uint32_t bits = c.bits, len = (uint32_t)(c.end - i0), rounds = len / (D_UNROLL * WAVE);
+    uint32_t shared_steps = 0;
+    for (uint32_t r = 0; r < rounds; r++) {
+        uint32_t w[D_UNROLL];
+#pragma unroll
+        for (int u = 0; u < D_UNROLL; u++)
+            w[u] = nxt[u];
+        const uint64_t i = i0 + (uint64_t)r * (D_UNROLL * WAVE);
+        if (r + 1 < rounds) {
+            const uint32_t *e = c.ev + i + D_UNROLL * WAVE + lane;
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u++)
+                nxt[u] = e[u * WAVE];
+        }
+        if (shared_steps >= D_TOGETHER) {
+            shared_steps = 0;
+            uint32_t v[PAIR];
+#pragma unroll
+            for (int q = 0; q < PAIR; q++)
+                v[q] = w[q];
+#pragma unroll 1
+            for (int u = 0; u < D_UNROLL; u += PAIR) {
+                Lane<DIR> L[PAIR];
+                uint32_t byte[PAIR], now[PAIR];
+                const int n = u + PAIR < D_UNROLL ? u + PAIR : u;
+#pragma unroll
+                for (int q = 0; q < PAIR; q++) {
+                    now[q] = v[q];
+                    L[q] = make_lane<DIR>(s_t, s_tab, v[q], c.clamped(v[q]), true);
+                    v[q] = c.ev[i + (n + q) * WAVE + lane];
+                }
+                steps_together<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
+#pragma unroll
+                for (int q = 0; q < PAIR; q++)
+                    out.step(lane, u + q, i + (u + q) * WAVE, now[q], byte[q], true);
+            }
+        } else {
+            shared_steps = 0;
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u += PAIR) {
+                Lane<DIR> L[PAIR];
+                uint32_t byte[PAIR];
+#pragma unroll
+                for (int q = 0; q < PAIR; q++)
+                    L[q] = make_lane<DIR>(s_t, s_tab, w[u + q], c.clamped(w[u + q]), true);
+                steps<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
+#pragma unroll
+                for (int q = 0; q < PAIR; q++)
+                    out.step(lane, u + q, i + (u + q) * WAVE, w[u + q], byte[q], true);
+            }
+        }
+        put.round(w, i);
+        out.round(lane, i, D_UNROLL, (r + 1) * (D_UNROLL * WAVE) == len);
+    }
+    // the events past the whole rounds, one step at a time
+    const uint32_t past = rounds * (D_UNROLL * WAVE);
+    for (uint32_t k = past; k < len; k += WAVE) {
+        const bool valid = k + lane < len;
+        const uint32_t w = valid ? c.ev[i0 + k + lane] : D::NOOP;
+        put.one(w, i0 + k + lane);
+        const Lane<DIR> one[1] = {make_lane<DIR>(s_t, s_tab, w, c.clamped(w), valid)};
+        uint32_t b[1];
+        steps_together<DIR, 1>(one, b, s_tab, bits, lane, shared_steps);
+        out.step(lane, (k - past) / WAVE, i0 + k, w, b[0], valid);
+    }
+    if (past < len)
+        out.round(lane, i0 + past, (len - past + WAVE - 1) / WAVE, true);
+}
+
+// words that were checked before
+struct Checked {
+    __device__ void round(const uint32_t (&)[D_UNROLL], uint64_t) const {}
+    __device__ void one(uint32_t, uint64_t) const {}
+};
+
+// words checked here, a round's after its steps (nothing waits for the round's last words
+// before its first steps): malformed ones are reported
+template <class C>
+struct Unchecked {
+    const C &c;
+    Control *ctl;
+    uint32_t lane;
+    __device__ void one(uint32_t w, uint64_t i) const
+    {
+        if (c.bad(w))
+            if (Control *const to = c.report_to(ctl))
+                atomicMin(reinterpret_cast<unsigned long long *>(&to->err_index_lo), (unsigned long long)i);
+    }
+    __device__ void round(const uint32_t (&w)[D_UNROLL], uint64_t i) const
+    {
+        if (__ballot(any_bad(c, w)))
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u++)
+                one(w[u], i + u * WAVE + lane);
+    }
+};
+
+struct NoOut {
+    __device__ void step(uint32_t, uint32_t, uint64_t, uint32_t, uint32_t, bool) const {}
+    __device__ void round(uint32_t, uint64_t, uint32_t, bool) const {}
+};
+
+// every chunk's functions into its row (left: of the chunks marked there only)
 template <class D, int PAIR, class CHUNKS>
 __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, uint32_t *__restrict__ rows,
-                                                     Control *ctl)
+                                                     Control *ctl, const uint32_t *__restrict__ left)
 {
     extern __shared__ __align__(16) uint32_t s_t[];
     uint32_t *const s_tab = s_t + table;
     const uint32_t lane = threadIdx.x, chunks = T.count();
     load_step_table<Fold<D>>(s_tab, lane);
     for (uint32_t c = blockIdx.x; c < chunks; c += gridDim.x) {
+        if (left && !left[c])
+            continue;
         const auto C = T.chunk(c);
         const uint64_t i0 = C.begin, i1 = C.end;
         const uint32_t row = C.row, bits = C.bits;
@@ -570,15 +700,75 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
     }
 }
 
+// The same forwards: an id whose function has become a constant still takes part, but a step
+// is shorter.  A chunk of skewed ids is left to the backward walk (marked in `left`): one in
+// whose first two pairs of steps so many events meet an id again as uniform ids above
+// FORWARD_IDS practically never do (4 of 256 at 4,096 ids; a single chunk that is left costs
+// as long as all of them).
+constexpr uint32_t FORWARD_IDS = 4096, FORWARD_MET = 16;
+template <class D, int PAIR, class CHUNKS>
+__global__ __launch_bounds__(WAVE) void k_dense_forward(CHUNKS T, uint32_t table, uint32_t *__restrict__ rows,
+                                                        Control *ctl, uint32_t *__restrict__ left)
+{
+    extern __shared__ __align__(16) uint32_t s_t[];
+    uint32_t *const s_tab = s_t + table;
+    const uint32_t lane = threadIdx.x, chunks = T.count();
+    load_step_table<Onto<D>>(s_tab, lane);
+    for (uint32_t c = blockIdx.x; c < chunks; c += gridDim.x) {
+        const auto C = T.chunk(c);
+        const uint32_t row = C.row;
+        uint32_t nxt[D_UNROLL];
+        const bool whole = C.end - C.begin >= D_UNROLL * WAVE;
+        if (whole) {
+            const uint32_t *e = C.ev + C.begin + lane;
+#pragma unroll
+            for (int u = 0; u < D_UNROLL; u++)
+                nxt[u] = e[u * WAVE];
+        }
+        for (uint32_t i = lane; i < row / 4; i += WAVE)
+            reinterpret_cast<uint4 *>(s_t)[i] = make_uint4(0, 0, 0, 0);
+        compiler_fence();
+        uint32_t again = 0; // events that meet an id again
+        if (whole) {
+#pragma unroll
+            for (int q = 0; q < 2 * PAIR; q += PAIR) {
+                uint32_t *at[PAIR], touch[PAIR];
+#pragma unroll
+                for (int u = 0; u < PAIR; u++) {
+                    const uint32_t id = C.clamped(nxt[q + u]);
+                    at[u] = s_t + D::word(id);
+                    touch[u] = D::touch(id);
+                    again += (uint32_t)__builtin_popcountll(__ballot((tab_touch(at[u], touch[u]) & touch[u]) != 0));
+                }
+                compiler_fence();
+#pragma unroll
+                for (int u = 0; u < PAIR; u++)
+                    tab_untouch(at[u], touch[u]);
+                compiler_fence();
+            }
+        }
+        if (lane == 0)
+            left[c] = again >= FORWARD_MET ? 1u : 0u;
+        if (again >= FORWARD_MET)
+            continue; // uniform
+        const Unchecked<decltype(C)> put{C, ctl, lane};
+        NoOut none;
+        walk_forward<Onto<D>, PAIR>(C, s_t, s_tab, lane, nxt, put, none);
+        compiler_fence();
+        uint4 *out = reinterpret_cast<uint4 *>(rows + C.row_at);
+        for (uint32_t i = lane; i < row / 4; i += WAVE)
+            out[i] = reinterpret_cast<const uint4 *>(s_t)[i];
+        compiler_fence();
+    }
+}
+
 // The events' results from their chunk's entering statuses (Apply), or every chunk's
 // functions into its row, the events' results the functions before them (Onto).  OUT takes
-// the results: step() a
-// step's (u: its number in its round or in the chunk's last, partial one), round() at the
-// end of each, chunk() at the chunk's.
+// the results: step() a step's (u: its number in its round or in the chunk's last, partial
+// one), round() at the end of each, chunk() at the chunk's.
 template <class DIR, int PAIR, class CHUNKS, class OUT>
 __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t table, uint32_t *__restrict__ rows, OUT out)
 {
-    using D = typename DIR::Dom;
     extern __shared__ __align__(16) uint32_t s_t[];
     uint32_t *const s_tab = s_t + table;
     const uint32_t lane = threadIdx.x, chunks = T.count();
@@ -586,84 +776,20 @@ __global__ __launch_bounds__(WAVE) void k_dense_apply(CHUNKS T, uint32_t table, 
     for (uint32_t c = blockIdx.x; c < chunks; c += gridDim.x) {
         const auto C = T.chunk(c);
         uint4 *const chunk_row = reinterpret_cast<uint4 *>(rows + C.row_at);
-        const uint64_t i0 = C.begin, i1 = C.end;
-        const uint32_t row = C.row, bits = C.bits;
-        const uint32_t len = (uint32_t)(i1 - i0), rounds = len / (D_UNROLL * WAVE);
+        const uint32_t row = C.row;
         out.begin(C, c);
         uint32_t nxt[D_UNROLL];
-        auto load = [&](uint32_t r) {
-            const uint32_t *e = C.ev + i0 + (uint64_t)r * (D_UNROLL * WAVE) + lane;
+        if (C.end - C.begin >= D_UNROLL * WAVE) {
+            const uint32_t *e = C.ev + C.begin + lane;
 #pragma unroll
             for (int u = 0; u < D_UNROLL; u++)
                 nxt[u] = e[u * WAVE];
-        };
-        if (rounds)
-            load(0);
+        }
         for (uint32_t i = lane; i < row / 4; i += WAVE)
             reinterpret_cast<uint4 *>(s_t)[i] = DIR::FUNCTIONS ? make_uint4(0, 0, 0, 0) : chunk_row[i];
         compiler_fence();
-        // (a malformed word, which was reported, only has to stay inside the table)
-        auto id_of = [&](uint32_t w) { return C.clamped(w); };
-        uint32_t shared_steps = 0;
-        for (uint32_t r = 0; r < rounds; r++) {
-            uint32_t w[D_UNROLL];
-#pragma unroll
-            for (int u = 0; u < D_UNROLL; u++)
-                w[u] = nxt[u];
-            if (r + 1 < rounds)
-                load(r + 1);
-            const uint64_t i = i0 + (uint64_t)r * (D_UNROLL * WAVE);
-            if (shared_steps >= D_TOGETHER) {
-                shared_steps = 0;
-                uint32_t v[PAIR];
-#pragma unroll
-                for (int q = 0; q < PAIR; q++)
-                    v[q] = w[q];
-#pragma unroll 1
-                for (int u = 0; u < D_UNROLL; u += PAIR) {
-                    Lane<DIR> L[PAIR];
-                    uint32_t byte[PAIR], now[PAIR];
-                    const int n = u + PAIR < D_UNROLL ? u + PAIR : u;
-#pragma unroll
-                    for (int q = 0; q < PAIR; q++) {
-                        now[q] = v[q];
-                        L[q] = make_lane<DIR>(s_t, s_tab, v[q], id_of(v[q]), true);
-                        v[q] = C.ev[i + (n + q) * WAVE + lane];
-                    }
-                    steps_together<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
-#pragma unroll
-                    for (int q = 0; q < PAIR; q++)
-                        out.step(lane, u + q, i + (u + q) * WAVE, now[q], byte[q], true);
-                }
-            } else {
-                shared_steps = 0;
-#pragma unroll
-                for (int u = 0; u < D_UNROLL; u += PAIR) {
-                    Lane<DIR> L[PAIR];
-                    uint32_t byte[PAIR];
-#pragma unroll
-                    for (int q = 0; q < PAIR; q++)
-                        L[q] = make_lane<DIR>(s_t, s_tab, w[u + q], id_of(w[u + q]), true);
-                    steps<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
-#pragma unroll
-                    for (int q = 0; q < PAIR; q++)
-                        out.step(lane, u + q, i + (u + q) * WAVE, w[u + q], byte[q], true);
-                }
-            }
-            out.round(lane, i, D_UNROLL, (r + 1) * (D_UNROLL * WAVE) == len);
-        }
-        // the events past the whole rounds, one step at a time
-        const uint32_t past = rounds * (D_UNROLL * WAVE);
-        for (uint32_t k = past; k < len; k += WAVE) {
-            const bool valid = k + lane < len;
-            const uint32_t w = valid ? C.ev[i0 + k + lane] : D::NOOP, id = id_of(w);
-            const Lane<DIR> one[1] = {make_lane<DIR>(s_t, s_tab, w, id, valid)};
-            uint32_t b[1];
-            steps_together<DIR, 1>(one, b, s_tab, bits, lane, shared_steps);
-            out.step(lane, (k - past) / WAVE, i0 + k, w, b[0], valid);
-        }
-        if (past < len)
-            out.round(lane, i0 + past, (len - past + WAVE - 1) / WAVE, true);
+        const Checked put;
+        walk_forward<DIR, PAIR>(C, s_t, s_tab, lane, nxt, put, out);
         out.chunk(lane, s_t);
         compiler_fence();
         if (DIR::FUNCTIONS)

@@ -164,3 +164,44 @@ def test_list_by_sums_and_by_scan(ctx, n, n_ids):
     v = t.violations()
     assert v.total == ref.violations.size and np.array_equal(v.indices, ref.violations) and v.first == ref.first
     t.free()
+
+
+@pytest.mark.parametrize("n,n_ids", [(1 << 22, 4097), ((1 << 22) + 511, 1 << 16), ((1 << 22) + 513, 9000)])
+@pytest.mark.parametrize("pattern", ["uniform", "skewed", "both"])
+def test_dense_forwards(ctx, n, n_ids, pattern):
+    """Traces long enough to be folded forwards: of uniform ids, of skewed ones, whose chunks
+    are left to the backward fold, and of stretches of either."""
+    from paper_1910_11110_amd import vcheck as V
+    print(f"[dense] forwards {pattern} {n} x {n_ids}", flush=True)
+    rng = np.random.default_rng(n + n_ids)
+    ids = ids_of("uniform" if pattern == "uniform" else "skewed", n, n_ids, rng)
+    if pattern == "both":
+        ids = np.where((np.arange(n) // 100_000) % 2 == 0, rng.integers(0, n_ids, n), ids)
+    e = gen.pack_events(ids, rng.integers(0, 5, n), rng.integers(0, 2, n))
+    init = rng.integers(0, 4, n_ids).astype(np.uint8)
+    t = V.Trace.load(ctx, e, n_ids, init)
+    t.check()
+    ref = O.check(e, n_ids, init)
+    assert np.array_equal(t.status(), ref.status)
+    assert np.array_equal(t.final(), ref.final)
+    v = t.violations()
+    assert np.array_equal(v.indices, ref.violations) and v.first == ref.first
+    t.free()
+
+
+@pytest.mark.parametrize("word", [5 << 24, 7 << 24, 1 << 28, 1 << 31, 50_000, (1 << 24) - 1])
+@pytest.mark.parametrize("at", [0, 70, 511, 4_096, (1 << 22) + 99])
+def test_dense_forwards_malformed(ctx, at, word):
+    """The first malformed word of a trace folded forwards is reported, wherever it lies."""
+    import torch
+    from paper_1910_11110_amd import vcheck as V
+    n, n_ids = (1 << 22) + 100, 50_000
+    e = gen.plain_events(n, n_ids, 3)
+    e[at] = word
+    e[-1] = 6 << 24
+    t = V.Trace.load(ctx, torch.from_numpy(e.view(np.int32)).cuda(), n_ids)
+    t.check()
+    with pytest.raises(V.VCError) as ex:
+        ctx.sync()
+    assert str(at) in str(ex.value)
+    t.free()
