@@ -215,7 +215,7 @@ void launch_batch_dense(const DenseBatch &B, hipStream_t s)
     for (int k = 0; k < DENSE_CLASSES; k++)
         if (const BatchChunks T = chunks_of(k); T.chunks) {
             ProfScope p(s, "batch_fold");
-            k_dense_fold<Two, B_PAIR, BatchChunks>
+            k_dense_fold<Fold<Two>, B_PAIR, BatchChunks>
                 <<<T.chunks, WAVE, table_lds(DENSE_CLASS[k]), s>>>(T, DENSE_CLASS[k], B.rows, nullptr, nullptr);
         }
     if (B.grouped) {

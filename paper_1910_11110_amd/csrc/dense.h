@@ -13,7 +13,7 @@ constexpr uint32_t DENSE_MAX_IDS = 1u << 16;
 // Events from which on chunks over many ids are folded forwards, by a launch of their own
 // that leaves those of skewed ids to the backward fold: 2^22 events x 2^16 ids 24.4 us by the
 // fold alone and 26.7 + 7.6 by both (whole check 80 and 79), 2^24 67 and 48 + 6, 2^26 231 and
-// 161 + 6; 2^24 of Zipf(1.1) ids 111 and 8 + 106.
+// 161 + 6; 2^24 of Zipf(1.1) ids 111 and 7 + 89.
 constexpr uint64_t DENSE_FORWARD_FROM = 1ull << 22;
 
 size_t dense_scratch_bytes(uint64_t n, uint32_t n_ids);

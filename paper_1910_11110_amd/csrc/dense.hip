@@ -314,15 +314,17 @@ void launch_fold(const CHUNKS &T, const Rows &R, Control *ctl, hipStream_t s)
 {
     if (!T.chunks)
         return;
-    const bool forward = T.n_ids > FORWARD_IDS && T.n >= DENSE_FORWARD_FROM;
-    if (forward) {
-        ProfScope p(s, "dense_forward");
-        k_dense_forward<Two, D_PAIR, CHUNKS><<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.rows, ctl, R.left);
-    }
-    {
+    const unsigned lds = dense_lds(R.row);
+    if (T.n_ids > FORWARD_IDS && T.n >= DENSE_FORWARD_FROM) {
+        {
+            ProfScope p(s, "dense_forward");
+            k_dense_forward<Two, D_PAIR, CHUNKS><<<T.chunks, WAVE, lds, s>>>(T, R.row, R.rows, ctl, R.left);
+        }
+        ProfScope p(s, "dense_fold"); // (of the chunks of skewed ids)
+        k_dense_fold<FoldSkewed<Two>, D_PAIR, CHUNKS><<<T.chunks, WAVE, lds, s>>>(T, R.row, R.rows, ctl, R.left);
+    } else {
         ProfScope p(s, "dense_fold");
-        k_dense_fold<Two, D_PAIR, CHUNKS>
-            <<<T.chunks, WAVE, dense_lds(R.row), s>>>(T, R.row, R.rows, ctl, forward ? R.left : nullptr);
+        k_dense_fold<Fold<Two>, D_PAIR, CHUNKS><<<T.chunks, WAVE, lds, s>>>(T, R.row, R.rows, ctl, nullptr);
     }
     launch_groups(R, s);
 }

@@ -275,7 +275,7 @@ static void wide_scan(const WideChunks &W, uint32_t row, const uint8_t *init, ui
     const dim3 pg((unsigned)ceil_div(row, BLOCK), groups);
     {
         ProfScope p(s, "wide_fold");
-        k_dense_fold<D, Q, BucketChunks><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, ctl, nullptr);
+        k_dense_fold<Fold<D>, Q, BucketChunks><<<most, WAVE, wide_lds(row), s>>>(T, row, rows, ctl, nullptr);
     }
     if (groups > 1) {
         ProfScope p(s, "wide_groups");
