@@ -109,15 +109,35 @@ __device__ __forceinline__ uint32_t el_of(uint32_t f4)
 // ----------------------------------------------------------------------------------
 // Domains: where an id lies in the table, and an event's part in each walk (`entry`, from
 // its word; `next`: the id's bits after it, and its result; `open`: whether an event can
-// still change the id in the fold), and the functions lanes pass along, with the lane
-// they came from (64: none) in spare bits.
+// still change the id in the fold), and how the functions of lanes that share an id are
+// composed (BY_MASKS: from ballots; else they are passed along, with the lane they came
+// from (64: none) in spare bits).
 // ----------------------------------------------------------------------------------
 struct __attribute__((packed)) Bytes8 { // at any address
     uint32_t lo, hi;
 };
 
 struct Two {
-    static constexpr uint32_t MASK = 7, IDENTITY = F_ID, NOOP = (uint32_t)OP_NOOP << 24;
+    static constexpr uint32_t MASK = 7, NOOP = (uint32_t)OP_NOOP << 24;
+    static constexpr bool BY_MASKS = true;
+    // The functions f of the lanes of `set` composed (any set for each lane), for one event's
+    // functions: a constant forgets what was before it, and the others add the CPU copy to
+    // a status with the GPU copy valid or the other way round, in any order.  So it is the
+    // latest constant of the set (BACK: lower lanes are later events) and, of the lanes
+    // after it, whether any adds either copy.  Bits 16 and 9 of a function are those, and of
+    // a constant its copies.  (Pointer jumping along the lanes waited for LDS in every round:
+    // 2^24 Zipf(1.1) events over 2^16 ids, the apply pass 180 -> 150 us.)
+    template <bool BACK>
+    __device__ static uint32_t compose_set(uint64_t set, uint32_t f)
+    {
+        const uint64_t cpu = __ballot((f >> 16) & 1u), gpu = __ballot((f >> 9) & 1u), k = set & __ballot(constant(f));
+        const uint64_t at = BACK ? k & (~k + 1) : (k ? 1ull << (63 - __builtin_clzll(k)) : 0ull); // the constant's lane
+        const uint64_t later = set & (BACK ? at - 1 : ~(k ? at | (at - 1) : 0ull));
+        const uint32_t x = (later & cpu) != 0, y = (later & gpu) != 0;
+        const uint32_t v = ((at & cpu) != 0 ? 1u : 0u) | ((at & gpu) != 0 ? 2u : 0u);
+        const uint32_t c = v | ((v >> 1) & x) | ((v & y) << 1);
+        return k ? c * 0x01010101u : F_ID | (x << 16) | (y << 9);
+    }
     __device__ static uint32_t word(uint32_t id) { return id >> 3; }
     __device__ static uint32_t shift(uint32_t id) { return 3u * (id & 7u); }
     __device__ static uint32_t touch(uint32_t id) { return T_TOUCH << (id & 7u); }
@@ -134,11 +154,7 @@ struct Two {
         return 4u | (byte & 3u);
     }
     __device__ static uint32_t function(const uint32_t *tab, uint32_t w) { return apply_entry(tab, w) & 0x03030303u; }
-    __device__ static uint32_t compose(uint32_t g, uint32_t f) { return fcompose(g, f); }
     __device__ static bool constant(uint32_t f) { return (f & 3u) != 0; } // (a constant's byte 0 is not 0)
-    __device__ static uint32_t pack(uint32_t f, uint32_t p) { return f | ((p & 63u) << 2) | ((p & 64u) << 4); }
-    __device__ static uint32_t packed_function(uint32_t v) { return v & 0x03030303u; }
-    __device__ static uint32_t packed_lane(uint32_t v) { return (v & (64u << 4)) ? 64u : (v >> 2) & 63u; }
     __device__ static uint32_t fold_all(uint32_t h, uint32_t f) { return el_compose(h, el_of(f)); }
     __device__ static uint32_t status_after(uint32_t f, uint32_t h) { return fapply(f, h & 3u); }
     // rows: a word's composition, the initial statuses of its ids (from id on, n_ids in all)
@@ -356,7 +372,7 @@ __device__ __forceinline__ void steps_together(const Lane<DIR> (&L)[Q], uint32_t
                                                uint32_t bits, uint32_t lane, uint32_t &shared)
 {
     using D = typename DIR::Dom;
-    uint32_t f[Q], p[Q], prev[Q];
+    uint32_t f[Q], p[Q], prev[Q], g[Q];
     bool in[Q], last[Q];
 #pragma unroll
     for (int q = 0; q < Q; q++) // (a later step's id may close before it: it then changes nothing)
@@ -370,13 +386,16 @@ __device__ __forceinline__ void steps_together(const Lane<DIR> (&L)[Q], uint32_t
         last[q] = in[q] && rank + 1 == (uint32_t)__builtin_popcountll(same); // of its id
         f[q] = D::function(s_tab, L[q].w);
         shared += __ballot(prev[q] < 64) ? 1u : 0u;
+        if constexpr (D::BY_MASKS)
+            (DIR::BACK ? f[q] : g[q]) = D::template compose_set<DIR::BACK>(DIR::BACK ? same : below, f[q]);
     }
-    compose_along<D, DIR::BACK, Q>(f, p);
-    uint32_t g[Q];
-    if constexpr (!DIR::BACK)
+    if constexpr (!D::BY_MASKS) {
+        compose_along<D, DIR::BACK, Q>(f, p);
+        if constexpr (!DIR::BACK)
 #pragma unroll
-        for (int q = 0; q < Q; q++)
-            g[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((prev[q] & 63u) * 4u), (int)f[q]);
+            for (int q = 0; q < Q; q++)
+                g[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((prev[q] & 63u) * 4u), (int)f[q]);
+    }
 #pragma unroll
     for (int q = 0; q < Q; q++) {
         const uint32_t h = L[q].field(tab_load(L[q].p));

@@ -205,3 +205,25 @@ def test_dense_forwards_malformed(ctx, at, word):
         ctx.sync()
     assert str(at) in str(ex.value)
     t.free()
+
+
+@pytest.mark.parametrize("few", [1, 2, 5, 31, 63])
+@pytest.mark.parametrize("ops", ["all", "transfers", "reads"])
+def test_dense_steps_that_share(ctx, few, ops):
+    """Steps in which most lanes share ids: the functions of an id's lanes composed at once,
+    with and without constants among them, from every status."""
+    from paper_1910_11110_amd import vcheck as V
+    n, n_ids = 20_011, 300
+    rng = np.random.default_rng(few)
+    ids = rng.permutation(n_ids)[:few][rng.integers(0, few, n)]
+    op = {"all": rng.integers(0, 5, n), "transfers": np.where(rng.random(n) < 0.03, 1, rng.integers(2, 4, n)),
+          "reads": np.where(rng.random(n) < 0.01, rng.integers(1, 4, n), 0)}[ops]
+    e = gen.pack_events(ids, op, rng.integers(0, 2, n))
+    init = rng.integers(0, 4, n_ids).astype(np.uint8)
+    t = V.Trace.load(ctx, e, n_ids, init)
+    t.check()
+    ref = O.check(e, n_ids, init)
+    assert np.array_equal(t.status(), ref.status)
+    assert np.array_equal(t.final(), ref.final)
+    assert np.array_equal(t.violations().indices, ref.violations)
+    t.free()
