@@ -50,7 +50,7 @@ struct BatchState {
     bool graph_ok = false;
     // device buffers
     DevBuf desc, init_all, fin_all, status_all, viol_all, items_a, items_b, cnt, pos, scratch, ind,
-        chunks, words, comb, vcnt, vpos, dchunks, jobs, rows, grp;
+        chunks, words, comb, vcnt, vpos, dchunks, jobs, rows, grp, strand_lb;
     uint64_t n_chunks = 0;
     Control *ctl = nullptr;
     // bucket route: groups of consecutive traces (their slice of the combined stream and
@@ -330,7 +330,8 @@ int reserve_all(BatchState &b, uint32_t n)
         if ((r = devbuf_reserve(b.words, 4 * (b.MB ? b.MB : 1))) != VC_OK) return r;
         if ((r = devbuf_reserve(b.vcnt, 4 * nd)) != VC_OK) return r;
         if ((r = devbuf_reserve(b.vpos, 8 * (nd + 1))) != VC_OK) return r;
-        sc = std::max({sc, excl_scan_scratch_bytes(nd), batch_strands_bytes(b.strands)});
+        if ((r = devbuf_reserve(b.strand_lb, batch_strands_bytes(b.strands ? b.strands : 1))) != VC_OK) return r;
+        sc = std::max(sc, excl_scan_scratch_bytes(nd));
     } else if (b.bucket) {
         // the status bytes go straight to the traces: no batch-wide status or violation
         // arrays
@@ -381,11 +382,11 @@ void enqueue_pipeline(BatchState &b, hipStream_t s)
         DenseBatch B{d, dch, {}, words, (const uint64_t *)b.pos.p, (const PrefixJob *)b.jobs.p, (uint32_t)b.h_jobs.size(),
                      b.grp_words != 0, (uint32_t *)b.rows.p, (uint32_t *)b.grp.p, vcnt};
         std::copy(b.class_at, b.class_at + DENSE_CLASSES + 1, B.class_at);
-        launch_batch_strands(d, dch, b.strands, vcnt, b.scratch.p, b.ctl->tickets[8], s);
+        launch_batch_strands(d, dch, b.strands, vcnt, (uint64_t *)b.strand_lb.p, b.ctl->tickets[8], s);
         launch_batch_dense(B, s);
         launch_excl_scan(vcnt, nd, vpos, nullptr, b.scratch.p, b.ctl->tickets[7], s);
         launch_batch_chunk_viol(d, dch, nd, vcnt, vpos, true, s);
-        launch_batch_counts(d, n, vpos, b.ctl, s);
+        launch_batch_counts(d, n, vpos, b.strands, (const uint64_t *)b.strand_lb.p, b.ctl, s);
         return;
     }
     if (b.bucket) {
@@ -633,7 +634,7 @@ void batch_free(BatchState *b)
     drop_graph(*b);
     for (DevBuf *d : { &b->desc, &b->init_all, &b->fin_all, &b->status_all, &b->viol_all,
                        &b->items_a, &b->items_b, &b->cnt, &b->pos, &b->scratch, &b->ind, &b->chunks, &b->words,
-                       &b->comb, &b->vcnt, &b->vpos, &b->dchunks, &b->jobs, &b->rows, &b->grp })
+                       &b->comb, &b->vcnt, &b->vpos, &b->dchunks, &b->jobs, &b->rows, &b->grp, &b->strand_lb })
         devbuf_free(*d);
     if (b->ctl)
         (void)hipFree(b->ctl);

@@ -73,10 +73,13 @@ void launch_batch_finish(const TraceDesc *d, uint32_t n_traces, uint64_t n_chunk
 
 // dense route, the traces without arrays over at most small_max_ids() ids and with an event
 // at least: checked by strands, a chunk (strand_chunk() events, a trace's last one the rest) a
-// tile; flagged events per chunk into vcnt.  Scratch of batch_strands_bytes(chunks).
+// tile; flagged events per chunk into vcnt.  The final statuses stay in the last chunks'
+// words of lbv (batch_strands_bytes(chunks)), STRAND_WORDS a chunk of STRAND_IDS ids each,
+// for launch_batch_counts.
+constexpr uint32_t STRAND_WORDS = 4, STRAND_IDS = 20;
 uint32_t strand_chunk();
 size_t batch_strands_bytes(uint64_t chunks);
-void launch_batch_strands(const TraceDesc *d, const ChunkDesc *ch, uint32_t chunks, uint32_t *vcnt, void *scratch,
+void launch_batch_strands(const TraceDesc *d, const ChunkDesc *ch, uint32_t chunks, uint32_t *vcnt, uint64_t *lbv,
                           uint32_t *ticket, hipStream_t s);
 // dense route, the others (every trace over at most DENSE_CLASS[last] * 8 ids): the chunks of all
 // traces by classes of row sizes, a trace's consecutive; the groups of B_GROUP chunks of
@@ -101,8 +104,10 @@ struct DenseBatch {
 };
 // status bytes, final statuses, flagged induced items, flagged events per chunk (vcnt)
 void launch_batch_dense(const DenseBatch &B, hipStream_t s);
-// every trace's number of violations, from vpos = the exclusive prefix of vcnt
-void launch_batch_counts(const TraceDesc *d, uint32_t n_traces, const uint64_t *vpos, const Control *bctl, hipStream_t s);
+// every trace's number of violations, from vpos = the exclusive prefix of vcnt, and the final
+// statuses of the traces checked by strands (the batch's first `strands` chunks)
+void launch_batch_counts(const TraceDesc *d, uint32_t n_traces, const uint64_t *vpos, uint32_t strands,
+                         const uint64_t *lbv, const Control *bctl, hipStream_t s);
 
 void launch_batch_reset(const TraceDesc *d, uint32_t n_traces, unsigned long long *ind, hipStream_t s);
 // every trace's initial statuses into its key range of init_all and fin_all (K keys)

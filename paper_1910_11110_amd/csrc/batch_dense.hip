@@ -9,9 +9,11 @@
 // 2. groups, prefix: per trace and word of its rows, the statuses entering every chunk,
 //    by groups of B_GROUP chunks.
 // 3. apply: the status bytes, the flagged events of every chunk and the flagged induced
-//    items of every trace; a trace's last chunk leaves its final statuses (after every
-//    read of its initial ones, which may lie in the same place).
-// 4. the violation lists, from a scan of the chunks' counts.
+//    items of every trace; a trace's last chunk leaves its final statuses.
+// 4. the violation lists, from a scan of the chunks' counts, and the counts.
+// A trace's initial and final statuses may lie in the same place: a launch that writes final
+// ones (3, and 4 of the traces checked by strands) comes after all that read initial ones (2
+// and the strands).
 // Bound like the dense check by the walks' LDS round trips and their instructions.  1,024
 // traces of 100 to 10^6 events over 8 to 65,536 ids, a fifth of them over arrays (110 M
 // events): kernels 2,133 us through the bucket engine (which relocates every event to a
@@ -183,16 +185,26 @@ __global__ __launch_bounds__(BLOCK) void k_batch_prefix(const TraceDesc *__restr
     }
 }
 
-// every trace's number of violations
+// a wave a trace: its number of violations and, checked by strands, its final statuses, which
+// its last chunk's words hold as constants
 __global__ __launch_bounds__(BLOCK) void k_batch_counts(const TraceDesc *__restrict__ d, uint32_t n_traces,
-                                                        const uint64_t *__restrict__ vpos,
+                                                        const uint64_t *__restrict__ vpos, uint32_t strands,
+                                                        const uint64_t *__restrict__ lbv,
                                                         const Control *__restrict__ bctl)
 {
-    const uint32_t t = blockIdx.x * BLOCK + threadIdx.x;
+    const uint32_t t = blockIdx.x * (BLOCK / WAVE) + threadIdx.x / WAVE, lane = lane_id();
     if (t >= n_traces)
         return;
     const TraceDesc &td = d[t];
-    td.ctl->n_viol = vpos[td.first_dense + td.dense_chunks] - vpos[td.first_dense];
+    const uint64_t end = td.first_dense + td.dense_chunks;
+    if (td.first_dense < strands && lane < td.n_ids) { // (at most 64 ids)
+        const Planes st = pl_unpack(lbv[(end - 1) * STRAND_WORDS + lane / STRAND_IDS]);
+        const uint32_t k = lane % STRAND_IDS;
+        td.fin[lane] = (uint8_t)(((st.x >> k) & 1u) | (((st.y >> k) & 1u) << 1));
+    }
+    if (lane)
+        return;
+    td.ctl->n_viol = vpos[end] - vpos[td.first_dense];
     if (bctl->err_code) // an internal error of the shared scan concerns every trace
         atomicOr(&td.ctl->err_code, bctl->err_code);
 }
@@ -234,10 +246,11 @@ void launch_batch_dense(const DenseBatch &B, hipStream_t s)
         }
 }
 
-void launch_batch_counts(const TraceDesc *d, uint32_t n_traces, const uint64_t *vpos, const Control *bctl, hipStream_t s)
+void launch_batch_counts(const TraceDesc *d, uint32_t n_traces, const uint64_t *vpos, uint32_t strands,
+                         const uint64_t *lbv, const Control *bctl, hipStream_t s)
 {
     ProfScope p(s, "batch_counts");
-    k_batch_counts<<<(unsigned)ceil_div(n_traces, BLOCK), BLOCK, 0, s>>>(d, n_traces, vpos, bctl);
+    k_batch_counts<<<(unsigned)ceil_div(n_traces, BLOCK / WAVE), BLOCK, 0, s>>>(d, n_traces, vpos, strands, lbv, bctl);
 }
 
 } // namespace vc

@@ -2,8 +2,8 @@
 //
 // Each stream owns a status table resident in device memory (n_ids bytes).  A chunk
 // is checked from the table and leaves its final statuses there: the batched
-// pipeline copies every descriptor's initial statuses into its own buffer before the
-// scan, so a chunk's descriptor can read and write the same table.  A server thread
+// pipeline writes final statuses in launches after those that read initial ones, so a
+// chunk's descriptor can read and write the same table.  A server thread
 // admits queued chunks while the device bytes they need fit the budget, packs the
 // ready ones (at most one per stream, in order) into one batched launch, and keeps
 // two launch slots so that a batch is staged and launched while the previous one

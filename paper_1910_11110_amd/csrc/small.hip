@@ -34,6 +34,7 @@ constexpr int SB = 256;              // threads per tile
 constexpr int SW = SB / WAVE;        // waves per tile
 constexpr int SPW = (SK + 19) / 20;  // look-back words per tile (20 variables each)
 static_assert(SPW <= SW, "one wave per look-back word");
+static_assert(SPW == (int)STRAND_WORDS && PL_MASK == (1u << STRAND_IDS) - 1, "the words that a batch's last pass reads");
 
 // Events per lane: long strands share the cost of a strand's planes and scan, short ones
 // keep a short trace on more lanes and its walks short.  The line lies where the long ones
@@ -168,6 +169,9 @@ constexpr uint32_t scatter_threads()
 // the scatter tiles.  BatchStrands: a batch's traces over few ids, a chunk a tile (consecutive
 // ones of a trace), whose flagged events are counted per tile; 200 of them of 100 to 10^6
 // events (23 M) take 55 us, 120 by the walks of the dense check.
+// A last tile does not wait for the first one (a constant word ends its look-back), so nothing
+// here orders its final statuses after the first tile's read of the initial ones: a batch's,
+// which may be the same table, stay in the last tile's look-back words for a later launch.
 struct StrandTile {
     const uint32_t *ev;
     uint64_t n; // of the trace
@@ -200,7 +204,7 @@ struct BatchStrands {
     {
         const ChunkDesc c = ch[t];
         const TraceDesc &T = d[c.trace];
-        return StrandTile{T.events, T.n, T.n_ids, T.init, T.status, T.fin, T.ctl, c.start, c.start == 0,
+        return StrandTile{T.events, T.n, T.n_ids, T.init, T.status, nullptr, T.ctl, c.start, c.start == 0,
                           c.start + c.len == T.n};
     }
 };
@@ -571,12 +575,11 @@ void launch_small_check(const uint32_t *events, uint64_t n, uint32_t n_ids, cons
 uint32_t strand_chunk() { return SB * EP_LONG; }
 size_t batch_strands_bytes(uint64_t chunks) { return chunks * SPW * sizeof(uint64_t); }
 
-void launch_batch_strands(const TraceDesc *d, const ChunkDesc *ch, uint32_t chunks, uint32_t *vcnt, void *scratch,
+void launch_batch_strands(const TraceDesc *d, const ChunkDesc *ch, uint32_t chunks, uint32_t *vcnt, uint64_t *lbv,
                           uint32_t *ticket, hipStream_t s)
 {
     if (!chunks)
         return;
-    uint64_t *lbv = reinterpret_cast<uint64_t *>(scratch);
     launch_clear_lookback(lbv, (size_t)chunks * SPW, ticket, s);
     ProfScope p(s, "batch_strands");
     const auto kernel = k_small_check<EP_LONG, BatchStrands>;

@@ -195,3 +195,31 @@ def test_served_batches_split_at_the_id_limit(ctx):
     for i, spec in enumerate(specs):
         ref = oracle_of(*spec)
         assert np.array_equal(bufs[i], ref.status) and np.array_equal(finals[i], ref.final), f"stream {i}"
+
+
+@pytest.mark.parametrize("chunk", [3 * 16_384, 9 * 16_384 + 1, 40 * 16_384 - 5])
+def test_served_long_chunks_over_few_ids(ctx, chunk):
+    """Chunks of 3 and more tiles over at most 64 ids, checked from the stream's table and
+    leaving their final statuses there.  Every chunk starts with a tile that never writes, so
+    that its statuses are those of the table it started from, and goes on with writes to all
+    ids, so that no later tile needs the tiles before."""
+    from paper_1910_11110_amd import vcheck as V
+    specs = []
+    for i, n_ids in enumerate((1, 7, 20, 21, 40, 41, 63, 64)):
+        ev = gen.plain_events(2 * chunk + 777 * i, n_ids, 300 + i)
+        for a in range(0, ev.size, chunk):
+            head = ev[a:a + 16_384]
+            op = (head >> 24) & 7
+            head[op == 1] = (head[op == 1] & ~np.uint32(7 << 24)) | np.uint32(4 << 24)  # w to Noop
+        init = np.random.default_rng(i).integers(0, 4, n_ids).astype(np.uint8)
+        specs.append((ev, n_ids, None, None, init))
+    say(f"[serve] {len(specs)} streams over few ids, chunks of {chunk}")
+    refs = [oracle_of(*spec) for spec in specs]
+    srv = V.Server(ctx, 64 << 30)
+    for turn in range(3):
+        bufs, comps, finals, _ = run_streams(srv, specs, chunk=chunk)
+        for i, ref in enumerate(refs):
+            assert np.array_equal(bufs[i], ref.status), f"stream {i} status, turn {turn}"
+            assert np.array_equal(finals[i], ref.final), f"stream {i} final, turn {turn}"
+            assert sum(c.n_violations for c in comps[i]) == ref.violations.size, f"stream {i} violations, turn {turn}"
+    srv.close()
