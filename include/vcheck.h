@@ -343,7 +343,7 @@ double vc_server_now(vc_server *srv);
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * It computes what vc_trace_load + vc_check compute for a trace over at most 64 ids
  * (the same single-kernel path), writing into the caller's device buffers.  Its work
- * space (control block, look-back words, tile counts, flag words) is one static device
+ * space (control block, initial statuses, look-back words, tile counts, flag words) is one static device
  * array of VC_NOALLOC_SCRATCH_BYTES per GPU, held from the first vc_ctx_create on that
  * GPU until the process ends; the call allocates nothing and does not wait.  Work is
  * enqueued on the context's stream.
@@ -351,7 +351,7 @@ double vc_server_now(vc_server *srv);
  *   n_ids        : 1..64; every id must be < n_ids
  *   init         : n_ids status codes (device), or NULL for (V,I)
  *   status       : n bytes (device): post | pre << 2 | stuck << 7
- *   final_status : n_ids bytes (device)
+ *   final_status : n_ids bytes (device); may be init
  *   violations   : room for n uint32 (device); the first counts[0] are the ascending
  *                  indices of the stuck events
  *   counts       : 3 uint64 (device): [0] number of violations, [1] first violation (n

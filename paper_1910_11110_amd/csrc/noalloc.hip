@@ -2,7 +2,9 @@
 //
 // For callers that cannot allocate device memory (code under HIP graph capture, tight
 // serving loops): the same kernels as the single-kernel check of vc_check, with the
-// control block and every work buffer carved out of one static device array per GPU.
+// control block and every work buffer carved out of one static device array per GPU,
+// and the initial statuses copied there first (the caller's may lie where the final ones
+// go, and the check's tiles read the one and write the other in no order).
 // In host code the array's name is only a stand-in for a device address, so its real
 // address is taken once per device with hipGetSymbolAddress (at context creation, with
 // that device current) and only that pointer is ever handed to kernels.
@@ -21,7 +23,8 @@ void small_warm_launch_shapes();
 namespace {
 
 constexpr uint64_t NOALLOC_MAX_EVENTS = VC_NOALLOC_MAX_EVENTS;
-constexpr size_t NOALLOC_BYTES = VC_NOALLOC_SCRATCH_BYTES; // control block + scratch of 2^24 events
+constexpr size_t NOALLOC_BYTES = VC_NOALLOC_SCRATCH_BYTES; // control block, initial statuses, scratch of 2^24 events
+constexpr size_t INIT_BYTES = 256;                         // at most 64 statuses
 constexpr int MAX_DEVICES = 64;
 
 // the work space: shared by every call on one GPU (each GPU holds its own copy)
@@ -51,7 +54,7 @@ int noalloc_setup(int device, void **out)
         return vc_fail(VC_EINVAL, "no-alloc work space: device %d beyond %d", device, MAX_DEVICES);
     std::lock_guard<std::mutex> g(g_mu);
     if (!g_ptr[device]) {
-        if (CONTROL_BYTES + small_scratch_bytes(NOALLOC_MAX_EVENTS) > NOALLOC_BYTES)
+        if (CONTROL_BYTES + INIT_BYTES + small_scratch_bytes(NOALLOC_MAX_EVENTS) > NOALLOC_BYTES || small_max_ids() > INIT_BYTES)
             return vc_fail(VC_EDEVICE, "no-alloc work space smaller than its largest layout");
         void *p = nullptr;
         hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
@@ -90,16 +93,18 @@ extern "C" int vc_check_small_noalloc(vc_ctx *c, const uint32_t *events, uint64_
     hipStream_t s = c->stream;
     char *base = static_cast<char *>(c->noalloc_scratch);
     Control *ctl = reinterpret_cast<Control *>(base);
-    void *work = base + CONTROL_BYTES;
-    // the initial statuses are copied, or written as (V,I) by the set-up launch, which
-    // also clears the control block and the look-back words left by the last call
+    uint8_t *const start = reinterpret_cast<uint8_t *>(base + CONTROL_BYTES);
+    void *work = base + CONTROL_BYTES + INIT_BYTES;
+    // the initial statuses are copied (without events they are the final ones), or written
+    // as (V,I) by the set-up launch, which also clears the control block and the look-back
+    // words left by the last call
     const FillJob fill{final_status, n_ids, 1};
-    if (init) {
-        hipError_t e = hipMemcpyAsync(final_status, init, n_ids, hipMemcpyDeviceToDevice, s);
+    if (init && (n || init != final_status)) {
+        hipError_t e = hipMemcpyAsync(n ? start : final_status, init, n_ids, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess)
             return vc_hip_fail(e, "hipMemcpyAsync(init)");
     }
-    launch_small_check(events, n, n_ids, init, status, final_status, violations, work, ctl, s,
+    launch_small_check(events, n, n_ids, init ? start : nullptr, status, final_status, violations, work, ctl, s,
                        8u * (unsigned)c->cu_count, init ? nullptr : &fill);
     k_noalloc_counts<<<1, 64, 0, s>>>(ctl, violations, n, reinterpret_cast<unsigned long long *>(counts));
     hipError_t e = hipGetLastError();

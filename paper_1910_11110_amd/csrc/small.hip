@@ -171,7 +171,8 @@ constexpr uint32_t scatter_threads()
 // events (23 M) take 55 us, 120 by the walks of the dense check.
 // A last tile does not wait for the first one (a constant word ends its look-back), so nothing
 // here orders its final statuses after the first tile's read of the initial ones: a batch's,
-// which may be the same table, stay in the last tile's look-back words for a later launch.
+// which may be the same table, stay in the last tile's look-back words for a later launch
+// (OneTrace: never the same table).
 struct StrandTile {
     const uint32_t *ev;
     uint64_t n; // of the trace

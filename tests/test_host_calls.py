@@ -1,0 +1,70 @@
+"""The library's host code on a runtime without a GPU (fake_hip.c): what it launches, and what
+it returns when a call into the runtime fails.  Each test runs in a process of its own, since
+the library binds to the first runtime it meets."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes as C, sys
+F = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+L = C.CDLL(sys.argv[2])
+F.fake_launch_name.restype = C.c_char_p
+F.fake_launch_arg0.restype = C.POINTER(C.c_uint64 * 8)
+F.fake_fail_kernel.argtypes = [C.c_char_p]
+L.vc_last_error.restype = C.c_char_p
+P, u64, u32 = C.c_void_p, C.c_uint64, C.c_uint32
+L.vc_trace_load.argtypes = [P, P, u64, u32, P, u32, C.POINTER(P)]
+L.vc_check_small_noalloc.argtypes = [P, P, u64, u32, P, P, P, P, P]
+for f in ("vc_check", "vc_sync", "vc_trace_free", "vc_ctx_destroy"):
+    getattr(L, f).argtypes = [P]
+def launches():
+    return [(F.fake_launch_name(i).decode(), list(F.fake_launch_arg0(i).contents)) for i in range(F.fake_launches())]
+def ok(rc):
+    assert rc == 0, (rc, L.vc_last_error())
+ctx = P()
+ok(L.vc_ctx_create(0, None, C.byref(ctx)))
+"""
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    so = tmp_path_factory.mktemp("fake_hip") / "fake_hip.so"
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", str(so), os.path.join(HERE, "fake_hip.c"),
+                    "-I", os.path.join(rocm, "include")], check=True)
+    return str(so)
+
+
+def run(runtime, body):
+    lib = os.path.join(ROOT, "paper_1910_11110_amd", "libvcheck.so")
+    r = subprocess.run([sys.executable, "-c", PRELUDE + body, runtime, lib], capture_output=True, text=True,
+                       timeout=100)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+def test_no_alloc_in_place_reads_a_copy(runtime):
+    """init and final_status in one buffer: the check, whose tiles read the one and write the
+    other in no order, is not handed the buffer as both; without events it stays as it is."""
+    run(runtime, """
+table = (C.c_uint8 * 64)(*range(64))
+ev, status, viol, counts = (C.c_uint32 * 65536)(), (C.c_uint8 * 65536)(), (C.c_uint32 * 65536)(), (C.c_uint64 * 3)()
+at = C.addressof(ev) + (-C.addressof(ev)) % 16
+for init in (table, None):
+    F.fake_reset()
+    ok(L.vc_check_small_noalloc(ctx, at, 60000, 64, init, status, table, viol, counts))
+    words = [a for name, a in launches() if "k_small_check" in name]
+    assert len(words) == 1, launches()
+    assert words[0].count(C.addressof(table)) == 1, [hex(w) for w in words[0]]
+assert list(table) == list(range(64))  # (the copy is the library's own; kernels do not run here)
+ok(L.vc_check_small_noalloc(ctx, at, 0, 64, table, status, table, viol, counts))
+other = (C.c_uint8 * 64)()
+ok(L.vc_check_small_noalloc(ctx, at, 0, 64, table, status, other, viol, counts))
+assert list(table) == list(other) == list(range(64))
+""")

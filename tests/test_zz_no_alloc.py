@@ -128,3 +128,35 @@ def test_no_alloc_reports_malformed_event(ctx):
     V.check_small_noalloc(ctx, ev, 16, None, st, fin, viol, counts)
     ctx.sync()
     assert int(counts.cpu().numpy().view(np.uint64)[2]) == 31_337
+
+
+@pytest.mark.parametrize("n_ids", [1, 20, 21, 64])
+@pytest.mark.parametrize("n", [0, 1, 12_289, 9 * 4096 + 1, 7_000_001])
+def test_no_alloc_in_place(ctx, n, n_ids):
+    """The final statuses over the initial ones.  The first tile never writes (its statuses are
+    those of the table), the others write all ids (and need no tile before them)."""
+    import torch
+
+    from oracle import oracle as O
+    from paper_1910_11110_amd import vcheck as V
+    e = gen.plain_events(n, n_ids, 26)
+    head = e[:4096 if n < 3 << 21 else 16_384]
+    w = ((head >> 24) & 7) == 1
+    head[w] = (head[w] & ~np.uint32(7 << 24)) | np.uint32(4 << 24)  # w to Noop
+    init = np.random.default_rng(n_ids).integers(0, 4, n_ids).astype(np.uint8)
+    ref = O.check(e, n_ids, init)
+    say(f"[no-alloc] in place: n={n} n_ids={n_ids}")
+    ev = torch.from_numpy(e.view(np.int32)).cuda()
+    st = torch.full((max(n, 1),), 0x5A, dtype=torch.uint8, device="cuda")
+    viol = torch.full((max(n, 1),), -1, dtype=torch.int32, device="cuda")
+    counts = torch.full((3,), -7, dtype=torch.int64, device="cuda")
+    for turn in range(3):
+        table = torch.from_numpy(init).cuda()
+        torch.cuda.synchronize()
+        V.check_small_noalloc(ctx, ev, n_ids, table, st[:n], table, viol, counts)
+        ctx.sync()
+        total, first, bad = counts.cpu().numpy().view(np.uint64).tolist()
+        assert bad == (1 << 64) - 1 and total == ref.violations.size and first == ref.first, f"turn {turn}"
+        assert np.array_equal(st[:n].cpu().numpy(), ref.status), f"turn {turn}: statuses"
+        assert np.array_equal(table.cpu().numpy(), ref.final), f"turn {turn}: final"
+        assert np.array_equal(viol[:total].cpu().numpy().view(np.uint32), ref.violations), f"turn {turn}: violations"
