@@ -469,7 +469,12 @@ int configure(BatchState &b)
 
 bool tuning_on() { return !getenv("VC_NO_AUTOTUNE"); }
 
-std::string bucket_key(uint64_t N, uint64_t K) { return "bucket:" + shape_key(N, K); }
+// of a planned batch on the bucket or the dense route (a choice timed on one of them says
+// nothing of the other, and the dense one has no groups to choose)
+std::string bucket_key(const BatchState &b)
+{
+    return "bucket:" + shape_key(b.N, b.K) + (b.dense ? ":dense" : "");
+}
 
 // FNV-1a digest of every trace's status bytes (read back from the device, one trace at
 // a time)
@@ -498,7 +503,7 @@ bool status_digests(const BatchState &b, std::vector<uint64_t> &out)
 int autotune_bucket(vc_ctx *c, BatchState &b)
 {
     hipStream_t s = c->stream;
-    const std::string key = bucket_key(b.N, b.K);
+    const std::string key = bucket_key(b);
     struct Cand {
         uint32_t group_bits, plain_chunk;
     };
@@ -759,11 +764,12 @@ extern "C" int vc_batch_check(vc_ctx *c, vc_trace *const *traces, uint32_t n)
         b.M = M;
         b.n_traces = n;
         b.h_desc = desc;
-        // the bucket route's settings: cached for this shape, else the defaults until
+        // the route, and its settings: cached for this shape, else the defaults until
         // the autotuner has run
+        plan_groups(b, b.h_desc);
         SortTuning cached{};
         unsigned unused = 0;
-        const bool hit = tune_lookup(bucket_key(N, K), cached, unused);
+        const bool hit = tune_lookup(bucket_key(b), cached, unused);
         b.group_bits = hit ? (uint32_t)cached.max_bits : 22u;
         b.plain_chunk = hit ? cached.grid_cap : BATCH_CHUNK_PLAIN;
         if (b.group_bits < 12 || b.group_bits > 22 || b.plain_chunk < BATCH_CHUNK || b.plain_chunk > (1u << 20)) {

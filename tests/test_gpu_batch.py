@@ -407,3 +407,30 @@ def test_batch_traces_over_few_ids(ctx, n):
             assert_trace(t, ref, f"trace {i}, turn {turn}")
     for t in traces:
         t.free()
+
+
+def test_batch_tunings_are_kept_by_route(ctx, tmp_path, monkeypatch):
+    """Batches of one rounded shape, the first without a trace over more than 65,536 ids and the
+    second with: each route tunes on its own batch and keeps its own choice, which a second
+    batch of each takes, and every trace equals the oracle."""
+    from paper_1910_11110_amd import vcheck as V
+    cache = tmp_path / "tune.json"
+    monkeypatch.setenv("VC_TUNE_CACHE", str(cache))
+    ids = (65_536, 65_537)
+    batches = [[(gen.plain_events(40_000 + k, n, 7 + k), n, None, None, None) for k in range(2)] + make_traces(5, 8)
+               for n in ids]
+    for turn in range(2):
+        for n, inputs in zip(ids, batches):
+            traces = load_all(ctx, inputs)
+            V.batch_check(ctx, traces)
+            ctx.sync()
+            for i, (t, inp) in enumerate(zip(traces, inputs)):
+                assert_trace(t, oracle_of(*inp), f"{n} ids, trace {i}, turn {turn}")
+            for t in traces:
+                t.free()
+            text = cache.read_text()
+            say(f"[batch] {n} ids, turn {turn}: {text.split()}")
+            if turn == 0:
+                assert text.count("bucket:gfx950") == 1 + ids.index(n) and text.count(":dense") == 1, text
+                tuned = text
+            assert text == tuned, (text, tuned)
