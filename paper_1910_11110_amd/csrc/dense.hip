@@ -321,7 +321,7 @@ void launch_fold(const CHUNKS &T, const Rows &R, Control *ctl, hipStream_t s)
             k_dense_forward<Two, D_PAIR, CHUNKS><<<T.chunks, WAVE, lds, s>>>(T, R.row, R.rows, ctl, R.left);
         }
         ProfScope p(s, "dense_fold"); // (of the chunks of skewed ids)
-        k_dense_fold<FoldSkewed<Two>, D_PAIR, CHUNKS><<<T.chunks, WAVE, lds, s>>>(T, R.row, R.rows, ctl, R.left);
+        k_dense_fold<Fold<Two>, D_PAIR, CHUNKS><<<T.chunks, WAVE, lds, s>>>(T, R.row, R.rows, ctl, R.left);
     } else {
         ProfScope p(s, "dense_fold");
         k_dense_fold<Fold<Two>, D_PAIR, CHUNKS><<<T.chunks, WAVE, lds, s>>>(T, R.row, R.rows, ctl, nullptr);

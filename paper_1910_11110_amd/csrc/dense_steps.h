@@ -52,7 +52,7 @@ constexpr uint32_t host_compose(uint32_t h, uint32_t f)
 }
 struct StepTable {
     uint32_t fold[16];  // (h o f) << 3h, the element in bits 24-26
-    uint32_t onto[16];  // (f o h) << 3h
+    uint32_t onto[16];  // (f o h) << 3h, the same
     uint32_t apply[16]; // status byte << 8s
 };
 constexpr StepTable make_step_table()
@@ -69,7 +69,7 @@ constexpr StepTable make_step_table()
             e = side ? 2u : 1u;
         for (uint32_t h = 0; h < 8; h++)
             t.fold[i] |= host_compose(h, e) << (3 * h), t.onto[i] |= host_compose(e, h) << (3 * h);
-        t.fold[i] |= e << 24;
+        t.fold[i] |= e << 24, t.onto[i] |= e << 24;
         const Effect x = make_effect(op <= OP_RWIND ? op : (uint32_t)OP_NOOP, side);
         for (uint32_t s = 0; s < 4; s++) {
             const uint32_t post = (x.f4 >> (8 * s)) & 3u;
@@ -100,18 +100,14 @@ __device__ __forceinline__ uint32_t tab_load(const uint32_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
-// a function in 4-byte form as an element
-__device__ __forceinline__ uint32_t el_of(uint32_t f4)
-{
-    return ((f4 >> 16) & 1u) | ((f4 >> 8) & 2u) | ((f4 & 3u) ? 4u : 0u);
-}
-
 // ----------------------------------------------------------------------------------
 // Domains: where an id lies in the table, and an event's part in each walk (`entry`, from
 // its word; `next`: the id's bits after it, and its result; `open`: whether an event can
 // still change the id in the fold), and how the functions of lanes that share an id are
 // composed (BY_MASKS: from ballots; else they are passed along, with the lane they came
-// from (64: none) in spare bits).
+// from (64: none) in spare bits).  ALIKE: the ids of a step that are looked for before all are
+// matched; CLOSES: chunks of skewed ids close constants first (k spaces, a bucket of 2^12 ids of
+// which half a lane a step meets, gain by neither: uniform ids 187 and 207 us, 2^26 events).
 // ----------------------------------------------------------------------------------
 struct __attribute__((packed)) Bytes8 { // at any address
     uint32_t lo, hi;
@@ -119,24 +115,54 @@ struct __attribute__((packed)) Bytes8 { // at any address
 
 struct Two {
     static constexpr uint32_t MASK = 7, NOOP = (uint32_t)OP_NOOP << 24;
-    static constexpr bool BY_MASKS = true;
-    // The functions f of the lanes of `set` composed (any set for each lane), for one event's
-    // functions: a constant forgets what was before it, and the others add the CPU copy to
-    // a status with the GPU copy valid or the other way round, in any order.  So it is the
-    // latest constant of the set (BACK: lower lanes are later events) and, of the lanes
-    // after it, whether any adds either copy.  Bits 16 and 9 of a function are those, and of
-    // a constant its copies.  (Pointer jumping along the lanes waited for LDS in every round:
-    // 2^24 Zipf(1.1) events over 2^16 ids, the apply pass 180 -> 150 us.)
+    static constexpr bool BY_MASKS = true, CLOSES = true;
+    static constexpr int ALIKE = 1;
+    // The lanes of a step by what their events do, in their order from bit 0 on: constants
+    // (t), of them those that leave the CPU copy (c: one event leaves one copy), and the others
+    // that add the CPU copy to a status with the GPU copy valid (x) or the other way round (y).
+    struct Kinds {
+        uint64_t t, c, x, y;
+    };
     template <bool BACK>
-    __device__ static uint32_t compose_set(uint64_t set, uint32_t f)
+    __device__ static uint64_t in_order(uint64_t m)
     {
-        const uint64_t cpu = __ballot((f >> 16) & 1u), gpu = __ballot((f >> 9) & 1u), k = set & __ballot(constant(f));
-        const uint64_t at = BACK ? k & (~k + 1) : (k ? 1ull << (63 - __builtin_clzll(k)) : 0ull); // the constant's lane
-        const uint64_t later = set & (BACK ? at - 1 : ~(k ? at | (at - 1) : 0ull));
-        const uint32_t x = (later & cpu) != 0, y = (later & gpu) != 0;
-        const uint32_t v = ((at & cpu) != 0 ? 1u : 0u) | ((at & gpu) != 0 ? 2u : 0u);
-        const uint32_t c = v | ((v >> 1) & x) | ((v & y) << 1);
-        return k ? c * 0x01010101u : F_ID | (x << 16) | (y << 9);
+        return BACK ? __builtin_bitreverse64(m) : m; // (lower lanes are later events)
+    }
+    // from an element's bits (of the fold's table entries), or a status byte's (the walk's: the
+    // statuses after (I,I), (V,I) and (I,V))
+    template <bool BACK>
+    __device__ static Kinds kinds(bool constant, bool cpu, bool gpu)
+    {
+        const uint64_t t = in_order<BACK>(__ballot(constant)), x = in_order<BACK>(__ballot(cpu));
+        return Kinds{t, t & x, x & ~t, in_order<BACK>(__ballot(gpu)) & ~t};
+    }
+    template <bool BACK>
+    __device__ static Kinds fold_kinds(uint32_t e)
+    {
+        return kinds<BACK>((e >> 26) & 1u, (e >> 24) & 1u, (e >> 25) & 1u);
+    }
+    __device__ static Kinds apply_kinds(uint32_t e) { return kinds<false>((e & 3u) != 0, (e >> 16) & 1u, (e >> 9) & 1u); }
+    // The functions of the lanes of `set` composed (any set for each lane): a constant forgets
+    // what was before it, and the others can be taken in any order.  So it is the latest
+    // constant (k: there is one, left: its status) and whether any lane after it adds either
+    // copy (x, y: bits 0 and 1).  Of two sets without common lanes the one with the latest lane
+    // is the larger number.  (2^24 events over 2^16 ids in runs of 128 an id, the apply pass: 149
+    // us by the position of the latest constant, with shifts and masks, and as functions in
+    // 4-byte form, 96 this way.)
+    struct Composed {
+        bool k;
+        uint32_t left, x, y;
+        __device__ uint32_t status(uint32_t h) const // after it, from status h
+        {
+            const uint32_t s = k ? left : h;
+            return s | ((s >> 1) & x) | ((s << 1) & y);
+        }
+        __device__ uint32_t element() const { return k ? 4u | status(0) : x | y; }
+    };
+    __device__ static Composed compose_set(uint64_t set, const Kinds &K)
+    {
+        const uint64_t k = set & K.t, c = set & K.c;
+        return Composed{k != 0, c > (k ^ c) ? 1u : 2u, (set & K.x) > k ? 1u : 0u, (set & K.y) > k ? 2u : 0u};
     }
     __device__ static uint32_t word(uint32_t id) { return id >> 3; }
     __device__ static uint32_t shift(uint32_t id) { return 3u * (id & 7u); }
@@ -146,17 +172,15 @@ struct Two {
     __device__ static uint32_t fold_next(uint32_t e, uint32_t h) { return (e >> (3u * h)) & 7u; }
     __device__ static bool fold_open(uint32_t h) { return (h & 4u) == 0; }
     __device__ static uint32_t onto_next(uint32_t e, uint32_t h) { return (e >> (3u * h)) & 7u; }
-    __device__ static uint32_t onto_all(uint32_t f, uint32_t h) { return el_compose(el_of(f), h); }
+    __device__ static uint32_t onto_all(const Composed &f, uint32_t h) { return el_compose(f.element(), h); }
     __device__ static uint32_t apply_entry(const uint32_t *tab, uint32_t w) { return tab[16 + ((w >> 24) & 15u)]; }
     __device__ static uint32_t apply_next(uint32_t e, uint32_t h, uint32_t &byte)
     {
         byte = e >> (8u * (h & 3u));
         return 4u | (byte & 3u);
     }
-    __device__ static uint32_t function(const uint32_t *tab, uint32_t w) { return apply_entry(tab, w) & 0x03030303u; }
-    __device__ static bool constant(uint32_t f) { return (f & 3u) != 0; } // (a constant's byte 0 is not 0)
-    __device__ static uint32_t fold_all(uint32_t h, uint32_t f) { return el_compose(h, el_of(f)); }
-    __device__ static uint32_t status_after(uint32_t f, uint32_t h) { return fapply(f, h & 3u); }
+    __device__ static uint32_t fold_all(uint32_t h, const Composed &f) { return el_compose(h, f.element()); }
+    __device__ static uint32_t status_after(const Composed &f, uint32_t h) { return f.status(h & 3u); }
     // rows: a word's composition, the initial statuses of its ids (from id on, n_ids in all)
     // as constants, and its statuses as final ones
     static constexpr uint32_t IDS = 8, ROW_IDENTITY = 0;
@@ -195,9 +219,22 @@ struct Two {
     }
 };
 
-// the lanes of `among` with this lane's id (ids of `bits` bits, at most 16)
+// The lanes of `among` with this lane's id (ids of `bits` bits, at most 16); of a lane that is
+// not among them, anything.  The first FIRST ids are taken one by one (a run of events on an id
+// fills steps), and if there are more all lanes are matched bit by bit.
+template <int FIRST>
 __device__ __forceinline__ uint64_t same_id(uint32_t id, uint64_t among, uint32_t bits)
 {
+    uint64_t rest = among, mine = 0;
+#pragma unroll
+    for (int k = 0; k < FIRST && rest; k++) {
+        const bool eq = id == (uint32_t)__builtin_amdgcn_readlane((int)id, __builtin_ctzll(rest));
+        const uint64_t with = among & __ballot(eq);
+        mine = eq ? with : mine;
+        rest &= ~with;
+    }
+    if (FIRST && !rest)
+        return mine;
     uint32_t lo = (uint32_t)among, hi = (uint32_t)(among >> 32);
     match_bits<0, 4>(id, lo, hi);
     if (bits > 4)
@@ -205,7 +242,9 @@ __device__ __forceinline__ uint64_t same_id(uint32_t id, uint64_t among, uint32_
     if (bits > 8)
         match_bits<8, 12>(id, lo, hi);
     if (bits > 12)
-        match_bits<12, 16>(id, lo, hi);
+        match_bits<12, 14>(id, lo, hi);
+    if (bits > 14)
+        match_bits<14, 16>(id, lo, hi);
     return ((uint64_t)hi << 32) | lo;
 }
 
@@ -241,40 +280,36 @@ __device__ __forceinline__ void compose_along(uint32_t (&f)[Q], uint32_t (&p)[Q]
 template <class D>
 struct Fold {
     static constexpr bool BACK = true;
-    static constexpr bool CLOSE_FIRST = false;
     using Dom = D;
     __device__ static uint32_t entry(const uint32_t *tab, uint32_t w) { return D::fold_entry(tab, w); }
     __device__ static bool takes_part(uint32_t e) { return D::fold_part(e); }
     __device__ static bool open(uint32_t h) { return D::fold_open(h); }
     __device__ static uint32_t next(uint32_t e, uint32_t h, uint32_t &) { return D::fold_next(e, h); }
     __device__ static uint32_t first_table(uint32_t i) { return STEPS.fold[i]; }
-};
-// ids that are constants already leave before the lanes enter: a read more a step (2^26
-// uniform events over 2^16 ids: 231 -> 273 us), but of skewed ids few still meet (2^24 of
-// Zipf(1.1): 106 -> 89 us)
-template <class D>
-struct FoldSkewed : Fold<D> {
-    static constexpr bool CLOSE_FIRST = true;
+    __device__ static auto kinds(uint32_t e) { return D::template fold_kinds<true>(e); }
 };
 template <class D>
 struct Apply {
     static constexpr bool BACK = false;
-    static constexpr bool CLOSE_FIRST = false;
     using Dom = D;
     __device__ static uint32_t entry(const uint32_t *tab, uint32_t w) { return D::apply_entry(tab, w); }
     __device__ static bool takes_part(uint32_t) { return true; }
     __device__ static bool open(uint32_t) { return true; }
     __device__ static uint32_t next(uint32_t e, uint32_t h, uint32_t &result) { return D::apply_next(e, h, result); }
     // the status after the functions before the event
-    __device__ static uint32_t after(uint32_t f, uint32_t h) { return D::status_after(f, h); }
+    template <class F>
+    __device__ static uint32_t after(const F &f, uint32_t h)
+    {
+        return D::status_after(f, h);
+    }
     static constexpr bool FUNCTIONS = false;
     __device__ static uint32_t first_table(uint32_t i) { return STEPS.fold[i]; }
+    __device__ static auto kinds(uint32_t e) { return D::apply_kinds(e); }
 };
 // every id's function composed forwards; an event's result is the one before it
 template <class D>
 struct Onto {
     static constexpr bool BACK = false;
-    static constexpr bool CLOSE_FIRST = false;
     using Dom = D;
     __device__ static uint32_t entry(const uint32_t *tab, uint32_t w) { return D::fold_entry(tab, w); }
     __device__ static bool takes_part(uint32_t) { return true; }
@@ -284,9 +319,14 @@ struct Onto {
         result = h;
         return D::onto_next(e, h);
     }
-    __device__ static uint32_t after(uint32_t f, uint32_t h) { return D::onto_all(f, h); }
+    template <class F>
+    __device__ static uint32_t after(const F &f, uint32_t h)
+    {
+        return D::onto_all(f, h);
+    }
     static constexpr bool FUNCTIONS = true;
     __device__ static uint32_t first_table(uint32_t i) { return STEPS.onto[i]; } // (in the fold's place)
+    __device__ static auto kinds(uint32_t e) { return D::template fold_kinds<false>(e); }
 };
 
 template <class DIR>
@@ -364,49 +404,85 @@ __device__ __forceinline__ uint32_t step_in_turn(const Lane<DIR> &L, uint64_t me
     return result;
 }
 
+// lanes of a step that share ids with others, at most, for which taking turns is the shorter way
+// (2^24 uniform events over 512 ids: 137 us, 148 with 5 and 165 with 2)
+constexpr int D_FEW = 10;
+
 // Q steps whose lanes may share ids, one after the other; no lane is in the table.  What
 // the lanes of an id do together does not depend on the table, so the steps work it out
-// side by side.  `shared` counts the steps where any did.
+// side by side.  `shared` counts the steps where any did (backwards, where the open ids go on
+// getting fewer, those where more than few did, and those without an open id).
 template <class DIR, int Q>
 __device__ __forceinline__ void steps_together(const Lane<DIR> (&L)[Q], uint32_t (&result)[Q], const uint32_t *s_tab,
                                                uint32_t bits, uint32_t lane, uint32_t &shared)
 {
     using D = typename DIR::Dom;
-    uint32_t f[Q], p[Q], prev[Q], g[Q];
-    bool in[Q], last[Q];
+    bool in[Q], any = false;
+    uint64_t same[Q];
+    const uint64_t under = (1ull << lane) - 1;
 #pragma unroll
-    for (int q = 0; q < Q; q++) // (a later step's id may close before it: it then changes nothing)
+    for (int q = 0; q < Q; q++) { // (a later step's id may close before it: it then changes nothing)
         in[q] = L[q].part && (!DIR::BACK || DIR::open(L[q].field(tab_load(L[q].p))));
+        any = any || in[q];
+    }
+    if (DIR::BACK && !__ballot(any)) { // nothing changes (and the next steps may be as much alike)
+        shared += Q;
+        return;
+    }
 #pragma unroll
     for (int q = 0; q < Q; q++) {
-        const uint64_t same = same_id(L[q].id, __ballot(in[q]), bits);
-        const uint32_t rank = mask_rank(same);
-        const uint64_t below = same & ((1ull << lane) - 1);
-        prev[q] = p[q] = in[q] && rank ? 63u - (uint32_t)__builtin_clzll(below) : 64u;
-        last[q] = in[q] && rank + 1 == (uint32_t)__builtin_popcountll(same); // of its id
-        f[q] = D::function(s_tab, L[q].w);
-        shared += __ballot(prev[q] < 64) ? 1u : 0u;
-        if constexpr (D::BY_MASKS)
-            (DIR::BACK ? f[q] : g[q]) = D::template compose_set<DIR::BACK>(DIR::BACK ? same : below, f[q]);
+        const uint64_t among = __ballot(in[q]);
+        same[q] = same_id<D::ALIKE>(L[q].id, among, bits);
+        same[q] = in[q] ? same[q] : 0ull;
+        const uint64_t m = __ballot((same[q] & under) != 0);
+        shared += (DIR::BACK ? !among || __builtin_popcountll(m) > D_FEW : m != 0) ? 1u : 0u;
     }
-    if constexpr (!D::BY_MASKS) {
+    // writes the table: the last lane of its id
+    auto last = [&](int q) { return (same[q] & ~under) == 1ull << lane; };
+    if constexpr (D::BY_MASKS) {
+        typename D::Composed f[Q]; // BACK: of all lanes of the id; else of those before
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            f[q] = D::compose_set(DIR::BACK ? D::template in_order<true>(same[q]) : same[q] & under,
+                                  DIR::kinds(L[q].entry));
+        }
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            const uint32_t h = L[q].field(tab_load(L[q].p));
+            uint32_t nh;
+            if constexpr (DIR::BACK)
+                nh = D::fold_all(h, f[q]);
+            else
+                nh = DIR::next(L[q].entry, DIR::after(f[q], h), result[q]);
+            if (last(q))
+                tab_xor(L[q].p, L[q].change(h, nh));
+            compiler_fence();
+        }
+    } else {
+        uint32_t f[Q], p[Q], prev[Q], g[Q];
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            const uint64_t below = same[q] & under;
+            prev[q] = p[q] = below ? 63u - (uint32_t)__builtin_clzll(below) : 64u;
+            f[q] = D::function(s_tab, L[q].w);
+        }
         compose_along<D, DIR::BACK, Q>(f, p);
         if constexpr (!DIR::BACK)
 #pragma unroll
             for (int q = 0; q < Q; q++)
                 g[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((prev[q] & 63u) * 4u), (int)f[q]);
-    }
 #pragma unroll
-    for (int q = 0; q < Q; q++) {
-        const uint32_t h = L[q].field(tab_load(L[q].p));
-        uint32_t nh;
-        if constexpr (DIR::BACK)
-            nh = D::fold_all(h, f[q]);
-        else
-            nh = DIR::next(L[q].entry, prev[q] < 64 ? DIR::after(g[q], h) : h, result[q]);
-        if (last[q])
-            tab_xor(L[q].p, L[q].change(h, nh));
-        compiler_fence();
+        for (int q = 0; q < Q; q++) {
+            const uint32_t h = L[q].field(tab_load(L[q].p));
+            uint32_t nh;
+            if constexpr (DIR::BACK)
+                nh = D::fold_all(h, f[q]);
+            else
+                nh = DIR::next(L[q].entry, prev[q] < 64 ? DIR::after(g[q], h) : h, result[q]);
+            if (last(q))
+                tab_xor(L[q].p, L[q].change(h, nh));
+            compiler_fence();
+        }
     }
 }
 
@@ -414,13 +490,15 @@ __device__ __forceinline__ void steps_together(const Lane<DIR> (&L)[Q], uint32_t
 // step nor of the ones before it, their reads are one wait and their changes independent.
 // Otherwise all leave and the steps take their turns; lanes that share ids within a step
 // take turns too when they are few, else they work their changes out together.
-constexpr int D_FEW = 10;
+// close: ids that are constants already leave before the lanes enter (only backwards; a read
+// more a step).  `again` counts the events that met an id of their own step.
 template <class DIR, int PAIR>
 __device__ __forceinline__ void steps(Lane<DIR> (&L)[PAIR], uint32_t (&result)[PAIR], const uint32_t *s_tab,
-                                      uint32_t bits, uint32_t lane, uint32_t &shared_steps)
+                                      uint32_t bits, uint32_t lane, uint32_t &shared_steps, bool close,
+                                      uint32_t &again)
 {
     bool met = false;
-    if constexpr (DIR::CLOSE_FIRST)
+    if (DIR::BACK && DIR::Dom::CLOSES && close)
 #pragma unroll
         for (int q = 0; q < PAIR; q++)
             L[q].part = L[q].part && DIR::open(L[q].field(tab_load(L[q].p)));
@@ -450,6 +528,7 @@ __device__ __forceinline__ void steps(Lane<DIR> (&L)[PAIR], uint32_t (&result)[P
         if (PAIR > 1 || DIR::BACK)
             L[q].enter();
         const uint64_t m = __ballot(L[q].met());
+        again += (uint32_t)__builtin_popcountll(m);
         if (!m) {
             result[q] = step_apart<DIR>(L[q]);
         } else {
@@ -471,6 +550,36 @@ __device__ __forceinline__ void steps(Lane<DIR> (&L)[PAIR], uint32_t (&result)[P
 constexpr int D_UNROLL = 8; // steps whose events are loaded together
 // a round whose last one worked out at least so many of its steps together does so for all
 constexpr uint32_t D_TOGETHER = D_UNROLL / 2;
+
+// a round's words turned by PAIR: a loop over the round's steps takes the first ones, so that
+// its code is not there for every step, nor are the words read from memory again (2^24 events
+// over 2^16 ids in runs of 128 an id: fold 130 -> 116 us)
+template <int PAIR>
+__device__ __forceinline__ void turn_words(uint32_t (&w)[D_UNROLL])
+{
+    uint32_t v[D_UNROLL];
+#pragma unroll
+    for (int u = 0; u < D_UNROLL; u++)
+        v[u] = w[(u + PAIR) % D_UNROLL];
+#pragma unroll
+    for (int u = 0; u < D_UNROLL; u++)
+        w[u] = v[u];
+}
+
+// The first round of a chunk goes that way when so many of its events have their neighbour's
+// id: about 500 times the chance that two events share theirs, where a step has about 2,000
+// times that of lanes that meet, and on one address the lanes' atomics take turns (2^24 events
+// over 2^20 ids in runs of 128 an id: fold 70 -> 59, apply 72 -> 47 us).
+constexpr uint32_t D_ALIKE = 4;
+__device__ __forceinline__ uint32_t first_shared(const uint32_t (&w)[D_UNROLL])
+{
+    uint32_t alike = 0;
+#pragma unroll
+    for (int u = 0; u < D_UNROLL; u++)
+        alike += (uint32_t)__builtin_popcountll(
+            __ballot(((dpp_move<DPP_WAVE_SHR1>(~w[u], w[u]) ^ w[u]) & 0xFFFFFFu) == 0));
+    return alike >= D_ALIKE ? D_TOGETHER : 0u;
+}
 
 template <class DIR>
 __device__ __forceinline__ void load_step_table(uint32_t *s_tab, uint32_t lane)
@@ -524,7 +633,7 @@ __device__ __forceinline__ void walk_forward(const C &c, uint32_t *s_t, const ui
     using D = typename DIR::Dom;
     const uint64_t i0 = c.begin;
     const uint32_t bits = c.bits, len = (uint32_t)(c.end - i0), rounds = len / (D_UNROLL * WAVE);
-    uint32_t shared_steps = 0;
+    uint32_t shared_steps = rounds ? first_shared(nxt) : 0u, again = 0;
     for (uint32_t r = 0; r < rounds; r++) {
         uint32_t w[D_UNROLL];
 #pragma unroll
@@ -539,25 +648,18 @@ __device__ __forceinline__ void walk_forward(const C &c, uint32_t *s_t, const ui
         }
         if (shared_steps >= D_TOGETHER) {
             shared_steps = 0;
-            uint32_t v[PAIR];
-#pragma unroll
-            for (int q = 0; q < PAIR; q++)
-                v[q] = w[q];
 #pragma unroll 1
             for (int u = 0; u < D_UNROLL; u += PAIR) {
                 Lane<DIR> L[PAIR];
-                uint32_t byte[PAIR], now[PAIR];
-                const int n = u + PAIR < D_UNROLL ? u + PAIR : u;
+                uint32_t byte[PAIR];
 #pragma unroll
-                for (int q = 0; q < PAIR; q++) {
-                    now[q] = v[q];
-                    L[q] = make_lane<DIR>(s_t, s_tab, v[q], c.clamped(v[q]), true);
-                    v[q] = c.ev[i + (n + q) * WAVE + lane];
-                }
+                for (int q = 0; q < PAIR; q++)
+                    L[q] = make_lane<DIR>(s_t, s_tab, w[q], c.clamped(w[q]), true);
                 steps_together<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
 #pragma unroll
                 for (int q = 0; q < PAIR; q++)
-                    out.step(lane, u + q, i + (u + q) * WAVE, now[q], byte[q], true);
+                    out.step(lane, u + q, i + (u + q) * WAVE, w[q], byte[q], true);
+                turn_words<PAIR>(w);
             }
         } else {
             shared_steps = 0;
@@ -568,7 +670,7 @@ __device__ __forceinline__ void walk_forward(const C &c, uint32_t *s_t, const ui
 #pragma unroll
                 for (int q = 0; q < PAIR; q++)
                     L[q] = make_lane<DIR>(s_t, s_tab, w[u + q], c.clamped(w[u + q]), true);
-                steps<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
+                steps<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps, false, again);
 #pragma unroll
                 for (int q = 0; q < PAIR; q++)
                     out.step(lane, u + q, i + (u + q) * WAVE, w[u + q], byte[q], true);
@@ -625,7 +727,13 @@ struct NoOut {
     __device__ void round(uint32_t, uint64_t, uint32_t, bool) const {}
 };
 
-// every chunk's functions into its row (left: of the chunks marked there only)
+// From a round on in which so many events met an id of their own step the ids of a chunk are
+// skewed: few still meet when those that are constants leave first (2^24 events of Zipf(1.1)
+// ids over 2^16: fold 106 -> 89 us, 2^26 over 2^20 211 -> 134; uniform ids, of which a round of
+// 512 has one or two that meet from 2^14 on, 231 -> 273 us at 2^26 over 2^16).
+constexpr uint32_t CLOSE_FROM = 32;
+
+// every chunk's functions into its row (left: of the chunks marked there, of skewed ids, only)
 template <class F, int PAIR, class CHUNKS>
 __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, uint32_t *__restrict__ rows,
                                                      Control *ctl, const uint32_t *__restrict__ left)
@@ -652,6 +760,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
                 atomicMin(reinterpret_cast<unsigned long long *>(&to->err_index_lo), (unsigned long long)i);
         };
         uint32_t shared_steps = 0;
+        bool close = left != nullptr;
         // the events past the whole rounds, one step at a time
         for (uint32_t left = len - rounds * (D_UNROLL * WAVE); left;) {
             const uint32_t m = left < WAVE ? left : WAVE;
@@ -676,8 +785,11 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
             for (int u = 0; u < D_UNROLL; u++)
                 nxt[u] = e[-(u * WAVE)];
         };
-        if (rounds)
+        if (rounds) {
             load(rounds);
+            shared_steps = first_shared(nxt);
+            close = close || shared_steps;
+        }
         for (uint32_t r = rounds; r > 0; r--) {
             uint32_t w[D_UNROLL], badm = 0;
 #pragma unroll
@@ -695,27 +807,20 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
             }
             if (shared_steps >= D_TOGETHER) {
                 shared_steps = 0;
-                const uint32_t *e = e0 + (uint64_t)r * (D_UNROLL * WAVE);
-                uint32_t v[PAIR];
-#pragma unroll
-                for (int q = 0; q < PAIR; q++)
-                    v[q] = w[q];
 #pragma unroll 1
                 for (int u = 0; u < D_UNROLL; u += PAIR) {
                     Lane<F> L[PAIR];
                     uint32_t none[PAIR];
-                    const int n = u + PAIR < D_UNROLL ? u + PAIR : u;
 #pragma unroll
-                    for (int q = 0; q < PAIR; q++) {
-                        const uint32_t x = clean(v[q], C.bad(v[q]));
-                        v[q] = e[-((n + q) * WAVE)];
-                        L[q] = make_lane<F>(s_t, s_tab, x, C.local(x), true);
-                    }
+                    for (int q = 0; q < PAIR; q++)
+                        L[q] = make_lane<F>(s_t, s_tab, w[q], C.local(w[q]), true);
                     steps_together<F, PAIR>(L, none, s_tab, bits, lane, shared_steps);
+                    turn_words<PAIR>(w);
                 }
                 continue;
             }
             shared_steps = 0;
+            uint32_t again = 0;
 #pragma unroll
             for (int u = 0; u < D_UNROLL; u += PAIR) {
                 Lane<F> L[PAIR];
@@ -723,8 +828,9 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
 #pragma unroll
                 for (int q = 0; q < PAIR; q++)
                     L[q] = make_lane<F>(s_t, s_tab, w[u + q], C.local(w[u + q]), true);
-                steps<F, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
+                steps<F, PAIR>(L, byte, s_tab, bits, lane, shared_steps, close, again);
             }
+            close = close || again >= CLOSE_FROM;
         }
         compiler_fence();
         uint4 *out = reinterpret_cast<uint4 *>(rows + C.row_at);

@@ -128,8 +128,10 @@ __device__ __forceinline__ uint32_t sign_bit(uint32_t v)
 __device__ __forceinline__ void match_bit(uint32_t sel, uint32_t &mlo, uint32_t &mhi)
 {
     const uint64_t bb = __ballot(sel != 0);
-    mlo &= ~(sel ^ (uint32_t)bb);
-    mhi &= ~(sel ^ (uint32_t)(bb >> 32));
+    // m & ~(sel ^ bb), one operation a half (left to itself the compiler takes an exclusive or
+    // a half and bit and then joins three bits at once: five operations a bit, not four)
+    mlo = __builtin_amdgcn_bitop3_b32(mlo, sel, (uint32_t)bb, 0x90);
+    mhi = __builtin_amdgcn_bitop3_b32(mhi, sel, (uint32_t)(bb >> 32), 0x90);
 }
 template <int B, int N>
 __device__ __forceinline__ void match_bits(uint32_t d, uint32_t &mlo, uint32_t &mhi)

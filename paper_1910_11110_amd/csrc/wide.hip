@@ -16,7 +16,8 @@ namespace {
 // k memory spaces: a word per id, its function (17 bits) and the touch bit
 struct Spaces {
     static constexpr uint32_t SELF = 0x8421u; // every location reaches itself
-    static constexpr bool BY_MASKS = false;
+    static constexpr bool BY_MASKS = false, CLOSES = false;
+    static constexpr int ALIKE = 0;
     static constexpr uint32_t MASK = 0x1FFFFu, IDENTITY = KF_ID, NOOP = 3u << 24, IDS = 1, ROW_IDENTITY = KF_ID;
     __device__ static uint32_t word(uint32_t id) { return id; }
     __device__ static uint32_t shift(uint32_t) { return 0; }

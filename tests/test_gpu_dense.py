@@ -227,3 +227,29 @@ def test_dense_steps_that_share(ctx, few, ops):
     assert np.array_equal(t.final(), ref.final)
     assert np.array_equal(t.violations().indices, ref.violations)
     t.free()
+
+
+@pytest.mark.parametrize("block", [300, 700, 5000])
+@pytest.mark.parametrize("n_ids", [300, 4096, 65_536, 1 << 17])
+def test_dense_ids_that_change_their_kind(ctx, n_ids, block):
+    """Chunks of several rounds whose blocks are uniform, runs of an id, two ids in turn, skewed
+    or a single id, without constants at times: every round goes another way than the last one,
+    the first rounds of the chunks too."""
+    from paper_1910_11110_amd import vcheck as V
+    n = 5_000_011
+    rng = np.random.default_rng(n_ids + block)
+    i = np.arange(n)
+    kind = (i // block) % 5
+    ids = np.choose(kind, [rng.integers(0, n_ids, n), np.repeat(rng.integers(0, n_ids, n // 100 + 1), 100)[:n],
+                           np.where(i & 1, n_ids - 1, 3), ids_of("skewed", n, n_ids, rng), np.full(n, n_ids // 2)])
+    op = np.where((i // (7 * block)) % 3 == 0, rng.integers(0, 5, n), rng.integers(2, 5, n))
+    e = gen.pack_events(ids, op, rng.integers(0, 2, n))
+    init = rng.integers(0, 4, n_ids).astype(np.uint8)
+    print(f"[dense] changing kinds, {block} x {n_ids}", flush=True)
+    t = V.Trace.load(ctx, e, n_ids, init)
+    t.check()
+    ref = O.check(e, n_ids, init)
+    assert np.array_equal(t.status(), ref.status)
+    assert np.array_equal(t.final(), ref.final)
+    assert np.array_equal(t.violations().indices, ref.violations)
+    t.free()
