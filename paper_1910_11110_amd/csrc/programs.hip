@@ -8,7 +8,7 @@
 // A wave first turns its 64 programs into steps in LDS (k_run_steps): one word per
 // statement holding the effect as bit masks, the condition, and the two statements that
 // can follow, so that running a step is straight-line code with one LDS read, the same
-// for effects, While and If.  Programs too long for that are walked in place
+// for effects, While and If.  Programs too long for that, or with too little fuel, are walked in place
 // (k_run_programs): their syntax tree, serialised in prefix order, with a stack of resume
 // points in LDS, where entering a While body or an If branch pushes where to go when the
 // block ends (the While header, which evaluates its condition again, or the word after
@@ -312,9 +312,23 @@ __global__ __launch_bounds__(WAVE) void k_run_steps(
 // Whether the programs run as steps in LDS: a step names statements by 9 bits, the
 // steps' counters have 32 bits, and a wave's columns (the longest program, its end and two
 // nesting frames per level) fit the 64 KiB that a launch may take.
+static size_t steps_lds(uint64_t longest, uint32_t depth) { return (longest + 1 + 2 * depth) * (size_t)(WAVE * 4); }
 static bool fits_steps(uint64_t longest, uint32_t depth, uint64_t fuel)
 {
-    return longest <= STEP_MAX && longest + 1 + 2 * depth <= 65536 / (4 * WAVE) && fuel < (1ull << 32);
+    return longest <= STEP_MAX && steps_lds(longest, depth) <= 65536 && fuel < (1ull << 32);
+}
+
+// Whether that is worth it: a wave makes the steps of all its words first (about 0.4 us a word,
+// in as many rounds as the columns leave waves on the device), and a reduction in place takes
+// 1.6 us (in rounds of 4,096 waves).  Kernel times in place and by steps, by program words and
+// fuel: 2^17 programs 24 / 8 21.6 and 25.1 us, 24 / 16 38 and 26, 64 / 16 43 and 49, 64 / 32 78
+// and 52, 240 / 128 264 and 449, 240 / 512 931 and 594; 2^20 programs 64 / 32 334 and 317; 2,048
+// programs 240 / 32 66 and 94, 240 / 128 208 and 102.
+static bool worth_steps(uint64_t n_prog, uint64_t longest, uint32_t depth, uint64_t fuel)
+{
+    const uint64_t waves = ceil_div(n_prog, (uint64_t)WAVE), per_cu = 163840 / steps_lds(longest, depth);
+    const uint64_t rounds = ceil_div(waves, 256 * (per_cu < 32 ? per_cu : 32)), in_place = ceil_div(waves, (uint64_t)4096);
+    return 7 * fuel * in_place >= 2 * longest * rounds;
 }
 
 void launch_run_programs(const uint64_t *prog_off, uint64_t n_prog, const uint32_t *words, uint32_t n_vars,
@@ -324,11 +338,11 @@ void launch_run_programs(const uint64_t *prog_off, uint64_t n_prog, const uint32
 {
     if (!n_prog)
         return;
-    if (fits_steps(longest, depth, fuel)) {
+    if (fits_steps(longest, depth, fuel) && worth_steps(n_prog, longest, depth, fuel)) {
         const uint64_t waves = ceil_div(n_prog, (uint64_t)WAVE);
         const unsigned grid = (unsigned)(waves > 1048576 ? 1048576 : waves);
         const uint32_t rows = (uint32_t)longest + 1;
-        const size_t lds = (rows + 2 * depth) * (size_t)WAVE * 4;
+        const size_t lds = steps_lds(longest, depth);
         const auto kernel = n_vars <= 16   ? k_run_steps<Statuses16>
                             : n_vars <= 32 ? k_run_steps<Statuses32>
                                            : k_run_steps<Statuses64>;

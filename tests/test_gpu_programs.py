@@ -111,3 +111,11 @@ def test_programs_step_limits(ctx, n_vars, longest):
                      rng.integers(0, 4, len(progs) * n_vars).astype(np.uint8))
     for fuel in (0, 7, 700):
         assert_parity(ctx, P, fuel, label=f"longest {longest}, {n_vars} variables")
+
+
+@pytest.mark.parametrize("n_prog,max_words,fuel", [(129, 64, 17), (129, 64, 18), (129, 64, 19), (70_001, 24, 6),
+                                                   (70_001, 24, 7), (5000, 240, 68), (5000, 240, 69), (40_001, 240, 200)])
+def test_programs_around_the_fuel_for_steps(ctx, n_prog, max_words, fuel):
+    """Around the fuel from which programs are made into steps."""
+    P = gen.structured_programs(n_prog, 9, n_prog + fuel, n_templates=256, max_words=max_words)
+    assert_parity(ctx, P, fuel, label=f"{max_words} words")

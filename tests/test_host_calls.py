@@ -68,3 +68,21 @@ other = (C.c_uint8 * 64)()
 ok(L.vc_check_small_noalloc(ctx, at, 0, 64, table, status, other, viol, counts))
 assert list(table) == list(other) == list(range(64))
 """)
+
+
+@pytest.mark.parametrize("n,words,fuel,steps", [(2048, 240, 32, False), (2048, 240, 128, True), (2048, 64, 4, False),
+                                                (2048, 64, 4096, True), (1 << 17, 240, 128, False),
+                                                (1 << 17, 240, 512, True), (1 << 17, 24, 16, True),
+                                                (300, 600, 4096, False), (300, 1, 0, False), (300, 0, 0, True)])
+def test_programs_with_little_fuel_are_walked_in_place(runtime, n, words, fuel, steps):
+    """Making the steps of all words is not worth it for programs that take few reductions."""
+    run(runtime, f"""
+import numpy as np
+off = np.arange({n} + 1, dtype=np.uint64) * {words}
+w = np.full(max({n} * {words}, 1), 4 << 24, np.uint32)
+L.vc_run_programs.argtypes = [P, P, u64, P, u32, P, P, u64, C.POINTER(P)]
+h = P()
+ok(L.vc_run_programs(ctx, off.ctypes.data, {n}, w.ctypes.data, 1, None, None, {fuel}, C.byref(h)))
+names = [name for name, _ in launches() if "k_run_" in name]
+assert len(names) == 1 and ("k_run_steps" in names[0]) == {steps}, names
+""")
