@@ -169,6 +169,8 @@ extern "C" int vc_sync(vc_ctx *c)
         if ((e = hipHostMalloc(&c->collect, cap * (sizeof(CollectPtrs) + 4 * COLLECT_WORDS), hipHostMallocDefault)) !=
             hipSuccess) {
             c->collect = nullptr;
+            (void)hipGetLastError();
+            (void)hipStreamSynchronize(c->stream); // (the call waits, also when it fails)
             return vc_hip_fail(e, "hipHostMalloc(collection)");
         }
         c->collect_cap = cap;
@@ -179,9 +181,13 @@ extern "C" int vc_sync(vc_ctx *c)
         const vc_trace *t = c->pending[i];
         ptrs[i] = CollectPtrs{t->translate_pending ? t->tr->ctl : nullptr, t->ctl, (const uint32_t *)t->viol.p};
     }
-    launch_collect(ptrs, (uint32_t)m, (uint32_t *)words, c->stream);
+    const hipError_t launched = launch_collect(ptrs, (uint32_t)m, (uint32_t *)words, c->stream);
+    if (launched != hipSuccess)
+        (void)hipGetLastError();
     if ((e = hipStreamSynchronize(c->stream)) != hipSuccess)
         return vc_hip_fail(e, "hipStreamSynchronize");
+    if (launched != hipSuccess) // (nothing was collected: the words are an earlier call's)
+        return vc_hip_fail(launched, "collection of finished work");
     prof_collect(c);
     int rc = VC_OK;
     for (size_t i = 0; i < m; i++) {

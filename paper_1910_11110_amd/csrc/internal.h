@@ -64,7 +64,7 @@ struct CollectPtrs {
     const uint32_t *viol;
 };
 constexpr uint32_t COLLECT_WORDS = 2 * (CONTROL_HEADER / 4) + 16;
-void launch_collect(const CollectPtrs *p, uint32_t n, uint32_t *out, hipStream_t s);
+hipError_t launch_collect(const CollectPtrs *p, uint32_t n, uint32_t *out, hipStream_t s);
 // the host-read headers of n control blocks and the first violation word of each (read
 // only when its block counts violations), GATHER_WORDS words per block into out
 constexpr uint32_t GATHER_WORDS = CONTROL_HEADER / 4 + 1;

@@ -363,10 +363,12 @@ void launch_gather_headers(const Control *const *ctl, const uint32_t *const *vio
         k_gather_headers<<<(n + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(ctl, viol, n, out);
 }
 
-void launch_collect(const CollectPtrs *p, uint32_t n, uint32_t *out, hipStream_t s)
+hipError_t launch_collect(const CollectPtrs *p, uint32_t n, uint32_t *out, hipStream_t s)
 {
-    if (n)
-        k_collect<<<n, WAVE, 0, s>>>(p, out);
+    if (!n)
+        return hipSuccess;
+    void *args[] = {&p, &out};
+    return hipLaunchKernel((const void *)k_collect, dim3(n), dim3(WAVE), args, 0, s);
 }
 
 void launch_prep(Control *c, Control *c2, const FillJob *jobs, int njobs, hipStream_t s)

@@ -86,3 +86,36 @@ ok(L.vc_run_programs(ctx, off.ctypes.data, {n}, w.ctypes.data, 1, None, None, {f
 names = [name for name, _ in launches() if "k_run_" in name]
 assert len(names) == 1 and ("k_run_steps" in names[0]) == {steps}, names
 """)
+
+
+CHECKED = """
+ev = (C.c_uint32 * 5000)()
+t = P()
+ok(L.vc_trace_load(ctx, ev, 5000, 100, None, 0, C.byref(t)))
+ok(L.vc_check(t))
+F.fake_reset()
+"""
+
+
+def test_sync_reports_a_collection_that_was_not_launched(runtime):
+    """What vc_sync takes of a trace comes from the launch behind its work: without it, from no
+    launch of that call.  The next synchronization collects the trace."""
+    run(runtime, CHECKED + """
+F.fake_fail_kernel(b"k_collect")
+assert L.vc_sync(ctx) == -3, L.vc_last_error()
+assert F.fake_syncs() >= 1
+F.fake_fail_kernel(b"")
+L.vc_sync(ctx)
+assert [n for n, _ in launches() if "k_collect" in n]
+ok(L.vc_check(t))
+""")
+
+
+def test_sync_waits_without_pinned_memory(runtime):
+    run(runtime, CHECKED + """
+F.fake_fail_pinned(1)
+assert L.vc_sync(ctx) == -2, L.vc_last_error()
+assert F.fake_syncs() >= 1
+F.fake_fail_pinned(0)
+ok(L.vc_check(t))
+""")
