@@ -530,9 +530,14 @@ static SmallLayout small_layout(void *scratch, uint64_t n)
     return L;
 }
 
-// (no shorter trace needs more: the short strands' look-back words reach their most just
-// below the first long trace, where the flag words are a fraction of the largest trace's)
-size_t small_scratch_bytes(uint64_t n) { return small_layout(nullptr, n).bytes; }
+// (the most a trace of n events or fewer takes: the longest one by short strands has more
+// look-back words than the first by long ones)
+size_t small_scratch_bytes(uint64_t n)
+{
+    const size_t own = small_layout(nullptr, n).bytes;
+    const size_t shorter = small_layout(nullptr, n < LONG_FROM ? n : LONG_FROM - 1).bytes;
+    return own > shorter ? own : shorter;
+}
 
 uint32_t small_max_ids() { return SK; }
 

@@ -119,3 +119,14 @@ assert F.fake_syncs() >= 1
 F.fake_fail_pinned(0)
 ok(L.vc_check(t))
 """)
+
+
+@pytest.mark.parametrize("name,at", [("small", 3 << 21), ("compact", 1 << 22)])
+def test_scratch_holds_every_shorter_trace(runtime, name, at):
+    """A work space sized for n events serves every shorter trace, also where the layout changes."""
+    run(runtime, f"""
+size = getattr(L, "_ZN2vc{len(name) + 14}{name}_scratch_bytesEm")
+size.argtypes, size.restype = [u64], C.c_size_t
+sizes = [size(n) for n in list(range(0, 40_000, 997)) + list(range({at} - 50_000, {at} + 900_000, 4_093)) + [1 << 24, 1 << 30]]
+assert sizes == sorted(sizes)
+""")
