@@ -434,3 +434,58 @@ def test_batch_tunings_are_kept_by_route(ctx, tmp_path, monkeypatch):
                 assert text.count("bucket:gfx950") == 1 + ids.index(n) and text.count(":dense") == 1, text
                 tuned = text
             assert text == tuned, (text, tuned)
+
+
+@pytest.mark.parametrize("bits", [12, 17, 20, 22])
+def test_batch_bucket_route_by_groups(ctx, tmp_path, monkeypatch, bits):
+    """A batch with a trace over more than 65,536 ids takes the bucket route, here with groups of
+    2^12 to 2^22 ids (the tuning comes from the cache): plain traces, with arrays (nearly all
+    overlapping in one), with initial statuses, empty; replayed, and equal to the sorted route."""
+    from paper_1910_11110_amd import vcheck as V
+    rng = np.random.default_rng(6)
+    lo = rng.integers(0, 500, 300).astype(np.uint32)
+    hi = (lo + rng.integers(300, 500, 300)).astype(np.uint32)
+    inputs = make_traces(25, 12, vars_range=(8, 3000))
+    inputs[3:3] = [(gen.plain_events(9_000, 300, 15), 300, lo, hi, None),
+                   (np.zeros(0, np.uint32), 5, None, None, np.arange(5, dtype=np.uint8) & 3)]
+    for at, n in ((10, 65_537), (20, 3 << 18)):
+        inputs.insert(at, (gen.plain_events(30_000, n, at), n, None, None, rng.integers(0, 4, n).astype(np.uint8)))
+    events, ids = sum(i[0].size for i in inputs), sum(i[1] for i in inputs)
+    cache = tmp_path / "tune.json"
+    up = lambda v: (v - 1).bit_length()  # noqa: E731
+    cache.write_text(f'{{"bucket:gfx950:n2^{up(events)}:k2^{up(ids)}": [{bits}, 4096, 0]}}')
+    monkeypatch.setenv("VC_TUNE_CACHE", str(cache))
+    say(f"[batch] {len(inputs)} traces over {ids} ids in groups of 2^{bits}")
+    traces = load_all(ctx, inputs)
+    refs = [oracle_of(*inp) for inp in inputs]
+    for turn in range(3):
+        V.batch_check(ctx, traces)
+        ctx.sync()
+        assert C_info(V, ctx)[1:3] == (bits, 4096)
+        for i, (t, ref) in enumerate(zip(traces, refs)):
+            assert_trace(t, ref, f"trace {i}, turn {turn}")
+    for t in traces:
+        t.free()
+    for i, (st, fin, viol, ind) in enumerate(_route_results(ctx, inputs, True)):
+        assert np.array_equal(st, refs[i].status) and np.array_equal(fin, refs[i].final), f"sorted {i}"
+        assert np.array_equal(viol, refs[i].violations) and ind == refs[i].n_induced_stuck, f"sorted {i}"
+
+
+def test_batch_bucket_route_tunes(ctx, tmp_path, monkeypatch):
+    """The bucket route's candidates are timed on the batch itself; the choice is among them and
+    cached, and the bytes are the oracle's before and after."""
+    from paper_1910_11110_amd import vcheck as V
+    monkeypatch.setenv("VC_TUNE_CACHE", str(tmp_path / "tune.json"))
+    inputs = make_traces(12, 13) + [(gen.plain_events(50_000, 1 << 20, 3), 1 << 20, None, None, None)]
+    refs = [oracle_of(*inp) for inp in inputs]
+    for turn in range(2):
+        traces = load_all(ctx, inputs)
+        V.batch_check(ctx, traces)
+        ctx.sync()
+        _, bits, chunk, scan = C_info(V, ctx)
+        assert bits in (20, 21, 22) and chunk in (4096, 16384) and scan == 0
+        text = (tmp_path / "tune.json").read_text()
+        assert "bucket:gfx950" in text and f"[{bits}, {chunk}, 0]" in text and ":dense" not in text
+        for i, (t, ref) in enumerate(zip(traces, refs)):
+            assert_trace(t, ref, f"trace {i}, turn {turn}")
+            t.free()

@@ -253,3 +253,24 @@ def test_dense_ids_that_change_their_kind(ctx, n_ids, block):
     assert np.array_equal(t.final(), ref.final)
     assert np.array_equal(t.violations().indices, ref.violations)
     t.free()
+
+
+@pytest.mark.parametrize("word", [5 << 24, (1 << 24) - 1])
+@pytest.mark.parametrize("n,n_ids", [(70_000, 60), (70_000, 300), ((1 << 22) + 100, 50_000), (70_000, 1 << 17)])
+@pytest.mark.parametrize("at", [0, 1, 511, 69_899])
+def test_malformed_index_exactly(ctx, n, n_ids, at, word):
+    """The index reported is that of the first of two malformed words, digit by digit, on the
+    routes of few, many and very many ids and of long traces folded forwards."""
+    import re
+
+    import torch
+
+    from paper_1910_11110_amd import vcheck as V
+    e = gen.plain_events(n, n_ids, 3)
+    e[[at, n - 70]] = word
+    t = V.Trace.load(ctx, torch.from_numpy(e.view(np.int32)).cuda(), n_ids)
+    t.check()
+    with pytest.raises(V.VCError) as ex:
+        ctx.sync()
+    assert ex.value.code == V.VC_EINVAL and re.search(rf"index {at}\b", str(ex.value)), str(ex.value)
+    t.free()
