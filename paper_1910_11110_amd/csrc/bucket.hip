@@ -37,18 +37,14 @@ namespace {
 constexpr EffectTable TABLE = make_table();
 
 // ----------------------------------------------------------------------------------
-// word sources: id and transition function of a 32-bit word; malformed words count as
-// Noop on id 0 (their index is reported by the histogram pass)
+// word sources: malformed words (their index is reported by the histogram pass) and, where
+// the bucket scan takes them, id and transition function of a 32-bit word (a malformed one
+// counts as Noop on id 0)
 // ----------------------------------------------------------------------------------
 struct EventWords {
     __device__ static bool ok(uint32_t w, uint32_t n_ids)
     {
         return (w >> 28) == 0 && ((w >> 24) & 7u) <= OP_NOOP && (w & 0xFFFFFFu) < n_ids;
-    }
-    __device__ static uint32_t key(uint32_t w, uint32_t n_ids) { return ok(w, n_ids) ? (w & 0xFFFFFFu) : 0u; }
-    __device__ static uint32_t fc(uint32_t w, uint32_t n_ids)
-    {
-        return ok(w, n_ids) ? fcode((w >> 24) & 7u, (w >> 27) & 1u) : fcode(OP_NOOP, 0);
     }
     __device__ static uint32_t arity(uint32_t, uint32_t) { return 0; }
 };

@@ -128,12 +128,12 @@ constexpr uint32_t NO_MOTHER = 0xFFFFFFFFu;
 
 struct DynLayout {
     uint32_t *cpos, *dpos;
-    uint8_t *init2, *pre;
+    uint8_t *init2;
     uint2 *life;
     size_t bytes;
 };
 
-DynLayout dyn_layout(void *base, uint64_t n, uint32_t n_ids, uint64_t n_nbr)
+DynLayout dyn_layout(void *base, uint32_t n_ids, uint64_t n_nbr)
 {
     char *p = (char *)base;
     size_t off = 0;
@@ -146,7 +146,6 @@ DynLayout dyn_layout(void *base, uint64_t n, uint32_t n_ids, uint64_t n_nbr)
     L.cpos = (uint32_t *)take((size_t)(n_ids ? n_ids : 1) * 4);
     L.dpos = (uint32_t *)take((size_t)(n_ids ? n_ids : 1) * 4);
     L.init2 = (uint8_t *)take(n_ids ? n_ids : 1);
-    L.pre = (uint8_t *)take(2 * n + 1);
     L.life = (uint2 *)take((size_t)(n_nbr + n_ids + 1) * sizeof(uint2));
     L.bytes = off;
     return L;
@@ -191,9 +190,9 @@ int dyn_count_items(vc_trace *t, hipStream_t s, Control *ctl, DynTrace &D)
     const uint64_t n = t->n;
     if ((r = devbuf_reserve(t->aux, dyn_aux(nullptr, n).bytes)) != VC_OK ||
         (r = devbuf_reserve(t->scratch, std::max(t->scratch.bytes, excl_scan_scratch_bytes(dyn_tiles(n))))) != VC_OK ||
-        (r = devbuf_reserve(t->dyn, dyn_layout(nullptr, n, t->n_ids, t->sets.n_nbr).bytes)) != VC_OK)
+        (r = devbuf_reserve(t->dyn, dyn_layout(nullptr, t->n_ids, t->sets.n_nbr).bytes)) != VC_OK)
         return r;
-    const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
+    const DynLayout L = dyn_layout(t->dyn.p, t->n_ids, t->sets.n_nbr);
     launch_dyn_life(t->events, n, t->n_ids, L.cpos, L.dpos, s);
     launch_dyn_near(&t->sets, t->n_ids, L.cpos, L.dpos, L.life, s);
     D = DynTrace{t->events, n, t->n_ids, t->mother, &t->sets, L.life};
@@ -297,7 +296,7 @@ static int dynamic_dense_enqueue(vc_trace *t, hipStream_t s)
     DynTrace D;
     if ((r = dyn_count_items(t, s, A.xctl, D)) != VC_OK)
         return r;
-    const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
+    const DynLayout L = dyn_layout(t->dyn.p, t->n_ids, t->sets.n_nbr);
     uint32_t *words = (uint32_t *)t->items_a.p;
     uint8_t *pre = (uint8_t *)t->items_b.p, *fin = (uint8_t *)t->fin.p;
     launch_dyn_words(D, true, A.tpos, A.pos32, A.bits, words, m, A.xctl, s);
@@ -336,7 +335,7 @@ static int dynamic_bucket_enqueue(vc_trace *t, hipStream_t s)
     DynTrace D;
     if ((r = dyn_count_items(t, s, A.xctl, D)) != VC_OK)
         return r;
-    const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
+    const DynLayout L = dyn_layout(t->dyn.p, t->n_ids, t->sets.n_nbr);
     uint32_t *words = (uint32_t *)t->items_a.p;
     uint8_t *comb = (uint8_t *)t->items_b.p, *fin = (uint8_t *)t->fin.p;
     launch_dyn_words(D, false, A.tpos, A.pos32, A.bits, words, m, A.xctl, s);
@@ -367,22 +366,24 @@ int dynamic_enqueue(vc_trace *t, hipStream_t s)
     int r;
     if ((r = trace_reserve(t, m)) != VC_OK)
         return r;
-    // probes write their bytes past the trace's n (payload n + t)
-    if ((r = devbuf_reserve(t->status, 2 * n + 1)) != VC_OK)
+    // probes write their bytes past the trace's n (payload n + t); their statuses before go to
+    // the buffer of k-space statuses, which a dynamic trace has none of
+    if ((r = devbuf_reserve(t->status, 2 * n + 1)) != VC_OK || (r = devbuf_reserve(t->status16, 2 * n + 1)) != VC_OK)
         return r;
+    uint8_t *const pre = (uint8_t *)t->status16.p;
     launch_reset_control(t->ctl, s);
     DynTrace D;
     if ((r = dyn_count_items(t, s, t->ctl, D)) != VC_OK)
         return r;
-    const DynLayout L = dyn_layout(t->dyn.p, n, t->n_ids, t->sets.n_nbr);
+    const DynLayout L = dyn_layout(t->dyn.p, t->n_ids, t->sets.n_nbr);
     const DynAux A = dyn_aux(t->aux.p, n);
     launch_dyn_items(D, A.tpos, A.pos32, A.bits, (uint64_t *)t->items_a.p, m, t->ctl, s);
     uint64_t *sorted = sort_items((uint64_t *)t->items_a.p, (uint64_t *)t->items_b.p, m,
                                   (int)key_bits_for(t->n_ids), t->scratch.p, t->ctl, s);
     // the first scan is read only at the probes (payloads n + t)
-    launch_segscan(sorted, m, t->init, t->n_ids, SCAN_PRE, L.pre, nullptr, t->scratch.p, t->ctl, s, nullptr, 1u << 30,
+    launch_segscan(sorted, m, t->init, t->n_ids, SCAN_PRE, pre, nullptr, t->scratch.p, t->ctl, s, nullptr, 1u << 30,
                    (uint32_t)n);
-    launch_dyn_inherit(t->mother, L.cpos, L.pre, n, t->init, t->n_ids, L.init2, (uint8_t *)t->fin.p, s);
+    launch_dyn_inherit(t->mother, L.cpos, pre, n, t->init, t->n_ids, L.init2, (uint8_t *)t->fin.p, s);
     launch_segscan(sorted, m, L.init2, t->n_ids, SCAN_STATUS, (uint8_t *)t->status.p, (uint8_t *)t->fin.p,
                    t->scratch.p, t->ctl, s);
     launch_compact((uint8_t *)t->status.p, n, (uint32_t *)t->viol.p, t->scratch.p, t->ctl, s);
