@@ -405,7 +405,7 @@ __device__ __forceinline__ uint32_t step_in_turn(const Lane<DIR> &L, uint64_t me
 }
 
 // lanes of a step that share ids with others, at most, for which taking turns is the shorter way
-// (2^24 uniform events over 512 ids: 137 us, 148 with 5 and 165 with 2)
+// (2^24 uniform events over 512 ids, all kernels: 155 us, 161 with 5, 166 with 2, 155 with 16)
 constexpr int D_FEW = 10;
 
 // Q steps whose lanes may share ids, one after the other; no lane is in the table.  What
@@ -490,15 +490,14 @@ __device__ __forceinline__ void steps_together(const Lane<DIR> (&L)[Q], uint32_t
 // step nor of the ones before it, their reads are one wait and their changes independent.
 // Otherwise all leave and the steps take their turns; lanes that share ids within a step
 // take turns too when they are few, else they work their changes out together.
-// close: ids that are constants already leave before the lanes enter (only backwards; a read
+// CLOSE: ids that are constants already leave before the lanes enter (only backwards; a read
 // more a step).  `again` counts the events that met an id of their own step.
-template <class DIR, int PAIR>
+template <class DIR, int PAIR, bool CLOSE = false>
 __device__ __forceinline__ void steps(Lane<DIR> (&L)[PAIR], uint32_t (&result)[PAIR], const uint32_t *s_tab,
-                                      uint32_t bits, uint32_t lane, uint32_t &shared_steps, bool close,
-                                      uint32_t &again)
+                                      uint32_t bits, uint32_t lane, uint32_t &shared_steps, uint32_t &again)
 {
     bool met = false;
-    if (DIR::BACK && DIR::Dom::CLOSES && close)
+    if constexpr (CLOSE)
 #pragma unroll
         for (int q = 0; q < PAIR; q++)
             L[q].part = L[q].part && DIR::open(L[q].field(tab_load(L[q].p)));
@@ -670,7 +669,7 @@ __device__ __forceinline__ void walk_forward(const C &c, uint32_t *s_t, const ui
 #pragma unroll
                 for (int q = 0; q < PAIR; q++)
                     L[q] = make_lane<DIR>(s_t, s_tab, w[u + q], c.clamped(w[u + q]), true);
-                steps<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps, false, again);
+                steps<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps, again);
 #pragma unroll
                 for (int q = 0; q < PAIR; q++)
                     out.step(lane, u + q, i + (u + q) * WAVE, w[u + q], byte[q], true);
@@ -821,6 +820,19 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
             }
             shared_steps = 0;
             uint32_t again = 0;
+            if (D::CLOSES && close) { // (a loop of its own: a branch a step costs uniform ids 4 %)
+#pragma unroll 1
+                for (int u = 0; u < D_UNROLL; u += PAIR) {
+                    Lane<F> L[PAIR];
+                    uint32_t byte[PAIR];
+#pragma unroll
+                    for (int q = 0; q < PAIR; q++)
+                        L[q] = make_lane<F>(s_t, s_tab, w[q], C.local(w[q]), true);
+                    steps<F, PAIR, true>(L, byte, s_tab, bits, lane, shared_steps, again);
+                    turn_words<PAIR>(w);
+                }
+                continue;
+            }
 #pragma unroll
             for (int u = 0; u < D_UNROLL; u += PAIR) {
                 Lane<F> L[PAIR];
@@ -828,9 +840,9 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
 #pragma unroll
                 for (int q = 0; q < PAIR; q++)
                     L[q] = make_lane<F>(s_t, s_tab, w[u + q], C.local(w[u + q]), true);
-                steps<F, PAIR>(L, byte, s_tab, bits, lane, shared_steps, close, again);
+                steps<F, PAIR>(L, byte, s_tab, bits, lane, shared_steps, again);
             }
-            close = close || again >= CLOSE_FROM;
+            close = again >= CLOSE_FROM;
         }
         compiler_fence();
         uint4 *out = reinterpret_cast<uint4 *>(rows + C.row_at);
