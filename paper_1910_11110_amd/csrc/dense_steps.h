@@ -491,10 +491,10 @@ __device__ __forceinline__ void steps_together(const Lane<DIR> (&L)[Q], uint32_t
 // Otherwise all leave and the steps take their turns; lanes that share ids within a step
 // take turns too when they are few, else they work their changes out together.
 // CLOSE: ids that are constants already leave before the lanes enter (only backwards; a read
-// more a step).  `again` counts the events that met an id of their own step.
+// more a step).
 template <class DIR, int PAIR, bool CLOSE = false>
 __device__ __forceinline__ void steps(Lane<DIR> (&L)[PAIR], uint32_t (&result)[PAIR], const uint32_t *s_tab,
-                                      uint32_t bits, uint32_t lane, uint32_t &shared_steps, uint32_t &again)
+                                      uint32_t bits, uint32_t lane, uint32_t &shared_steps)
 {
     bool met = false;
     if constexpr (CLOSE)
@@ -527,7 +527,6 @@ __device__ __forceinline__ void steps(Lane<DIR> (&L)[PAIR], uint32_t (&result)[P
         if (PAIR > 1 || DIR::BACK)
             L[q].enter();
         const uint64_t m = __ballot(L[q].met());
-        again += (uint32_t)__builtin_popcountll(m);
         if (!m) {
             result[q] = step_apart<DIR>(L[q]);
         } else {
@@ -566,10 +565,12 @@ __device__ __forceinline__ void turn_words(uint32_t (&w)[D_UNROLL])
 }
 
 // The first round of a chunk goes that way when so many of its events have their neighbour's
-// id: about 500 times the chance that two events share theirs, where a step has about 2,000
-// times that of lanes that meet, and on one address the lanes' atomics take turns (2^24 events
-// over 2^20 ids in runs of 128 an id: fold 70 -> 59, apply 72 -> 47 us).
-constexpr uint32_t D_ALIKE = 4;
+// id: about 500 times the chance that two events share theirs, which is 14 for Zipf(1.1) ids over
+// 2^16 and 4 for uniform ones over 128, where a step has about 2,000 times that of lanes that
+// meet; on one address the lanes' atomics take turns (2^24 events over 2^20 ids in runs of 128
+// an id: fold 70 -> 59, apply 72 -> 47 us; uniform ids over 512, of which 2 % of the chunks have
+// 4, fold 47.7 with 8 and 48-57 with 4).
+constexpr uint32_t D_ALIKE = 8;
 __device__ __forceinline__ uint32_t first_shared(const uint32_t (&w)[D_UNROLL])
 {
     uint32_t alike = 0;
@@ -632,7 +633,7 @@ __device__ __forceinline__ void walk_forward(const C &c, uint32_t *s_t, const ui
     using D = typename DIR::Dom;
     const uint64_t i0 = c.begin;
     const uint32_t bits = c.bits, len = (uint32_t)(c.end - i0), rounds = len / (D_UNROLL * WAVE);
-    uint32_t shared_steps = rounds ? first_shared(nxt) : 0u, again = 0;
+    uint32_t shared_steps = rounds ? first_shared(nxt) : 0u;
     for (uint32_t r = 0; r < rounds; r++) {
         uint32_t w[D_UNROLL];
 #pragma unroll
@@ -669,7 +670,7 @@ __device__ __forceinline__ void walk_forward(const C &c, uint32_t *s_t, const ui
 #pragma unroll
                 for (int q = 0; q < PAIR; q++)
                     L[q] = make_lane<DIR>(s_t, s_tab, w[u + q], c.clamped(w[u + q]), true);
-                steps<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps, again);
+                steps<DIR, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
 #pragma unroll
                 for (int q = 0; q < PAIR; q++)
                     out.step(lane, u + q, i + (u + q) * WAVE, w[u + q], byte[q], true);
@@ -726,13 +727,10 @@ struct NoOut {
     __device__ void round(uint32_t, uint64_t, uint32_t, bool) const {}
 };
 
-// From a round on in which so many events met an id of their own step the ids of a chunk are
-// skewed: few still meet when those that are constants leave first (2^24 events of Zipf(1.1)
-// ids over 2^16: fold 106 -> 89 us, 2^26 over 2^20 211 -> 134; uniform ids, of which a round of
-// 512 has one or two that meet from 2^14 on, 231 -> 273 us at 2^26 over 2^16).
-constexpr uint32_t CLOSE_FROM = 32;
-
-// every chunk's functions into its row (left: of the chunks marked there, of skewed ids, only)
+// Every chunk's functions into its row (left: of the chunks marked there, of skewed ids, only).
+// In chunks of skewed ids, or whose first words show it, few still meet when those that are
+// constants leave first (2^24 events of Zipf(1.1) ids over 2^16: 106 -> 89 us, 2^26 over 2^20
+// 211 -> 140; uniform ids 231 -> 273 us at 2^26 over 2^16).
 template <class F, int PAIR, class CHUNKS>
 __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, uint32_t *__restrict__ rows,
                                                      Control *ctl, const uint32_t *__restrict__ left)
@@ -819,7 +817,6 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
                 continue;
             }
             shared_steps = 0;
-            uint32_t again = 0;
             if (D::CLOSES && close) { // (a loop of its own: a branch a step costs uniform ids 4 %)
 #pragma unroll 1
                 for (int u = 0; u < D_UNROLL; u += PAIR) {
@@ -828,7 +825,7 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
 #pragma unroll
                     for (int q = 0; q < PAIR; q++)
                         L[q] = make_lane<F>(s_t, s_tab, w[q], C.local(w[q]), true);
-                    steps<F, PAIR, true>(L, byte, s_tab, bits, lane, shared_steps, again);
+                    steps<F, PAIR, true>(L, byte, s_tab, bits, lane, shared_steps);
                     turn_words<PAIR>(w);
                 }
                 continue;
@@ -840,9 +837,8 @@ __global__ __launch_bounds__(WAVE) void k_dense_fold(CHUNKS T, uint32_t table, u
 #pragma unroll
                 for (int q = 0; q < PAIR; q++)
                     L[q] = make_lane<F>(s_t, s_tab, w[u + q], C.local(w[u + q]), true);
-                steps<F, PAIR>(L, byte, s_tab, bits, lane, shared_steps, again);
+                steps<F, PAIR>(L, byte, s_tab, bits, lane, shared_steps);
             }
-            close = again >= CLOSE_FROM;
         }
         compiler_fence();
         uint4 *out = reinterpret_cast<uint4 *>(rows + C.row_at);
