@@ -282,16 +282,17 @@ int vc_profile_read(vc_ctx *ctx, char *names, uint32_t names_cap, double *ms, ui
 
 /* ---------------------------------------------------------------------------------
  * Batched check: n independent traces of uneven length checked together in one
- * enqueued pipeline (ids of each trace are relocated to a private key range, so no
- * status crosses traces; the sort and scan kernels are persistent and pull tiles
- * from a device ticket counter).  Each trace's results are
- * then read with the vc_read_* functions as if vc_check had run on it alone.
+ * enqueued pipeline: where they lie when every trace has at most 2^16 ids, else with the
+ * ids of each trace relocated to a private key range; no status crosses traces.  Each
+ * trace's results are then read with the vc_read_* functions as if vc_check had run on it
+ * alone.
  * The launch sequence is captured once per batch shape in a hipGraph and replayed.
  * --------------------------------------------------------------------------------- */
 int vc_batch_check(vc_ctx *ctx, vc_trace *const *traces, uint32_t n);
 /* settings of the last batch: whether it runs from a captured hipGraph; on the bucket
- * route (every trace with 1 to 2^22 ids) the ids per group as a power of two (max_bits)
- * and the events per chunk of a trace without arrays (grid_cap), scan_grid 0; on the
+ * route (every trace with 1 to 2^22 ids) the ids per group as a power of two (max_bits;
+ * without a meaning where all traces have at most 2^16) and the events per chunk of a
+ * trace without arrays (grid_cap), scan_grid 0; on the
  * sorted route the sort digit width and the persistent grid bounds (0 = one workgroup
  * per tile).  The autotuner runs on a batch shape's first check unless VC_NO_AUTOTUNE
  * is set in the environment, and caches its choice per shape in $VC_TUNE_CACHE

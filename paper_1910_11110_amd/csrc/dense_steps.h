@@ -148,7 +148,7 @@ struct Two {
     // copy (x, y: bits 0 and 1).  Of two sets without common lanes the one with the latest lane
     // is the larger number.  (2^24 events over 2^16 ids in runs of 128 an id, the apply pass: 149
     // us by the position of the latest constant, with shifts and masks, and as functions in
-    // 4-byte form, 96 this way.)
+    // 4-byte form, 96 this way, 88 with the rest of what steps that share ids do.)
     struct Composed {
         bool k;
         uint32_t left, x, y;
