@@ -384,6 +384,23 @@ def test_batch_row_sizes(ctx, n_ids):
         t.free()
 
 
+@pytest.mark.parametrize("extra", [0, 1])
+def test_batch_classes_at_what_the_device_holds(ctx, extra):
+    """1,000 chunks over 40,000 ids and 24 or 25 over 20,000, next to smaller ones: classes
+    that share a launch, and one chunk more than that."""
+    from paper_1910_11110_amd import vcheck as V
+    rng = np.random.default_rng(extra)
+    inputs = [(gen.plain_events(n, k, 70 + k), k, None, None, rng.integers(0, 4, k).astype(np.uint8))
+              for k, n in ((300, 5000), (40_000, 1000 * 1536), (20_000, 24 * 1024 + extra), (10_000, 600))]
+    say(f"[batch] classes, {extra} more")
+    traces = load_all(ctx, inputs)
+    V.batch_check(ctx, traces)
+    ctx.sync()
+    for i, (t, inp) in enumerate(zip(traces, inputs)):
+        assert_trace(t, oracle_of(*inp), f"trace {i}")
+        t.free()
+
+
 @pytest.mark.parametrize("n", [1, 63, 16_383, 16_384, 16_385, 50_000])
 def test_batch_traces_over_few_ids(ctx, n):
     """Traces over 1 to 64 ids around a tile of strands, next to each other, with and without

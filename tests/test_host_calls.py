@@ -88,6 +88,33 @@ assert len(names) == 1 and ("k_run_steps" in names[0]) == {steps}, names
 """)
 
 
+@pytest.mark.parametrize("sizes,walks", [
+    (((40000, 1000 * 1536), (20000, 24 * 1024)), 1),
+    (((40000, 1000 * 1536), (20000, 24 * 1024 + 1)), 2),
+    (((20000, 1000),), 1),
+    (((65536, 1), (32768, 1), (16384, 1), (8192, 1)), 1),
+    (((65536, 1), (300, 10 ** 6)), 2),
+    (((65536, 1), (16384, 0), (300, 10 ** 6)), 2)])
+def test_batch_classes_share_launches(runtime, sizes, walks):
+    """A batch that leaves the device idle is walked by one launch for several classes of ids:
+    while the device holds all their chunks (1,024 of more than 32,768 ids) at once."""
+    run(runtime, f"""
+import os
+os.environ["VC_NO_AUTOTUNE"] = "1"
+L.vc_batch_check.argtypes = [P, C.POINTER(P), u32]
+traces = []
+for ids, n in {sizes}:
+    ev, t = (C.c_uint32 * max(n, 1))(), P()
+    ok(L.vc_trace_load(ctx, ev, n, ids, None, 0, C.byref(t)))
+    traces.append(t)
+F.fake_reset()
+ok(L.vc_batch_check(ctx, (P * len(traces))(*traces), len(traces)))
+names = [n for n, _ in launches()]
+for walk in ("k_dense_fold", "k_dense_apply"):
+    assert len([n for n in names if walk in n]) == {walks}, names
+""")
+
+
 CHECKED = """
 ev = (C.c_uint32 * 5000)()
 t = P()
